@@ -94,6 +94,7 @@ struct Instance {
   std::vector<int> qmap;  // [nk*nk] -> table index or -1
   // workspace offsets (bytes)
   size_t vtab_off = 0, kw_off = 0, qmap_off = 0;
+  int ovl_span = 0;  // grid points per split-K chunk of the overlap
   int first_ebatch = 0, n_ebatches = 0;
   int first_eblk = 0, n_eblk = 0;  // whole-pair apply-with-energy partials of this instance
   int first_aslot = 0, n_aslot = 0;  // register-line apply-with-energy sum slots
@@ -166,7 +167,7 @@ struct Plan {
   size_t epart_off = 0, epart_bytes = 0;
   size_t ebsum_off = 0, ebsum_bytes = 0;
   size_t partial_off = 0, partial_bytes = 0;
-  size_t ovl_off = 0, ovl_bytes = 0;  // overlap split-K partials
+  size_t ovl_off = 0, ovl_bytes = 0;  // overlap split-K partials (share the pair buffer's memory)
   size_t eblk_off = 0, eblk_bytes = 0;  // per-block energy partials of the whole-pair apply
   size_t total_bytes = 0;
   std::vector<unsigned char> host_image;  // constant prefix, uploaded by set_workspace
@@ -218,7 +219,10 @@ hipError_t launch_energy_reduce(const Plan& p, const Batch& b, const double* occ
 bool fused_supported(fock_precision prec, const int grid[3]);
 size_t fused_lds_bytes(fock_precision prec, int L);
 int fused_threads(fock_precision prec, int L);
-size_t overlap_scratch_bytes(const Instance& in);
+// split-K chunk of the overlap: a multiple of kOvChunkMin, at most kOvChunkMax
+constexpr int kOvChunkMin = 128, kOvChunkMax = 4096;
+int overlap_span(const Instance& in);
+size_t overlap_scratch_bytes(const Instance& in, int span);
 void prepare_fused_kernels(fock_precision prec, int lim);
 bool reg_supported(fock_precision prec, const int grid[3]);
 // grids where the register-line path can run its pencil pass over slabs of

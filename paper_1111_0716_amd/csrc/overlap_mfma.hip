@@ -27,7 +27,6 @@ namespace fock {
 namespace {
 
 constexpr int kOvWaves = 4;
-constexpr int kOvChunk = 4096;  // grid points per workgroup (split-K chunk)
 constexpr int kOvSub = 1024;    // points accumulated in the MFMA precision before an FP64 fold
 constexpr int kBlk = 32;        // bands per block side (2 x 2 tiles of 16)
 
@@ -62,14 +61,15 @@ struct OvStage {
   static constexpr int kPerBand = kSlab / kVec;
   static constexpr int kLoads = kBlk * kPerBand / (64 * kOvWaves);
   static_assert(kLoads >= 1 && kBlk * kPerBand % (64 * kOvWaves) == 0, "slab does not divide over the threads");
-  static_assert(kOvChunk % kOvSub == 0 && kOvSub % kSlab == 0, "chunk of whole sub-chunks of whole slabs");
+  static_assert(kOvChunkMax % kOvSub == 0 && kOvSub % kSlab == 0 && kOvChunkMin % kSlab == 0,
+                "chunks and sub-chunks of whole slabs");
 };
 
 // grid: (block_i * nbj + block_j, chunk, k); 256 threads
 template <typename T>
 __global__ __launch_bounds__(64 * kOvWaves) void k_overlap_mfma(const typename cx<T>::t* __restrict__ psi,
                                                                  const typename cx<T>::t* __restrict__ vx, int nbands,
-                                                                 long long bs, long long npts, int nt,
+                                                                 long long bs, long long npts, int nt, int span,
                                                                  double* __restrict__ part) {
   using C = typename cx<T>::t;
   using M = Mfma<T>;
@@ -83,8 +83,8 @@ __global__ __launch_bounds__(64 * kOvWaves) void k_overlap_mfma(const typename c
   const int nbj = (nt + 1) / 2;
   const int bi = blockIdx.x / nbj, bj = blockIdx.x - bi * nbj;
   const int chunk = blockIdx.y, k = blockIdx.z;
-  const long long c0 = static_cast<long long>(chunk) * kOvChunk;
-  const long long c1 = c0 + kOvChunk < npts ? c0 + kOvChunk : npts;
+  const long long c0 = static_cast<long long>(chunk) * span;
+  const long long c1 = c0 + span < npts ? c0 + span : npts;
   const size_t kb = static_cast<size_t>(k) * nbands;
   // this wave's tile (ti, tj) of the block, and whether it lies inside M
   const int ti = 2 * bi + (wave >> 1), tj = 2 * bj + (wave & 1);
@@ -179,27 +179,41 @@ __global__ __launch_bounds__(64 * kOvWaves) void k_overlap_mfma(const typename c
   }
 }
 
-// vmat[k][i][j] = dV sum_chunks part[chunk][k][tile][row][col]
+// vmat[k][i][j] = dV sum_chunks part[chunk][k][tile][row][col].  One workgroup
+// per (k, tile, row): 16 columns x 16 shares of the chunks, each share summed
+// in order, then the shares in order (one thread per element over all chunks
+// waits on one load after another: at a Gamma cell of 48 bands that chain is
+// longer than the product itself).
 template <typename T>
-__global__ __launch_bounds__(256) void k_overlap_reduce(const double* __restrict__ part, int nchunks, int nk,
+__global__ __launch_bounds__(256) void k_overlap_reduce(const double2* __restrict__ part, int nchunks, int nk,
                                                         int nbands, int ntj, double dv,
                                                         typename cx<T>::t* __restrict__ vmat) {
   using C = typename cx<T>::t;
-  const long long total = static_cast<long long>(nk) * nbands * nbands;
-  for (long long id = blockIdx.x * 256LL + threadIdx.x; id < total; id += static_cast<long long>(gridDim.x) * 256) {
-    const int k = static_cast<int>(id / (static_cast<long long>(nbands) * nbands));
-    const int ij = static_cast<int>(id - static_cast<long long>(k) * nbands * nbands);
-    const int i = ij / nbands, j = ij - i * nbands;
-    const int tile = (i / 16) * ntj + (j / 16), row = i % 16, col = j % 16;
-    const int ntiles = ((nbands + 15) / 16) * ntj;
-    double sr = 0.0, si = 0.0;
-    for (int c = 0; c < nchunks; ++c) {
-      const double* src = part + ((static_cast<size_t>(c) * nk + k) * ntiles + tile) * 512 + (row * 16 + col) * 2;
-      sr += src[0];
-      si += src[1];
-    }
-    vmat[id] = C{static_cast<T>(sr * dv), static_cast<T>(si * dv)};
+  __shared__ double2 red[16][16];
+  const int row = blockIdx.x & 15, tile = blockIdx.x >> 4, k = blockIdx.y;
+  const int ti = tile / ntj, tj = tile - ti * ntj;
+  const int i = ti * 16 + row;
+  if (i >= nbands) return;  // the whole workgroup
+  const int col = threadIdx.x & 15, share = threadIdx.x >> 4;
+  const size_t step = static_cast<size_t>(nk) * (gridDim.x >> 4) * 256;  // elements from chunk to chunk
+  const double2* src = part + (static_cast<size_t>(k) * (gridDim.x >> 4) + tile) * 256 + row * 16 + col;
+  double sr = 0.0, si = 0.0;
+#pragma unroll 4
+  for (int c = share; c < nchunks; c += 16) {
+    const double2 v = src[c * step];
+    sr += v.x;
+    si += v.y;
   }
+  red[share][col] = double2{sr, si};
+  __syncthreads();
+  const int j = tj * 16 + col;
+  if (share != 0 || j >= nbands) return;
+#pragma unroll
+  for (int s = 1; s < 16; ++s) {
+    sr += red[s][col].x;
+    si += red[s][col].y;
+  }
+  vmat[(static_cast<size_t>(k) * nbands + i) * nbands + j] = C{static_cast<T>(sr * dv), static_cast<T>(si * dv)};
 }
 
 template <typename T>
@@ -208,25 +222,40 @@ hipError_t overlap_t(const Plan& p, int inst, const void* psi, const void* vx, v
   const Instance& in = p.inst[inst];
   const int nt = (in.nbands + 15) / 16;
   const int nbj = (nt + 1) / 2;
-  const int nchunks = static_cast<int>((in.npts + kOvChunk - 1) / kOvChunk);
+  const int span = in.ovl_span;
+  const int nchunks = static_cast<int>((in.npts + span - 1) / span);
   double* part = reinterpret_cast<double*>(p.ws + p.ovl_off);
   p.prof.begin(FOCK_K_OVERLAP, p.stream);
   hipLaunchKernelGGL((k_overlap_mfma<T>), dim3(nbj * nbj, nchunks, in.nk), dim3(64 * kOvWaves), 0, p.stream,
                      static_cast<const C*>(psi), static_cast<const C*>(vx), in.nbands,
-                     static_cast<long long>(in.band_stride), static_cast<long long>(in.npts), nt, part);
-  const long long total = static_cast<long long>(in.nk) * in.nbands * in.nbands;
-  const int gx = static_cast<int>(std::min<long long>(1024, (total + 255) / 256));
-  hipLaunchKernelGGL((k_overlap_reduce<T>), dim3(gx), dim3(256), 0, p.stream, static_cast<const double*>(part),
-                     nchunks, in.nk, in.nbands, nt, in.omega / static_cast<double>(in.npts), static_cast<C*>(vmat));
+                     static_cast<long long>(in.band_stride), static_cast<long long>(in.npts), nt, span, part);
+  hipLaunchKernelGGL((k_overlap_reduce<T>), dim3(nt * nt * 16, in.nk), dim3(256), 0, p.stream,
+                     reinterpret_cast<const double2*>(part), nchunks, in.nk, in.nbands, nt, in.omega / static_cast<double>(in.npts), static_cast<C*>(vmat));
   p.prof.end(FOCK_K_OVERLAP, p.stream);
   return hipGetLastError();
 }
 
 }  // namespace
 
-size_t overlap_scratch_bytes(const Instance& in) {
+// Grid points per workgroup (split-K chunk).  A workgroup waits out one slab
+// load after another, about 1 us a slab, so a chunk of 4096 points takes about
+// 130 (FP32) to 250 us (FP64) however small the problem is.  The chunks are
+// made short enough for about 1024 workgroups (four per compute unit, what LDS
+// holds), as long as the grid has them, and stay at 4096 points where that
+// many are there anyway.  One apply with its overlap, always 4096 points
+// against this rule: 16^3 Gamma, 8 bands, FP64 285 -> 36 us; 48^3 Gamma, 48
+// bands, mixed 3.19 -> 2.93 ms; 32^3 2x2x2, 18 bands, FP64 (with the gradient)
+// 12.79 -> 12.40 ms; 72^3 2x2x2, 24 bands, FP32 77.0 ms both ways.
+int overlap_span(const Instance& in) {
+  const long long nbj = ((in.nbands + 15) / 16 + 1) / 2;
+  const long long want = std::max<long long>(1, 1024 / (nbj * nbj * in.nk));  // chunks
+  const long long span = (in.npts + want - 1) / want;
+  return static_cast<int>(std::min<long long>(kOvChunkMax, (span + kOvChunkMin - 1) / kOvChunkMin * kOvChunkMin));
+}
+
+size_t overlap_scratch_bytes(const Instance& in, int span) {
   const size_t nt = (in.nbands + 15) / 16;
-  const size_t nchunks = (in.npts + kOvChunk - 1) / kOvChunk;
+  const size_t nchunks = (in.npts + span - 1) / span;
   return nchunks * in.nk * nt * nt * 512 * sizeof(double);
 }
 

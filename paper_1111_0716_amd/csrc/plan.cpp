@@ -562,7 +562,20 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   } else {
     p->tbuf_bytes = max_pairs_elems * p->csize;
   }
-  off = align_up(off + p->tbuf_bytes);
+  // the overlap's split-K partials take the same memory: it runs after the
+  // last batch of an apply, when the pair buffer is no longer read
+  p->ovl_off = p->tbuf_off;
+  const size_t scratch0 = off;
+  const auto share_scratch = [&](bool fine) {
+    p->ovl_bytes = 0;
+    for (auto& in : p->inst) {
+      in.ovl_span = fine ? overlap_span(in) : kOvChunkMax;
+      p->ovl_bytes = std::max(p->ovl_bytes, overlap_scratch_bytes(in, in.ovl_span));
+    }
+    return align_up(scratch0 + std::max(p->tbuf_bytes, p->ovl_bytes));
+  };
+  off = share_scratch(true);
+  const size_t scratch_fine = off;
   p->epart_off = off;
   // per (pair, line block) energy partials: energy batches and apply-with-energy batches
   p->epart_bytes = std::max(std::max(max_epairs, max_apply_epairs) * max_n2, max_fused_epairs) * sizeof(double);
@@ -570,9 +583,6 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   p->partial_off = off;
   p->partial_bytes = max_partial;
   off = align_up(off + p->partial_bytes);
-  p->ovl_off = off;
-  for (const auto& in : p->inst) p->ovl_bytes = std::max(p->ovl_bytes, overlap_scratch_bytes(in));
-  off = align_up(off + p->ovl_bytes);
   // energy partials of the whole-pair apply: one per block, contiguous per instance
   int neblk = 0;
   for (int i = 0; i < n_inst; ++i) {
@@ -596,6 +606,15 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   p->ebsum_off = off;
   p->ebsum_bytes = static_cast<size_t>(std::max(slot, 1)) * sizeof(double);
   off = align_up(off + p->ebsum_bytes);
+  if (off > FOCK_STATIC_WORKSPACE_BYTES) {
+    // shorter overlap chunks must not take a plan out of the static workspace
+    const size_t saved = scratch_fine - share_scratch(false);
+    if (off - saved <= FOCK_STATIC_WORKSPACE_BYTES) {
+      for (size_t* o : {&p->epart_off, &p->partial_off, &p->eblk_off, &p->ebsum_off, &off}) *o -= saved;
+    } else {
+      share_scratch(true);
+    }
+  }
   p->total_bytes = off;
   for (const auto& in : p->inst) {
     const size_t plane = static_cast<size_t>(in.grid[1]) * in.grid[2], tile = static_cast<size_t>(in.grid[0]) * in.grid[2];
