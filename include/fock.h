@@ -119,8 +119,7 @@ fock_status fock_plan(const fock_desc* descs, int32_t n_inst, fock_precision pre
  *                   |O| x |P| pairs per batch
  *   fused_split     whole-pair path: partner slices per output (1..4)
  *   no_fused        1: use the three-pass path for every grid
- *   no_pair_symmetry 1: three-pass register-line path transforms every
- *                   ordered pair; 0: with the full k-pair set it transforms
+ *   no_pair_symmetry 1: the three-pass paths transform every ordered pair; 0: with the full k-pair set it transforms
  *                   each unordered pair once, W_nm(k,k') = conj W_mn(k',k)
  *                   serving both (blocks of outputs x partners of about
  *                   sqrt(tbuf_mb / pair size) orbitals each; acc_workgroups
@@ -276,6 +275,8 @@ fock_status fock_plan_stats(fock_plan_t plan, int64_t* ordered_pairs, int64_t* a
 
 /* Kernel kinds for per-kernel timing. */
 typedef enum {
+  /* register-line grids; on general grids the first and third pass take
+   * axis 1 and the second axes 2 and 3 */
   FOCK_K_PLANE = 0,          /* apply: co-density + forward FFT of axes 3, 2       */
   FOCK_K_PENCIL = 1,         /* apply: FFT of axis 1, x v_q, inverse FFT of axis 1 */
   FOCK_K_ACCUMULATE = 2,     /* apply: inverse FFT of axes 2, 3 + accumulate       */

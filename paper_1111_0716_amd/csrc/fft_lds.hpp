@@ -1,16 +1,9 @@
-// LDS-staged mixed-radix FFT building blocks for gfx950.
+// FFT building blocks for gfx950: complex helpers, in-register DFTs of the
+// small radices, the factorisation of a line and the twiddle tables.
 //
-// A workgroup transforms many lines (rows or columns of a 2-D tile held in
-// LDS) of one compile-time length L at once.  Each radix pass is a Stockham
-// step: every thread loads R elements of its butterflies into registers,
-// applies the inter-pass twiddles, runs an in-register radix-R DFT, and after
-// a barrier writes the R results to their autosorted positions in the same
-// LDS tile (in place; the barrier separates all reads from all writes).
-//
-// Lengths: every {2,3,5}-smooth L in [2, 72].  Radices 8, 4, 2, 3, 5 are
-// taken greedily from the remaining factor, so L = 72 runs as 8*3*3.
-// Twiddles come from a per-L table W_L^t = exp(-2 pi i t / L) built in FP64
-// on the host and rounded once to the working precision.
+// Lengths: every {2,3,5}-smooth L in [2, 72].  Twiddles come from a per-L
+// table W_L^t = exp(-2 pi i t / L) built in FP64 on the host and rounded once
+// to the working precision.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -18,7 +11,7 @@
 namespace fock {
 
 constexpr int kNMax = 72;   // largest supported grid axis
-constexpr int kBlock = 256; // threads per workgroup of the plane/pencil kernels
+constexpr int kBlock = 256; // threads per workgroup of the fills and reductions
 
 // ---------------------------------------------------------------------------
 // complex helpers on HIP vector types (x = real, y = imaginary)
@@ -149,114 +142,11 @@ __host__ __device__ constexpr int twiddle_offset(int L) {
 }
 constexpr int kTwiddleTotal = twiddle_offset(kNMax + 1);
 
-// fast quotient for idx < 2^20 and 1 <= n <= kNMax: the fractional part of
-// (idx + 0.5)/n stays >= 0.5/n away from an integer, far above FP32 error.
+// fast quotient for idx < 2^20 and any n >= 1: the fractional part of
+// (idx + 0.5)/n stays >= 0.5/n away from an integer, and the FP32 error of
+// the product is at most 3 2^-24 idx/n, less than 0.19/n.
 __device__ __forceinline__ int fdiv(int idx, float rcp) {
   return static_cast<int>((static_cast<float>(idx) + 0.5f) * rcp);
-}
-
-// ---------------------------------------------------------------------------
-// one Stockham pass of radix R over `nlines` lines of length L in LDS.
-// ROWS: elements of a line are contiguous (estride 1) and consecutive lanes
-// take consecutive butterflies of one line; otherwise lines are contiguous
-// (lstride 1) and consecutive lanes take consecutive lines.
-// ---------------------------------------------------------------------------
-template <typename C, int L, int R, int NS, int S, bool ROWS>
-__device__ __forceinline__ void stockham_pass(C* s, int nlines, float rcp_lines, int lstride, int estride,
-                                              const C* __restrict__ tw) {
-  constexpr int M = L / R;
-  constexpr int MAXB = (kNMax * M + kBlock - 1) / kBlock;
-  const int nbf = nlines * M;
-  C v[MAXB][R];
-#pragma unroll
-  for (int b = 0; b < MAXB; ++b) {
-    const int idx = static_cast<int>(threadIdx.x) + b * kBlock;
-    if (idx < nbf) {
-      int line, j;
-      if (ROWS) {
-        line = idx / M;
-        j = idx - line * M;
-      } else {
-        j = fdiv(idx, rcp_lines);
-        line = idx - j * nlines;
-      }
-      const C* src = s + line * lstride;
-      const int k = j % NS;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        C x = src[(j + r * M) * estride];
-        if (NS > 1 && r > 0) {
-          C w = tw[r * k * (L / (NS * R))];
-          if (S > 0) w.y = -w.y;
-          x = cmul(x, w);
-        }
-        v[b][r] = x;
-      }
-      Dft<R, S, C>::run(v[b]);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int b = 0; b < MAXB; ++b) {
-    const int idx = static_cast<int>(threadIdx.x) + b * kBlock;
-    if (idx < nbf) {
-      int line, j;
-      if (ROWS) {
-        line = idx / M;
-        j = idx - line * M;
-      } else {
-        j = fdiv(idx, rcp_lines);
-        line = idx - j * nlines;
-      }
-      C* dst = s + line * lstride;
-      const int k = j % NS;
-      const int d = (j / NS) * NS * R + k;
-#pragma unroll
-      for (int r = 0; r < R; ++r) dst[(d + r * NS) * estride] = v[b][r];
-    }
-  }
-  __syncthreads();
-}
-
-template <typename C, int L, int NS, int S, bool ROWS>
-__device__ __forceinline__ void stockham_passes(C* s, int nlines, float rcp_lines, int lstride, int estride,
-                                                const C* __restrict__ tw) {
-  if constexpr (NS < L) {
-    constexpr int R = pick_radix(L / NS);
-    stockham_pass<C, L, R, NS, S, ROWS>(s, nlines, rcp_lines, lstride, estride, tw);
-    stockham_passes<C, L, NS * R, S, ROWS>(s, nlines, rcp_lines, lstride, estride, tw);
-  }
-}
-
-// Transform `nlines` lines of runtime length L (a supported size) in LDS.
-// `twall` is the concatenated twiddle table.  Must be called by all threads.
-template <typename C, int S, bool ROWS>
-__device__ __forceinline__ void fft_lines(C* s, int L, int nlines, int lstride, int estride,
-                                       const C* __restrict__ twall) {
-  const float rcp = 1.0f / static_cast<float>(nlines);
-#define FOCK_FFT_CASE(LL)                                                                  \
-  case LL:                                                                                 \
-    stockham_passes<C, LL, 1, S, ROWS>(s, nlines, rcp, lstride, estride, twall + twiddle_offset(LL)); \
-    break;
-  switch (L) {
-    FOCK_FFT_CASE(2) FOCK_FFT_CASE(3) FOCK_FFT_CASE(4) FOCK_FFT_CASE(5) FOCK_FFT_CASE(6)
-    FOCK_FFT_CASE(8) FOCK_FFT_CASE(9) FOCK_FFT_CASE(10) FOCK_FFT_CASE(12) FOCK_FFT_CASE(15)
-    FOCK_FFT_CASE(16) FOCK_FFT_CASE(18) FOCK_FFT_CASE(20) FOCK_FFT_CASE(24) FOCK_FFT_CASE(25)
-    FOCK_FFT_CASE(27) FOCK_FFT_CASE(30) FOCK_FFT_CASE(32) FOCK_FFT_CASE(36) FOCK_FFT_CASE(40)
-    FOCK_FFT_CASE(45) FOCK_FFT_CASE(48) FOCK_FFT_CASE(50) FOCK_FFT_CASE(54) FOCK_FFT_CASE(60)
-    FOCK_FFT_CASE(64) FOCK_FFT_CASE(72)
-    default:
-      break;  // unreachable: the planner admits supported lengths only
-  }
-#undef FOCK_FFT_CASE
-}
-
-// Out-of-line copy for kernels that keep large register state live across
-// several transforms (the accumulate pass): keeps the allocator from spilling.
-template <typename C, int S, bool ROWS>
-__device__ __noinline__ void fft_lines_call(C* s, int L, int nlines, int lstride, int estride,
-                                            const C* __restrict__ twall) {
-  fft_lines<C, S, ROWS>(s, L, nlines, lstride, estride, twall);
 }
 
 }  // namespace fock

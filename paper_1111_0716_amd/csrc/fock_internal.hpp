@@ -74,6 +74,15 @@ struct FusedRounds {
   int32_t eslot = -1;
 };
 
+// The plane passes of general grids: axes, radices of axes 2 and 3 (n = a b,
+// plane_fft.hpp), LDS row pitch, and planes per tile.
+struct PlaneGeo {
+  int n1, n2, n3;
+  int a2, b2, a3, b3;
+  int pitch;
+  int g;
+};
+
 struct Instance {
   double lattice[9];
   int grid[3];
@@ -85,6 +94,9 @@ struct Instance {
   bool reg = false;                          // three-pass path with register-line kernels (N1 x L x L)
   bool slab = false;                         // cubic FP32 register-line path with the slab pencil (pair buffer [j1][c2][c3])
   int rounds = -1;                           // whole-pair path by unordered pairs: its FusedRounds
+  bool line = false;                         // three-pass path of general grids (pass_line.hip)
+  PlaneGeo pg;                               // its tiles (and those of the general DFT)
+  int pg_threads = 0;
   int nbands;
   int64_t band_stride;
   double mu;
@@ -205,7 +217,6 @@ hipError_t launch_energy_finish(const Plan& p, int inst, double* ex);
 hipError_t launch_eblk_finish(const Plan& p, int inst, double* ex);
 hipError_t launch_zero_outputs(const Plan& p, int inst, void* out);
 hipError_t launch_zero_all_bands(const Plan& p, int inst, void* out);
-void prepare_dft_kernels(fock_precision prec, int lim);
 bool reg_dft_supported(fock_precision prec, const int grid[3]);
 void prepare_reg_dft_kernels(fock_precision prec, int lim);
 hipError_t launch_reg_dft3(const Plan& p, int inst, int sign, int count, void* data, long long stride);
@@ -242,6 +253,16 @@ bool batch_apply_energy(const Plan& p, int inst);
 hipError_t launch_sum_slot(const Plan& p, long long n, int slot, double mult);
 // E_x of a three-pass instance from its apply-with-energy slots
 hipError_t launch_aslot_finish(const Plan& p, int inst, double* ex);
+// three-pass path of general grids (pass_line.hip)
+int plane_tiles(const PlaneGeo& g);
+size_t plane_lds_bytes(const PlaneGeo& g, size_t csize);
+// planes_of: pairs in flight, each with n1 planes
+void plane_geometry(const int grid[3], long long planes_of, PlaneGeo* g, int* threads);
+hipError_t launch_line_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
+                                   const double* gscale, double hscale, bool backward, bool energy);
+hipError_t launch_line_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ);
+hipError_t launch_line_dft3(const Plan& p, int inst, int sign, int count, void* data, long long stride);
+void prepare_line_kernels(fock_precision prec, int lim);
 hipError_t launch_reg_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ);
 // eblk: if not null, the apply also writes per-block energy partials there
 hipError_t launch_fused_apply(const Plan& p, const FusedGroup& g, const void* psi, const double* occ, void* out,

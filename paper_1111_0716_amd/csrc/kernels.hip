@@ -1,22 +1,7 @@
-// HIP kernels of the exchange hot path for gfx950 and their launchers.
+// Reductions and fills of the exchange hot path for gfx950, and the dispatch
+// of a batch to its path's kernels.
 //
-// One band pair (output n at k, partner m at k') is carried through three
-// passes over the FFT grid (paper, "Our Implementation": the band-pair loop
-// that runs on the GPU; "CPU Performance Analysis": FFTs, data manipulation
-// and the accumulate that make up FOCK_ACC):
-//
-//   plane pass   per j1-plane: rho = conj(u_m) u_n (coalesced reads of both
-//                orbitals), forward FFT along axis 3 then axis 2 in LDS,
-//                plane stored to the pair buffer T.
-//   pencil pass  per c2-slab [j1][c3]: forward FFT along axis 1, multiply by
-//                v_q(c)/N (apply) or accumulate sum v_q |P|^2 in FP64
-//                (energy), inverse FFT along axis 1 (apply).
-//   acc pass     per (output n, j1-plane): for every partner of the batch,
-//                inverse FFT along axis 2 then axis 3 and
-//                acc += -w_k' f_k'm u_m * W in registers; one write of the
-//                output plane per batch (no atomics, fixed order).
-//
-// Energies: per (pair, c2) partial sums in FP64, then a fixed-order tree per
+// Energies: per (pair, tile) partial sums in FP64, then a fixed-order tree per
 // batch and a compensated (Neumaier) sum over batches.
 #include <algorithm>
 
@@ -24,12 +9,6 @@
 #include "fock_internal.hpp"
 
 namespace fock {
-
-struct Geo {
-  int n1, n2, n3;
-  int nk, nbands;
-  long long bs;  // band stride in elements
-};
 
 // ---------------------------------------------------------------------------
 // deterministic block reduction of a double (kBlock threads, wave64)
@@ -46,209 +25,6 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   }
   __syncthreads();
   return t;  // valid in thread 0
-}
-
-// ---------------------------------------------------------------------------
-// plane pass
-// ---------------------------------------------------------------------------
-template <typename T, bool EXPLICIT>
-__global__ __launch_bounds__(kBlock) void k_fwd_plane(Geo g, const typename cx<T>::t* __restrict__ psi, int o0,
-                                                      int nP, const int2* __restrict__ parts,
-                                                      const PairRef* __restrict__ pairs,
-                                                      typename cx<T>::t* __restrict__ tbuf,
-                                                      const typename cx<T>::t* __restrict__ tw) {
-  using C = typename cx<T>::t;
-  extern __shared__ unsigned char smem_raw[];
-  C* s = reinterpret_cast<C*>(smem_raw);
-  const int j1 = blockIdx.x, pi = blockIdx.y;
-  int okn, pkm;  // global band indices k*nbands + n
-  if (EXPLICIT) {
-    const PairRef pr = pairs[pi];
-    okn = pr.k * g.nbands + pr.n;
-    pkm = pr.kp * g.nbands + pr.m;
-  } else {
-    const int o = pi / nP, p = pi - o * nP;
-    okn = o0 + o;
-    const int2 r = parts[p];
-    pkm = r.x * g.nbands + r.y;
-  }
-  const int plane = g.n2 * g.n3;
-  const C* a = psi + static_cast<size_t>(okn) * g.bs + static_cast<size_t>(j1) * plane;
-  const C* b = psi + static_cast<size_t>(pkm) * g.bs + static_cast<size_t>(j1) * plane;
-  for (int e = threadIdx.x; e < plane; e += kBlock) s[e] = cmulconj(b[e], a[e]);
-  __syncthreads();
-  fft_lines<C, -1, true>(s, g.n3, g.n2, g.n3, 1, tw);   // axis 3 (rows)
-  fft_lines<C, -1, false>(s, g.n2, g.n3, 1, g.n3, tw);  // axis 2 (columns)
-  C* t = tbuf + (static_cast<size_t>(pi) * g.n1 + j1) * plane;
-  for (int e = threadIdx.x; e < plane; e += kBlock) t[e] = s[e];
-}
-
-// ---------------------------------------------------------------------------
-// pencil pass, apply: FFT_1, x v_q / N, IFFT_1
-// ---------------------------------------------------------------------------
-// EN (fock_apply_energy): also w_o f_o w'_p f'_p sum v/N |P|^2 of the slab,
-// in FP64, into epart[pair * n2 + c2]
-template <typename T, bool EN = false>
-__global__ __launch_bounds__(kBlock) void k_pencil_apply(Geo g, int o0, int nP, const int2* __restrict__ parts,
-                                                         const int* __restrict__ qmap,
-                                                         typename cx<T>::t* __restrict__ tbuf,
-                                                         const T* __restrict__ vtab,
-                                                         const typename cx<T>::t* __restrict__ tw,
-                                                         const double* __restrict__ occ,
-                                                         const double* __restrict__ kw,
-                                                         double* __restrict__ epart) {
-  using C = typename cx<T>::t;
-  extern __shared__ unsigned char smem_raw[];
-  C* s = reinterpret_cast<C*>(smem_raw);
-  const int c2 = blockIdx.x, pi = blockIdx.y;
-  const int o = pi / nP, p = pi - o * nP;
-  const int ok = (o0 + o) / g.nbands;
-  const int q = qmap[ok * g.nk + parts[p].x];
-  const int plane = g.n2 * g.n3, tile = g.n1 * g.n3;
-  const size_t npts = static_cast<size_t>(g.n1) * plane;
-  C* base = tbuf + static_cast<size_t>(pi) * npts + static_cast<size_t>(c2) * g.n3;
-  const float rcp3 = 1.0f / static_cast<float>(g.n3);
-  for (int e = threadIdx.x; e < tile; e += kBlock) {
-    const int j1 = fdiv(e, rcp3), c3 = e - j1 * g.n3;
-    s[e] = base[static_cast<size_t>(j1) * plane + c3];
-  }
-  __syncthreads();
-  fft_lines<C, -1, false>(s, g.n1, g.n3, 1, g.n3, tw);  // axis 1
-  const T* v = vtab + static_cast<size_t>(q) * npts + static_cast<size_t>(c2) * g.n3;
-  double en = 0.0;
-  for (int e = threadIdx.x; e < tile; e += kBlock) {
-    const int c1 = fdiv(e, rcp3), c3 = e - c1 * g.n3;
-    const T vv = v[static_cast<size_t>(c1) * plane + c3];
-    if constexpr (EN) {
-      const double px = static_cast<double>(s[e].x), py = static_cast<double>(s[e].y);
-      en += static_cast<double>(vv) * (px * px + py * py);
-    }
-    s[e] = cscale(s[e], vv);
-  }
-  if constexpr (EN) {
-    __shared__ double red[kBlock / 64];
-    const double tot = block_sum(en, red);  // ends with a barrier
-    if (threadIdx.x == 0) {
-      const int2 r = parts[p];
-      epart[static_cast<size_t>(pi) * g.n2 + c2] =
-          kw[ok] * occ[o0 + o] * kw[r.x] * occ[r.x * g.nbands + r.y] * tot;
-    }
-  } else {
-    __syncthreads();
-  }
-  fft_lines<C, +1, false>(s, g.n1, g.n3, 1, g.n3, tw);  // inverse axis 1
-  for (int e = threadIdx.x; e < tile; e += kBlock) {
-    const int j1 = fdiv(e, rcp3), c3 = e - j1 * g.n3;
-    base[static_cast<size_t>(j1) * plane + c3] = s[e];
-  }
-}
-
-// ---------------------------------------------------------------------------
-// pencil pass, energy: FFT_1 and sum_c v_q(c)/N |P(c)|^2 in FP64
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_pencil_energy(Geo g, const PairRef* __restrict__ pairs,
-                                                          const typename cx<T>::t* __restrict__ tbuf,
-                                                          const T* __restrict__ vtab,
-                                                          const typename cx<T>::t* __restrict__ tw,
-                                                          double* __restrict__ epart) {
-  using C = typename cx<T>::t;
-  extern __shared__ unsigned char smem_raw[];
-  __shared__ double red[kBlock / 64];
-  C* s = reinterpret_cast<C*>(smem_raw);
-  const int c2 = blockIdx.x, pi = blockIdx.y;
-  const int q = pairs[pi].q;
-  const int plane = g.n2 * g.n3, tile = g.n1 * g.n3;
-  const size_t npts = static_cast<size_t>(g.n1) * plane;
-  const C* base = tbuf + static_cast<size_t>(pi) * npts + static_cast<size_t>(c2) * g.n3;
-  const float rcp3 = 1.0f / static_cast<float>(g.n3);
-  for (int e = threadIdx.x; e < tile; e += kBlock) {
-    const int j1 = fdiv(e, rcp3), c3 = e - j1 * g.n3;
-    s[e] = base[static_cast<size_t>(j1) * plane + c3];
-  }
-  __syncthreads();
-  fft_lines<C, -1, false>(s, g.n1, g.n3, 1, g.n3, tw);
-  const T* v = vtab + static_cast<size_t>(q) * npts + static_cast<size_t>(c2) * g.n3;
-  double acc = 0.0;
-  for (int e = threadIdx.x; e < tile; e += kBlock) {
-    const int c1 = fdiv(e, rcp3), c3 = e - c1 * g.n3;
-    const double px = static_cast<double>(s[e].x), py = static_cast<double>(s[e].y);
-    acc += static_cast<double>(v[static_cast<size_t>(c1) * plane + c3]) * (px * px + py * py);
-  }
-  const double tot = block_sum(acc, red);
-  if (threadIdx.x == 0) epart[static_cast<size_t>(pi) * g.n2 + c2] = tot;
-}
-
-// ---------------------------------------------------------------------------
-// accumulate pass: inverse FFT of axes 2 and 3 per partner, acc in registers
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_inv_plane_acc(Geo g, int o0, int nP, const int2* __restrict__ parts,
-                                                          const typename cx<T>::t* __restrict__ tbuf,
-                                                          const typename cx<T>::t* __restrict__ psi,
-                                                          const double* __restrict__ occ,
-                                                          const double* __restrict__ kw,
-                                                          typename cx<T>::t* __restrict__ out, int first,
-                                                          const double* __restrict__ gscale, double hscale,
-                                                          int backward, const typename cx<T>::t* __restrict__ tw) {
-  using C = typename cx<T>::t;
-  constexpr int E = (kNMax * kNMax + kBlock - 1) / kBlock;
-  extern __shared__ unsigned char smem_raw[];
-  C* s = reinterpret_cast<C*>(smem_raw);
-  const int j1 = blockIdx.x, o = blockIdx.y;
-  const int plane = g.n2 * g.n3;
-  const size_t npts = static_cast<size_t>(g.n1) * plane;
-  C acc[E];
-#pragma unroll
-  for (int i = 0; i < E; ++i) acc[i] = C{T(0), T(0)};
-  for (int p = 0; p < nP; ++p) {
-    const int2 r = parts[p];
-    const C* src = tbuf + (static_cast<size_t>(o) * nP + p) * npts + static_cast<size_t>(j1) * plane;
-    for (int e = threadIdx.x; e < plane; e += kBlock) s[e] = src[e];
-    __syncthreads();
-    fft_lines_call<C, +1, false>(s, g.n2, g.n3, 1, g.n3, tw);  // inverse axis 2
-    fft_lines_call<C, +1, true>(s, g.n3, g.n2, g.n3, 1, tw);   // inverse axis 3
-    const T coef = static_cast<T>(-kw[r.x] * occ[r.x * g.nbands + r.y]);
-    const C* um = psi + static_cast<size_t>(r.x * g.nbands + r.y) * g.bs + static_cast<size_t>(j1) * plane;
-    // elements past the plane load element 0 (in bounds) and are not used:
-    // the loads stay unconditional and overlap
-    C u[E];
-#pragma unroll
-    for (int i = 0; i < E; ++i) {
-      const int e = threadIdx.x + i * kBlock;
-      u[i] = um[e < plane ? e : 0];
-    }
-#pragma unroll
-    for (int i = 0; i < E; ++i) {
-      const int e = threadIdx.x + i * kBlock;
-      if (e < plane) {
-        const C w = cmul(u[i], s[e]);
-        acc[i].x += coef * w.x;
-        acc[i].y += coef * w.y;
-      }
-    }
-    __syncthreads();
-  }
-  const int okn = o0 + o;
-  double f = hscale;
-  if (gscale) f *= gscale[0];
-  if (backward) {
-    const int ok = okn / g.nbands;
-    f *= kw[ok] * occ[okn];
-  }
-  const T ft = static_cast<T>(f);
-  C* dst = out + static_cast<size_t>(okn) * g.bs + static_cast<size_t>(j1) * plane;
-  C old[E];
-#pragma unroll
-  for (int i = 0; i < E; ++i) {
-    const int e = threadIdx.x + i * kBlock;
-    old[i] = first ? C{T(0), T(0)} : dst[e < plane ? e : 0];  // all loads before the first store
-  }
-#pragma unroll
-  for (int i = 0; i < E; ++i) {
-    const int e = threadIdx.x + i * kBlock;
-    if (e < plane) dst[e] = cadd(old[i], cscale(acc[i], ft));
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -334,92 +110,6 @@ __global__ __launch_bounds__(kBlock) void k_zero_bands(typename cx<T>::t* __rest
 // ---------------------------------------------------------------------------
 namespace {
 
-inline Geo geo_of(const Instance& in) {
-  return Geo{in.grid[0], in.grid[1], in.grid[2], in.nk, in.nbands, static_cast<long long>(in.band_stride)};
-}
-
-template <typename T>
-hipError_t apply_batch_t(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out, bool energy,
-                         const double* gscale, double hscale, bool backward) {
-  using C = typename cx<T>::t;
-  const Instance& in = p.inst[b.inst];
-  energy = energy && batch_apply_energy(p, b.inst);
-  if (in.reg) return launch_reg_apply_batch(p, b, psi, occ, out, gscale, hscale, backward, energy);
-  const Geo g = geo_of(in);
-  const C* tw = reinterpret_cast<const C*>(p.ws + p.tw_off);
-  const int2* parts = reinterpret_cast<const int2*>(p.ws + b.part_off);
-  const int* qmap = reinterpret_cast<const int*>(p.ws + in.qmap_off);
-  const T* vtab = reinterpret_cast<const T*>(p.ws + in.vtab_off);
-  const double* kw = reinterpret_cast<const double*>(p.ws + in.kw_off);
-  C* tbuf = reinterpret_cast<C*>(p.ws + p.tbuf_off);
-  const size_t lds_plane = static_cast<size_t>(g.n2) * g.n3 * sizeof(C);
-  const size_t lds_tile = static_cast<size_t>(g.n1) * g.n3 * sizeof(C);
-  p.prof.begin(FOCK_K_PLANE, p.stream);
-  hipLaunchKernelGGL((k_fwd_plane<T, false>), dim3(g.n1, b.npairs), dim3(kBlock), lds_plane, p.stream, g,
-                     static_cast<const C*>(psi), b.o0, b.nP, parts, static_cast<const PairRef*>(nullptr), tbuf, tw);
-  p.prof.end(FOCK_K_PLANE, p.stream);
-  p.prof.begin(FOCK_K_PENCIL, p.stream);
-  if (energy)
-    hipLaunchKernelGGL((k_pencil_apply<T, true>), dim3(g.n2, b.npairs), dim3(kBlock), lds_tile, p.stream, g, b.o0,
-                       b.nP, parts, qmap, tbuf, vtab, tw, occ, kw, reinterpret_cast<double*>(p.ws + p.epart_off));
-  else
-    hipLaunchKernelGGL((k_pencil_apply<T, false>), dim3(g.n2, b.npairs), dim3(kBlock), lds_tile, p.stream, g, b.o0,
-                       b.nP, parts, qmap, tbuf, vtab, tw, occ, kw, static_cast<double*>(nullptr));
-  p.prof.end(FOCK_K_PENCIL, p.stream);
-  if (energy) {
-    const hipError_t e = launch_sum_slot(p, static_cast<long long>(b.npairs) * g.n2, b.eslot, 1.0);
-    if (e != hipSuccess) return e;
-  }
-  p.prof.begin(FOCK_K_ACCUMULATE, p.stream);
-  hipLaunchKernelGGL((k_inv_plane_acc<T>), dim3(g.n1, b.nO), dim3(kBlock), lds_plane, p.stream, g, b.o0, b.nP,
-                     parts, static_cast<const C*>(tbuf), static_cast<const C*>(psi), occ, kw, static_cast<C*>(out),
-                     b.first, gscale, hscale, backward ? 1 : 0, tw);
-  p.prof.end(FOCK_K_ACCUMULATE, p.stream);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t energy_batch_t(const Plan& p, const Batch& b, const void* psi, const double* occ) {
-  using C = typename cx<T>::t;
-  const Instance& in = p.inst[b.inst];
-  if (in.reg) return launch_reg_energy_batch(p, b, psi, occ);
-  const Geo g = geo_of(in);
-  const C* tw = reinterpret_cast<const C*>(p.ws + p.tw_off);
-  const PairRef* pairs = reinterpret_cast<const PairRef*>(p.ws + b.pair_off);
-  const T* vtab = reinterpret_cast<const T*>(p.ws + in.vtab_off);
-  C* tbuf = reinterpret_cast<C*>(p.ws + p.tbuf_off);
-  double* epart = reinterpret_cast<double*>(p.ws + p.epart_off);
-  const size_t lds_plane = static_cast<size_t>(g.n2) * g.n3 * sizeof(C);
-  const size_t lds_tile = static_cast<size_t>(g.n1) * g.n3 * sizeof(C);
-  p.prof.begin(FOCK_K_ENERGY_PLANE, p.stream);
-  hipLaunchKernelGGL((k_fwd_plane<T, true>), dim3(g.n1, b.npairs), dim3(kBlock), lds_plane, p.stream, g,
-                     static_cast<const C*>(psi), 0, 1, static_cast<const int2*>(nullptr), pairs, tbuf, tw);
-  p.prof.end(FOCK_K_ENERGY_PLANE, p.stream);
-  p.prof.begin(FOCK_K_ENERGY_PENCIL, p.stream);
-  hipLaunchKernelGGL((k_pencil_energy<T>), dim3(g.n2, b.npairs), dim3(kBlock), lds_tile, p.stream, g, pairs,
-                     static_cast<const C*>(tbuf), vtab, tw, epart);
-  p.prof.end(FOCK_K_ENERGY_PENCIL, p.stream);
-  return launch_energy_reduce(p, b, occ, g.n2);
-}
-
-
-// Dynamic LDS above 64 KiB: ask for the device's per-block limit.  The call
-// is advisory on ROCm (launches beyond 64 KiB succeed up to the hardware
-// limit); a refusal is cleared so it does not surface at an unrelated call.
-template <typename T>
-void allow_large_lds(int lim) {
-  const void* fs[] = {reinterpret_cast<const void*>(&k_fwd_plane<T, false>),
-                      reinterpret_cast<const void*>(&k_fwd_plane<T, true>),
-                      reinterpret_cast<const void*>(&k_pencil_apply<T, false>),
-                      reinterpret_cast<const void*>(&k_pencil_apply<T, true>),
-                      reinterpret_cast<const void*>(&k_pencil_energy<T>),
-                      reinterpret_cast<const void*>(&k_inv_plane_acc<T>)};
-  for (const void* f : fs) {
-    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) != hipSuccess)
-      (void)hipGetLastError();
-  }
-}
-
 template <typename T>
 hipError_t zero_outputs_t(const Plan& p, int inst, void* out) {
   using C = typename cx<T>::t;
@@ -468,24 +158,19 @@ hipError_t prepare_kernels(fock_precision prec, size_t* max_lds) {
   *max_lds = static_cast<size_t>(lim);
   prepare_fused_kernels(prec, lim - 256);
   prepare_reg_kernels(prec, lim - 64);
-  prepare_dft_kernels(prec, lim - 64);
-  if (lim > 65536) {
-    if (prec != FOCK_C64)
-      allow_large_lds<double>(lim - 64);
-    else
-      allow_large_lds<float>(lim - 64);
-  }
+  prepare_line_kernels(prec, lim - 64);
   return hipSuccess;
 }
 
 hipError_t launch_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
                               bool energy, const double* gscale, double hscale, bool backward) {
-  return p.io64() ? apply_batch_t<double>(p, b, psi, occ, out, energy, gscale, hscale, backward)
-                  : apply_batch_t<float>(p, b, psi, occ, out, energy, gscale, hscale, backward);
+  energy = energy && batch_apply_energy(p, b.inst);
+  return p.inst[b.inst].line ? launch_line_apply_batch(p, b, psi, occ, out, gscale, hscale, backward, energy)
+                             : launch_reg_apply_batch(p, b, psi, occ, out, gscale, hscale, backward, energy);
 }
 
 hipError_t launch_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ) {
-  return p.io64() ? energy_batch_t<double>(p, b, psi, occ) : energy_batch_t<float>(p, b, psi, occ);
+  return p.inst[b.inst].line ? launch_line_energy_batch(p, b, psi, occ) : launch_reg_energy_batch(p, b, psi, occ);
 }
 
 hipError_t launch_energy_reduce(const Plan& p, const Batch& b, const double* occ, int n2) {

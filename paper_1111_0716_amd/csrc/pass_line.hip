@@ -1,0 +1,603 @@
+// Three-pass kernels for every grid without a whole-pair or register-line
+// plane kernel (any {2,3,5}-smooth axes up to 72), and the batched 3-D DFT on
+// grids without register-line DFT kernels.
+//
+// The pair buffer keeps the grid's own order, T[c1][j2][j3], and only axis 1,
+// the one with the largest stride, is transformed in registers:
+//
+//   forward  thread (j2, j3): rho = conj(u_m) u_n along axis 1, FFT_1 -> T
+//   plane    workgroup (pair, planes of fixed c1): FFT_2, FFT_3, x v_q/N (the
+//            pair energies), IFFT_3, IFFT_2, all in LDS (plane_fft.hpp)
+//   acc      thread (j2, j3): for every partner of the batch IFFT_1 of its
+//            line of T, acc += -w' f' u_m W in registers; one write (or add)
+//            of the output per batch
+//
+// So the first and the last pass are compiled for one axis length and take
+// the other two at run time, their loads are contiguous over the whole plane
+// whatever its shape, and the accumulate, which runs once per ordered pair,
+// has one transform of the six and no LDS.  Lines too long for a lane's
+// registers live in a lane pair (split_fft.hpp).
+//
+// Every pass is meant to be bound by the pair buffer's traffic: one write, one
+// read and write, two reads (one per order of a pair).  Against the passes it
+// replaced (all transforms in LDS with a barrier around every radix pass,
+// ordered pairs), per call: 24x24x60, 3x3x1 k, 12 bands, FP32 step 27.8 -> 4.5
+// ms; 36x40x45, 2x1x1 k, 16 bands, FP64 apply 4.55 -> 0.80 ms; twelve uneven
+// Gamma cells of 16 to 40 points a side, FP32 4.23 -> 1.22 ms; 160 DFTs of
+// 48^3 FP64 498 -> 319 us.
+#include <algorithm>
+
+#include "fft_lds.hpp"
+#include "fock_internal.hpp"
+#include "pass_common.hpp"
+#include "plane_fft.hpp"
+#include "reg_fft.hpp"
+#include "split_fft.hpp"
+
+namespace fock {
+
+// A line of L in one lane, or half of it in each lane of a pair where line
+// (and accumulator) would take more registers than half a SIMD's.
+template <typename T, int L>
+struct LineShape {
+  static constexpr int REGS = L * static_cast<int>(2 * sizeof(T)) / 4;
+  static constexpr bool FP32 = sizeof(T) == 4;
+  static constexpr bool SPLIT_FWD = L % 2 == 0 && REGS > 144;
+  static constexpr bool SPLIT_ACC = L % 2 == 0 && (FP32 ? L == 60 || L == 64 : REGS > 80);
+  static constexpr int FWD_REGS = SPLIT_FWD ? REGS / 2 : REGS;
+  static constexpr int ACC_REGS = SPLIT_ACC ? REGS / 2 : REGS;
+  // waves per SIMD (register budget 512 / WPE)
+  static constexpr int WPE_FWD = FWD_REGS <= 144 ? 2 : 1;
+  static constexpr int WPE_ACC = 2 * ACC_REGS <= 160 ? 2 : 1;
+};
+
+// Item of workgroup b when `total` items are dealt to the eight XCDs in
+// contiguous runs (workgroups go to the XCDs in turn): neighbouring items,
+// which share orbital slices, then share an L2.  >= total: no item.
+__device__ __forceinline__ unsigned xcd_item(unsigned b, unsigned total) {
+  return (b & 7u) * ((total + 7u) >> 3) + (b >> 3);
+}
+inline unsigned xcd_grid(unsigned total) { return ((total + 7u) >> 3) * 8u; }
+
+// x[j] = conj(b[j * stride]) a[j * stride] at the lane's byte offset o (a and
+// b wave-uniform); see load_codensity_line
+template <typename C, int L>
+__device__ __forceinline__ void load_codensity_u(C* x, const C* __restrict__ a, const C* __restrict__ b, unsigned o,
+                                                 size_t stride) {
+  constexpr int B = batch_of(L, kRegB);
+  constexpr int NB = L / B;
+#pragma unroll
+  for (int j = 0; j < L; ++j) x[j] = *lane_at(a + j * stride, o);
+  C bb[2][B];
+#pragma unroll
+  for (int j = 0; j < B; ++j) bb[0][j] = *lane_at(b + j * stride, o);
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    if (n + 1 < NB) {
+#pragma unroll
+      for (int j = 0; j < B; ++j) bb[(n + 1) & 1][j] = *lane_at(b + ((n + 1) * B + j) * stride, o);
+    }
+    reg_fence();
+#pragma unroll
+    for (int j = 0; j < B; ++j) x[n * B + j] = cmulconj(bb[n & 1][j], x[n * B + j]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// forward pass: rho = conj(u_m) u_n, FFT along axis 1, T[c1][j2][j3]
+// ---------------------------------------------------------------------------
+// items (line block, pair), pairs fastest; pairs not null: the explicit pair
+// list of an energy batch
+template <typename T, int L>
+__global__ __launch_bounds__(256, (LineShape<T, L>::WPE_FWD)) void k_line_fwd(
+    int plane, int npairs, unsigned total, int nbands, long long bs, const typename cx<T>::t* __restrict__ psi, int o0,
+    int nP, int tri, const int2* __restrict__ parts, const PairRef* __restrict__ pairs,
+    typename cx<T>::t* __restrict__ tbuf) {
+  using C = typename cx<T>::t;
+  constexpr bool SPLIT = LineShape<T, L>::SPLIT_FWD;
+  constexpr int LN = SPLIT ? L / 2 : L;
+  const unsigned it = xcd_item(blockIdx.x, total);
+  if (it >= total) return;
+  const int lb = it / npairs, pi = it - lb * npairs;
+  const int id = lb * blockDim.x + threadIdx.x;
+  const int l = SPLIT ? id >> 1 : id, h = SPLIT ? id & 1 : 0;
+  if (l >= plane) return;  // both lanes of a pair together; no barrier in this kernel
+  int okn, pkm;
+  if (pairs) {
+    const PairRef pr = pairs[pi];
+    okn = pr.k * nbands + pr.n;
+    pkm = pr.kp * nbands + pr.m;
+  } else {
+    int o, p;
+    batch_pair(pi, nP, tri, &o, &p);
+    okn = o0 + o;
+    const int2 r = parts[p];
+    pkm = r.x * nbands + r.y;
+  }
+  C x[LN];
+  const unsigned lo = (static_cast<unsigned>(h) * plane + l) * sizeof(C);  // split: samples j1 = 2m + h
+  load_codensity_u<C, LN>(x, psi + static_cast<size_t>(okn) * bs, psi + static_cast<size_t>(pkm) * bs, lo,
+                          static_cast<size_t>(SPLIT ? 2 : 1) * plane);
+  if constexpr (SPLIT)
+    split_fft_fwd<C, L>(x, h);  // x[k] at c1 = h L/2 + k
+  else
+    reg_fft<C, L, -1>(x);
+  C* base = tbuf + static_cast<size_t>(pi) * plane * L;
+  const unsigned so = opaque((static_cast<unsigned>(h) * LN * plane + l) * sizeof(C));
+#pragma unroll
+  for (int k = 0; k < LN; ++k) *lane_at(base + static_cast<size_t>(k) * plane, so) = x[k];
+}
+
+// ---------------------------------------------------------------------------
+// plane pass: axes 2 and 3 forward, x v_q/N, and back, in place
+// ---------------------------------------------------------------------------
+// EN: the weighted pair energies into epart[pair * tiles + tile]; BACK: the
+// inverse transforms (an energy batch has neither weights nor a way back).
+// What the pass has to do is one read and one write of the tile; the rest are
+// six LDS round trips of the values.
+template <typename T, bool EN, bool BACK>
+__global__ __launch_bounds__(512, 4) void k_plane_pair(PlaneGeo g, int nbands, int nk, int o0, int nP, int tri,
+                                                        const int2* __restrict__ parts, const int* __restrict__ qmap,
+                                                        const PairRef* __restrict__ pairs,
+                                                        typename cx<T>::t* __restrict__ tbuf,
+                                                        const T* __restrict__ vtab,
+                                                        const typename cx<T>::t* __restrict__ tw2,
+                                                        const typename cx<T>::t* __restrict__ tw3,
+                                                        const double* __restrict__ occ, const double* __restrict__ kw,
+                                                        double* __restrict__ epart) {
+  using C = typename cx<T>::t;
+  extern __shared__ unsigned char smem_raw[];
+  C* t2 = reinterpret_cast<C*>(smem_raw);  // twiddles of the two axes, then the tile
+  C* t3 = t2 + g.n2;
+  C* s = t3 + g.n3;
+  const int pi = blockIdx.x, tile = blockIdx.y, g0 = tile * g.g, gc = min(g.g, g.n1 - g0);
+  const int plane = g.n2 * g.n3, rows = gc * g.n2;
+  int q;
+  double w = 1.0;
+  if constexpr (BACK) {
+    int o, p;
+    batch_pair(pi, nP, tri, &o, &p);
+    const int ok = (o0 + o) / nbands;
+    const int2 r = parts[p];
+    q = qmap[ok * nk + r.x];
+    // an unordered pair of a block with itself stands for both orders
+    if constexpr (EN) w = (tri && o != p ? 2.0 : 1.0) * kw[ok] * occ[o0 + o] * kw[r.x] * occ[r.x * nbands + r.y];
+  } else {
+    q = pairs[pi].q;
+  }
+  for (int i = threadIdx.x; i < g.n2 + g.n3; i += blockDim.x) t2[i] = i < g.n2 ? tw2[i] : tw3[i - g.n2];
+  C* t = tbuf + (static_cast<size_t>(pi) * g.n1 + g0) * plane;
+  const T* v = vtab + (static_cast<size_t>(q) * g.n1 + g0) * plane;
+  const int ra = g.a2 > 1 ? g.a2 : g.b2;  // the pass that touches memory
+  FOCK_RADIX(ra, (ax2_load<R, -1, C>(s, t, g, gc, tw2)))
+  __syncthreads();
+  if (g.a2 > 1) {
+    FOCK_RADIX(g.b2, (ax2_b<R, -1, C>(s, g, gc)))
+    __syncthreads();
+  }
+  if (g.a3 > 1) {
+    FOCK_RADIX(g.a3, (ax3_a<R, -1, false, C>(s, g, rows, t3)))
+    __syncthreads();
+  }
+  double e = 0.0;
+  FOCK_RADIX(g.b3, (ax3_kernel<R, EN, BACK, C, T>(s, g, rows, v, &e)))
+  if constexpr (BACK) {
+    __syncthreads();
+    if (g.a3 > 1) {
+      FOCK_RADIX(g.a3, (ax3_a<R, +1, true, C>(s, g, rows, t3)))
+      __syncthreads();
+    }
+    if (g.a2 > 1) {
+      FOCK_RADIX(g.b2, (ax2_b<R, +1, C>(s, g, gc)))
+      __syncthreads();
+    }
+    FOCK_RADIX(ra, (ax2_store<R, +1, C>(s, t, g, gc, t2)))
+  }
+  if constexpr (EN) {  // fixed order: across the lanes, then the waves in turn
+    __shared__ double red[8];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) e += __shfl_xor(e, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = e;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double sum = 0.0;
+      for (unsigned i = 0; i < blockDim.x / 64; ++i) sum += red[i];
+      epart[static_cast<size_t>(pi) * gridDim.y + tile] = w * sum;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// accumulate pass (rows and partners as in acc_source)
+// ---------------------------------------------------------------------------
+// One wave per item (line block, row), rows fastest: the waves of one line
+// block, which read the same slices of the partners' orbitals at about the
+// same time, run on one XCD and take them from its L2.
+template <typename T, int L>
+__global__ __launch_bounds__(64, (LineShape<T, L>::WPE_ACC)) void k_line_acc(
+    int plane, int rows, unsigned total, int nbands, long long bs, int o0, int nO, int nP, int tri,
+    const int2* __restrict__ parts, const typename cx<T>::t* __restrict__ tbuf,
+    const typename cx<T>::t* __restrict__ psi, const double* __restrict__ occ, const double* __restrict__ kw,
+    typename cx<T>::t* __restrict__ out, int first, int first_mirror, const double* __restrict__ gscale, double hscale,
+    int backward) {
+  using C = typename cx<T>::t;
+  using Sh = LineShape<T, L>;
+  constexpr bool SPLIT = Sh::SPLIT_ACC;
+  constexpr int LN = SPLIT ? L / 2 : L;
+  constexpr int B = batch_of(LN, Sh::WPE_ACC == 1 ? 16 : kRegB);
+  constexpr int NB = LN / B;
+  const unsigned it = xcd_item(blockIdx.x, total);
+  if (it >= total) return;
+  const int lb = it / rows, row = it - lb * rows;
+  const int id = lb * 64 + static_cast<int>(threadIdx.x);
+  const int l = SPLIT ? id >> 1 : id, h = SPLIT ? id & 1 : 0;
+  if (l >= plane) return;  // both lanes of a pair together; no barrier in this kernel
+  const bool mirror = row >= nO;
+  const int o = mirror ? row - nO : row;
+  const int nsrc = mirror ? nO : nP;
+  const unsigned lt = (static_cast<unsigned>(h) * LN * plane + l) * sizeof(C);  // split: c1 = h L/2 + k
+  const unsigned lu = (static_cast<unsigned>(h) * plane + l) * sizeof(C);       // split: j1 = 2m + h
+  const size_t us = static_cast<size_t>(SPLIT ? 2 : 1) * plane;
+  C acc[LN];
+#pragma unroll
+  for (int j = 0; j < LN; ++j) acc[j] = C{T(0), T(0)};
+  for (int p = 0; p < nsrc; ++p) {
+    int sb;
+    size_t pair;
+    bool cj;
+    acc_source(mirror, p, o, o0, nP, tri, nbands, parts, &sb, &pair, &cj);
+    const C* src = tbuf + pair * plane * L;
+    C x[LN];
+#pragma unroll
+    for (int k = 0; k < LN; ++k) x[k] = *lane_at(src + static_cast<size_t>(k) * plane, lt);
+    if constexpr (SPLIT)
+      split_fft_inv<C, L>(x, h);
+    else
+      reg_fft<C, L, +1>(x);
+    if (cj) {
+#pragma unroll
+      for (int j = 0; j < LN; ++j) x[j].y = -x[j].y;
+    }
+    const T coef = static_cast<T>(-kw[sb / nbands] * occ[sb]);
+    const C* um = psi + static_cast<size_t>(sb) * bs;
+    C mb[2][B];
+#pragma unroll
+    for (int j = 0; j < B; ++j) mb[0][j] = *lane_at(um + j * us, lu);
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      if (n + 1 < NB) {
+#pragma unroll
+        for (int j = 0; j < B; ++j) mb[(n + 1) & 1][j] = *lane_at(um + ((n + 1) * B + j) * us, lu);
+      }
+      reg_fence();
+#pragma unroll
+      for (int j = 0; j < B; ++j) {
+        const C w = cmul(mb[n & 1][j], x[n * B + j]);
+        acc[n * B + j].x += coef * w.x;
+        acc[n * B + j].y += coef * w.y;
+      }
+    }
+  }
+  const int okn = mirror ? parts[o].x * nbands + parts[o].y : o0 + o;
+  double f = hscale;
+  if (gscale) f *= gscale[0];
+  if (backward) f *= kw[okn / nbands] * occ[okn];
+  const T ft = static_cast<T>(f);
+  C* dst = out + static_cast<size_t>(okn) * bs;
+  if (!(mirror ? first_mirror : first)) {
+    C old[LN];  // loaded before the first store, so the loads overlap
+#pragma unroll
+    for (int j = 0; j < LN; ++j) old[j] = *lane_at(dst + j * us, lu);
+#pragma unroll
+    for (int j = 0; j < LN; ++j) *lane_at(dst + j * us, lu) = cadd(old[j], cscale(acc[j], ft));
+  } else {
+#pragma unroll
+    for (int j = 0; j < LN; ++j) *lane_at(dst + j * us, lu) = cscale(acc[j], ft);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// plain batched 3-D DFT in the natural layout
+// ---------------------------------------------------------------------------
+// axis 1 of line (j2, j3) = l, coalesced across lanes
+template <typename T, int L, int S>
+__global__ __launch_bounds__(256, (LineShape<T, L>::WPE_FWD)) void k_dft_line(int plane,
+                                                                              typename cx<T>::t* __restrict__ data,
+                                                                              long long stride) {
+  using C = typename cx<T>::t;
+  constexpr bool SPLIT = LineShape<T, L>::SPLIT_FWD;
+  constexpr int LN = SPLIT ? L / 2 : L;
+  const int id = blockIdx.x * blockDim.x + threadIdx.x;
+  const int l = SPLIT ? id >> 1 : id, h = SPLIT ? id & 1 : 0;
+  if (l >= plane) return;
+  C* d = data + static_cast<size_t>(blockIdx.y) * stride;
+  // split lines: samples 2m + h and half spectra h L/2 + k, in the order the transform takes and gives
+  const unsigned eo = (static_cast<unsigned>(h) * plane + l) * sizeof(C);
+  const unsigned hf = (static_cast<unsigned>(h) * LN * plane + l) * sizeof(C);
+  const size_t s1 = static_cast<size_t>(plane), s2 = static_cast<size_t>(SPLIT ? 2 : 1) * plane;
+  C x[LN];
+#pragma unroll
+  for (int j = 0; j < LN; ++j) x[j] = *lane_at(d + j * (S < 0 ? s2 : s1), S < 0 ? eo : hf);
+  if constexpr (!SPLIT)
+    reg_fft<C, L, S>(x);
+  else if constexpr (S < 0)
+    split_fft_fwd<C, L>(x, h);
+  else
+    split_fft_inv<C, L>(x, h);
+  const unsigned so = opaque(S < 0 ? hf : eo);
+#pragma unroll
+  for (int j = 0; j < LN; ++j) *lane_at(d + j * (S < 0 ? s1 : s2), so) = x[j];
+}
+
+// axes 2 and 3 of a tile of planes; the frequencies leave LDS in order
+template <typename T, int S>
+__global__ __launch_bounds__(512, 4) void k_dft_plane(PlaneGeo g, typename cx<T>::t* __restrict__ data, long long stride,
+                                                      const typename cx<T>::t* __restrict__ tw2,
+                                                      const typename cx<T>::t* __restrict__ tw3) {
+  using C = typename cx<T>::t;
+  extern __shared__ unsigned char smem_raw[];
+  C* t3 = reinterpret_cast<C*>(smem_raw);
+  C* s = t3 + g.n3;
+  const int g0 = blockIdx.x * g.g, gc = min(g.g, g.n1 - g0);
+  const int plane = g.n2 * g.n3, rows = gc * g.n2;
+  for (int i = threadIdx.x; i < g.n3; i += blockDim.x) t3[i] = tw3[i];
+  C* t = data + static_cast<size_t>(blockIdx.y) * stride + static_cast<size_t>(g0) * plane;
+  FOCK_RADIX((g.a2 > 1 ? g.a2 : g.b2), (ax2_load<R, S, C>(s, t, g, gc, tw2)))
+  __syncthreads();
+  if (g.a2 > 1) {
+    FOCK_RADIX(g.b2, (ax2_b<R, S, C>(s, g, gc)))
+    __syncthreads();
+  }
+  if (g.a3 > 1) {
+    FOCK_RADIX(g.a3, (ax3_a<R, S, false, C>(s, g, rows, t3)))
+    __syncthreads();
+  }
+  FOCK_RADIX(g.b3, (ax3_b<R, S, C>(s, g, rows)))
+  __syncthreads();
+  const float r3 = 1.0f / static_cast<float>(g.n3), r2 = 1.0f / static_cast<float>(g.n2);
+  const float ra2 = 1.0f / static_cast<float>(g.a2), ra3 = 1.0f / static_cast<float>(g.a3);
+  for (int e = threadIdx.x; e < gc * plane; e += blockDim.x) {
+    const int row = fdiv(e, r3), c3 = e - row * g.n3;
+    const int gg = fdiv(row, r2), c2 = row - gg * g.n2;
+    const int k2 = fdiv(c2, ra2), k3 = fdiv(c3, ra3);  // c = (c mod a) + a k at position (c mod a) b + k
+    t[e] = s[(gg * g.n2 + (c2 - k2 * g.a2) * g.b2 + k2) * g.pitch + (c3 - k3 * g.a3) * g.b3 + k3];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// launchers
+// ---------------------------------------------------------------------------
+namespace {
+
+// every {2,3,5}-smooth axis length
+#define FOCK_SMOOTH_L(X)                                                                                       \
+  X(2) X(3) X(4) X(5) X(6) X(8) X(9) X(10) X(12) X(15) X(16) X(18) X(20) X(24) X(25) X(27) X(30) X(32) X(36) \
+  X(40) X(45) X(48) X(50) X(54) X(60) X(64) X(72)
+
+size_t plane_lds(const PlaneGeo& g, size_t csize) {
+  return (static_cast<size_t>(g.g) * g.n2 * g.pitch + g.n2 + g.n3) * csize;
+}
+
+template <typename T, int L>
+void line_fwd_L(const Plan& p, const Batch& b, const Instance& in, const void* psi, const int2* parts,
+                const PairRef* pairs, typename cx<T>::t* tbuf) {
+  const int plane = in.grid[1] * in.grid[2];
+  const int lanes = plane * (LineShape<T, L>::SPLIT_FWD ? 2 : 1);
+  const int nt = std::min(256, (lanes + 63) / 64 * 64);
+  const unsigned total = static_cast<unsigned>((lanes + nt - 1) / nt) * b.npairs;
+  hipLaunchKernelGGL((k_line_fwd<T, L>), dim3(xcd_grid(total)), dim3(nt), 0, p.stream, plane, b.npairs, total,
+                     in.nbands, static_cast<long long>(in.band_stride), static_cast<const typename cx<T>::t*>(psi),
+                     b.o0, b.nP, b.tri, parts, pairs, tbuf);
+}
+
+template <typename T, int L>
+void line_acc_L(const Plan& p, const Batch& b, const Instance& in, const int2* parts, const typename cx<T>::t* tbuf,
+                const void* psi, const double* occ, const double* kw, void* out, const double* gscale, double hscale,
+                bool backward) {
+  using C = typename cx<T>::t;
+  const int plane = in.grid[1] * in.grid[2];
+  const int lanes = plane * (LineShape<T, L>::SPLIT_ACC ? 2 : 1);
+  const int rows = b.nO + (b.mirror ? b.nP : 0);
+  const unsigned total = static_cast<unsigned>((lanes + 63) / 64) * rows;
+  hipLaunchKernelGGL((k_line_acc<T, L>), dim3(xcd_grid(total)), dim3(64), 0, p.stream, plane, rows, total, in.nbands,
+                     static_cast<long long>(in.band_stride), b.o0, b.nO, b.nP, b.tri, parts, tbuf,
+                     static_cast<const C*>(psi), occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale,
+                     hscale, backward ? 1 : 0);
+}
+
+template <typename T>
+hipError_t line_fwd(const Plan& p, const Batch& b, const Instance& in, const void* psi, const int2* parts,
+                    const PairRef* pairs, typename cx<T>::t* tbuf) {
+  switch (in.grid[0]) {
+#define CASE(N) \
+  case N: line_fwd_L<T, N>(p, b, in, psi, parts, pairs, tbuf); break;
+    FOCK_SMOOTH_L(CASE)
+#undef CASE
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t line_apply_t(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
+                        const double* gscale, double hscale, bool backward, bool energy) {
+  using C = typename cx<T>::t;
+  const Instance& in = p.inst[b.inst];
+  const PlaneGeo& g = in.pg;
+  const int2* parts = reinterpret_cast<const int2*>(p.ws + b.part_off);
+  const int* qmap = reinterpret_cast<const int*>(p.ws + in.qmap_off);
+  const T* vtab = reinterpret_cast<const T*>(p.ws + in.vtab_off);
+  const double* kw = reinterpret_cast<const double*>(p.ws + in.kw_off);
+  const C* tw = reinterpret_cast<const C*>(p.ws + p.tw_off);
+  C* tbuf = reinterpret_cast<C*>(p.ws + p.tbuf_off);
+  double* epart = reinterpret_cast<double*>(p.ws + p.epart_off);
+  p.prof.begin(FOCK_K_PLANE, p.stream);
+  hipError_t e = line_fwd<T>(p, b, in, psi, parts, nullptr, tbuf);
+  p.prof.end(FOCK_K_PLANE, p.stream);
+  if (e != hipSuccess) return e;
+  const int tiles = plane_tiles(g);
+  const dim3 grid(b.npairs, tiles);
+  const C *tw2 = tw + twiddle_offset(g.n2), *tw3 = tw + twiddle_offset(g.n3);
+  p.prof.begin(FOCK_K_PENCIL, p.stream);
+  if (energy)
+    hipLaunchKernelGGL((k_plane_pair<T, true, true>), grid, dim3(in.pg_threads), plane_lds(g, sizeof(C)), p.stream, g,
+                       in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, static_cast<const PairRef*>(nullptr), tbuf,
+                       vtab, tw2, tw3, occ, kw, epart);
+  else
+    hipLaunchKernelGGL((k_plane_pair<T, false, true>), grid, dim3(in.pg_threads), plane_lds(g, sizeof(C)), p.stream, g,
+                       in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, static_cast<const PairRef*>(nullptr), tbuf,
+                       vtab, tw2, tw3, occ, kw, epart);
+  p.prof.end(FOCK_K_PENCIL, p.stream);
+  if (energy) {
+    e = launch_sum_slot(p, static_cast<long long>(b.npairs) * tiles, b.eslot, b.mirror ? 2.0 : 1.0);
+    if (e != hipSuccess) return e;
+  }
+  p.prof.begin(FOCK_K_ACCUMULATE, p.stream);
+  switch (g.n1) {
+#define CASE(N) \
+  case N: line_acc_L<T, N>(p, b, in, parts, tbuf, psi, occ, kw, out, gscale, hscale, backward); break;
+    FOCK_SMOOTH_L(CASE)
+#undef CASE
+    default: return hipErrorInvalidValue;
+  }
+  p.prof.end(FOCK_K_ACCUMULATE, p.stream);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t line_energy_t(const Plan& p, const Batch& b, const void* psi, const double* occ) {
+  using C = typename cx<T>::t;
+  const Instance& in = p.inst[b.inst];
+  const PlaneGeo& g = in.pg;
+  const PairRef* pairs = reinterpret_cast<const PairRef*>(p.ws + b.pair_off);
+  const C* tw = reinterpret_cast<const C*>(p.ws + p.tw_off);
+  C* tbuf = reinterpret_cast<C*>(p.ws + p.tbuf_off);
+  p.prof.begin(FOCK_K_ENERGY_PLANE, p.stream);
+  const hipError_t e = line_fwd<T>(p, b, in, psi, nullptr, pairs, tbuf);
+  p.prof.end(FOCK_K_ENERGY_PLANE, p.stream);
+  if (e != hipSuccess) return e;
+  const int tiles = plane_tiles(g);
+  p.prof.begin(FOCK_K_ENERGY_PENCIL, p.stream);
+  hipLaunchKernelGGL((k_plane_pair<T, true, false>), dim3(b.npairs, tiles), dim3(in.pg_threads),
+                     plane_lds(g, sizeof(C)), p.stream, g, in.nbands, in.nk, 0, 1, 0,
+                     static_cast<const int2*>(nullptr), static_cast<const int*>(nullptr), pairs, tbuf,
+                     reinterpret_cast<const T*>(p.ws + in.vtab_off), tw + twiddle_offset(g.n2),
+                     tw + twiddle_offset(g.n3), occ, static_cast<const double*>(nullptr),
+                     reinterpret_cast<double*>(p.ws + p.epart_off));
+  p.prof.end(FOCK_K_ENERGY_PENCIL, p.stream);
+  return launch_energy_reduce(p, b, occ, tiles);
+}
+
+template <typename T, int L, int S>
+void dft_line_L(const Plan& p, int plane, int count, typename cx<T>::t* d, long long stride) {
+  const int lanes = plane * (LineShape<T, L>::SPLIT_FWD ? 2 : 1);
+  const int nt = std::min(256, (lanes + 63) / 64 * 64);
+  hipLaunchKernelGGL((k_dft_line<T, L, S>), dim3((lanes + nt - 1) / nt, count), dim3(nt), 0, p.stream, plane, d, stride);
+}
+
+template <typename T, int S>
+hipError_t line_dft3_t(const Plan& p, const Instance& in, int count, void* data, long long stride) {
+  using C = typename cx<T>::t;
+  const PlaneGeo& g = in.pg;
+  C* d = static_cast<C*>(data);
+  const C* tw = reinterpret_cast<const C*>(p.ws + p.tw_off);
+  hipLaunchKernelGGL((k_dft_plane<T, S>), dim3(plane_tiles(g), count), dim3(in.pg_threads), plane_lds(g, sizeof(C)),
+                     p.stream, g, d, stride, tw + twiddle_offset(g.n2), tw + twiddle_offset(g.n3));
+  switch (g.n1) {
+#define CASE(N) \
+  case N: dft_line_L<T, N, S>(p, g.n2 * g.n3, count, d, stride); break;
+    FOCK_SMOOTH_L(CASE)
+#undef CASE
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <typename T>
+void plane_lds_attr(int lim) {
+  const void* fs[] = {reinterpret_cast<const void*>(&k_plane_pair<T, true, true>),
+                      reinterpret_cast<const void*>(&k_plane_pair<T, false, true>),
+                      reinterpret_cast<const void*>(&k_plane_pair<T, true, false>),
+                      reinterpret_cast<const void*>(&k_dft_plane<T, -1>),
+                      reinterpret_cast<const void*>(&k_dft_plane<T, +1>)};
+  for (const void* f : fs)
+    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) != hipSuccess) (void)hipGetLastError();
+}
+
+// n = a b with both at most 10 (never 7), the least a + b; a = 1 if n itself is one radix
+void radix_pair(int n, int* a, int* b) {
+  *a = 1;
+  *b = n;
+  if (n <= 10) return;
+  int best = 1000;
+  for (int x = 2; x <= 10; ++x) {
+    if (n % x != 0 || x == 7 || n / x > 10 || n / x < x) continue;
+    if (x + n / x < best) {
+      best = x + n / x;
+      *a = x;
+      *b = n / x;
+    }
+  }
+}
+
+}  // namespace
+
+int plane_tiles(const PlaneGeo& g) { return (g.n1 + g.g - 1) / g.g; }
+
+size_t plane_lds_bytes(const PlaneGeo& g, size_t csize) { return plane_lds(g, csize); }
+
+// Tile and workgroup of the plane passes.  A tile is as many whole planes as
+// make about 2048 points (small planes alone would not fill a workgroup), but
+// never so many that fewer than 1024 workgroups are left while a tile holds
+// more than one plane.
+void plane_geometry(const int grid[3], long long planes_of, PlaneGeo* g, int* threads) {
+  g->n1 = grid[0];
+  g->n2 = grid[1];
+  g->n3 = grid[2];
+  radix_pair(g->n2, &g->a2, &g->b2);
+  radix_pair(g->n3, &g->a3, &g->b3);
+  g->pitch = g->n3 | 1;
+  g->g = std::max(1, std::min(g->n1, 2048 / (g->n2 * g->n3)));
+  while (g->g > 1 && planes_of * plane_tiles(*g) < 1024) g->g = (g->g + 1) / 2;
+  // the workgroup size with the fewest lane slots over the passes, a round of
+  // any pass costing about 96 lanes' worth of waiting besides
+  const int pts = g->g * g->n2 * g->n3;
+  long long best = -1;
+  for (int nt = 64; nt <= 512; nt += 64) {
+    long long cost = 0;
+    for (int r : {g->a2, g->b2, g->a3, g->b3})
+      if (r > 1) cost += ((pts / r + nt - 1) / nt) * static_cast<long long>(nt + 96);
+    if (best < 0 || cost < best) {
+      best = cost;
+      *threads = nt;
+    }
+  }
+}
+
+hipError_t launch_line_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
+                                   const double* gscale, double hscale, bool backward, bool energy) {
+  return p.io64() ? line_apply_t<double>(p, b, psi, occ, out, gscale, hscale, backward, energy)
+                  : line_apply_t<float>(p, b, psi, occ, out, gscale, hscale, backward, energy);
+}
+
+hipError_t launch_line_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ) {
+  return p.io64() ? line_energy_t<double>(p, b, psi, occ) : line_energy_t<float>(p, b, psi, occ);
+}
+
+hipError_t launch_line_dft3(const Plan& p, int inst, int sign, int count, void* data, long long stride) {
+  const Instance& in = p.inst[inst];
+  if (p.io64())
+    return sign < 0 ? line_dft3_t<double, -1>(p, in, count, data, stride)
+                    : line_dft3_t<double, +1>(p, in, count, data, stride);
+  return sign < 0 ? line_dft3_t<float, -1>(p, in, count, data, stride)
+                  : line_dft3_t<float, +1>(p, in, count, data, stride);
+}
+
+void prepare_line_kernels(fock_precision prec, int lim) {
+  if (prec == FOCK_C64)
+    plane_lds_attr<float>(lim);
+  else
+    plane_lds_attr<double>(lim);
+}
+
+}  // namespace fock

@@ -318,10 +318,18 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
     const bool mixed = prec == FOCK_MIXED || prec == FOCK_MIXED_INV;
     in.fused = !mixed && fused_supported(prec, in.grid) && !no_fused && !sym_three_pass;
     in.reg = !in.fused && reg_supported(prec, in.grid) && !no_reg;
+    in.line = !in.fused && !in.reg;
     in.slab = in.reg && (slab_force < 0 ? reg_slab_default(prec, in.grid)
                                         : slab_force == 1 && reg_slab_supported(prec, in.grid));
     if (mixed && !in.reg)
       return set_error(FOCK_ERR_UNSUPPORTED, "mixed precision needs a grid N1 x L x L with N1 and L in {24, 32, 36, 40, 48, 50, 54, 60, 64, 72}");
+  }
+
+  // tiles of the plane passes: the pair kernels of the line path, the DFT of
+  // the others (a grid per band)
+  for (auto& in : p->inst) {
+    const long long orb = static_cast<long long>(in.nk) * in.nbands;
+    plane_geometry(in.grid, in.line ? orb * (orb + 1) / 2 : orb, &in.pg, &in.pg_threads);
   }
 
   // ---- batch shapes ----
@@ -430,7 +438,12 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
     }
     const size_t pair_bytes = static_cast<size_t>(in.npts) * p->csize;
     const int pmax = static_cast<int>(std::max<size_t>(1, std::min<size_t>(65535, tbuf_target / pair_bytes)));
-    if (in.reg && !no_sym && g.k0 == 0 && g.k1 == in.nk && full_kset(in)) {
+    // Unordered pairs halve the transforms.  A call of at most 32768 points in
+    // all its ordered pairs is the time of its launches either way (12x10x9,
+    // two k-points of three bands, 38880 points: 27.3 us with unordered and
+    // 27.5 with ordered pairs; 8^3, 18432 points, 27.6) and keeps the plain order.
+    const bool tiny = in.line && static_cast<int64_t>(nout) * npart * in.npts <= 32768;
+    if (!no_sym && !tiny && g.k0 == 0 && g.k1 == in.nk && full_kset(in)) {
       // Pair symmetry: W_ba = conj(W_ab) (the Nyquist-averaged kernel is even
       // in c -> -c, q -> -q), so each unordered pair is transformed once.  The
       // orbitals (partner order = global order k' nbands + m) are cut into
@@ -470,7 +483,9 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
       }
       continue;
     }
-    int nO = std::max(1, std::min(nout, (acc_wgs + in.grid[0] - 1) / in.grid[0]));
+    // outputs per batch: enough accumulate workgroups (planes, or 64-lane line blocks on the line path)
+    const int per_out = in.line ? (in.grid[1] * in.grid[2] + 63) / 64 : in.grid[0];
+    int nO = std::max(1, std::min(nout, (acc_wgs + per_out - 1) / per_out));
     nO = std::min(nO, pmax);
     const int nP = std::max(1, std::min(npart, pmax / nO));
     for (int ob = 0; ob < nout; ob += nO) {
@@ -493,7 +508,11 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   // a dedicated apply batch with no partners: not needed, the wrapper zero-fills.
   // energy pair lists
   std::vector<std::vector<PairRef>> elists(n_inst);
-  size_t max_epairs = 0, max_n2 = 0, max_fused_epairs = 0;
+  // energy partials of a three-pass batch: per pair one per line block, slab or tile
+  const auto eparts = [](const Instance& in) {
+    return static_cast<size_t>(in.line ? plane_tiles(in.pg) : in.grid[1]);
+  };
+  size_t max_eparts = 0, max_fused_epairs = 0;
   int slot = 0;
   for (int i = 0; i < n_inst; ++i) {
     Instance& in = p->inst[i];
@@ -529,17 +548,15 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
         b.per_wg = std::max(1, b.npairs / 1024);
         max_fused_epairs = std::max(max_fused_epairs, static_cast<size_t>(b.npairs));
       } else {
-        max_epairs = std::max(max_epairs, static_cast<size_t>(b.npairs));
+        max_eparts = std::max(max_eparts, static_cast<size_t>(b.npairs) * eparts(in));
         max_pairs_elems = std::max(max_pairs_elems, static_cast<size_t>(b.npairs) * in.npts);
       }
       p->energy_batches.push_back(b);
       p->energy_fft_pairs += b.npairs;
     }
-    max_n2 = std::max(max_n2, static_cast<size_t>(in.grid[1]));
   }
   // apply-with-energy sum slots: one per apply batch of a three-pass
   // instance, contiguous per instance
-  size_t max_apply_epairs = 0;
   for (int i = 0; i < n_inst; ++i) {
     Instance& in = p->inst[i];
     in.first_aslot = slot;
@@ -547,7 +564,7 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
       for (Batch& b : p->apply_batches) {
         if (b.inst != i) continue;
         b.eslot = slot++;
-        max_apply_epairs = std::max(max_apply_epairs, static_cast<size_t>(b.npairs));
+        max_eparts = std::max(max_eparts, static_cast<size_t>(b.npairs) * eparts(in));
       }
     }
     in.n_aslot = slot - in.first_aslot;
@@ -577,8 +594,8 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   off = share_scratch(true);
   const size_t scratch_fine = off;
   p->epart_off = off;
-  // per (pair, line block) energy partials: energy batches and apply-with-energy batches
-  p->epart_bytes = std::max(std::max(max_epairs, max_apply_epairs) * max_n2, max_fused_epairs) * sizeof(double);
+  // energy partials: energy batches and apply-with-energy batches
+  p->epart_bytes = std::max(max_eparts, max_fused_epairs) * sizeof(double);
   off = align_up(off + p->epart_bytes);
   p->partial_off = off;
   p->partial_bytes = max_partial;
@@ -617,10 +634,9 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   }
   p->total_bytes = off;
   for (const auto& in : p->inst) {
-    const size_t plane = static_cast<size_t>(in.grid[1]) * in.grid[2], tile = static_cast<size_t>(in.grid[0]) * in.grid[2];
     const size_t need = in.fused ? fused_lds_bytes(prec, in.grid[0]) + 256
                         : in.reg ? reg_lds_bytes(prec, in.grid[1]) + 64
-                                 : std::max(plane, tile) * p->csize + 64;
+                                 : plane_lds_bytes(in.pg, p->csize) + 64;
     p->lds_needed = std::max(p->lds_needed, need);
   }
   p->apply_launches = 0;
@@ -661,6 +677,23 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
           for (int c2 = 0; c2 < L; ++c2)
             for (int c3 = 0; c3 < L; ++c3)
               r[(static_cast<size_t>(c3) * L + c2) * L + c1] = t[(static_cast<size_t>(c1) * L + c2) * L + c3];
+        t.swap(r);
+      } else if (in.line) {
+        // line path: per tile of planes the positions of the plane passes, as
+        // [k2][k1][row] (plane_fft.hpp): row (plane, r2 b2 + i2) holds the
+        // class r2 + a2 i2 of axis 2, column (k1, k2) the class k1 + a3 k2
+        const PlaneGeo& g = in.pg;
+        const size_t plane = static_cast<size_t>(g.n2) * g.n3;
+        std::vector<double> r(t.size());
+        double* d = r.data();
+        for (int g0 = 0; g0 < g.n1; g0 += g.g)
+          for (int k2 = 0; k2 < g.b3; ++k2)
+            for (int k1 = 0; k1 < g.a3; ++k1)
+              for (int c1 = g0; c1 < std::min(g0 + g.g, g.n1); ++c1)
+                for (int p2 = 0; p2 < g.n2; ++p2) {
+                  const int c2 = p2 / g.b2 + g.a2 * (p2 % g.b2), c3 = k1 + g.a3 * k2;
+                  *d++ = t[c1 * plane + static_cast<size_t>(c2) * g.n3 + c3];
+                }
         t.swap(r);
       } else if (in.reg && !in.slab) {
         // register-line three-pass path reads the table as [c1][c3][c2]

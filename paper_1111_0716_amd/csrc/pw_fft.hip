@@ -13,52 +13,14 @@
 //
 // DFT passes: on grids N1 x L x L with register-line kernels (pass_reg.hip) a
 // plane pass (axes 2 and 3, one line per lane) and a pencil pass (axis 1);
-// elsewhere per (grid, j1-plane) the axes 3 and 2 in LDS and per (grid,
-// c2-slab) the axis 1 in LDS (the LDS Stockham transforms of fft_lds.hpp),
-// so every {2,3,5}-smooth axis up to 72 works.
+// elsewhere (pass_line.hip) the axes 3 and 2 of whole planes in LDS and the
+// axis 1 in registers, for every {2,3,5}-smooth axis up to 72.
 #include <algorithm>
 
 #include "fft_lds.hpp"
 #include "fock_internal.hpp"
 
 namespace fock {
-
-template <typename T, int S>
-__global__ __launch_bounds__(kBlock) void k_dft_planes(int n2, int n3, typename cx<T>::t* __restrict__ data,
-                                                       long long stride, long long plane0,
-                                                       const typename cx<T>::t* __restrict__ tw) {
-  using C = typename cx<T>::t;
-  extern __shared__ unsigned char smem_raw[];
-  C* s = reinterpret_cast<C*>(smem_raw);
-  const int plane = n2 * n3;
-  C* g = data + static_cast<size_t>(blockIdx.y) * stride + (plane0 + blockIdx.x) * static_cast<size_t>(plane);
-  for (int e = threadIdx.x; e < plane; e += kBlock) s[e] = g[e];
-  __syncthreads();
-  fft_lines<C, S, true>(s, n3, n2, n3, 1, tw);   // axis 3 (rows)
-  fft_lines<C, S, false>(s, n2, n3, 1, n3, tw);  // axis 2 (columns)
-  for (int e = threadIdx.x; e < plane; e += kBlock) g[e] = s[e];
-}
-
-template <typename T, int S>
-__global__ __launch_bounds__(kBlock) void k_dft_pencils(int n1, int n2, int n3, typename cx<T>::t* __restrict__ data,
-                                                        long long stride, const typename cx<T>::t* __restrict__ tw) {
-  using C = typename cx<T>::t;
-  extern __shared__ unsigned char smem_raw[];
-  C* s = reinterpret_cast<C*>(smem_raw);
-  const int c2 = blockIdx.x, plane = n2 * n3, tile = n1 * n3;
-  C* base = data + static_cast<size_t>(blockIdx.y) * stride + static_cast<size_t>(c2) * n3;
-  const float rcp3 = 1.0f / static_cast<float>(n3);
-  for (int e = threadIdx.x; e < tile; e += kBlock) {
-    const int j1 = fdiv(e, rcp3), c3 = e - j1 * n3;
-    s[e] = base[static_cast<size_t>(j1) * plane + c3];
-  }
-  __syncthreads();
-  fft_lines<C, S, false>(s, n1, n3, 1, n3, tw);  // axis 1
-  for (int e = threadIdx.x; e < tile; e += kBlock) {
-    const int j1 = fdiv(e, rcp3), c3 = e - j1 * n3;
-    base[static_cast<size_t>(j1) * plane + c3] = s[e];
-  }
-}
 
 // out[b][gidx[k][p]] = scale * coef[b][p] for p < min(npw[k], npw_max), b = k nbands + n;
 // slots whose class lies outside the grid are skipped
@@ -100,33 +62,15 @@ template <typename T>
 hipError_t dft3_t(const Plan& p, int inst, int sign, long long count, void* data, long long stride) {
   using C = typename cx<T>::t;
   const Instance& in = p.inst[inst];
-  const int n1 = in.grid[0], n2 = in.grid[1], n3 = in.grid[2];
-  const C* tw = reinterpret_cast<const C*>(p.ws + p.tw_off);
-  const size_t lds_plane = static_cast<size_t>(n2) * n3 * sizeof(C);
-  const size_t lds_tile = static_cast<size_t>(n1) * n3 * sizeof(C);
   C* d = static_cast<C*>(data);
   for (long long b0 = 0; b0 < count; b0 += 65535) {
     const int nb = static_cast<int>(std::min<long long>(65535, count - b0));
     C* db = d + static_cast<size_t>(b0) * stride;
     p.prof.begin(FOCK_K_DFT, p.stream);
-    if (reg_dft_supported(p.prec, in.grid)) {
-      const hipError_t e = launch_reg_dft3(p, inst, sign, nb, db, stride);
-      p.prof.end(FOCK_K_DFT, p.stream);
-      if (e != hipSuccess) return e;
-      continue;
-    }
-    if (sign < 0) {
-      hipLaunchKernelGGL((k_dft_planes<T, -1>), dim3(n1, nb), dim3(kBlock), lds_plane, p.stream, n2, n3, db, stride,
-                         0LL, tw);
-      hipLaunchKernelGGL((k_dft_pencils<T, -1>), dim3(n2, nb), dim3(kBlock), lds_tile, p.stream, n1, n2, n3, db,
-                         stride, tw);
-    } else {
-      hipLaunchKernelGGL((k_dft_planes<T, +1>), dim3(n1, nb), dim3(kBlock), lds_plane, p.stream, n2, n3, db, stride,
-                         0LL, tw);
-      hipLaunchKernelGGL((k_dft_pencils<T, +1>), dim3(n2, nb), dim3(kBlock), lds_tile, p.stream, n1, n2, n3, db,
-                         stride, tw);
-    }
+    const hipError_t e = reg_dft_supported(p.prec, in.grid) ? launch_reg_dft3(p, inst, sign, nb, db, stride)
+                                                            : launch_line_dft3(p, inst, sign, nb, db, stride);
     p.prof.end(FOCK_K_DFT, p.stream);
+    if (e != hipSuccess) return e;
   }
   return hipGetLastError();
 }
@@ -172,25 +116,7 @@ hipError_t grid_to_pw_t(const Plan& p, int inst, void* f, const int* gidx, const
   return hipGetLastError();
 }
 
-template <typename T>
-void dft_lds_attr(int lim) {
-  const void* fs[] = {reinterpret_cast<const void*>(&k_dft_planes<T, -1>),
-                      reinterpret_cast<const void*>(&k_dft_planes<T, +1>),
-                      reinterpret_cast<const void*>(&k_dft_pencils<T, -1>),
-                      reinterpret_cast<const void*>(&k_dft_pencils<T, +1>)};
-  for (const void* f : fs)
-    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) != hipSuccess) (void)hipGetLastError();
-}
-
 }  // namespace
-
-void prepare_dft_kernels(fock_precision prec, int lim) {
-  prepare_reg_dft_kernels(prec, lim);
-  if (prec != FOCK_C64)
-    dft_lds_attr<double>(lim);
-  else
-    dft_lds_attr<float>(lim);
-}
 
 hipError_t launch_dft3(const Plan& p, int inst, int sign, long long count, void* data, long long stride) {
   return p.io64() ? dft3_t<double>(p, inst, sign, count, data, stride)
