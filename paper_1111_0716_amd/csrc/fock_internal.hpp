@@ -79,6 +79,7 @@ struct FusedRounds {
 struct PlaneGeo {
   int n1, n2, n3;
   int a2, b2, a3, b3;
+  int tw2, tw3;  // twiddles of axes 2 and 3
   int pitch;
   int g;
 };
@@ -257,7 +258,7 @@ hipError_t launch_aslot_finish(const Plan& p, int inst, double* ex);
 int plane_tiles(const PlaneGeo& g);
 size_t plane_lds_bytes(const PlaneGeo& g, size_t csize);
 // planes_of: pairs in flight, each with n1 planes
-void plane_geometry(const int grid[3], long long planes_of, PlaneGeo* g, int* threads);
+void plane_geometry(const int grid[3], long long planes_of, size_t csize, PlaneGeo* g, int* threads);
 hipError_t launch_line_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
                                    const double* gscale, double hscale, bool backward, bool energy);
 hipError_t launch_line_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ);

@@ -2,6 +2,8 @@
 // line passes of general grids (pass_line.hip).
 #pragma once
 
+#include <type_traits>
+
 #include "fft_lds.hpp"
 
 namespace fock {
@@ -34,8 +36,11 @@ __device__ __forceinline__ void batch_pair(int pi, int nP, int tri, int* o, int*
     *p = pi - *o * nP;
     return;
   }
-  const double b = 2.0 * nP + 1.0;
-  int r = static_cast<int>((b - sqrt(b * b - 8.0 * pi)) * 0.5);
+  // FP32 estimate of the row (the block index is uniform: one scalar value),
+  // then exact
+  const float b = 2.0f * nP + 1.0f;
+  int r = static_cast<int>((b - __builtin_amdgcn_sqrtf(fmaxf(b * b - 8.0f * pi, 0.0f))) * 0.5f);
+  r = __builtin_amdgcn_readfirstlane(r);
   r = r < 0 ? 0 : (r > nP - 1 ? nP - 1 : r);
   while (r > 0 && tri_slot(r, r, nP) > static_cast<size_t>(pi)) --r;
   while (r + 1 < nP && tri_slot(r + 1, r + 1, nP) <= static_cast<size_t>(pi)) ++r;
@@ -55,7 +60,72 @@ __device__ __forceinline__ C cvt(CI v) {
 // byte offset, so the loads of a line take no 64-bit address per element.
 template <typename C>
 __device__ __forceinline__ C* lane_at(C* u, unsigned o) {
-  return reinterpret_cast<C*>(reinterpret_cast<uintptr_t>(u) + o);
+  using Byte = typename std::conditional<std::is_const<C>::value, const char, char>::type;
+  return reinterpret_cast<C*>(reinterpret_cast<Byte*>(u) + o);
+}
+
+// The pair buffer goes through memory once per pass and fits no cache: its
+// accesses are marked non-temporal, so that they do not push the orbitals and
+// tables out of L2 (the accumulate's reads included, although a pair is read
+// once for each of its orders: the two reads are far apart).  Without and with,
+// per call: 32^3 4x4x4 k FP32 step 367.5 -> 336.6 ms, 32^3 2x2x2 k FP64 12.40
+// -> 11.48, 64^3 Gamma FP32 17.85 -> 17.05, 24x24x60 FP32 4.02 -> 3.70, 60^3
+// Gamma FP64 1.76 -> 1.50; 72^3 FP32 77.0 -> 76.5.  Stores alone: 344.9, 11.89,
+// 17.32, 3.82, 1.69; all but the accumulate's reads: 340.9, 11.71, 17.47, 3.76,
+// 1.66, and 0.62 against 0.65 ms at 36x40x45 FP64, whose 0.5 GB buffer lies
+// partly in the last-level cache.
+template <typename C>
+__device__ __forceinline__ C stream_load(const C* p) {
+  typedef decltype(C{}.x) V2 __attribute__((ext_vector_type(2)));
+  const V2 v = __builtin_nontemporal_load(reinterpret_cast<const V2*>(p));
+  return C{v.x, v.y};
+}
+template <typename C>
+__device__ __forceinline__ void stream_store(C* p, C a) {
+  typedef decltype(C{}.x) V2 __attribute__((ext_vector_type(2)));
+  V2 v;
+  v.x = a.x;
+  v.y = a.y;
+  __builtin_nontemporal_store(v, reinterpret_cast<V2*>(p));
+}
+// Loads and stores at a wave-uniform base plus the lane's 32-bit byte offset
+// (lane_at's addresses): the base goes through an empty asm in scalar
+// registers, so that it is formed there, and the access takes the two as they
+// are instead of one 64-bit vector addition for every element.
+template <typename V>
+__device__ __forceinline__ __attribute__((address_space(1))) V* lane_ptr(const void* u, unsigned o) {
+  typedef __attribute__((address_space(1))) char* Bytes;
+  Bytes b = (Bytes)(const_cast<void*>(u));
+  asm("" : "+s"(b));
+  return (__attribute__((address_space(1))) V*)(b + o);
+}
+template <typename R> struct lane_vec { typedef decltype(R{}.x) type __attribute__((ext_vector_type(2))); };
+template <> struct lane_vec<float> { typedef float type; };
+template <> struct lane_vec<double> { typedef double type; };
+template <typename R, typename V>
+__device__ __forceinline__ R from_vec(V v) {
+  if constexpr (sizeof(R) == sizeof(v) && std::is_arithmetic<R>::value)
+    return v;
+  else
+    return R{v.x, v.y};
+}
+template <typename C>
+__device__ __forceinline__ C lane_load(const C* u, unsigned o) {
+  return from_vec<C>(*lane_ptr<typename lane_vec<C>::type>(u, o));
+}
+template <typename C>
+__device__ __forceinline__ C lane_load_nt(const C* u, unsigned o) {
+  return from_vec<C>(__builtin_nontemporal_load(lane_ptr<typename lane_vec<C>::type>(u, o)));
+}
+template <typename C>
+__device__ __forceinline__ void lane_store(C* u, unsigned o, C a) {
+  typename lane_vec<C>::type v = {a.x, a.y};
+  *lane_ptr<typename lane_vec<C>::type>(u, o) = v;
+}
+template <typename C>
+__device__ __forceinline__ void lane_store_nt(C* u, unsigned o, C a) {
+  typename lane_vec<C>::type v = {a.x, a.y};
+  __builtin_nontemporal_store(v, lane_ptr<typename lane_vec<C>::type>(u, o));
 }
 
 // v, through an empty asm the compiler cannot see through: addresses built

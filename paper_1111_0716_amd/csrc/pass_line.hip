@@ -19,12 +19,13 @@
 // registers live in a lane pair (split_fft.hpp).
 //
 // Every pass is meant to be bound by the pair buffer's traffic: one write, one
-// read and write, two reads (one per order of a pair).  Against the passes it
-// replaced (all transforms in LDS with a barrier around every radix pass,
-// ordered pairs), per call: 24x24x60, 3x3x1 k, 12 bands, FP32 step 27.8 -> 4.5
-// ms; 36x40x45, 2x1x1 k, 16 bands, FP64 apply 4.55 -> 0.80 ms; twelve uneven
-// Gamma cells of 16 to 40 points a side, FP32 4.23 -> 1.22 ms; 160 DFTs of
-// 48^3 FP64 498 -> 319 us.
+// read and write, two reads (one per order of a pair).  At 32^3 4x4x4 k FP32
+// (3.9 GB a batch) the passes take 730, 1440 and 1525 us: 5.3, 5.4 and 5.1 TB/s,
+// a large copy's 4.9 to 5.4.  Against the passes it replaced (all transforms
+// in LDS with a barrier around every radix pass, ordered pairs), per call:
+// 24x24x60, 3x3x1 k, 12 bands, FP32 step 27.8 -> 3.5 ms; 36x40x45, 2x1x1 k, 16
+// bands, FP64 apply 4.55 -> 0.60 ms; twelve uneven Gamma cells of 16 to 40
+// points a side, FP32 4.23 -> 0.77 ms; 160 DFTs of 48^3 FP64 498 -> 300 us.
 #include <algorithm>
 
 #include "fft_lds.hpp"
@@ -43,12 +44,23 @@ struct LineShape {
   static constexpr int REGS = L * static_cast<int>(2 * sizeof(T)) / 4;
   static constexpr bool FP32 = sizeof(T) == 4;
   static constexpr bool SPLIT_FWD = L % 2 == 0 && REGS > 144;
-  static constexpr bool SPLIT_ACC = L % 2 == 0 && (FP32 ? L == 60 || L == 64 : REGS > 80);
+  // the accumulate over lane pairs: always, or (FP32 54 and 72 points) where a
+  // lane per line leaves the chip short of waves
+  static constexpr bool SPLIT_ACC = L % 2 == 0 && (FP32 ? L == 48 || L == 50 || L == 60 || L == 64 : REGS > 80);
+  static constexpr bool SPLIT_ACC_FEW = FP32 && (L == 54 || L == 72);
   static constexpr int FWD_REGS = SPLIT_FWD ? REGS / 2 : REGS;
-  static constexpr int ACC_REGS = SPLIT_ACC ? REGS / 2 : REGS;
   // waves per SIMD (register budget 512 / WPE)
   static constexpr int WPE_FWD = FWD_REGS <= 144 ? 2 : 1;
-  static constexpr int WPE_ACC = 2 * ACC_REGS <= 160 ? 2 : 1;
+};
+
+template <typename T, int L, bool SPLIT>
+struct AccShape {
+  static constexpr int REGS = LineShape<T, L>::REGS / (SPLIT ? 2 : 1);
+  static constexpr int WPE = 2 * REGS <= 160 ? 2 : 1;
+  // most waves of a workgroup: two per SIMD, or what 64 KiB of LDS take of their sums
+  static constexpr int BYTES = REGS * 64 * 4;
+  static constexpr int WAVES0 = 64 * 1024 / BYTES + 1;
+  static constexpr int WAVES = WAVES0 < 4 * WPE ? WAVES0 : 4 * WPE;
 };
 
 // Item of workgroup b when `total` items are dealt to the eight XCDs in
@@ -86,10 +98,14 @@ __device__ __forceinline__ void load_codensity_u(C* x, const C* __restrict__ a, 
 // ---------------------------------------------------------------------------
 // forward pass: rho = conj(u_m) u_n, FFT along axis 1, T[c1][j2][j3]
 // ---------------------------------------------------------------------------
-// items (line block, pair), pairs fastest; pairs not null: the explicit pair
-// list of an energy batch
+// Items (line block, pair), pairs fastest; pairs not null: the explicit pair
+// list of an energy batch.  The pass writes the pair buffer once and should
+// read orbitals from L2 only, so a line block is one wave: the slices of a
+// batch's 128 partners (32^3: 16 KB each) then stay in an XCD's 4 MB while it
+// walks the pairs; four waves' slices (8 MB) come from further away.  32^3
+// 4x4x4 k FP32, 3.9 GB a batch: 1060 us at four waves, 730 at one (5.3 TB/s).
 template <typename T, int L>
-__global__ __launch_bounds__(256, (LineShape<T, L>::WPE_FWD)) void k_line_fwd(
+__global__ __launch_bounds__(64, (LineShape<T, L>::WPE_FWD)) void k_line_fwd(
     int plane, int npairs, unsigned total, int nbands, long long bs, const typename cx<T>::t* __restrict__ psi, int o0,
     int nP, int tri, const int2* __restrict__ parts, const PairRef* __restrict__ pairs,
     typename cx<T>::t* __restrict__ tbuf) {
@@ -99,7 +115,7 @@ __global__ __launch_bounds__(256, (LineShape<T, L>::WPE_FWD)) void k_line_fwd(
   const unsigned it = xcd_item(blockIdx.x, total);
   if (it >= total) return;
   const int lb = it / npairs, pi = it - lb * npairs;
-  const int id = lb * blockDim.x + threadIdx.x;
+  const int id = lb * 64 + static_cast<int>(threadIdx.x);
   const int l = SPLIT ? id >> 1 : id, h = SPLIT ? id & 1 : 0;
   if (l >= plane) return;  // both lanes of a pair together; no barrier in this kernel
   int okn, pkm;
@@ -125,7 +141,7 @@ __global__ __launch_bounds__(256, (LineShape<T, L>::WPE_FWD)) void k_line_fwd(
   C* base = tbuf + static_cast<size_t>(pi) * plane * L;
   const unsigned so = opaque((static_cast<unsigned>(h) * LN * plane + l) * sizeof(C));
 #pragma unroll
-  for (int k = 0; k < LN; ++k) *lane_at(base + static_cast<size_t>(k) * plane, so) = x[k];
+  for (int k = 0; k < LN; ++k) lane_store_nt(base + static_cast<size_t>(k) * plane, so, x[k]);
 }
 
 // ---------------------------------------------------------------------------
@@ -148,8 +164,8 @@ __global__ __launch_bounds__(512, 4) void k_plane_pair(PlaneGeo g, int nbands, i
   using C = typename cx<T>::t;
   extern __shared__ unsigned char smem_raw[];
   C* t2 = reinterpret_cast<C*>(smem_raw);  // twiddles of the two axes, then the tile
-  C* t3 = t2 + g.n2;
-  C* s = t3 + g.n3;
+  C* t3 = t2 + g.tw2;
+  C* s = t3 + g.tw3;
   const int pi = blockIdx.x, tile = blockIdx.y, g0 = tile * g.g, gc = min(g.g, g.n1 - g0);
   const int plane = g.n2 * g.n3, rows = gc * g.n2;
   int q;
@@ -165,33 +181,53 @@ __global__ __launch_bounds__(512, 4) void k_plane_pair(PlaneGeo g, int nbands, i
   } else {
     q = pairs[pi].q;
   }
-  for (int i = threadIdx.x; i < g.n2 + g.n3; i += blockDim.x) t2[i] = i < g.n2 ? tw2[i] : tw3[i - g.n2];
+  for (int i = threadIdx.x; i < g.tw2 + g.tw3; i += blockDim.x) t2[i] = i < g.tw2 ? tw2[i] : tw3[i - g.tw2];
   C* t = tbuf + (static_cast<size_t>(pi) * g.n1 + g0) * plane;
   const T* v = vtab + (static_cast<size_t>(q) * g.n1 + g0) * plane;
-  const int ra = g.a2 > 1 ? g.a2 : g.b2;  // the pass that touches memory
-  FOCK_RADIX(ra, (ax2_load<R, -1, C>(s, t, g, gc, tw2)))
-  __syncthreads();
-  if (g.a2 > 1) {
-    FOCK_RADIX(g.b2, (ax2_b<R, -1, C>(s, g, gc)))
-    __syncthreads();
-  }
-  if (g.a3 > 1) {
-    FOCK_RADIX(g.a3, (ax3_a<R, -1, false, C>(s, g, rows, t3)))
-    __syncthreads();
-  }
   double e = 0.0;
-  FOCK_RADIX(g.b3, (ax3_kernel<R, EN, BACK, C, T>(s, g, rows, v, &e)))
+  switch (g.n2) {
+#define CASE(N)                                              \
+  case N:                                                    \
+    ax2_load<N, -1, C>(s, t, g.n3, g.pitch, gc, tw2);        \
+    __syncthreads();                                         \
+    if constexpr (radix_a(N) > 1) {                          \
+      ax2_b<N, -1, C>(s, g.n3, g.pitch, gc);                 \
+      __syncthreads();                                       \
+    }                                                        \
+    break;
+    FOCK_SMOOTH_L(CASE)
+#undef CASE
+  }
+  switch (g.n3) {
+#define CASE(N)                                              \
+  case N:                                                    \
+    if constexpr (radix_a(N) > 1) {                          \
+      ax3_a<N, -1, false, C>(s, rows, t3);                   \
+      __syncthreads();                                       \
+    }                                                        \
+    ax3_kernel<N, EN, BACK, C, T>(s, rows, v, &e);           \
+    if constexpr (BACK && radix_a(N) > 1) {                  \
+      __syncthreads();                                       \
+      ax3_a<N, +1, true, C>(s, rows, t3);                    \
+    }                                                        \
+    break;
+    FOCK_SMOOTH_L(CASE)
+#undef CASE
+  }
   if constexpr (BACK) {
     __syncthreads();
-    if (g.a3 > 1) {
-      FOCK_RADIX(g.a3, (ax3_a<R, +1, true, C>(s, g, rows, t3)))
-      __syncthreads();
+    switch (g.n2) {
+#define CASE(N)                                              \
+  case N:                                                    \
+    if constexpr (radix_a(N) > 1) {                          \
+      ax2_b<N, +1, C>(s, g.n3, g.pitch, gc);                 \
+      __syncthreads();                                       \
+    }                                                        \
+    ax2_store<N, +1, C>(s, t, g.n3, g.pitch, gc, t2);        \
+    break;
+      FOCK_SMOOTH_L(CASE)
+#undef CASE
     }
-    if (g.a2 > 1) {
-      FOCK_RADIX(g.b2, (ax2_b<R, +1, C>(s, g, gc)))
-      __syncthreads();
-    }
-    FOCK_RADIX(ra, (ax2_store<R, +1, C>(s, t, g, gc, t2)))
   }
   if constexpr (EN) {  // fixed order: across the lanes, then the waves in turn
     __shared__ double red[8];
@@ -210,28 +246,34 @@ __global__ __launch_bounds__(512, 4) void k_plane_pair(PlaneGeo g, int nbands, i
 // ---------------------------------------------------------------------------
 // accumulate pass (rows and partners as in acc_source)
 // ---------------------------------------------------------------------------
-// One wave per item (line block, row), rows fastest: the waves of one line
-// block, which read the same slices of the partners' orbitals at about the
-// same time, run on one XCD and take them from its L2.
-template <typename T, int L>
-__global__ __launch_bounds__(64, (LineShape<T, L>::WPE_ACC)) void k_line_acc(
+// One workgroup per item (line block, row), rows fastest: the workgroups of one
+// line block, which read the same slices of the partners' orbitals at about
+// the same time, run on one XCD and take them from its L2.  Its waves share
+// the row's partners out in contiguous slices and their sums meet in LDS in
+// order: where lines and rows are few, a chain of one partner after another in
+// one wave is what the pass takes (two memory latencies each).
+// Once they do, loading a partner's orbital together with its pair gains no
+// more (the batch of twelve cells 834 -> 822 us, 12x10x9 53.0 -> 54.6).
+template <typename T, int L, bool SPLIT>
+__global__ __launch_bounds__((AccShape<T, L, SPLIT>::WAVES * 64), (AccShape<T, L, SPLIT>::WPE)) void k_line_acc(
     int plane, int rows, unsigned total, int nbands, long long bs, int o0, int nO, int nP, int tri,
     const int2* __restrict__ parts, const typename cx<T>::t* __restrict__ tbuf,
     const typename cx<T>::t* __restrict__ psi, const double* __restrict__ occ, const double* __restrict__ kw,
     typename cx<T>::t* __restrict__ out, int first, int first_mirror, const double* __restrict__ gscale, double hscale,
     int backward) {
   using C = typename cx<T>::t;
-  using Sh = LineShape<T, L>;
-  constexpr bool SPLIT = Sh::SPLIT_ACC;
   constexpr int LN = SPLIT ? L / 2 : L;
-  constexpr int B = batch_of(LN, Sh::WPE_ACC == 1 ? 16 : kRegB);
+  constexpr int B = batch_of(LN, AccShape<T, L, SPLIT>::WPE == 1 ? 16 : kRegB);
   constexpr int NB = LN / B;
+  extern __shared__ unsigned char smem_raw[];
   const unsigned it = xcd_item(blockIdx.x, total);
-  if (it >= total) return;
+  if (it >= total) return;  // the whole workgroup
   const int lb = it / rows, row = it - lb * rows;
-  const int id = lb * 64 + static_cast<int>(threadIdx.x);
-  const int l = SPLIT ? id >> 1 : id, h = SPLIT ? id & 1 : 0;
-  if (l >= plane) return;  // both lanes of a pair together; no barrier in this kernel
+  const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int id = lb * 64 + lane;
+  const int lv = SPLIT ? id >> 1 : id, h = SPLIT ? id & 1 : 0;
+  const int l = min(lv, plane - 1);  // lanes past the plane repeat its last line and store nothing
   const bool mirror = row >= nO;
   const int o = mirror ? row - nO : row;
   const int nsrc = mirror ? nO : nP;
@@ -241,15 +283,19 @@ __global__ __launch_bounds__(64, (LineShape<T, L>::WPE_ACC)) void k_line_acc(
   C acc[LN];
 #pragma unroll
   for (int j = 0; j < LN; ++j) acc[j] = C{T(0), T(0)};
-  for (int p = 0; p < nsrc; ++p) {
+  const int p1 = (wave + 1) * nsrc / nw;
+  for (int p = wave * nsrc / nw; p < p1; ++p) {
     int sb;
     size_t pair;
     bool cj;
     acc_source(mirror, p, o, o0, nP, tri, nbands, parts, &sb, &pair, &cj);
     const C* src = tbuf + pair * plane * L;
+    // copies made here: an offset from outside the loop would be widened there
+    // and added to the base for every element
+    const unsigned ot = opaque(lt), ou = opaque(lu);
     C x[LN];
 #pragma unroll
-    for (int k = 0; k < LN; ++k) x[k] = *lane_at(src + static_cast<size_t>(k) * plane, lt);
+    for (int k = 0; k < LN; ++k) x[k] = lane_load_nt(src + static_cast<size_t>(k) * plane, ot);
     if constexpr (SPLIT)
       split_fft_inv<C, L>(x, h);
     else
@@ -262,12 +308,12 @@ __global__ __launch_bounds__(64, (LineShape<T, L>::WPE_ACC)) void k_line_acc(
     const C* um = psi + static_cast<size_t>(sb) * bs;
     C mb[2][B];
 #pragma unroll
-    for (int j = 0; j < B; ++j) mb[0][j] = *lane_at(um + j * us, lu);
+    for (int j = 0; j < B; ++j) mb[0][j] = lane_load(um + j * us, ou);
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
       if (n + 1 < NB) {
 #pragma unroll
-        for (int j = 0; j < B; ++j) mb[(n + 1) & 1][j] = *lane_at(um + ((n + 1) * B + j) * us, lu);
+        for (int j = 0; j < B; ++j) mb[(n + 1) & 1][j] = lane_load(um + ((n + 1) * B + j) * us, ou);
       }
       reg_fence();
 #pragma unroll
@@ -278,6 +324,20 @@ __global__ __launch_bounds__(64, (LineShape<T, L>::WPE_ACC)) void k_line_acc(
       }
     }
   }
+  if (nw > 1) {
+    C* s = reinterpret_cast<C*>(smem_raw) + lane;  // [wave - 1][j][lane]
+    if (wave > 0) {
+#pragma unroll
+      for (int j = 0; j < LN; ++j) s[((wave - 1) * LN + j) * 64] = acc[j];
+    }
+    __syncthreads();
+    if (wave > 0) return;
+    for (int w = 1; w < nw; ++w) {
+#pragma unroll
+      for (int j = 0; j < LN; ++j) acc[j] = cadd(acc[j], s[((w - 1) * LN + j) * 64]);
+    }
+  }
+  if (lv >= plane) return;
   const int okn = mirror ? parts[o].x * nbands + parts[o].y : o0 + o;
   double f = hscale;
   if (gscale) f *= gscale[0];
@@ -285,14 +345,16 @@ __global__ __launch_bounds__(64, (LineShape<T, L>::WPE_ACC)) void k_line_acc(
   const T ft = static_cast<T>(f);
   C* dst = out + static_cast<size_t>(okn) * bs;
   if (!(mirror ? first_mirror : first)) {
+    const unsigned ou = opaque(lu);
     C old[LN];  // loaded before the first store, so the loads overlap
 #pragma unroll
-    for (int j = 0; j < LN; ++j) old[j] = *lane_at(dst + j * us, lu);
+    for (int j = 0; j < LN; ++j) old[j] = lane_load(dst + j * us, ou);
 #pragma unroll
-    for (int j = 0; j < LN; ++j) *lane_at(dst + j * us, lu) = cadd(old[j], cscale(acc[j], ft));
+    for (int j = 0; j < LN; ++j) lane_store(dst + j * us, ou, cadd(old[j], cscale(acc[j], ft)));
   } else {
+    const unsigned ou = opaque(lu);
 #pragma unroll
-    for (int j = 0; j < LN; ++j) *lane_at(dst + j * us, lu) = cscale(acc[j], ft);
+    for (int j = 0; j < LN; ++j) lane_store(dst + j * us, ou, cscale(acc[j], ft));
   }
 }
 
@@ -317,7 +379,7 @@ __global__ __launch_bounds__(256, (LineShape<T, L>::WPE_FWD)) void k_dft_line(in
   const size_t s1 = static_cast<size_t>(plane), s2 = static_cast<size_t>(SPLIT ? 2 : 1) * plane;
   C x[LN];
 #pragma unroll
-  for (int j = 0; j < LN; ++j) x[j] = *lane_at(d + j * (S < 0 ? s2 : s1), S < 0 ? eo : hf);
+  for (int j = 0; j < LN; ++j) x[j] = lane_load(d + j * (S < 0 ? s2 : s1), S < 0 ? eo : hf);
   if constexpr (!SPLIT)
     reg_fft<C, L, S>(x);
   else if constexpr (S < 0)
@@ -326,7 +388,7 @@ __global__ __launch_bounds__(256, (LineShape<T, L>::WPE_FWD)) void k_dft_line(in
     split_fft_inv<C, L>(x, h);
   const unsigned so = opaque(S < 0 ? hf : eo);
 #pragma unroll
-  for (int j = 0; j < LN; ++j) *lane_at(d + j * (S < 0 ? s1 : s2), so) = x[j];
+  for (int j = 0; j < LN; ++j) lane_store(d + j * (S < 0 ? s1 : s2), so, x[j]);
 }
 
 // axes 2 and 3 of a tile of planes; the frequencies leave LDS in order
@@ -337,25 +399,38 @@ __global__ __launch_bounds__(512, 4) void k_dft_plane(PlaneGeo g, typename cx<T>
   using C = typename cx<T>::t;
   extern __shared__ unsigned char smem_raw[];
   C* t3 = reinterpret_cast<C*>(smem_raw);
-  C* s = t3 + g.n3;
+  C* s = t3 + g.tw3;
   const int g0 = blockIdx.x * g.g, gc = min(g.g, g.n1 - g0);
   const int plane = g.n2 * g.n3, rows = gc * g.n2;
-  for (int i = threadIdx.x; i < g.n3; i += blockDim.x) t3[i] = tw3[i];
+  for (int i = threadIdx.x; i < g.tw3; i += blockDim.x) t3[i] = tw3[i];
   C* t = data + static_cast<size_t>(blockIdx.y) * stride + static_cast<size_t>(g0) * plane;
-  FOCK_RADIX((g.a2 > 1 ? g.a2 : g.b2), (ax2_load<R, S, C>(s, t, g, gc, tw2)))
-  __syncthreads();
-  if (g.a2 > 1) {
-    FOCK_RADIX(g.b2, (ax2_b<R, S, C>(s, g, gc)))
-    __syncthreads();
+  switch (g.n2) {
+#define CASE(N)                                              \
+  case N:                                                    \
+    ax2_load<N, S, C>(s, t, g.n3, g.pitch, gc, tw2);         \
+    if constexpr (radix_a(N) > 1) {                          \
+      __syncthreads();                                       \
+      ax2_b<N, S, C>(s, g.n3, g.pitch, gc);                  \
+    }                                                        \
+    break;
+    FOCK_SMOOTH_L(CASE)
+#undef CASE
   }
-  if (g.a3 > 1) {
-    FOCK_RADIX(g.a3, (ax3_a<R, S, false, C>(s, g, rows, t3)))
-    __syncthreads();
-  }
-  FOCK_RADIX(g.b3, (ax3_b<R, S, C>(s, g, rows)))
   __syncthreads();
-  const float r3 = 1.0f / static_cast<float>(g.n3), r2 = 1.0f / static_cast<float>(g.n2);
-  const float ra2 = 1.0f / static_cast<float>(g.a2), ra3 = 1.0f / static_cast<float>(g.a3);
+  switch (g.n3) {
+#define CASE(N)                                              \
+  case N:                                                    \
+    if constexpr (radix_a(N) > 1) {                          \
+      ax3_a<N, S, false, C>(s, rows, t3);                    \
+      __syncthreads();                                       \
+    }                                                        \
+    ax3_b<N, S, C>(s, rows);                                 \
+    break;
+    FOCK_SMOOTH_L(CASE)
+#undef CASE
+  }
+  __syncthreads();
+  const float r3 = rcp_of(g.n3), r2 = rcp_of(g.n2), ra2 = rcp_of(g.a2), ra3 = rcp_of(g.a3);
   for (int e = threadIdx.x; e < gc * plane; e += blockDim.x) {
     const int row = fdiv(e, r3), c3 = e - row * g.n3;
     const int gg = fdiv(row, r2), c2 = row - gg * g.n2;
@@ -369,13 +444,8 @@ __global__ __launch_bounds__(512, 4) void k_dft_plane(PlaneGeo g, typename cx<T>
 // ---------------------------------------------------------------------------
 namespace {
 
-// every {2,3,5}-smooth axis length
-#define FOCK_SMOOTH_L(X)                                                                                       \
-  X(2) X(3) X(4) X(5) X(6) X(8) X(9) X(10) X(12) X(15) X(16) X(18) X(20) X(24) X(25) X(27) X(30) X(32) X(36) \
-  X(40) X(45) X(48) X(50) X(54) X(60) X(64) X(72)
-
 size_t plane_lds(const PlaneGeo& g, size_t csize) {
-  return (static_cast<size_t>(g.g) * g.n2 * g.pitch + g.n2 + g.n3) * csize;
+  return (static_cast<size_t>(g.g) * g.n2 * g.pitch + g.tw2 + g.tw3) * csize;
 }
 
 template <typename T, int L>
@@ -383,26 +453,53 @@ void line_fwd_L(const Plan& p, const Batch& b, const Instance& in, const void* p
                 const PairRef* pairs, typename cx<T>::t* tbuf) {
   const int plane = in.grid[1] * in.grid[2];
   const int lanes = plane * (LineShape<T, L>::SPLIT_FWD ? 2 : 1);
-  const int nt = std::min(256, (lanes + 63) / 64 * 64);
-  const unsigned total = static_cast<unsigned>((lanes + nt - 1) / nt) * b.npairs;
-  hipLaunchKernelGGL((k_line_fwd<T, L>), dim3(xcd_grid(total)), dim3(nt), 0, p.stream, plane, b.npairs, total,
+  const unsigned total = static_cast<unsigned>((lanes + 63) / 64) * b.npairs;
+  hipLaunchKernelGGL((k_line_fwd<T, L>), dim3(xcd_grid(total)), dim3(64), 0, p.stream, plane, b.npairs, total,
                      in.nbands, static_cast<long long>(in.band_stride), static_cast<const typename cx<T>::t*>(psi),
                      b.o0, b.nP, b.tri, parts, pairs, tbuf);
+}
+
+template <typename T, int L, bool SPLIT>
+void line_acc_launch(const Plan& p, const Batch& b, const Instance& in, const int2* parts, const typename cx<T>::t* tbuf,
+                const void* psi, const double* occ, const double* kw, void* out, const double* gscale, double hscale,
+                bool backward) {
+  using C = typename cx<T>::t;
+  const int plane = in.grid[1] * in.grid[2];
+  const int lanes = plane * (SPLIT ? 2 : 1);
+  const int rows = b.nO + (b.mirror ? b.nP : 0);
+  const unsigned total = static_cast<unsigned>((lanes + 63) / 64) * rows;
+  // Partners shared out among waves while that leaves at most 4096 waves in all
+  // (the chip holds 2048 to 8192) and two partners to a wave.  One wave per
+  // row and line block, sharing up to 2048 waves, up to 4096: batch of twelve
+  // cells (288 to 600 waves a launch) 1203, 834, 822 us; 12x10x9 step (12
+  // waves) 59, 53, 53; 36x40x45 FP64 apply (1824 waves) 793, 792, 779.
+  const int nsrc = b.mirror ? std::min(b.nO, b.nP) : b.nP;
+  using Sh = AccShape<T, L, SPLIT>;
+  int nw = 1;
+  while (nw < Sh::WAVES && total * static_cast<unsigned>(nw + 1) <= 4096u && 2 * (nw + 1) <= nsrc) ++nw;
+  const size_t lds = static_cast<size_t>(nw - 1) * Sh::BYTES;
+  hipLaunchKernelGGL((k_line_acc<T, L, SPLIT>), dim3(xcd_grid(total)), dim3(64 * nw), lds, p.stream, plane, rows, total,
+                     in.nbands, static_cast<long long>(in.band_stride), b.o0, b.nO, b.nP, b.tri, parts, tbuf,
+                     static_cast<const C*>(psi), occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale,
+                     hscale, backward ? 1 : 0);
 }
 
 template <typename T, int L>
 void line_acc_L(const Plan& p, const Batch& b, const Instance& in, const int2* parts, const typename cx<T>::t* tbuf,
                 const void* psi, const double* occ, const double* kw, void* out, const double* gscale, double hscale,
                 bool backward) {
-  using C = typename cx<T>::t;
-  const int plane = in.grid[1] * in.grid[2];
-  const int lanes = plane * (LineShape<T, L>::SPLIT_ACC ? 2 : 1);
-  const int rows = b.nO + (b.mirror ? b.nP : 0);
-  const unsigned total = static_cast<unsigned>((lanes + 63) / 64) * rows;
-  hipLaunchKernelGGL((k_line_acc<T, L>), dim3(xcd_grid(total)), dim3(64), 0, p.stream, plane, rows, total, in.nbands,
-                     static_cast<long long>(in.band_stride), b.o0, b.nO, b.nP, b.tri, parts, tbuf,
-                     static_cast<const C*>(psi), occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale,
-                     hscale, backward ? 1 : 0);
+  using Sh = LineShape<T, L>;
+  if constexpr (Sh::SPLIT_ACC_FEW) {
+    // 72^3 FP32 apply, 20 bands (1620 waves of whole lines): 0.79 against 0.81
+    // ms, 72x24x24, 60 bands (540) 0.75 against 0.82; 64 bands (5184) 7.84
+    // against 7.73 ms
+    const long long waves = static_cast<long long>((in.grid[1] * in.grid[2] + 63) / 64) * (b.nO + (b.mirror ? b.nP : 0));
+    if (waves <= 2048) {
+      line_acc_launch<T, L, true>(p, b, in, parts, tbuf, psi, occ, kw, out, gscale, hscale, backward);
+      return;
+    }
+  }
+  line_acc_launch<T, L, Sh::SPLIT_ACC>(p, b, in, parts, tbuf, psi, occ, kw, out, gscale, hscale, backward);
 }
 
 template <typename T>
@@ -524,54 +621,37 @@ void plane_lds_attr(int lim) {
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) != hipSuccess) (void)hipGetLastError();
 }
 
-// n = a b with both at most 10 (never 7), the least a + b; a = 1 if n itself is one radix
-void radix_pair(int n, int* a, int* b) {
-  *a = 1;
-  *b = n;
-  if (n <= 10) return;
-  int best = 1000;
-  for (int x = 2; x <= 10; ++x) {
-    if (n % x != 0 || x == 7 || n / x > 10 || n / x < x) continue;
-    if (x + n / x < best) {
-      best = x + n / x;
-      *a = x;
-      *b = n / x;
-    }
-  }
-}
-
 }  // namespace
 
 int plane_tiles(const PlaneGeo& g) { return (g.n1 + g.g - 1) / g.g; }
 
 size_t plane_lds_bytes(const PlaneGeo& g, size_t csize) { return plane_lds(g, csize); }
 
-// Tile and workgroup of the plane passes.  A tile is as many whole planes as
-// make about 2048 points (small planes alone would not fill a workgroup), but
-// never so many that fewer than 1024 workgroups are left while a tile holds
-// more than one plane.
-void plane_geometry(const int grid[3], long long planes_of, PlaneGeo* g, int* threads) {
+// Tile and workgroup of the plane passes, from sweeps of both on eleven plane
+// sizes (256 to 5184 points) in both precisions.
+//   Tile: whole planes of up to 2880 points in FP32, 1440 in FP64 (23 KB of LDS:
+//   seven tiles a compute unit; one larger plane is a tile by itself), but
+//   several planes only while that leaves 1024 workgroups.  24x60 FP32: two
+//   planes 276 us, one 293; 40x40 FP32: one 261, two 264; 40x40 FP64 249, 264.
+//   Threads: five to eleven points each, and a multiple of four waves where the
+//   tile gives them: 320 or 384 threads leave the SIMDs unevenly filled.
+//   40x40 FP32: 256 threads 261 us, 320 323, 384 353, 192 262, 128 270; 48x48
+//   FP64: 256 247, 384 286; 72x72 FP64: 512 449, 384 475, 256 525.
+void plane_geometry(const int grid[3], long long planes_of, size_t csize, PlaneGeo* g, int* threads) {
   g->n1 = grid[0];
   g->n2 = grid[1];
   g->n3 = grid[2];
-  radix_pair(g->n2, &g->a2, &g->b2);
-  radix_pair(g->n3, &g->a3, &g->b3);
+  g->a2 = radix_a(g->n2);
+  g->b2 = g->n2 / g->a2;
+  g->a3 = radix_a(g->n3);
+  g->b3 = g->n3 / g->a3;
+  g->tw2 = twiddle_count(g->n2);
+  g->tw3 = twiddle_count(g->n3);
   g->pitch = g->n3 | 1;
-  g->g = std::max(1, std::min(g->n1, 2048 / (g->n2 * g->n3)));
+  g->g = std::max(1, std::min(g->n1, (csize == 16 ? 1440 : 2880) / (g->n2 * g->n3)));
   while (g->g > 1 && planes_of * plane_tiles(*g) < 1024) g->g = (g->g + 1) / 2;
-  // the workgroup size with the fewest lane slots over the passes, a round of
-  // any pass costing about 96 lanes' worth of waiting besides
   const int pts = g->g * g->n2 * g->n3;
-  long long best = -1;
-  for (int nt = 64; nt <= 512; nt += 64) {
-    long long cost = 0;
-    for (int r : {g->a2, g->b2, g->a3, g->b3})
-      if (r > 1) cost += ((pts / r + nt - 1) / nt) * static_cast<long long>(nt + 96);
-    if (best < 0 || cost < best) {
-      best = cost;
-      *threads = nt;
-    }
-  }
+  *threads = pts >= 3200 ? 512 : pts >= 1440 ? 256 : pts >= 1050 ? 192 : pts >= 500 ? 128 : 64;
 }
 
 hipError_t launch_line_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,

@@ -240,11 +240,11 @@ __global__ __launch_bounds__((RegShape<T, L>::NTP), (sizeof(TI) == sizeof(T) ? R
       C* dst = tbuf + static_cast<size_t>(pi) * n1 * LL;
       const unsigned so = opaque((static_cast<unsigned>(j1) * LL + col) * sizeof(C));
 #pragma unroll
-      for (int c3 = 0; c3 < L; ++c3) *lane_at(dst + c3 * L, so) = x[c3];
+      for (int c3 = 0; c3 < L; ++c3) stream_store(lane_at(dst + c3 * L, so), x[c3]);
     } else {
       C* dst = tbuf + (static_cast<size_t>(pi) * n1 + j1) * LL + col;
 #pragma unroll
-      for (int c3 = 0; c3 < L; ++c3) dst[c3 * L] = x[c3];
+      for (int c3 = 0; c3 < L; ++c3) stream_store(dst + c3 * L, x[c3]);
     }
   }
 }
@@ -262,14 +262,14 @@ __device__ __forceinline__ void pencil_apply_line(int l, int LL, int pi, int q, 
   const unsigned lo = static_cast<unsigned>(l) * sizeof(C);
   C x[L];
 #pragma unroll
-  for (int j1 = 0; j1 < L; ++j1) x[j1] = *lane_at(base + static_cast<size_t>(j1) * LL, lo);
+  for (int j1 = 0; j1 < L; ++j1) x[j1] = stream_load(lane_at(base + static_cast<size_t>(j1) * LL, lo));
   reg_fft<C, L, -1>(x);
   mul_table_line_u<C, T, L, EN>(x, vtab + static_cast<size_t>(q) * LL * L,
                                 opaque(static_cast<unsigned>(l) * sizeof(T)), LL, es);
   reg_fft<C, L, +1>(x);
   const unsigned so = opaque(lo);
 #pragma unroll
-  for (int j1 = 0; j1 < L; ++j1) *lane_at(base + static_cast<size_t>(j1) * LL, so) = x[j1];
+  for (int j1 = 0; j1 < L; ++j1) stream_store(lane_at(base + static_cast<size_t>(j1) * LL, so), x[j1]);
 }
 
 template <typename T, int L, bool EN = false>
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256, (RegShape<T, L>::WPE_PENCIL)) void k_pencil_en
     const C* base = tbuf + static_cast<size_t>(pi) * LL * L;
     C x[L];
 #pragma unroll
-    for (int j1 = 0; j1 < L; ++j1) x[j1] = *lane_at(base + static_cast<size_t>(j1) * LL, static_cast<unsigned>(l) * sizeof(C));
+    for (int j1 = 0; j1 < L; ++j1) x[j1] = stream_load(lane_at(base + static_cast<size_t>(j1) * LL, static_cast<unsigned>(l) * sizeof(C)));
     reg_fft<C, L, -1>(x);
     const TV* v = vtab + static_cast<size_t>(q) * LL * L;
     const unsigned lv = opaque(static_cast<unsigned>(l) * sizeof(TV));
@@ -399,7 +399,7 @@ __global__ __launch_bounds__((RegShape<T, L>::NTP), (RegShape<T, L>::WPE_ACC)) v
     if (valid) {
       const C* src = tbuf + pair * LL * n1 + static_cast<size_t>(j1) * LL + col;
 #pragma unroll
-      for (int c3 = 0; c3 < L; ++c3) x[c3] = src[c3 * L];  // row (j1, c2 = col)
+      for (int c3 = 0; c3 < L; ++c3) x[c3] = stream_load(src + c3 * L);  // row (j1, c2 = col)
     } else {
 #pragma unroll
       for (int c3 = 0; c3 < L; ++c3) x[c3] = C{T(0), T(0)};
@@ -619,7 +619,7 @@ __global__ __launch_bounds__((SplitShape<T, L>::NTP), (SplitShape<T, L>::WPE_LIN
   if (valid) {
     C* dst = tbuf + (static_cast<size_t>(pi) * n1 + j1) * LL + static_cast<size_t>(h) * LH * L + col;
 #pragma unroll
-    for (int k = 0; k < LH; ++k) dst[k * L] = y[k];
+    for (int k = 0; k < LH; ++k) stream_store(dst + k * L, y[k]);
   }
 }
 
@@ -633,14 +633,14 @@ __device__ __forceinline__ void pencil_apply_split_line(int l, int h, int LL, in
   const unsigned lo = (static_cast<unsigned>(h) * LL + l) * sizeof(C);
   C y[LH];
 #pragma unroll
-  for (int m = 0; m < LH; ++m) y[m] = *lane_at(base + static_cast<size_t>(2 * m) * LL, lo);  // j1 = 2m + h
+  for (int m = 0; m < LH; ++m) y[m] = stream_load(lane_at(base + static_cast<size_t>(2 * m) * LL, lo));  // j1 = 2m + h
   split_fft_fwd<C, L>(y, h);  // y[k] at c1 = h L/2 + k
   mul_table_line_u<C, T, LH, EN>(y, vtab + static_cast<size_t>(q) * LL * L,
                                  opaque((static_cast<unsigned>(h) * LH * LL + l) * sizeof(T)), LL, es);
   split_fft_inv<C, L>(y, h);
   const unsigned so = opaque(lo);
 #pragma unroll
-  for (int m = 0; m < LH; ++m) *lane_at(base + static_cast<size_t>(2 * m) * LL, so) = y[m];
+  for (int m = 0; m < LH; ++m) stream_store(lane_at(base + static_cast<size_t>(2 * m) * LL, so), y[m]);
 }
 
 template <typename T, int L, bool EN = false>
@@ -703,7 +703,7 @@ __global__ __launch_bounds__((RegShape<T, L>::NTP), (RegShape<T, L>::WPE_PLANE))
   if (valid) {
     const unsigned lo = (static_cast<unsigned>(c2) * L + col) * sizeof(C);
 #pragma unroll
-    for (int j1 = 0; j1 < L; ++j1) x[j1] = *lane_at(base + static_cast<size_t>(j1) * LL, lo);
+    for (int j1 = 0; j1 < L; ++j1) x[j1] = stream_load(lane_at(base + static_cast<size_t>(j1) * LL, lo));
     reg_fft<C, L, -1>(x);  // axis 1: x[c1] at (c2, c3 = col)
     mul_table_line_u<C, T, L, EN>(x, vtab + static_cast<size_t>(q) * LL * L,
                                   opaque((static_cast<unsigned>(c2) * L + col) * sizeof(T)), LL, &e);
@@ -718,7 +718,7 @@ __global__ __launch_bounds__((RegShape<T, L>::NTP), (RegShape<T, L>::WPE_PLANE))
   if (valid) {
     const unsigned so = opaque((static_cast<unsigned>(c2) * L + col) * sizeof(C));
 #pragma unroll
-    for (int j1 = 0; j1 < L; ++j1) *lane_at(base + static_cast<size_t>(j1) * LL, so) = x[j1];
+    for (int j1 = 0; j1 < L; ++j1) stream_store(lane_at(base + static_cast<size_t>(j1) * LL, so), x[j1]);
   }
   if constexpr (EN) {
     // block sum in a fixed order (the block's last wave may be partly empty):
@@ -758,7 +758,7 @@ __global__ __launch_bounds__(256, (SplitShape<T, L>::WPE_LINE)) void k_pencil_en
     const unsigned lo = (static_cast<unsigned>(h) * LL + l) * sizeof(C);
     C y[LH];
 #pragma unroll
-    for (int m = 0; m < LH; ++m) y[m] = *lane_at(base + static_cast<size_t>(2 * m) * LL, lo);
+    for (int m = 0; m < LH; ++m) y[m] = stream_load(lane_at(base + static_cast<size_t>(2 * m) * LL, lo));
     split_fft_fwd<C, L>(y, h);
     const TV* v = vtab + static_cast<size_t>(q) * LL * L;
     const unsigned lv = opaque((static_cast<unsigned>(h) * LH * LL + l) * sizeof(TV));
@@ -814,7 +814,7 @@ __global__ __launch_bounds__((SplitShape<T, L>::NTP), (SplitShape<T, L>::WPE_ACC
     if (valid) {
       const C* src = tbuf + pair * LL * n1 + static_cast<size_t>(j1) * LL + static_cast<size_t>(h) * LH * L + col;
 #pragma unroll
-      for (int k = 0; k < LH; ++k) y[k] = src[k * L];  // row (j1, c2 = col), c3 = h L/2 + k
+      for (int k = 0; k < LH; ++k) y[k] = stream_load(src + k * L);  // row (j1, c2 = col), c3 = h L/2 + k
     } else {
 #pragma unroll
       for (int k = 0; k < LH; ++k) y[k] = C{T(0), T(0)};
@@ -923,7 +923,7 @@ __global__ __launch_bounds__(256, (RegShape<T, L>::WPE_ACC)) void k_acc_line(
     const C* src = tbuf + pair * LL * L + eoff;
     C x[L];
 #pragma unroll
-    for (int c2 = 0; c2 < L; ++c2) x[c2] = src[c2 * L];
+    for (int c2 = 0; c2 < L; ++c2) x[c2] = stream_load(src + c2 * L);
     reg_fft<C, L, +1>(x);  // inverse axis 2: x[j2] at (j1, j3)
     if (cj) {
 #pragma unroll
@@ -1002,7 +1002,7 @@ __global__ __launch_bounds__(256, (SplitShape<T, L>::WPE_ACC)) void k_acc_line_s
     const C* src = tbuf + pair * LL * L + eoff + static_cast<size_t>(h) * LH * L;
     C y[LH];
 #pragma unroll
-    for (int k = 0; k < LH; ++k) y[k] = src[k * L];  // c2 = h L/2 + k
+    for (int k = 0; k < LH; ++k) y[k] = stream_load(src + k * L);  // c2 = h L/2 + k
     split_fft_inv<C, L>(y, h);                       // y[m] at j2 = 2m + h
     if (cj) {
 #pragma unroll
@@ -1061,7 +1061,7 @@ __device__ __forceinline__ void pencil_apply_mixed_line(int l, int h, int LL, in
   {
     float2 f[LH];
 #pragma unroll
-    for (int m = 0; m < LH; ++m) f[m] = *lane_at(t32 + base + static_cast<size_t>(2 * m) * LL, le * 8u);  // j1 = 2m + h
+    for (int m = 0; m < LH; ++m) f[m] = stream_load(lane_at(t32 + base + static_cast<size_t>(2 * m) * LL, le * 8u));  // j1 = 2m + h
     split_fft_fwd<float2, L>(f, h);  // f[k] at c1 = h L/2 + k
 #pragma unroll
     for (int k = 0; k < LH; ++k) y[k] = cvt<double2>(f[k]);
@@ -1071,7 +1071,7 @@ __device__ __forceinline__ void pencil_apply_mixed_line(int l, int h, int LL, in
   split_fft_inv<double2, L>(y, h);
   const unsigned so = opaque(le * 16u);
 #pragma unroll
-  for (int m = 0; m < LH; ++m) *lane_at(t64 + base + static_cast<size_t>(2 * m) * LL, so) = y[m];
+  for (int m = 0; m < LH; ++m) stream_store(lane_at(t64 + base + static_cast<size_t>(2 * m) * LL, so), y[m]);
 }
 
 // EN: the energy variant (see k_pencil_apply_reg), from the FP32 forward
@@ -1123,7 +1123,7 @@ __device__ __forceinline__ void pencil_apply_mixinv_line(int l, int h, int LL, i
   {
     double2 y[LH];
 #pragma unroll
-    for (int m = 0; m < LH; ++m) y[m] = *lane_at(t64 + base + static_cast<size_t>(2 * m) * LL, le * 16u);  // j1 = 2m + h
+    for (int m = 0; m < LH; ++m) y[m] = stream_load(lane_at(t64 + base + static_cast<size_t>(2 * m) * LL, le * 16u));  // j1 = 2m + h
     split_fft_fwd<double2, L>(y, h);  // y[k] at c1 = h L/2 + k
     mul_table_line_u<double2, double, LH, EN>(y, vtab + static_cast<size_t>(q) * LL * L,
                                               opaque((static_cast<unsigned>(h) * LH * LL + l) * 8u), LL, es);
@@ -1133,7 +1133,7 @@ __device__ __forceinline__ void pencil_apply_mixinv_line(int l, int h, int LL, i
   split_fft_inv<float2, L>(f, h);
   const unsigned so = opaque(le * 8u);
 #pragma unroll
-  for (int m = 0; m < LH; ++m) *lane_at(t32 + base + static_cast<size_t>(2 * m) * LL, so) = f[m];
+  for (int m = 0; m < LH; ++m) stream_store(lane_at(t32 + base + static_cast<size_t>(2 * m) * LL, so), f[m]);
 }
 
 // EN: the energy variant (see k_pencil_apply_reg), from the FP64 spectrum

@@ -14,6 +14,7 @@
 
 #include "fft_lds.hpp"
 #include "fock_internal.hpp"
+#include "plane_fft.hpp"
 
 namespace fock {
 
@@ -329,7 +330,7 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   // the others (a grid per band)
   for (auto& in : p->inst) {
     const long long orb = static_cast<long long>(in.nk) * in.nbands;
-    plane_geometry(in.grid, in.line ? orb * (orb + 1) / 2 : orb, &in.pg, &in.pg_threads);
+    plane_geometry(in.grid, in.line ? orb * (orb + 1) / 2 : orb, p->csize, &in.pg, &in.pg_threads);
   }
 
   // ---- batch shapes ----
@@ -649,10 +650,10 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   unsigned char* img = p->host_image.data();
   for (int L = 2; L <= kNMax; ++L) {
     if (!smooth235(L)) continue;
-    const int o = twiddle_offset(L);
-    for (int t = 0; t < L; ++t) {
-      // exp(-2 pi i t/L) in FP64, rounded once
-      const double ang = -2.0 * M_PI * static_cast<double>(t) / static_cast<double>(L);
+    const int o = twiddle_offset(L), a = radix_a(L), b = L / a;
+    for (int t = 0; t < twiddle_count(L); ++t) {
+      // W_L^{r j} = exp(-2 pi i r j / L) at (r - 1) b + j, in FP64, rounded once
+      const double ang = -2.0 * M_PI * static_cast<double>((t / b + 1) * (t % b)) / static_cast<double>(L);
       const double c = std::cos(ang), s = std::sin(ang);
       if (prec != FOCK_C64) {
         double* w = reinterpret_cast<double*>(img + p->tw_off) + 2 * (o + t);

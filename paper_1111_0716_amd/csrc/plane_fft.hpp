@@ -17,7 +17,7 @@
 #pragma once
 
 #include "fft_lds.hpp"
-#include "fock_internal.hpp"
+#include "pass_common.hpp"
 
 namespace fock {
 
@@ -86,18 +86,28 @@ template <int S, typename C> struct Dft<10, S, C> {  // 2 x 5, prime factors: no
   }
 };
 
-// `call` with the compile-time radix R
-#define FOCK_RADIX(r, call)                            \
-  switch (r) {                                         \
-    case 2: { constexpr int R = 2; call; break; }      \
-    case 3: { constexpr int R = 3; call; break; }      \
-    case 4: { constexpr int R = 4; call; break; }      \
-    case 5: { constexpr int R = 5; call; break; }      \
-    case 6: { constexpr int R = 6; call; break; }      \
-    case 8: { constexpr int R = 8; call; break; }      \
-    case 9: { constexpr int R = 9; call; break; }      \
-    default: { constexpr int R = 10; call; break; }    \
+// n = a b with both at most 10 (never 7), the least a + b; a = 1 if n itself is one radix
+__host__ __device__ constexpr int radix_a(int n) {
+  if (n <= 10) return 1;
+  int a = 1, best = 1000;
+  for (int x = 2; x <= 10; ++x) {
+    if (n % x != 0 || x == 7 || n / x > 10 || n / x < x) continue;
+    if (x + n / x < best) {
+      best = x + n / x;
+      a = x;
+    }
   }
+  return a;
+}
+
+// every {2,3,5}-smooth axis length
+#define FOCK_SMOOTH_L(X)                                                                                       \
+  X(2) X(3) X(4) X(5) X(6) X(8) X(9) X(10) X(12) X(15) X(16) X(18) X(20) X(24) X(25) X(27) X(30) X(32) X(36) \
+  X(40) X(45) X(48) X(50) X(54) X(60) X(64) X(72)
+
+// 1 / n to one unit in the last place: fdiv's quotients stay exact (its error
+// is then at most 5 2^-24 idx/n, under 0.32/n at idx < 2^20)
+__device__ __forceinline__ float rcp_of(int n) { return __builtin_amdgcn_rcpf(static_cast<float>(n)); }
 
 template <typename C>
 __device__ __forceinline__ C cconj(C a) { return C{a.x, -a.y}; }
@@ -106,98 +116,111 @@ __device__ __forceinline__ C cconj(C a) { return C{a.x, -a.y}; }
 template <int S, typename C>
 __device__ __forceinline__ C twid(C w) { return S < 0 ? w : cconj(w); }
 
+// Twiddles of a length n = a b: W_n^{r j} at (r - 1) b + j, 1 <= r < a, j < b
+// (plan.cpp), at twiddle_offset(n) of the plan's table.
+constexpr int twiddle_count(int n) { return (radix_a(n) - 1) * (n / radix_a(n)); }
+
 // axis 2, pass a (or the only pass), from the planes in memory: consecutive
 // lanes take consecutive elements, so every load is coalesced
-template <int R, int S, typename C>
-__device__ __forceinline__ void ax2_load(C* s, const C* __restrict__ src, const PlaneGeo& g, int gc,
+template <int N, int S, typename C>
+__device__ __forceinline__ void ax2_load(C* s, const C* __restrict__ src, int n3, int pitch, int gc,
                                          const C* __restrict__ tw) {
-  const int M = g.n2 / R, mn = M * g.n3, total = gc * mn;
-  const float rmn = 1.0f / static_cast<float>(mn), r3 = 1.0f / static_cast<float>(g.n3);
+  constexpr int A = radix_a(N), R = A > 1 ? A : N, M = N / R;
+  const int mn = M * n3, total = gc * mn;
+  const float rmn = rcp_of(mn), r3 = rcp_of(n3);
   for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-    const int gg = fdiv(idx, rmn), rem = idx - gg * mn;
-    const int m = fdiv(rem, r3), j3 = rem - m * g.n3;
-    const C* p = src + (gg * (g.n2 * g.n3) + rem);
+    const int gg = gc > 1 ? fdiv(idx, rmn) : 0, rem = idx - __mul24(gg, mn);
+    const int m = M > 1 ? fdiv(rem, r3) : 0, j3 = rem - __mul24(m, n3);
+    const unsigned o = static_cast<unsigned>(__mul24(gg, N * n3) + rem) * sizeof(C);
     C v[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = p[r * mn];
+    for (int r = 0; r < R; ++r) v[r] = stream_load(lane_at(src + r * mn, o));
     Dft<R, S, C>::run(v);
-    C* d = s + (gg * g.n2 + m) * g.pitch + j3;
-    d[0] = v[0];
+    if constexpr (M > 1) {
 #pragma unroll
-    for (int r = 1; r < R; ++r) d[r * M * g.pitch] = M > 1 ? cmul(v[r], twid<S>(tw[r * m])) : v[r];
+      for (int r = 1; r < R; ++r) v[r] = cmul(v[r], twid<S>(tw[(r - 1) * M + m]));
+    }
+    C* d = s + __mul24(gg * N + m, pitch) + j3;
+#pragma unroll
+    for (int r = 0; r < R; ++r) d[r * (M * pitch)] = v[r];
   }
 }
 
 // axis 2, inverse pass a, to the planes in memory
-template <int R, int S, typename C>
-__device__ __forceinline__ void ax2_store(const C* s, C* __restrict__ dst, const PlaneGeo& g, int gc, const C* tw) {
-  const int M = g.n2 / R, mn = M * g.n3, total = gc * mn;
-  const float rmn = 1.0f / static_cast<float>(mn), r3 = 1.0f / static_cast<float>(g.n3);
+template <int N, int S, typename C>
+__device__ __forceinline__ void ax2_store(const C* s, C* __restrict__ dst, int n3, int pitch, int gc, const C* tw) {
+  constexpr int A = radix_a(N), R = A > 1 ? A : N, M = N / R;
+  const int mn = M * n3, total = gc * mn;
+  const float rmn = rcp_of(mn), r3 = rcp_of(n3);
   for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-    const int gg = fdiv(idx, rmn), rem = idx - gg * mn;
-    const int m = fdiv(rem, r3), j3 = rem - m * g.n3;
-    const C* p = s + (gg * g.n2 + m) * g.pitch + j3;
+    const int gg = gc > 1 ? fdiv(idx, rmn) : 0, rem = idx - __mul24(gg, mn);
+    const int m = M > 1 ? fdiv(rem, r3) : 0, j3 = rem - __mul24(m, n3);
+    const C* p = s + __mul24(gg * N + m, pitch) + j3;
     C v[R];
-    v[0] = p[0];
 #pragma unroll
-    for (int r = 1; r < R; ++r) {
-      v[r] = p[r * M * g.pitch];
-      if (M > 1) v[r] = cmul(v[r], twid<S>(tw[r * m]));
+    for (int r = 0; r < R; ++r) v[r] = p[r * (M * pitch)];
+    if constexpr (M > 1) {
+#pragma unroll
+      for (int r = 1; r < R; ++r) v[r] = cmul(v[r], twid<S>(tw[(r - 1) * M + m]));
     }
     Dft<R, S, C>::run(v);
-    C* d = dst + (gg * (g.n2 * g.n3) + rem);
+    const unsigned o = static_cast<unsigned>(__mul24(gg, N * n3) + rem) * sizeof(C);
 #pragma unroll
-    for (int r = 0; r < R; ++r) d[r * mn] = v[r];
+    for (int r = 0; r < R; ++r) stream_store(lane_at(dst + r * mn, o), v[r]);
   }
 }
 
 // axis 2, pass b
-template <int R, int S, typename C>
-__device__ __forceinline__ void ax2_b(C* s, const PlaneGeo& g, int gc) {
-  const int total = gc * g.a2 * g.n3;
-  const float r3 = 1.0f / static_cast<float>(g.n3);
+template <int N, int S, typename C>
+__device__ __forceinline__ void ax2_b(C* s, int n3, int pitch, int gc) {
+  constexpr int A = radix_a(N), R = N / A;
+  const int total = gc * A * n3;
+  const float r3 = rcp_of(n3);
   for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-    const int gk = fdiv(idx, r3), j3 = idx - gk * g.n3;
-    C* p = s + gk * R * g.pitch + j3;
+    const int gk = fdiv(idx, r3), j3 = idx - __mul24(gk, n3);
+    C* p = s + __mul24(gk * R, pitch) + j3;
     C v[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = p[r * g.pitch];
+    for (int r = 0; r < R; ++r) v[r] = p[r * pitch];
     Dft<R, S, C>::run(v);
 #pragma unroll
-    for (int r = 0; r < R; ++r) p[r * g.pitch] = v[r];
+    for (int r = 0; r < R; ++r) p[r * pitch] = v[r];
   }
 }
 
-// axis 3: consecutive lanes take consecutive rows, whose pitch is odd, so the
-// lanes spread over all LDS banks
-// pass a (S = -1: forward, twiddles after; INV: backwards, twiddles before)
-template <int R, int S, bool INV, typename C>
-__device__ __forceinline__ void ax3_a(C* s, const PlaneGeo& g, int rows, const C* tw) {
-  const int total = rows * g.b3;
-  const float rr = 1.0f / static_cast<float>(rows);
+// axis 3: consecutive lanes take consecutive rows, whose pitch N | 1 is odd,
+// so the lanes spread over all LDS banks
+// pass a (INV: backwards, twiddles before the DFT)
+template <int N, int S, bool INV, typename C>
+__device__ __forceinline__ void ax3_a(C* s, int rows, const C* tw) {
+  constexpr int R = radix_a(N), M = N / R, P = N | 1;
+  const int total = rows * M;
+  const float rr = rcp_of(rows);
   for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-    const int j = fdiv(idx, rr), row = idx - j * rows;
-    C* p = s + row * g.pitch + j;
+    const int j = fdiv(idx, rr), row = idx - __mul24(j, rows);
+    C* p = s + __mul24(row, P) + j;
+    const C* w = tw + j;
     C v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      v[r] = p[r * g.b3];
-      if (INV && r > 0) v[r] = cmul(v[r], twid<S>(tw[r * j]));
+      v[r] = p[r * M];
+      if (INV && r > 0) v[r] = cmul(v[r], twid<S>(w[(r - 1) * M]));
     }
     Dft<R, S, C>::run(v);
 #pragma unroll
-    for (int r = 0; r < R; ++r) p[r * g.b3] = !INV && r > 0 ? cmul(v[r], twid<S>(tw[r * j])) : v[r];
+    for (int r = 0; r < R; ++r) p[r * M] = !INV && r > 0 ? cmul(v[r], twid<S>(w[(r - 1) * M])) : v[r];
   }
 }
 
 // axis 3, pass b (or the only pass)
-template <int R, int S, typename C>
-__device__ __forceinline__ void ax3_b(C* s, const PlaneGeo& g, int rows) {
-  const int total = rows * g.a3;
-  const float rr = 1.0f / static_cast<float>(rows);
+template <int N, int S, typename C>
+__device__ __forceinline__ void ax3_b(C* s, int rows) {
+  constexpr int A = radix_a(N), R = N / A, P = N | 1;
+  const int total = rows * A;
+  const float rr = rcp_of(rows);
   for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-    const int k1 = fdiv(idx, rr), row = idx - k1 * rows;
-    C* p = s + row * g.pitch + k1 * R;
+    const int k1 = fdiv(idx, rr), row = idx - __mul24(k1, rows);
+    C* p = s + __mul24(row, P) + k1 * R;
     C v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = p[r];
@@ -209,16 +232,17 @@ __device__ __forceinline__ void ax3_b(C* s, const PlaneGeo& g, int rows) {
 
 // axis 3, pass b, times the kernel and back (BACK), with the energy sum (EN).
 // v: the tile's kernel values in the order [k2][k1][row]
-template <int R, bool EN, bool BACK, typename C, typename T>
-__device__ __forceinline__ void ax3_kernel(C* s, const PlaneGeo& g, int rows, const T* __restrict__ v, double* en) {
-  const int total = rows * g.a3;
-  const float rr = 1.0f / static_cast<float>(rows);
+template <int N, bool EN, bool BACK, typename C, typename T>
+__device__ __forceinline__ void ax3_kernel(C* s, int rows, const T* __restrict__ v, double* en) {
+  constexpr int A = radix_a(N), R = N / A, P = N | 1;
+  const int total = rows * A;
+  const float rr = rcp_of(rows);
   for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-    const int k1 = fdiv(idx, rr), row = idx - k1 * rows;
+    const int k1 = fdiv(idx, rr), row = idx - __mul24(k1, rows);
     T vv[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) vv[r] = v[r * total + idx];
-    C* p = s + row * g.pitch + k1 * R;
+    for (int r = 0; r < R; ++r) vv[r] = *lane_at(v + r * total, static_cast<unsigned>(idx) * sizeof(T));
+    C* p = s + __mul24(row, P) + k1 * R;
     C x[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) x[r] = p[r];
