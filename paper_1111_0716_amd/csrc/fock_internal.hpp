@@ -232,7 +232,7 @@ bool fused_supported(fock_precision prec, const int grid[3]);
 size_t fused_lds_bytes(fock_precision prec, int L);
 int fused_threads(fock_precision prec, int L);
 // split-K chunk of the overlap: a multiple of kOvChunkMin, at most kOvChunkMax
-constexpr int kOvChunkMin = 128, kOvChunkMax = 4096;
+constexpr int kOvChunkMin = 32, kOvChunkMax = 4096;
 int overlap_span(const Instance& in);
 size_t overlap_scratch_bytes(const Instance& in, int span);
 void prepare_fused_kernels(fock_precision prec, int lim);

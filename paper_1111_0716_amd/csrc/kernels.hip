@@ -27,6 +27,13 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   return t;  // valid in thread 0
 }
 
+// one step of a compensated (Neumaier) sum
+__device__ __forceinline__ void neumaier(double& sum, double& comp, double x) {
+  const double t = sum + x;
+  comp += (fabs(sum) >= fabs(x)) ? (sum - t) + x : (x - t) + sum;
+  sum = t;
+}
+
 // ---------------------------------------------------------------------------
 // energy reductions
 // ---------------------------------------------------------------------------
@@ -44,9 +51,7 @@ __global__ __launch_bounds__(kBlock) void k_energy_batch(const PairRef* __restri
     for (int c = 0; c < n2; ++c) e += epart[static_cast<size_t>(pi) * n2 + c];
     const double w = pr.mult * kw[pr.k] * occ[pr.k * nbands + pr.n] * kw[pr.kp] * occ[pr.kp * nbands + pr.m];
     const double x = w * e;
-    const double t = sum + x;  // Neumaier
-    comp += (fabs(sum) >= fabs(x)) ? (sum - t) + x : (x - t) + sum;
-    sum = t;
+    neumaier(sum, comp, x);
   }
   const double tot = block_sum(sum + comp, red);
   if (threadIdx.x == 0) ebsum[slot] = tot;
@@ -54,18 +59,20 @@ __global__ __launch_bounds__(kBlock) void k_energy_batch(const PairRef* __restri
 
 // slots[slot] = mult * (sum of part[0..n)) in a fixed order: Neumaier per
 // thread over a strided share, then the waves in order (1024 threads: the
-// partials of a batch run to tens of thousands, read once).  mult is 2 for a
-// batch of unordered pairs (each stands for both orders), else 1.
+// partials of a batch run to hundreds of thousands, read once, eight loads in
+// flight: 141264 partials took 75 us one at a time, 70632 take 14).  mult is 2 for a batch of
+// unordered pairs (each stands for both orders), else 1.
 constexpr int kSumBlock = 1024;
 __global__ __launch_bounds__(kSumBlock) void k_sum_slot(const double* __restrict__ part, long long n,
                                                         double* __restrict__ slots, int slot, double mult) {
   __shared__ double red[kSumBlock / 64];
   double sum = 0.0, comp = 0.0;
-  for (long long i = threadIdx.x; i < n; i += kSumBlock) {
-    const double x = part[i];
-    const double t = sum + x;
-    comp += (fabs(sum) >= fabs(x)) ? (sum - t) + x : (x - t) + sum;
-    sum = t;
+  for (long long i0 = threadIdx.x; i0 < n; i0 += 8 * kSumBlock) {
+    double x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = i0 + u * kSumBlock < n ? part[i0 + u * kSumBlock] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) neumaier(sum, comp, x[u]);
   }
   double v = sum + comp;
 #pragma unroll
@@ -79,17 +86,19 @@ __global__ __launch_bounds__(kSumBlock) void k_sum_slot(const double* __restrict
   }
 }
 
-__global__ void k_energy_finish(const double* __restrict__ ebsum, int first, int count, double factor,
-                                double* __restrict__ ex) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// ex = factor * (sum of ebsum[first .. first + count)) in order.  One wave: its
+// lanes load 64 values at once and hand them on in turn (a load for each value
+// in turn is a memory latency per value: 32 partials 3.5 -> 3.2 us).
+__global__ __launch_bounds__(64) void k_energy_finish(const double* __restrict__ ebsum, int first, int count,
+                                                      double factor, double* __restrict__ ex) {
   double sum = 0.0, comp = 0.0;
-  for (int i = 0; i < count; ++i) {
-    const double x = ebsum[first + i];
-    const double t = sum + x;
-    comp += (fabs(sum) >= fabs(x)) ? (sum - t) + x : (x - t) + sum;
-    sum = t;
+  for (int i0 = 0; i0 < count; i0 += 64) {
+    const int i = i0 + static_cast<int>(threadIdx.x);
+    const double mine = i < count ? ebsum[first + i] : 0.0;
+    const int n = min(64, count - i0);
+    for (int u = 0; u < n; ++u) neumaier(sum, comp, __shfl(mine, u, 64));
   }
-  ex[0] = factor * (sum + comp);
+  if (threadIdx.x == 0) ex[0] = factor * (sum + comp);
 }
 
 // ---------------------------------------------------------------------------

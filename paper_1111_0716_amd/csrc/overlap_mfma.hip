@@ -246,10 +246,13 @@ hipError_t overlap_t(const Plan& p, int inst, const void* psi, const void* vx, v
 // against this rule: 16^3 Gamma, 8 bands, FP64 285 -> 36 us; 48^3 Gamma, 48
 // bands, mixed 3.19 -> 2.93 ms; 32^3 2x2x2, 18 bands, FP64 (with the gradient)
 // 12.79 -> 12.40 ms; 72^3 2x2x2, 24 bands, FP32 77.0 ms both ways.
+// On small grids the shortest chunk is a 128th of the grid, down to 32 points:
+// 12x10x9 FP64, two k-points of three bands, 12.9 -> 5.3 us (9 chunks -> 34).
 int overlap_span(const Instance& in) {
   const long long nbj = ((in.nbands + 15) / 16 + 1) / 2;
   const long long want = std::max<long long>(1, 1024 / (nbj * nbj * in.nk));  // chunks
-  const long long span = (in.npts + want - 1) / want;
+  const long long least = std::max<long long>(kOvChunkMin, std::min<long long>(128, in.npts / 128));
+  const long long span = std::max(least, (in.npts + want - 1) / want);
   return static_cast<int>(std::min<long long>(kOvChunkMax, (span + kOvChunkMin - 1) / kOvChunkMin * kOvChunkMin));
 }
 

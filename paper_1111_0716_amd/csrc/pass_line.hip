@@ -148,7 +148,7 @@ __global__ __launch_bounds__(64, (LineShape<T, L>::WPE_FWD)) void k_line_fwd(
 // plane pass: axes 2 and 3 forward, x v_q/N, and back, in place
 // ---------------------------------------------------------------------------
 // EN: the weighted pair energies into epart[pair * tiles + tile]; BACK: the
-// inverse transforms (an energy batch has neither weights nor a way back).
+// inverse transforms (an energy batch has no way back).
 // What the pass has to do is one read and one write of the tile; the rest are
 // six LDS round trips of the values.
 template <typename T, bool EN, bool BACK>
@@ -179,7 +179,9 @@ __global__ __launch_bounds__(512, 4) void k_plane_pair(PlaneGeo g, int nbands, i
     // an unordered pair of a block with itself stands for both orders
     if constexpr (EN) w = (tri && o != p ? 2.0 : 1.0) * kw[ok] * occ[o0 + o] * kw[r.x] * occ[r.x * nbands + r.y];
   } else {
-    q = pairs[pi].q;
+    const PairRef pr = pairs[pi];
+    q = pr.q;
+    w = pr.mult * kw[pr.k] * occ[pr.k * nbands + pr.n] * kw[pr.kp] * occ[pr.kp * nbands + pr.m];
   }
   for (int i = threadIdx.x; i < g.tw2 + g.tw3; i += blockDim.x) t2[i] = i < g.tw2 ? tw2[i] : tw3[i - g.tw2];
   C* t = tbuf + (static_cast<size_t>(pi) * g.n1 + g0) * plane;
@@ -579,10 +581,10 @@ hipError_t line_energy_t(const Plan& p, const Batch& b, const void* psi, const d
                      plane_lds(g, sizeof(C)), p.stream, g, in.nbands, in.nk, 0, 1, 0,
                      static_cast<const int2*>(nullptr), static_cast<const int*>(nullptr), pairs, tbuf,
                      reinterpret_cast<const T*>(p.ws + in.vtab_off), tw + twiddle_offset(g.n2),
-                     tw + twiddle_offset(g.n3), occ, static_cast<const double*>(nullptr),
+                     tw + twiddle_offset(g.n3), occ, reinterpret_cast<const double*>(p.ws + in.kw_off),
                      reinterpret_cast<double*>(p.ws + p.epart_off));
   p.prof.end(FOCK_K_ENERGY_PENCIL, p.stream);
-  return launch_energy_reduce(p, b, occ, tiles);
+  return launch_sum_slot(p, static_cast<long long>(b.npairs) * tiles, b.slot, 1.0);
 }
 
 template <typename T, int L, int S>
