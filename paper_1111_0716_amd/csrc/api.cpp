@@ -254,7 +254,7 @@ fock_status run_overlaps(Plan* p, const void* const* psi, void* const* vx_psi, v
 fock_status run_energy(Plan* p, const void* const* psi, const double* const* occ, double* ex, bool after_apply) {
   for (const Batch& b : p->energy_batches) {
     const bool fused = p->inst[b.inst].fused;
-    if (after_apply && (fused || batch_apply_energy(*p, b.inst))) continue;
+    if (after_apply) continue;
     hipError_t e;
     if (fused) {
       e = launch_fused_energy(*p, b, psi[b.inst]);
@@ -266,10 +266,9 @@ fock_status run_energy(Plan* p, const void* const* psi, const double* const* occ
   }
   for (size_t i = 0; i < p->inst.size(); ++i) {
     const int ii = static_cast<int>(i);
-    const hipError_t e = !after_apply             ? launch_energy_finish(*p, ii, ex + i)
-                         : p->inst[i].fused       ? launch_eblk_finish(*p, ii, ex + i)
-                         : batch_apply_energy(*p, ii) ? launch_aslot_finish(*p, ii, ex + i)
-                                                  : launch_energy_finish(*p, ii, ex + i);
+    const hipError_t e = !after_apply       ? launch_energy_finish(*p, ii, ex + i)
+                         : p->inst[i].fused ? launch_eblk_finish(*p, ii, ex + i)
+                                            : launch_aslot_finish(*p, ii, ex + i);
     if (e != hipSuccess) return hip_fail(e, "energy finish launch");
   }
   return FOCK_OK;

@@ -47,7 +47,7 @@ struct Batch {
   int32_t npairs = 0;   // pairs in the batch (apply: nO*nP)
   int32_t slot = 0;
   int32_t per_wg = 1;   // energy on the whole-pair path: pairs per workgroup
-  int32_t eslot = -1;   // apply batch of the register-line path: its energy sum slot
+  int32_t eslot = -1;   // its energy sum slot (apply with energy)
 };
 
 // Outputs o0..o0+nout-1 of one instance on the whole-pair path, all sharing
@@ -92,11 +92,8 @@ struct Instance {
   std::vector<std::vector<int>> kpartners;  // k -> list of k'
   bool symmetric = true;                     // (k, k') listed iff (k', k) listed
   bool fused = false;                        // whole-pair path (cubic grid that fits one CU)
-  bool reg = false;                          // three-pass path with register-line kernels (N1 x L x L)
-  bool slab = false;                         // cubic FP32 register-line path with the slab pencil (pair buffer [j1][c2][c3])
   int rounds = -1;                           // whole-pair path by unordered pairs: its FusedRounds
-  bool line = false;                         // three-pass path of general grids (pass_line.hip)
-  PlaneGeo pg;                               // its tiles (and those of the general DFT)
+  PlaneGeo pg;                               // tiles of the three-pass path and of the DFT
   int pg_threads = 0;
   int nbands;
   int64_t band_stride;
@@ -110,7 +107,7 @@ struct Instance {
   int ovl_span = 0;  // grid points per split-K chunk of the overlap
   int first_ebatch = 0, n_ebatches = 0;
   int first_eblk = 0, n_eblk = 0;  // whole-pair apply-with-energy partials of this instance
-  int first_aslot = 0, n_aslot = 0;  // register-line apply-with-energy sum slots
+  int first_aslot = 0, n_aslot = 0;  // three-pass apply-with-energy sum slots
 };
 
 // Event-based per-kernel timing (see fock_profile_enable).
@@ -219,7 +216,6 @@ hipError_t launch_eblk_finish(const Plan& p, int inst, double* ex);
 hipError_t launch_zero_outputs(const Plan& p, int inst, void* out);
 hipError_t launch_zero_all_bands(const Plan& p, int inst, void* out);
 bool reg_dft_supported(fock_precision prec, const int grid[3]);
-void prepare_reg_dft_kernels(fock_precision prec, int lim);
 hipError_t launch_reg_dft3(const Plan& p, int inst, int sign, int count, void* data, long long stride);
 hipError_t launch_dft3(const Plan& p, int inst, int sign, long long count, void* data, long long stride);
 hipError_t launch_pw_to_grid(const Plan& p, int inst, const void* coef, const int* gidx, const int* npw, int npw_max,
@@ -236,35 +232,19 @@ constexpr int kOvChunkMin = 32, kOvChunkMax = 4096;
 int overlap_span(const Instance& in);
 size_t overlap_scratch_bytes(const Instance& in, int span);
 void prepare_fused_kernels(fock_precision prec, int lim);
-bool reg_supported(fock_precision prec, const int grid[3]);
-// grids where the register-line path can run its pencil pass over slabs of
-// fixed c2 (and the accumulate over independent lines)
-bool reg_slab_supported(fock_precision prec, const int grid[3]);
-// where it is taken without FOCK_SLAB=1 (measured per size)
-bool reg_slab_default(fock_precision prec, const int grid[3]);
-size_t reg_lds_bytes(fock_precision prec, int L);
-void prepare_reg_kernels(fock_precision prec, int lim);
-// energy: the pencil pass also writes the batch's weighted pair energies to
-// its slot (b.eslot); only where batch_apply_energy(inst)
-hipError_t launch_reg_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
-                                  const double* gscale, double hscale, bool backward, bool energy);
-// the instance's apply batches take its energy (the three-pass paths)
-bool batch_apply_energy(const Plan& p, int inst);
 // ebsum[slot] = mult * fixed-order sum of the first n energy partials (epart)
 hipError_t launch_sum_slot(const Plan& p, long long n, int slot, double mult);
 // E_x of a three-pass instance from its apply-with-energy slots
 hipError_t launch_aslot_finish(const Plan& p, int inst, double* ex);
-// three-pass path of general grids (pass_line.hip)
+// three-pass path (pass_line.hip)
 int plane_tiles(const PlaneGeo& g);
 size_t plane_lds_bytes(const PlaneGeo& g, size_t csize);
-// planes_of: pairs in flight, each with n1 planes
+// planes_of: pairs (or grids) in flight, each with n1 planes
 void plane_geometry(const int grid[3], long long planes_of, size_t csize, PlaneGeo* g, int* threads);
-hipError_t launch_line_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
-                                   const double* gscale, double hscale, bool backward, bool energy);
-hipError_t launch_line_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ);
 hipError_t launch_line_dft3(const Plan& p, int inst, int sign, int count, void* data, long long stride);
+// grids of the mixed precisions
+bool mixed_supported(const int grid[3]);
 void prepare_line_kernels(fock_precision prec, int lim);
-hipError_t launch_reg_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ);
 // eblk: if not null, the apply also writes per-block energy partials there
 hipError_t launch_fused_apply(const Plan& p, const FusedGroup& g, const void* psi, const double* occ, void* out,
                               const double* gscale, double hscale, bool backward, double* eblk);

@@ -166,20 +166,8 @@ hipError_t prepare_kernels(fock_precision prec, size_t* max_lds) {
   if (e != hipSuccess) return e;
   *max_lds = static_cast<size_t>(lim);
   prepare_fused_kernels(prec, lim - 256);
-  prepare_reg_kernels(prec, lim - 64);
   prepare_line_kernels(prec, lim - 64);
   return hipSuccess;
-}
-
-hipError_t launch_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
-                              bool energy, const double* gscale, double hscale, bool backward) {
-  energy = energy && batch_apply_energy(p, b.inst);
-  return p.inst[b.inst].line ? launch_line_apply_batch(p, b, psi, occ, out, gscale, hscale, backward, energy)
-                             : launch_reg_apply_batch(p, b, psi, occ, out, gscale, hscale, backward, energy);
-}
-
-hipError_t launch_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ) {
-  return p.inst[b.inst].line ? launch_line_energy_batch(p, b, psi, occ) : launch_reg_energy_batch(p, b, psi, occ);
 }
 
 hipError_t launch_energy_reduce(const Plan& p, const Batch& b, const double* occ, int n2) {
@@ -193,8 +181,6 @@ hipError_t launch_energy_reduce(const Plan& p, const Batch& b, const double* occ
   p.prof.end(FOCK_K_ENERGY_REDUCE, p.stream);
   return hipGetLastError();
 }
-
-bool batch_apply_energy(const Plan& p, int inst) { return !p.inst[inst].fused; }
 
 hipError_t launch_sum_slot(const Plan& p, long long n, int slot, double mult) {
   p.prof.begin(FOCK_K_ENERGY_REDUCE, p.stream);

@@ -1,5 +1,5 @@
-// Device helpers shared by the register-line passes (pass_reg.hip) and the
-// line passes of general grids (pass_line.hip).
+// Device helpers of the three-pass kernels (pass_line.hip, plane_fft.hpp) and
+// the register-line DFT (dft_reg.hip).
 #pragma once
 
 #include <type_traits>

@@ -186,6 +186,22 @@ bool rounds_valid(const Instance& in, const std::vector<int32_t>& pairs, const s
   return true;
 }
 
+// Where the three-pass path beats the whole-pair kernel on a grid L^3 with the
+// full k-pair set (`orb` orbitals).  The whole-pair kernel moves no pair buffer
+// but runs a workgroup per output and partner slice and transforms both orders
+// of a pair: it loses where outputs are too few to fill the chip, and at 32^3,
+// where it read-modify-writes its output per partner (4x4x4 k, 18 bands: 606 ms
+// a step against 337).  Apply with energy, whole-pair / three-pass, us:
+//   16^3 FP32   8 orbitals 20/23, 16 34/27, 48 87/62, 96 198/190, 128 263/290
+//   16^3 FP64   8 23/23, 16 40/34, 48 106/93, 64 140/140, 128 347/507
+//   24^3 FP32   4 25/22, 16 72/42, 48 204/161, 96 731/561, 128 982/950; within
+//               3 % from there on
+bool fused_loses(fock_precision prec, int L, int orb) {
+  if (L == 32) return true;
+  if (L == 24) return orb <= 128;
+  return orb > 8 && orb <= (prec == FOCK_C128 ? 56 : 96);
+}
+
 size_t env_mb(const char* name, size_t dflt) {
   const char* s = std::getenv(name);
   if (!s || !*s) return dflt;
@@ -299,38 +315,24 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   }
   const char* nofused = std::getenv("FOCK_NO_FUSED");
   const bool no_fused = tn.no_fused != 0 || (nofused && *nofused && *nofused != '0');
-  const char* noreg = std::getenv("FOCK_NO_REG");
-  const bool no_reg = noreg && *noreg && *noreg != '0';
   const char* nosym = std::getenv("FOCK_NO_PAIR_SYMMETRY");
   const bool no_sym = tn.no_pair_symmetry != 0 || (nosym && *nosym && *nosym != '0');
-  // FOCK_SLAB=0 keeps every grid on the plane-wise accumulate, FOCK_SLAB=1 puts
-  // every supported cubic grid on the slab path (measurement switch)
-  const char* slab_env = std::getenv("FOCK_SLAB");
-  const int slab_force = slab_env && *slab_env ? (*slab_env != '0' ? 1 : 0) : -1;
   const char* rounds_env = std::getenv("FOCK_FUSED_ROUNDS");
   const bool use_rounds = tn.fused_rounds != 0 || (rounds_env && *rounds_env && *rounds_env != '0');
   for (auto& in : p->inst) {
-    // The 32^3 FP32 whole-pair kernel read-modify-writes its output per
-    // partner; with the full k-pair set the three-pass path with pair
-    // symmetry moves fewer bytes per ordered pair and is faster (alpha boron
-    // 416 against 606 ms per step), so it takes those instances.
-    const bool sym_three_pass = !no_sym && !use_rounds && fused_rounds_supported(prec, in.grid) && full_kset(in) &&
-                                reg_supported(prec, in.grid) && !no_reg;
     const bool mixed = prec == FOCK_MIXED || prec == FOCK_MIXED_INV;
-    in.fused = !mixed && fused_supported(prec, in.grid) && !no_fused && !sym_three_pass;
-    in.reg = !in.fused && reg_supported(prec, in.grid) && !no_reg;
-    in.line = !in.fused && !in.reg;
-    in.slab = in.reg && (slab_force < 0 ? reg_slab_default(prec, in.grid)
-                                        : slab_force == 1 && reg_slab_supported(prec, in.grid));
-    if (mixed && !in.reg)
+    if (mixed && !mixed_supported(in.grid))
       return set_error(FOCK_ERR_UNSUPPORTED, "mixed precision needs a grid N1 x L x L with N1 and L in {24, 32, 36, 40, 48, 50, 54, 60, 64, 72}");
+    in.fused = !mixed && fused_supported(prec, in.grid) && !no_fused;
+    if (in.fused && !no_sym && !use_rounds && full_kset(in) && fused_loses(prec, in.grid[0], in.nk * in.nbands))
+      in.fused = false;
   }
 
   // tiles of the plane passes: the pair kernels of the line path, the DFT of
   // the others (a grid per band)
   for (auto& in : p->inst) {
     const long long orb = static_cast<long long>(in.nk) * in.nbands;
-    plane_geometry(in.grid, in.line ? orb * (orb + 1) / 2 : orb, p->csize, &in.pg, &in.pg_threads);
+    plane_geometry(in.grid, in.fused ? orb : orb * (orb + 1) / 2, p->csize, &in.pg, &in.pg_threads);
   }
 
   // ---- batch shapes ----
@@ -443,7 +445,7 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
     // all its ordered pairs is the time of its launches either way (12x10x9,
     // two k-points of three bands, 38880 points: 27.3 us with unordered and
     // 27.5 with ordered pairs; 8^3, 18432 points, 27.6) and keeps the plain order.
-    const bool tiny = in.line && static_cast<int64_t>(nout) * npart * in.npts <= 32768;
+    const bool tiny = static_cast<int64_t>(nout) * npart * in.npts <= 32768;
     if (!no_sym && !tiny && g.k0 == 0 && g.k1 == in.nk && full_kset(in)) {
       // Pair symmetry: W_ba = conj(W_ab) (the Nyquist-averaged kernel is even
       // in c -> -c, q -> -q), so each unordered pair is transformed once.  The
@@ -484,8 +486,8 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
       }
       continue;
     }
-    // outputs per batch: enough accumulate workgroups (planes, or 64-lane line blocks on the line path)
-    const int per_out = in.line ? (in.grid[1] * in.grid[2] + 63) / 64 : in.grid[0];
+    // outputs per batch: enough accumulate workgroups (64-lane line blocks)
+    const int per_out = static_cast<int>((static_cast<int64_t>(in.grid[1]) * in.grid[2] + 63) / 64);
     int nO = std::max(1, std::min(nout, (acc_wgs + per_out - 1) / per_out));
     nO = std::min(nO, pmax);
     const int nP = std::max(1, std::min(npart, pmax / nO));
@@ -509,10 +511,8 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   // a dedicated apply batch with no partners: not needed, the wrapper zero-fills.
   // energy pair lists
   std::vector<std::vector<PairRef>> elists(n_inst);
-  // energy partials of a three-pass batch: per pair one per line block, slab or tile
-  const auto eparts = [](const Instance& in) {
-    return static_cast<size_t>(in.line ? plane_tiles(in.pg) : in.grid[1]);
-  };
+  // energy partials of a three-pass batch: one per pair and tile
+  const auto eparts = [](const Instance& in) { return static_cast<size_t>(plane_tiles(in.pg)); };
   size_t max_eparts = 0, max_fused_epairs = 0;
   int slot = 0;
   for (int i = 0; i < n_inst; ++i) {
@@ -635,9 +635,8 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   }
   p->total_bytes = off;
   for (const auto& in : p->inst) {
-    const size_t need = in.fused ? fused_lds_bytes(prec, in.grid[0]) + 256
-                        : in.reg ? reg_lds_bytes(prec, in.grid[1]) + 64
-                                 : plane_lds_bytes(in.pg, p->csize) + 64;
+    const size_t need =
+        in.fused ? fused_lds_bytes(prec, in.grid[0]) + 256 : plane_lds_bytes(in.pg, p->csize) + 64;
     p->lds_needed = std::max(p->lds_needed, need);
   }
   p->apply_launches = 0;
@@ -679,7 +678,7 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
             for (int c3 = 0; c3 < L; ++c3)
               r[(static_cast<size_t>(c3) * L + c2) * L + c1] = t[(static_cast<size_t>(c1) * L + c2) * L + c3];
         t.swap(r);
-      } else if (in.line) {
+      } else {
         // line path: per tile of planes the positions of the plane passes, as
         // [k2][k1][row] (plane_fft.hpp): row (plane, r2 b2 + i2) holds the
         // class r2 + a2 i2 of axis 2, column (k1, k2) the class k1 + a3 k2
@@ -695,16 +694,6 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
                   const int c2 = p2 / g.b2 + g.a2 * (p2 % g.b2), c3 = k1 + g.a3 * k2;
                   *d++ = t[c1 * plane + static_cast<size_t>(c2) * g.n3 + c3];
                 }
-        t.swap(r);
-      } else if (in.reg && !in.slab) {
-        // register-line three-pass path reads the table as [c1][c3][c2]
-        // (grids N1 x L x L; the slab pencil reads it in grid order)
-        const int n1 = in.grid[0], L = in.grid[1];
-        std::vector<double> r(t.size());
-        for (int c1 = 0; c1 < n1; ++c1)
-          for (int c2 = 0; c2 < L; ++c2)
-            for (int c3 = 0; c3 < L; ++c3)
-              r[(static_cast<size_t>(c1) * L + c3) * L + c2] = t[(static_cast<size_t>(c1) * L + c2) * L + c3];
         t.swap(r);
       }
       if (prec != FOCK_C64) {

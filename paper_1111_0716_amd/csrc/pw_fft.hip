@@ -11,8 +11,8 @@
 //                  class of G, inverse DFT (unnormalised, exp(+))
 //   to the sphere  forward DFT in place, gather sqrt(Omega)/N F(class of G)
 //
-// DFT passes: on grids N1 x L x L with register-line kernels (pass_reg.hip) a
-// plane pass (axes 2 and 3, one line per lane) and a pencil pass (axis 1);
+// DFT passes: on small N1 x L x L grids (dft_reg.hip) a register-line
+// plane pass (axes 2 and 3, one line per lane) and pencil pass (axis 1);
 // elsewhere (pass_line.hip) the axes 3 and 2 of whole planes in LDS and the
 // axis 1 in registers, for every {2,3,5}-smooth axis up to 72.
 #include <algorithm>
