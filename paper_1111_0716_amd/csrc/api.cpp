@@ -240,12 +240,8 @@ fock_status run_apply(Plan* p, const void* const* psi, const double* const* occ,
 // band overlaps M of every instance with a non-null vmat entry (vmat may be null)
 fock_status run_overlaps(Plan* p, const void* const* psi, void* const* vx_psi, void* const* vmat) {
   if (!vmat) return FOCK_OK;
-  for (size_t i = 0; i < p->inst.size(); ++i) {
-    if (!vmat[i]) continue;
-    const hipError_t e = launch_overlap(*p, static_cast<int>(i), psi[i], vx_psi[i], vmat[i]);
-    if (e != hipSuccess) return hip_fail(e, "overlap launch");
-  }
-  return FOCK_OK;
+  const hipError_t e = launch_overlaps(*p, psi, vx_psi, vmat);
+  return e == hipSuccess ? FOCK_OK : hip_fail(e, "overlap launch");
 }
 
 // E_x of every instance into ex[i].  after_apply: every instance takes its
@@ -264,14 +260,8 @@ fock_status run_energy(Plan* p, const void* const* psi, const double* const* occ
     }
     if (e != hipSuccess) return hip_fail(e, "energy batch launch");
   }
-  for (size_t i = 0; i < p->inst.size(); ++i) {
-    const int ii = static_cast<int>(i);
-    const hipError_t e = !after_apply       ? launch_energy_finish(*p, ii, ex + i)
-                         : p->inst[i].fused ? launch_eblk_finish(*p, ii, ex + i)
-                                            : launch_aslot_finish(*p, ii, ex + i);
-    if (e != hipSuccess) return hip_fail(e, "energy finish launch");
-  }
-  return FOCK_OK;
+  const hipError_t e = launch_energy_finish(*p, ex, after_apply);
+  return e == hipSuccess ? FOCK_OK : hip_fail(e, "energy finish launch");
 }
 
 // Argument checks of the apply-with-energy calls (after check_ready).

@@ -210,9 +210,9 @@ hipError_t prepare_kernels(fock_precision prec, size_t* max_lds);
 hipError_t launch_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* vx, bool energy,
                               const double* gscale, double hscale, bool backward);
 hipError_t launch_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ);
-hipError_t launch_energy_finish(const Plan& p, int inst, double* ex);
-// E_x of a whole-pair instance from the per-block partials of an apply with energy
-hipError_t launch_eblk_finish(const Plan& p, int inst, double* ex);
+// E_x of every instance: from its energy batches, or (after_apply) from what
+// the apply wrote (its batches' slots, or the whole-pair kernel's partials)
+hipError_t launch_energy_finish(const Plan& p, double* ex, bool after_apply);
 hipError_t launch_zero_outputs(const Plan& p, int inst, void* out);
 hipError_t launch_zero_all_bands(const Plan& p, int inst, void* out);
 bool reg_dft_supported(fock_precision prec, const int grid[3]);
@@ -234,8 +234,6 @@ size_t overlap_scratch_bytes(const Instance& in, int span);
 void prepare_fused_kernels(fock_precision prec, int lim);
 // ebsum[slot] = mult * fixed-order sum of the first n energy partials (epart)
 hipError_t launch_sum_slot(const Plan& p, long long n, int slot, double mult);
-// E_x of a three-pass instance from its apply-with-energy slots
-hipError_t launch_aslot_finish(const Plan& p, int inst, double* ex);
 // three-pass path (pass_line.hip)
 int plane_tiles(const PlaneGeo& g);
 size_t plane_lds_bytes(const PlaneGeo& g, size_t csize);
@@ -256,6 +254,7 @@ hipError_t launch_fused_rounds(const Plan& p, const FusedRounds& r, const void* 
                                const double* gscale, double hscale, bool backward, double* eblk);
 // ebsum[slot] = fixed-order sum of n partials at part (FP64)
 hipError_t launch_sum_partials(const Plan& p, const double* part, long long n, int slot);
-hipError_t launch_overlap(const Plan& p, int inst, const void* psi, const void* vx, void* vmat);
+// M of every instance whose vmat entry is not null
+hipError_t launch_overlaps(const Plan& p, const void* const* psi, void* const* vx, void* const* vmat);
 
 }  // namespace fock

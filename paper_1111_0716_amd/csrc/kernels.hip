@@ -86,19 +86,29 @@ __global__ __launch_bounds__(kSumBlock) void k_sum_slot(const double* __restrict
   }
 }
 
-// ex = factor * (sum of ebsum[first .. first + count)) in order.  One wave: its
+// ex[i] = factor * (sum of src[0 .. count)) in order, a workgroup for each
+// instance of the launch (one launch for each costs a few us apiece).  Its
 // lanes load 64 values at once and hand them on in turn (a load for each value
 // in turn is a memory latency per value: 32 partials 3.5 -> 3.2 us).
-__global__ __launch_bounds__(64) void k_energy_finish(const double* __restrict__ ebsum, int first, int count,
-                                                      double factor, double* __restrict__ ex) {
+struct FinishItem {
+  const double* src;
+  double factor;
+  int count;
+};
+constexpr int kFinishItems = 64;
+struct FinishArgs {
+  FinishItem it[kFinishItems];
+};
+__global__ __launch_bounds__(64) void k_energy_finish(const FinishArgs args, double* __restrict__ ex) {
+  const FinishItem& in = args.it[blockIdx.x];
   double sum = 0.0, comp = 0.0;
-  for (int i0 = 0; i0 < count; i0 += 64) {
+  for (int i0 = 0; i0 < in.count; i0 += 64) {
     const int i = i0 + static_cast<int>(threadIdx.x);
-    const double mine = i < count ? ebsum[first + i] : 0.0;
-    const int n = min(64, count - i0);
+    const double mine = i < in.count ? in.src[i] : 0.0;
+    const int n = min(64, in.count - i0);
     for (int u = 0; u < n; ++u) neumaier(sum, comp, __shfl(mine, u, 64));
   }
-  if (threadIdx.x == 0) ex[0] = factor * (sum + comp);
+  if (threadIdx.x == 0) ex[blockIdx.x] = in.factor * (sum + comp);
 }
 
 // ---------------------------------------------------------------------------
@@ -190,16 +200,6 @@ hipError_t launch_sum_slot(const Plan& p, long long n, int slot, double mult) {
   return hipGetLastError();
 }
 
-hipError_t launch_aslot_finish(const Plan& p, int inst, double* ex) {
-  const Instance& in = p.inst[inst];
-  const double factor = -0.5 * in.omega / static_cast<double>(in.npts);  // as in launch_energy_finish
-  p.prof.begin(FOCK_K_ENERGY_REDUCE, p.stream);
-  hipLaunchKernelGGL(k_energy_finish, dim3(1), dim3(64), 0, p.stream,
-                     reinterpret_cast<const double*>(p.ws + p.ebsum_off), in.first_aslot, in.n_aslot, factor, ex);
-  p.prof.end(FOCK_K_ENERGY_REDUCE, p.stream);
-  return hipGetLastError();
-}
-
 hipError_t launch_sum_partials(const Plan& p, const double* part, long long n, int slot) {
   p.prof.begin(FOCK_K_ENERGY_REDUCE, p.stream);
   hipLaunchKernelGGL(k_sum_slot, dim3(1), dim3(kSumBlock), 0, p.stream, part, n,
@@ -208,40 +208,42 @@ hipError_t launch_sum_partials(const Plan& p, const double* part, long long n, i
   return hipGetLastError();
 }
 
-hipError_t launch_eblk_finish(const Plan& p, int inst, double* ex) {
-  const Instance& in = p.inst[inst];
-  const double factor = -0.5 * in.omega / static_cast<double>(in.npts);  // as in launch_energy_finish
-  if (in.rounds >= 0) {
-    // one partial per unordered pair: summed in a fixed order into the
-    // instance's slot, then scaled
-    const FusedRounds& r = p.fused_rounds[in.rounds];
-    hipError_t e = launch_sum_partials(p, reinterpret_cast<const double*>(p.ws + p.eblk_off) + r.eblk0, r.npairs,
-                                       r.eslot);
-    if (e != hipSuccess) return e;
+hipError_t launch_energy_finish(const Plan& p, double* ex, bool after_apply) {
+  const double* slots = reinterpret_cast<const double*>(p.ws + p.ebsum_off);
+  const double* eblk = reinterpret_cast<const double*>(p.ws + p.eblk_off);
+  const int n = static_cast<int>(p.inst.size());
+  for (int i0 = 0; i0 < n; i0 += kFinishItems) {
+    const int m = std::min(kFinishItems, n - i0);
+    FinishArgs a{};
+    for (int j = 0; j < m; ++j) {
+      const Instance& in = p.inst[i0 + j];
+      FinishItem& t = a.it[j];
+      // the tables hold v/N, so e = N * sum; E_x = -1/2 (Omega/N^2) * N * sum
+      t.factor = -0.5 * in.omega / static_cast<double>(in.npts);
+      if (!after_apply) {
+        t.src = slots + in.first_ebatch;
+        t.count = in.n_ebatches;
+      } else if (!in.fused) {
+        t.src = slots + in.first_aslot;
+        t.count = in.n_aslot;
+      } else if (in.rounds >= 0) {
+        // one partial per unordered pair: summed in a fixed order into the
+        // instance's slot first
+        const FusedRounds& r = p.fused_rounds[in.rounds];
+        const hipError_t e = launch_sum_partials(p, eblk + r.eblk0, r.npairs, r.eslot);
+        if (e != hipSuccess) return e;
+        t.src = slots + r.eslot;
+        t.count = 1;
+      } else {
+        t.src = eblk + in.first_eblk;
+        t.count = in.n_eblk;
+      }
+    }
     p.prof.begin(FOCK_K_ENERGY_REDUCE, p.stream);
-    hipLaunchKernelGGL(k_energy_finish, dim3(1), dim3(64), 0, p.stream,
-                       reinterpret_cast<const double*>(p.ws + p.ebsum_off), r.eslot, 1, factor, ex);
+    hipLaunchKernelGGL(k_energy_finish, dim3(m), dim3(64), 0, p.stream, a, ex + i0);
     p.prof.end(FOCK_K_ENERGY_REDUCE, p.stream);
-    return hipGetLastError();
   }
-  p.prof.begin(FOCK_K_ENERGY_REDUCE, p.stream);
-  hipLaunchKernelGGL(k_energy_finish, dim3(1), dim3(64), 0, p.stream,
-                     reinterpret_cast<const double*>(p.ws + p.eblk_off), in.first_eblk, in.n_eblk, factor, ex);
-  p.prof.end(FOCK_K_ENERGY_REDUCE, p.stream);
   return hipGetLastError();
 }
-
-hipError_t launch_energy_finish(const Plan& p, int inst, double* ex) {
-  const Instance& in = p.inst[inst];
-  // the tables hold v/N, so e = N * sum; E_x = -1/2 (Omega/N^2) * N * sum
-  const double factor = -0.5 * in.omega / static_cast<double>(in.npts);
-  p.prof.begin(FOCK_K_ENERGY_REDUCE, p.stream);
-  hipLaunchKernelGGL(k_energy_finish, dim3(1), dim3(64), 0, p.stream,
-                     reinterpret_cast<const double*>(p.ws + p.ebsum_off), in.first_ebatch, in.n_ebatches, factor,
-                     ex);
-  p.prof.end(FOCK_K_ENERGY_REDUCE, p.stream);
-  return hipGetLastError();
-}
-
 
 }  // namespace fock

@@ -17,6 +17,7 @@
 // A[i = l % 16][k = l / 16] and B[k = l / 16][j = l % 16]; it receives
 // D[i][j = l % 16] for v = 0..3 with i = 4 (l / 16) + v (FP32) or
 // i = l / 16 + 4 v (FP64), as measured on gfx950.
+#include <algorithm>
 #include <type_traits>
 
 #include "fock_internal.hpp"
@@ -65,13 +66,45 @@ struct OvStage {
                 "chunks and sub-chunks of whole slabs");
 };
 
-// grid: (block_i * nbj + block_j, chunk, k); 256 threads
+// The instances of one launch.  A plan of many small instances would otherwise
+// take two launches of a few workgroups for each (twelve Gamma cells of 16 to
+// 40 points: 160 us of the 770 of an apply), so up to kOvItems share both.
+struct OvItem {
+  const void* psi;
+  const void* vx;
+  void* vmat;
+  double* part;
+  long long bs, npts;
+  double dv;
+  int nbands, nk, nt, span, nchunks;
+  unsigned blk1, red1;  // end of its workgroups in the product and in the reduction
+};
+constexpr int kOvItems = 16;
+struct OvArgs {
+  OvItem it[kOvItems];
+  int n;
+};
+
+// The instance of workgroup b, and b's number within it.
+template <unsigned OvItem::*END>
+__device__ __forceinline__ const OvItem& ov_item(const OvArgs& a, unsigned& b) {
+  int i = 0;
+  while (i + 1 < a.n && b >= a.it[i].*END) ++i;
+  if (i > 0) b -= a.it[i - 1].*END;
+  return a.it[i];
+}
+
+// workgroups of an instance: (k, chunk, block_i * nbj + block_j), the last fastest; 256 threads
 template <typename T>
-__global__ __launch_bounds__(64 * kOvWaves) void k_overlap_mfma(const typename cx<T>::t* __restrict__ psi,
-                                                                 const typename cx<T>::t* __restrict__ vx, int nbands,
-                                                                 long long bs, long long npts, int nt, int span,
-                                                                 double* __restrict__ part) {
+__global__ __launch_bounds__(64 * kOvWaves) void k_overlap_mfma(const OvArgs args) {
   using C = typename cx<T>::t;
+  unsigned wg = blockIdx.x;
+  const OvItem& in = ov_item<&OvItem::blk1>(args, wg);
+  const C* __restrict__ psi = static_cast<const C*>(in.psi);
+  const C* __restrict__ vx = static_cast<const C*>(in.vx);
+  double* __restrict__ part = in.part;
+  const int nbands = in.nbands, nt = in.nt, span = in.span;
+  const long long bs = in.bs, npts = in.npts;
   using M = Mfma<T>;
   using S = OvStage<T>;
   using V = typename S::V;
@@ -81,8 +114,9 @@ __global__ __launch_bounds__(64 * kOvWaves) void k_overlap_mfma(const typename c
   __shared__ C sb[2][kBlk][kSlab + 1];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int nbj = (nt + 1) / 2;
-  const int bi = blockIdx.x / nbj, bj = blockIdx.x - bi * nbj;
-  const int chunk = blockIdx.y, k = blockIdx.z;
+  const int kc = wg / (nbj * nbj), bij = wg - kc * (nbj * nbj);
+  const int bi = bij / nbj, bj = bij - bi * nbj;
+  const int k = kc / in.nchunks, chunk = kc - k * in.nchunks;
   const long long c0 = static_cast<long long>(chunk) * span;
   const long long c1 = c0 + span < npts ? c0 + span : npts;
   const size_t kb = static_cast<size_t>(k) * nbands;
@@ -169,7 +203,7 @@ __global__ __launch_bounds__(64 * kOvWaves) void k_overlap_mfma(const typename c
     buf ^= 1;
   }
   if (!live) return;
-  double* dst = part + ((static_cast<size_t>(chunk) * gridDim.z + k) * (static_cast<size_t>(nt) * nt) +
+  double* dst = part + ((static_cast<size_t>(chunk) * in.nk + k) * (static_cast<size_t>(nt) * nt) +
                         static_cast<size_t>(ti) * nt + tj) * 512;
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
@@ -185,18 +219,23 @@ __global__ __launch_bounds__(64 * kOvWaves) void k_overlap_mfma(const typename c
 // waits on one load after another: at a Gamma cell of 48 bands that chain is
 // longer than the product itself).
 template <typename T>
-__global__ __launch_bounds__(256) void k_overlap_reduce(const double2* __restrict__ part, int nchunks, int nk,
-                                                        int nbands, int ntj, double dv,
-                                                        typename cx<T>::t* __restrict__ vmat) {
+__global__ __launch_bounds__(256) void k_overlap_reduce(const OvArgs args) {
   using C = typename cx<T>::t;
   __shared__ double2 red[16][16];
-  const int row = blockIdx.x & 15, tile = blockIdx.x >> 4, k = blockIdx.y;
+  unsigned wg = blockIdx.x;
+  const OvItem& in = ov_item<&OvItem::red1>(args, wg);
+  const double2* __restrict__ part = reinterpret_cast<const double2*>(in.part);
+  C* __restrict__ vmat = static_cast<C*>(in.vmat);
+  const int nbands = in.nbands, nchunks = in.nchunks, nk = in.nk, ntj = in.nt, tiles = in.nt * in.nt;
+  const double dv = in.dv;
+  const int k = wg / (tiles * 16), kt = wg - k * (tiles * 16);
+  const int row = kt & 15, tile = kt >> 4;
   const int ti = tile / ntj, tj = tile - ti * ntj;
   const int i = ti * 16 + row;
   if (i >= nbands) return;  // the whole workgroup
   const int col = threadIdx.x & 15, share = threadIdx.x >> 4;
-  const size_t step = static_cast<size_t>(nk) * (gridDim.x >> 4) * 256;  // elements from chunk to chunk
-  const double2* src = part + (static_cast<size_t>(k) * (gridDim.x >> 4) + tile) * 256 + row * 16 + col;
+  const size_t step = static_cast<size_t>(nk) * tiles * 256;  // elements from chunk to chunk
+  const double2* src = part + (static_cast<size_t>(k) * tiles + tile) * 256 + row * 16 + col;
   double sr = 0.0, si = 0.0;
 #pragma unroll 4
   for (int c = share; c < nchunks; c += 16) {
@@ -217,22 +256,50 @@ __global__ __launch_bounds__(256) void k_overlap_reduce(const double2* __restric
 }
 
 template <typename T>
-hipError_t overlap_t(const Plan& p, int inst, const void* psi, const void* vx, void* vmat) {
-  using C = typename cx<T>::t;
-  const Instance& in = p.inst[inst];
-  const int nt = (in.nbands + 15) / 16;
-  const int nbj = (nt + 1) / 2;
-  const int span = in.ovl_span;
-  const int nchunks = static_cast<int>((in.npts + span - 1) / span);
-  double* part = reinterpret_cast<double*>(p.ws + p.ovl_off);
+hipError_t launch_items(const Plan& p, const OvArgs& a) {
+  const OvItem& last = a.it[a.n - 1];
   p.prof.begin(FOCK_K_OVERLAP, p.stream);
-  hipLaunchKernelGGL((k_overlap_mfma<T>), dim3(nbj * nbj, nchunks, in.nk), dim3(64 * kOvWaves), 0, p.stream,
-                     static_cast<const C*>(psi), static_cast<const C*>(vx), in.nbands,
-                     static_cast<long long>(in.band_stride), static_cast<long long>(in.npts), nt, span, part);
-  hipLaunchKernelGGL((k_overlap_reduce<T>), dim3(nt * nt * 16, in.nk), dim3(256), 0, p.stream,
-                     reinterpret_cast<const double2*>(part), nchunks, in.nk, in.nbands, nt, in.omega / static_cast<double>(in.npts), static_cast<C*>(vmat));
+  hipLaunchKernelGGL((k_overlap_mfma<T>), dim3(last.blk1), dim3(64 * kOvWaves), 0, p.stream, a);
+  hipLaunchKernelGGL((k_overlap_reduce<T>), dim3(last.red1), dim3(256), 0, p.stream, a);
   p.prof.end(FOCK_K_OVERLAP, p.stream);
   return hipGetLastError();
+}
+
+template <typename T>
+hipError_t overlaps_t(const Plan& p, const void* const* psi, void* const* vx, void* const* vmat) {
+  const size_t room = std::max(p.tbuf_bytes, p.ovl_bytes);  // the pair buffer's memory, free by now
+  OvArgs a{};
+  size_t used = 0;
+  for (size_t i = 0; i < p.inst.size(); ++i) {
+    if (!vmat[i]) continue;
+    const Instance& in = p.inst[i];
+    const size_t bytes = overlap_scratch_bytes(in, in.ovl_span);
+    if (a.n == kOvItems || (a.n > 0 && used + bytes > room)) {
+      const hipError_t e = launch_items<T>(p, a);
+      if (e != hipSuccess) return e;
+      a.n = 0;
+      used = 0;
+    }
+    const unsigned blk0 = a.n ? a.it[a.n - 1].blk1 : 0, red0 = a.n ? a.it[a.n - 1].red1 : 0;
+    OvItem& t = a.it[a.n++];
+    t.psi = psi[i];
+    t.vx = vx[i];
+    t.vmat = vmat[i];
+    t.part = reinterpret_cast<double*>(p.ws + p.ovl_off + used);
+    t.bs = static_cast<long long>(in.band_stride);
+    t.npts = static_cast<long long>(in.npts);
+    t.dv = in.omega / static_cast<double>(in.npts);
+    t.nbands = in.nbands;
+    t.nk = in.nk;
+    t.nt = (in.nbands + 15) / 16;
+    t.span = in.ovl_span;
+    t.nchunks = static_cast<int>((in.npts + t.span - 1) / t.span);
+    const unsigned nbj = (t.nt + 1) / 2;
+    t.blk1 = blk0 + nbj * nbj * t.nchunks * t.nk;
+    t.red1 = red0 + static_cast<unsigned>(t.nt) * t.nt * 16 * t.nk;
+    used += bytes;
+  }
+  return a.n ? launch_items<T>(p, a) : hipSuccess;
 }
 
 }  // namespace
@@ -262,8 +329,8 @@ size_t overlap_scratch_bytes(const Instance& in, int span) {
   return nchunks * in.nk * nt * nt * 512 * sizeof(double);
 }
 
-hipError_t launch_overlap(const Plan& p, int inst, const void* psi, const void* vx, void* vmat) {
-  return p.io64() ? overlap_t<double>(p, inst, psi, vx, vmat) : overlap_t<float>(p, inst, psi, vx, vmat);
+hipError_t launch_overlaps(const Plan& p, const void* const* psi, void* const* vx, void* const* vmat) {
+  return p.io64() ? overlaps_t<double>(p, psi, vx, vmat) : overlaps_t<float>(p, psi, vx, vmat);
 }
 
 }  // namespace fock
