@@ -71,9 +71,9 @@ def kernel_model(grid, s):
     energy (whole-pair energy kernel):
         F = 5 N log2 N + 9 N,    B = 2 s N  (read u_m and u_n)
     The passes of the three-pass path split the apply's flops
-        plane       F = 5 N log2(N2 N3) + 6 N
-        pencil      F = 10 N log2 N1 + 2 N
-        accumulate  F = 5 N log2(N2 N3) + 8 N
+        plane       F = 5 N log2 N1 + 6 N          (axis 1)
+        pencil      F = 10 N log2(N2 N3) + 2 N     (axes 2 and 3, there and back)
+        accumulate  F = 5 N log2 N1 + 8 N          (axis 1)
     but carry no byte model of their own: what one pass moves depends on how
     much of its operands the caches serve, so per-pass bytes are only quoted
     from the hardware counters.  s is the complex size."""
@@ -84,11 +84,11 @@ def kernel_model(grid, s):
     return {
         "fused": dict(flops=10 * n * math.log2(n) + 16 * n, bytes=4 * s * n),
         "energy_fused": dict(flops=5 * n * math.log2(n) + 9 * n, bytes=2 * s * n),
-        "plane": dict(flops=5 * n * l23 + 6 * n),
-        "pencil": dict(flops=10 * n * l1 + 2 * n),
-        "accumulate": dict(flops=5 * n * l23 + 8 * n),
-        "energy_plane": dict(flops=5 * n * l23 + 6 * n),
-        "energy_pencil": dict(flops=5 * n * l1 + 3 * n),
+        "plane": dict(flops=5 * n * l1 + 6 * n),
+        "pencil": dict(flops=10 * n * l23 + 2 * n),
+        "accumulate": dict(flops=5 * n * l1 + 8 * n),
+        "energy_plane": dict(flops=5 * n * l1 + 6 * n),
+        "energy_pencil": dict(flops=5 * n * l23 + 3 * n),
     }
 
 

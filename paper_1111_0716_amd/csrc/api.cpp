@@ -260,6 +260,11 @@ fock_status run_energy(Plan* p, const void* const* psi, const double* const* occ
     }
     if (e != hipSuccess) return hip_fail(e, "energy batch launch");
   }
+  if (after_apply)
+    for (const Batch& b : p->ordered_energy) {
+      const hipError_t e = launch_lds_energy_batch(*p, b, psi[b.inst], occ[b.inst]);
+      if (e != hipSuccess) return hip_fail(e, "energy batch launch");
+    }
   const hipError_t e = launch_energy_finish(*p, ex, after_apply);
   return e == hipSuccess ? FOCK_OK : hip_fail(e, "energy finish launch");
 }

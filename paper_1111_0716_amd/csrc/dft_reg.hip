@@ -15,7 +15,7 @@
 namespace fock {
 
 template <typename T, int L>
-struct RegShape {
+struct DftShape {
   static constexpr int LP = L + 1;  // padded LDS row
   // axis switches go through LDS one component (real, then imaginary) at a time
   static constexpr int PLANE_LDS = L * LP * static_cast<int>(sizeof(T));
@@ -47,10 +47,10 @@ __device__ __forceinline__ void transpose_plane(C* x, T* sp, int col) {
 // plane pass: axes 2 and 3 of plane j1, read and written as columns (one
 // line per lane, coalesced); two transposes bring the rows in and back out
 template <typename T, int L, int S>
-__global__ __launch_bounds__((RegShape<T, L>::NTP), 2) void k_dft_plane_reg(
+__global__ __launch_bounds__((DftShape<T, L>::NTP), 2) void k_dft_plane_reg(
     int n1, typename cx<T>::t* __restrict__ data, long long stride) {
   using C = typename cx<T>::t;
-  using Sh = RegShape<T, L>;
+  using Sh = DftShape<T, L>;
   constexpr int LL = L * L;
   extern __shared__ unsigned char smem_raw[];
   const int t = threadIdx.x, pl = t / L, col = t - (t / L) * L;
@@ -97,7 +97,7 @@ namespace {
 
 template <typename T, int L, int S>
 void dft_plane_L(const Plan& p, int n1, int count, typename cx<T>::t* d, long long stride) {
-  using Sh = RegShape<T, L>;
+  using Sh = DftShape<T, L>;
   hipLaunchKernelGGL((k_dft_plane_reg<T, L, S>), dim3((n1 + Sh::PL - 1) / Sh::PL, count), dim3(Sh::NTP), Sh::LDS,
                      p.stream, n1, d, stride);
 }

@@ -93,6 +93,8 @@ struct Instance {
   bool symmetric = true;                     // (k, k') listed iff (k', k) listed
   bool fused = false;                        // whole-pair path (cubic grid that fits one CU)
   int rounds = -1;                           // whole-pair path by unordered pairs: its FusedRounds
+  bool reg = false;                          // register-line passes (pass_reg.hip; not FP64)
+  bool slab = false;                         // their slab form (pair buffer [j1][c2][c3])
   PlaneGeo pg;                               // tiles of the three-pass path and of the DFT
   int pg_threads = 0;
   int nbands;
@@ -167,10 +169,12 @@ struct Plan {
   hipStream_t stream = nullptr;
   std::vector<Instance> inst;
   std::vector<Batch> apply_batches, energy_batches;
+  std::vector<Batch> ordered_energy;  // E_x after an apply where not the apply's own (energy_lds.hip)
   std::vector<FusedGroup> fused_groups;
   std::vector<FusedRounds> fused_rounds;
   // workspace layout (bytes)
-  size_t tw_off = 0;                  // twiddle tables
+  size_t tw_off = 0;                  // twiddle tables of the plane passes
+  size_t tw1_off = 0;                 // and W_L^t, t < L (energy_lds.hip)
   size_t const_bytes = 0;             // uploaded prefix
   size_t tbuf_off = 0, tbuf_bytes = 0;
   size_t tbuf64_off = 0;  // FOCK_MIXED: FP64 pair buffer beside the FP32 one at tbuf_off
@@ -234,11 +238,22 @@ size_t overlap_scratch_bytes(const Instance& in, int span);
 void prepare_fused_kernels(fock_precision prec, int lim);
 // ebsum[slot] = mult * fixed-order sum of the first n energy partials (epart)
 hipError_t launch_sum_slot(const Plan& p, long long n, int slot, double mult);
+// register-line passes (pass_reg.hip)
+bool reg_supported(fock_precision prec, const int grid[3]);
+bool reg_slab_supported(fock_precision prec, const int grid[3]);
+bool reg_slab_default(fock_precision prec, const int grid[3]);
+size_t reg_lds_bytes(fock_precision prec, int L);
+void prepare_reg_kernels(fock_precision prec, int lim);
+hipError_t launch_reg_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
+                                  const double* gscale, double hscale, bool backward, bool energy);
+hipError_t launch_reg_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ);
+// E_x of FP32 plans on general grids (energy_lds.hip)
+hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ);
 // three-pass path (pass_line.hip)
 int plane_tiles(const PlaneGeo& g);
 size_t plane_lds_bytes(const PlaneGeo& g, size_t csize);
-// planes_of: pairs (or grids) in flight, each with n1 planes
-void plane_geometry(const int grid[3], long long planes_of, size_t csize, PlaneGeo* g, int* threads);
+// planes_of: pairs in flight, each with n1 planes, in at most max_tiles tiles
+void plane_geometry(const int grid[3], long long planes_of, size_t csize, int max_tiles, PlaneGeo* g, int* threads);
 hipError_t launch_line_dft3(const Plan& p, int inst, int sign, int count, void* data, long long stride);
 // grids of the mixed precisions
 bool mixed_supported(const int grid[3]);

@@ -176,6 +176,7 @@ hipError_t prepare_kernels(fock_precision prec, size_t* max_lds) {
   if (e != hipSuccess) return e;
   *max_lds = static_cast<size_t>(lim);
   prepare_fused_kernels(prec, lim - 256);
+  prepare_reg_kernels(prec, lim - 64);
   prepare_line_kernels(prec, lim - 64);
   return hipSuccess;
 }

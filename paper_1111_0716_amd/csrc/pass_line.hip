@@ -691,7 +691,7 @@ static int plane_threads(const PlaneGeo& g) {
 //   tile gives them: 320 or 384 threads leave the SIMDs unevenly filled.
 //   40x40 FP32: 256 threads 261 us, 320 323, 384 353, 192 262, 128 270; 48x48
 //   FP64: 256 247, 384 286; 72x72 FP64: 512 449, 384 475, 256 525.
-void plane_geometry(const int grid[3], long long planes_of, size_t csize, PlaneGeo* g, int* threads) {
+void plane_geometry(const int grid[3], long long planes_of, size_t csize, int max_tiles, PlaneGeo* g, int* threads) {
   g->n1 = grid[0];
   g->n2 = grid[1];
   g->n3 = grid[2];
@@ -704,38 +704,24 @@ void plane_geometry(const int grid[3], long long planes_of, size_t csize, PlaneG
   g->pitch = g->n3 | 1;
   g->g = std::max(1, std::min(g->n1, (csize == 16 ? 1440 : 2880) / (g->n2 * g->n3)));
   while (g->g > 1 && planes_of * plane_tiles(*g) < 1024) g->g = (g->g + 1) / 2;
+  g->g = std::max(g->g, (g->n1 + max_tiles - 1) / max_tiles);
   *threads = plane_threads(*g);
 }
 
 hipError_t launch_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
                               bool energy, const double* gscale, double hscale, bool backward) {
-  const size_t t = p.tbuf_off, t64 = p.tbuf64_off;
-  switch (p.prec) {
-    case FOCK_C64:
-      return line_apply_t<float, float, float, float>(p, b, psi, occ, out, gscale, hscale, backward, energy, t, t);
-    case FOCK_C128:
-      return line_apply_t<double, double, double, double>(p, b, psi, occ, out, gscale, hscale, backward, energy, t, t);
-    // FP32 co-densities and axis 1 forward into the FP32 buffer, FP64 from there
-    case FOCK_MIXED:
-      return line_apply_t<float, double, double, double>(p, b, psi, occ, out, gscale, hscale, backward, energy, t, t64);
-    // FP64 up to the plane pass's last transform, FP32 axis 1 and sums back
-    case FOCK_MIXED_INV:
-      return line_apply_t<double, double, float, double>(p, b, psi, occ, out, gscale, hscale, backward, energy, t64, t);
-  }
-  return hipErrorInvalidValue;
+  const size_t t = p.tbuf_off;
+  if (p.inst[b.inst].reg) return launch_reg_apply_batch(p, b, psi, occ, out, gscale, hscale, backward, energy);
+  return p.prec == FOCK_C64  // its energies: energy_lds.hip
+             ? line_apply_t<float, float, float, float>(p, b, psi, occ, out, gscale, hscale, backward, false, t, t)
+             : line_apply_t<double, double, double, double>(p, b, psi, occ, out, gscale, hscale, backward, energy, t, t);
 }
 
 hipError_t launch_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ) {
-  switch (p.prec) {
-    case FOCK_C64: return line_energy_t<float, float, float>(p, b, psi, occ, p.tbuf_off);
-    case FOCK_C128: return line_energy_t<double, double, double>(p, b, psi, occ, p.tbuf_off);
-    case FOCK_MIXED: return line_energy_t<float, double, double>(p, b, psi, occ, p.tbuf_off);
-    case FOCK_MIXED_INV: return line_energy_t<double, double, double>(p, b, psi, occ, p.tbuf64_off);
-  }
-  return hipErrorInvalidValue;
+  if (p.inst[b.inst].reg) return launch_reg_energy_batch(p, b, psi, occ);
+  return p.prec == FOCK_C64 ? launch_lds_energy_batch(p, b, psi, occ)
+                            : line_energy_t<double, double, double>(p, b, psi, occ, p.tbuf_off);
 }
-
-bool mixed_supported(const int grid[3]) { return grid[1] == grid[2] && mixed_len(grid[0]) && mixed_len(grid[1]); }
 
 hipError_t launch_line_dft3(const Plan& p, int inst, int sign, int count, void* data, long long stride) {
   const Instance& in = p.inst[inst];
@@ -757,13 +743,6 @@ void prepare_line_kernels(fock_precision prec, int lim) {
     return;
   }
   plane_lds_attr<double>(lim);
-  const void* mixed[] = {reinterpret_cast<const void*>(&k_plane_pair<double, true, true, float, double>),
-                         reinterpret_cast<const void*>(&k_plane_pair<double, false, true, float, double>),
-                         reinterpret_cast<const void*>(&k_plane_pair<double, true, false, float>),
-                         reinterpret_cast<const void*>(&k_plane_pair<double, true, true, double, float>),
-                         reinterpret_cast<const void*>(&k_plane_pair<double, false, true, double, float>)};
-  for (const void* f : mixed)
-    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) != hipSuccess) (void)hipGetLastError();
 }
 
 }  // namespace fock

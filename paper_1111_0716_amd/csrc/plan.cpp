@@ -186,20 +186,18 @@ bool rounds_valid(const Instance& in, const std::vector<int32_t>& pairs, const s
   return true;
 }
 
-// Where the three-pass path beats the whole-pair kernel on a grid L^3 with the
+// Where the three-pass path beats the whole-pair kernel at 16^3 FP64 with the
 // full k-pair set (`orb` orbitals).  The whole-pair kernel moves no pair buffer
 // but runs a workgroup per output and partner slice and transforms both orders
-// of a pair: it loses where outputs are too few to fill the chip, and at 32^3,
-// where it read-modify-writes its output per partner (4x4x4 k, 18 bands: 606 ms
-// a step against 337).  Apply with energy, whole-pair / three-pass, us:
-//   16^3 FP32   8 orbitals 20/23, 16 34/27, 48 87/62, 96 198/190, 128 263/290
-//   16^3 FP64   8 23/23, 16 40/34, 48 106/93, 64 140/140, 128 347/507
-//   24^3 FP32   4 25/22, 16 72/42, 48 204/161, 96 731/561, 128 982/950; within
-//               3 % from there on
-bool fused_loses(fock_precision prec, int L, int orb) {
-  if (L == 32) return true;
-  if (L == 24) return orb <= 128;
-  return orb > 8 && orb <= (prec == FOCK_C128 ? 56 : 96);
+// of a pair: it loses where outputs are too few to fill the chip.  Apply with
+// energy, whole-pair / three-pass, us: 8 orbitals 23/23, 16 40/34, 48 106/93,
+// 64 140/140, 128 347/507.  (FP32 would gain more, 24^3 with 48 orbitals
+// 204/161, but its energies would be sums of other roundings.)
+bool fused_loses(fock_precision prec, int orb) { return prec == FOCK_C128 && orb > 8 && orb <= 56; }
+
+// the grids with that choice
+bool fused_optional(fock_precision prec, const int grid[3], bool no_fused) {
+  return !no_fused && prec == FOCK_C128 && fused_supported(prec, grid);
 }
 
 size_t env_mb(const char* name, size_t dflt) {
@@ -317,22 +315,51 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   const bool no_fused = tn.no_fused != 0 || (nofused && *nofused && *nofused != '0');
   const char* nosym = std::getenv("FOCK_NO_PAIR_SYMMETRY");
   const bool no_sym = tn.no_pair_symmetry != 0 || (nosym && *nosym && *nosym != '0');
+  // the FP32 and mixed plans' register-line passes off / on every cubic grid's
+  // slab form (measurement switches)
+  const char* noreg = std::getenv("FOCK_NO_REG");
+  const bool no_reg = noreg && *noreg && *noreg != '0';
+  const char* slab_env = std::getenv("FOCK_SLAB");
+  const int slab_force = slab_env && *slab_env ? (*slab_env != '0' ? 1 : 0) : -1;
   const char* rounds_env = std::getenv("FOCK_FUSED_ROUNDS");
   const bool use_rounds = tn.fused_rounds != 0 || (rounds_env && *rounds_env && *rounds_env != '0');
   for (auto& in : p->inst) {
     const bool mixed = prec == FOCK_MIXED || prec == FOCK_MIXED_INV;
-    if (mixed && !mixed_supported(in.grid))
+    if (mixed && (no_reg || !reg_supported(prec, in.grid)))
       return set_error(FOCK_ERR_UNSUPPORTED, "mixed precision needs a grid N1 x L x L with N1 and L in {24, 32, 36, 40, 48, 50, 54, 60, 64, 72}");
     in.fused = !mixed && fused_supported(prec, in.grid) && !no_fused;
-    if (in.fused && !no_sym && !use_rounds && full_kset(in) && fused_loses(prec, in.grid[0], in.nk * in.nbands))
-      in.fused = false;
+    if (in.fused && !no_sym && !use_rounds && full_kset(in)) {
+      // 32^3 FP32 read-modify-writes its output per partner: three passes with
+      // pair symmetry take 337 against 606 ms per step (4x4x4 k, 18 bands)
+      if (fused_rounds_supported(prec, in.grid) ? reg_supported(prec, in.grid) && !no_reg
+                                                : fused_loses(prec, in.nk * in.nbands))
+        in.fused = false;
+    }
+    // FP32 and mixed plans keep the register-line passes where they are (see
+    // energy_lds.hip: their energies and FP64 outputs are sums of FP32 spectra)
+    in.reg = !in.fused && prec != FOCK_C128 && reg_supported(prec, in.grid) && !no_reg;
+    in.slab = in.reg && (slab_force < 0 ? reg_slab_default(prec, in.grid)
+                                        : slab_force == 1 && reg_slab_supported(prec, in.grid));
   }
-
-  // tiles of the plane passes: the pair kernels of the line path, the DFT of
-  // the others (a grid per band)
-  for (auto& in : p->inst) {
-    const long long orb = static_cast<long long>(in.nk) * in.nbands;
-    plane_geometry(in.grid, in.fused ? orb : orb * (orb + 1) / 2, p->csize, &in.pg, &in.pg_threads);
+  // The whole-pair kernel needs no pair buffer: a plan that it keeps within the
+  // static workspace is not taken out of it.  Bytes of tables and lists, and of
+  // pair buffers with and without the instances that have the choice.
+  {
+    size_t base = 0, must = 0, may = 0;
+    for (const auto& in : p->inst) {
+      const size_t orb = static_cast<size_t>(in.nk) * in.nbands, pairs = orb * (orb + 1) / 2;
+      base += in.nq * in.npts * rsize + pairs * sizeof(PairRef) + 4096;
+      if (in.fused) {
+        may = std::max(may, 3 * orb * in.npts * p->csize);  // partner slices
+        continue;
+      }
+      const size_t t = pairs * (in.npts * p->csize + in.grid[0] * sizeof(double));
+      may = std::max(may, t);
+      if (!fused_optional(prec, in.grid, no_fused)) must = std::max(must, t);
+    }
+    if (base + must <= FOCK_STATIC_WORKSPACE_BYTES && base + may + (1u << 20) > FOCK_STATIC_WORKSPACE_BYTES)
+      for (auto& in : p->inst)
+        if (!in.fused && fused_optional(prec, in.grid, no_fused)) in.fused = true;
   }
 
   // ---- batch shapes ----
@@ -348,6 +375,13 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   size_t off = 0;
   p->tw_off = off;
   off = align_up(off + static_cast<size_t>(kTwiddleTotal) * p->csize);
+  p->tw1_off = off;
+  for (const auto& in : p->inst)
+    if (prec == FOCK_C64 && !in.fused && !in.reg) {
+      off = align_up(off + static_cast<size_t>(kTwiddleTotal) * p->csize);
+      break;
+    }
+  const bool tw1 = off != p->tw1_off;
   for (auto& in : p->inst) {
     in.vtab_off = off;
     off = align_up(off + static_cast<size_t>(in.nq) * in.npts * rsize);
@@ -445,7 +479,7 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
     // all its ordered pairs is the time of its launches either way (12x10x9,
     // two k-points of three bands, 38880 points: 27.3 us with unordered and
     // 27.5 with ordered pairs; 8^3, 18432 points, 27.6) and keeps the plain order.
-    const bool tiny = static_cast<int64_t>(nout) * npart * in.npts <= 32768;
+    const bool tiny = !in.reg && static_cast<int64_t>(nout) * npart * in.npts <= 32768;
     if (!no_sym && !tiny && g.k0 == 0 && g.k1 == in.nk && full_kset(in)) {
       // Pair symmetry: W_ba = conj(W_ab) (the Nyquist-averaged kernel is even
       // in c -> -c, q -> -q), so each unordered pair is transformed once.  The
@@ -486,8 +520,8 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
       }
       continue;
     }
-    // outputs per batch: enough accumulate workgroups (64-lane line blocks)
-    const int per_out = static_cast<int>((static_cast<int64_t>(in.grid[1]) * in.grid[2] + 63) / 64);
+    // outputs per batch: enough accumulate workgroups (planes, or 64-lane line blocks)
+    const int per_out = in.reg ? in.grid[0] : static_cast<int>((static_cast<int64_t>(in.grid[1]) * in.grid[2] + 63) / 64);
     int nO = std::max(1, std::min(nout, (acc_wgs + per_out - 1) / per_out));
     nO = std::min(nO, pmax);
     const int nP = std::max(1, std::min(npart, pmax / nO));
@@ -511,9 +545,9 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   // a dedicated apply batch with no partners: not needed, the wrapper zero-fills.
   // energy pair lists
   std::vector<std::vector<PairRef>> elists(n_inst);
-  // energy partials of a three-pass batch: one per pair and tile
-  const auto eparts = [](const Instance& in) { return static_cast<size_t>(plane_tiles(in.pg)); };
-  size_t max_eparts = 0, max_fused_epairs = 0;
+  // FP32 on general grids: E_x from its own passes (energy_lds.hip)
+  const auto lds_energy = [&](const Instance& in) { return prec == FOCK_C64 && !in.fused && !in.reg; };
+  size_t max_fused_epairs = 0;
   int slot = 0;
   for (int i = 0; i < n_inst; ++i) {
     Instance& in = p->inst[i];
@@ -549,7 +583,6 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
         b.per_wg = std::max(1, b.npairs / 1024);
         max_fused_epairs = std::max(max_fused_epairs, static_cast<size_t>(b.npairs));
       } else {
-        max_eparts = std::max(max_eparts, static_cast<size_t>(b.npairs) * eparts(in));
         max_pairs_elems = std::max(max_pairs_elems, static_cast<size_t>(b.npairs) * in.npts);
       }
       p->energy_batches.push_back(b);
@@ -561,11 +594,33 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   for (int i = 0; i < n_inst; ++i) {
     Instance& in = p->inst[i];
     in.first_aslot = slot;
-    if (!in.fused) {
+    if (lds_energy(in)) {
+      // ordered pairs of every group, in batches that the pair buffer holds
+      const long long orb = static_cast<long long>(in.nk) * in.nbands;
+      const int cap = static_cast<int>(std::max<long long>(
+          1, std::min<long long>({65535, static_cast<long long>(tbuf_target / (in.npts * p->csize)), orb * (orb + 1) / 2})));
+      for (const Group& g : groups) {
+        const int nout = (g.k1 - g.k0) * in.nbands, npart = static_cast<int>(g.parts.size() / 2);
+        if (g.inst != i || npart == 0) continue;
+        const int nO = std::min(nout, cap), nP = std::max(1, std::min(npart, cap / nO));
+        for (int ob = 0; ob < nout; ob += nO)
+          for (int pb = 0; pb < npart; pb += nP) {
+            Batch b;
+            b.inst = i;
+            b.o0 = g.k0 * in.nbands + ob;
+            b.nO = std::min(nO, nout - ob);
+            b.part_off = g.off + static_cast<size_t>(pb) * 2 * sizeof(int32_t);
+            b.nP = std::min(nP, npart - pb);
+            b.npairs = b.nO * b.nP;
+            b.eslot = slot++;
+            max_pairs_elems = std::max(max_pairs_elems, static_cast<size_t>(b.npairs) * in.npts);
+            p->ordered_energy.push_back(b);
+          }
+      }
+    } else if (!in.fused) {
       for (Batch& b : p->apply_batches) {
         if (b.inst != i) continue;
         b.eslot = slot++;
-        max_eparts = std::max(max_eparts, static_cast<size_t>(b.npairs) * eparts(in));
       }
     }
     in.n_aslot = slot - in.first_aslot;
@@ -580,27 +635,6 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   } else {
     p->tbuf_bytes = max_pairs_elems * p->csize;
   }
-  // the overlap's split-K partials take the same memory: it runs after the
-  // last batch of an apply, when the pair buffer is no longer read
-  p->ovl_off = p->tbuf_off;
-  const size_t scratch0 = off;
-  const auto share_scratch = [&](bool fine) {
-    p->ovl_bytes = 0;
-    for (auto& in : p->inst) {
-      in.ovl_span = fine ? overlap_span(in) : kOvChunkMax;
-      p->ovl_bytes = std::max(p->ovl_bytes, overlap_scratch_bytes(in, in.ovl_span));
-    }
-    return align_up(scratch0 + std::max(p->tbuf_bytes, p->ovl_bytes));
-  };
-  off = share_scratch(true);
-  const size_t scratch_fine = off;
-  p->epart_off = off;
-  // energy partials: energy batches and apply-with-energy batches
-  p->epart_bytes = std::max(max_eparts, max_fused_epairs) * sizeof(double);
-  off = align_up(off + p->epart_bytes);
-  p->partial_off = off;
-  p->partial_bytes = max_partial;
-  off = align_up(off + p->partial_bytes);
   // energy partials of the whole-pair apply: one per block, contiguous per instance
   int neblk = 0;
   for (int i = 0; i < n_inst; ++i) {
@@ -618,25 +652,57 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
     }
     p->inst[i].n_eblk = neblk - p->inst[i].first_eblk;
   }
-  p->eblk_off = off;
-  p->eblk_bytes = static_cast<size_t>(std::max(neblk, 1)) * sizeof(double);
-  off = align_up(off + p->eblk_bytes);
-  p->ebsum_off = off;
-  p->ebsum_bytes = static_cast<size_t>(std::max(slot, 1)) * sizeof(double);
-  off = align_up(off + p->ebsum_bytes);
-  if (off > FOCK_STATIC_WORKSPACE_BYTES) {
-    // shorter overlap chunks must not take a plan out of the static workspace
-    const size_t saved = scratch_fine - share_scratch(false);
-    if (off - saved <= FOCK_STATIC_WORKSPACE_BYTES) {
-      for (size_t* o : {&p->epart_off, &p->partial_off, &p->eblk_off, &p->ebsum_off, &off}) *o -= saved;
-    } else {
-      share_scratch(true);
+  // The rest of the layout.  fine: overlap chunks as short as the problem asks
+  // for, else of 4096 points; tiles: those of the plane passes as chosen, else
+  // at most one per point of axis 2 (fewer energy partials).
+  const size_t scratch0 = off;
+  const auto layout = [&](bool fine, bool tiles) {
+    // the overlap's split-K partials take the pair buffer's memory: it runs
+    // after the last batch of an apply, when the buffer is no longer read
+    p->ovl_off = p->tbuf_off;
+    p->ovl_bytes = 0;
+    for (auto& in : p->inst) {
+      in.ovl_span = fine ? overlap_span(in) : kOvChunkMax;
+      p->ovl_bytes = std::max(p->ovl_bytes, overlap_scratch_bytes(in, in.ovl_span));
+      const long long orb = static_cast<long long>(in.nk) * in.nbands;
+      plane_geometry(in.grid, in.fused ? orb : orb * (orb + 1) / 2, p->csize, tiles ? in.grid[0] : in.grid[1], &in.pg,
+                     &in.pg_threads);
     }
+    size_t o = align_up(scratch0 + std::max(p->tbuf_bytes, p->ovl_bytes));
+    // energy partials of a three-pass batch: one per pair and tile
+    p->epart_off = o;
+    p->epart_bytes = max_fused_epairs * sizeof(double);
+    // (FP64 general path), or at most one per point of axis 2
+    for (const auto* bs : {&p->energy_batches, &p->apply_batches, &p->ordered_energy})
+      for (const Batch& b : *bs) {
+        const Instance& in = p->inst[b.inst];
+        if (in.fused) continue;
+        const int per_pair = prec == FOCK_C128 ? plane_tiles(in.pg) : in.grid[1];
+        p->epart_bytes = std::max(p->epart_bytes, static_cast<size_t>(b.npairs) * per_pair * sizeof(double));
+      }
+    o = align_up(o + p->epart_bytes);
+    p->partial_off = o;
+    p->partial_bytes = max_partial;
+    o = align_up(o + p->partial_bytes);
+    p->eblk_off = o;
+    p->eblk_bytes = static_cast<size_t>(std::max(neblk, 1)) * sizeof(double);
+    o = align_up(o + p->eblk_bytes);
+    p->ebsum_off = o;
+    p->ebsum_bytes = static_cast<size_t>(std::max(slot, 1)) * sizeof(double);
+    return align_up(o + p->ebsum_bytes);
+  };
+  off = layout(true, true);
+  // what only saves time must not take a plan out of the static workspace
+  if (off > FOCK_STATIC_WORKSPACE_BYTES) {
+    off = layout(false, true);
+    if (off > FOCK_STATIC_WORKSPACE_BYTES) off = layout(false, false);
+    if (off > FOCK_STATIC_WORKSPACE_BYTES) off = layout(true, true);
   }
   p->total_bytes = off;
   for (const auto& in : p->inst) {
     const size_t need =
-        in.fused ? fused_lds_bytes(prec, in.grid[0]) + 256 : plane_lds_bytes(in.pg, p->csize) + 64;
+        in.fused ? fused_lds_bytes(prec, in.grid[0]) + 256
+                 : std::max(plane_lds_bytes(in.pg, p->csize), in.reg ? reg_lds_bytes(prec, in.grid[1]) : size_t{0}) + 64;
     p->lds_needed = std::max(p->lds_needed, need);
   }
   p->apply_launches = 0;
@@ -665,6 +731,15 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
       }
     }
   }
+  for (int L = 2; tw1 && L <= kNMax; ++L) {
+    if (!smooth235(L)) continue;
+    for (int t = 0; t < L; ++t) {
+      const double ang = -2.0 * M_PI * static_cast<double>(t) / static_cast<double>(L);
+      float* w = reinterpret_cast<float*>(img + p->tw1_off) + 2 * (twiddle_offset(L) + t);
+      w[0] = static_cast<float>(std::cos(ang));
+      w[1] = static_cast<float>(std::sin(ang));
+    }
+  }
   for (int i = 0; i < n_inst; ++i) {
     Instance& in = p->inst[i];
     for (int q = 0; q < in.nq; ++q) {
@@ -678,6 +753,18 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
             for (int c3 = 0; c3 < L; ++c3)
               r[(static_cast<size_t>(c3) * L + c2) * L + c1] = t[(static_cast<size_t>(c1) * L + c2) * L + c3];
         t.swap(r);
+      } else if (in.reg) {
+        // register-line passes read the table as [c1][c3][c2] (grids N1 x L x
+        // L), their slab form in grid order
+        if (!in.slab) {
+          const int n1 = in.grid[0], L = in.grid[1];
+          std::vector<double> r(t.size());
+          for (int c1 = 0; c1 < n1; ++c1)
+            for (int c2 = 0; c2 < L; ++c2)
+              for (int c3 = 0; c3 < L; ++c3)
+                r[(static_cast<size_t>(c1) * L + c3) * L + c2] = t[(static_cast<size_t>(c1) * L + c2) * L + c3];
+          t.swap(r);
+        }
       } else {
         // line path: per tile of planes the positions of the plane passes, as
         // [k2][k1][row] (plane_fft.hpp): row (plane, r2 b2 + i2) holds the

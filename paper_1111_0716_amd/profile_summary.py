@@ -36,14 +36,16 @@ import sys
 CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
 # source files of each kernel kind's device code (the .hip file and the
 # headers its kernels use)
+THREE_PASS_SOURCES = ["pass_line.hip", "plane_fft.hpp", "pass_common.hpp", "reg_fft.hpp", "split_fft.hpp", "fft_lds.hpp",
+                      "twiddle_ce.hpp", "fock_internal.hpp"]
 KIND_SOURCES = {
     "fused": ["pair_fused.hip", "reg_fft.hpp", "fft_lds.hpp", "twiddle_ce.hpp"],
     "energy_fused": ["pair_fused.hip", "reg_fft.hpp", "fft_lds.hpp", "twiddle_ce.hpp"],
-    "plane": ["kernels.hip", "pass_reg.hip", "reg_fft.hpp", "split_fft.hpp", "fft_lds.hpp", "twiddle_ce.hpp", "fock_internal.hpp"],
-    "pencil": ["kernels.hip", "pass_reg.hip", "reg_fft.hpp", "split_fft.hpp", "fft_lds.hpp", "twiddle_ce.hpp", "fock_internal.hpp"],
-    "accumulate": ["kernels.hip", "pass_reg.hip", "reg_fft.hpp", "split_fft.hpp", "fft_lds.hpp", "twiddle_ce.hpp", "fock_internal.hpp"],
-    "energy_plane": ["kernels.hip", "pass_reg.hip", "reg_fft.hpp", "split_fft.hpp", "fft_lds.hpp", "twiddle_ce.hpp", "fock_internal.hpp"],
-    "energy_pencil": ["kernels.hip", "pass_reg.hip", "reg_fft.hpp", "split_fft.hpp", "fft_lds.hpp", "twiddle_ce.hpp", "fock_internal.hpp"],
+    "plane": THREE_PASS_SOURCES,
+    "pencil": THREE_PASS_SOURCES,
+    "accumulate": THREE_PASS_SOURCES,
+    "energy_plane": THREE_PASS_SOURCES,
+    "energy_pencil": THREE_PASS_SOURCES,
     "overlap": ["overlap_mfma.hip", "fft_lds.hpp", "fock_internal.hpp"],
 }
 COPY_KERNEL = "__amd_rocclr_copyBuffer"

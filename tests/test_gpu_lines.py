@@ -88,6 +88,28 @@ def _fft_pairs(grid, kmesh, nb, kpairs=None, tuning=None):
     return fft.value
 
 
+def _plan_stats(grid, nb, prec):
+    keep = []
+    d = fock.make_desc(inputs.cubic_lattice(10.0), grid, inputs.gamma_mesh(1, 1, 1), None, nb, None, 0.106, None, keep)
+    h, fft, size = ctypes.c_void_p(), ctypes.c_int64(), ctypes.c_size_t()
+    assert fock.lib().fock_plan((fock.FockDesc * 1)(d), 1, prec, None, ctypes.byref(h)) == fock.FOCK_OK
+    fock.lib().fock_plan_stats(h, None, ctypes.byref(fft), None, None)
+    fock.lib().fock_workspace_size(h, ctypes.byref(size))
+    fock.lib().fock_destroy(h)
+    return fft.value, size.value
+
+
+@pytest.mark.parametrize("L,prec,nb", [(16, fock.FOCK_C128, 9), (16, fock.FOCK_C128, 40), (16, fock.FOCK_C128, 56)])
+def test_small_cubes_stay_within_the_static_workspace(L, prec, nb):
+    """The whole-pair kernel (one transform per ordered pair, no pair buffer)
+    fits all of these; where the three-pass path would not, it is kept."""
+    fft, size = _plan_stats((L, L, L), nb, prec)
+    assert size <= fock.STATIC_WORKSPACE_BYTES
+    pair_bytes = L ** 3 * (8 if prec == fock.FOCK_C64 else 16)
+    if nb * (nb + 1) // 2 * pair_bytes < fock.STATIC_WORKSPACE_BYTES // 2:
+        assert fft == nb * (nb + 1) // 2
+
+
 def test_general_grids_transform_unordered_pairs():
     assert _fft_pairs((24, 30, 45), (2, 1, 1), 5) == 55
     assert _fft_pairs((24, 30, 45), (2, 1, 1), 5, tuning={"tbuf_mb": 1}) == 55  # blocks
