@@ -102,6 +102,14 @@ __device__ __forceinline__ void mul_table_line(C* x, const T* __restrict__ v, si
   }
 }
 
+// lane_at without an address space, and plain accesses: the mixed precisions'
+// FP32 transforms compile to other roundings around global or non-temporal
+// ones, and their FP64 outputs then move by 1e-9 of themselves.
+template <typename C>
+__device__ __forceinline__ C* lane_flat(C* u, unsigned o) {
+  return reinterpret_cast<C*>(reinterpret_cast<uintptr_t>(u) + o);
+}
+
 // x[j] *= u[j * stride] at the lane's byte offset o, j < L (u wave-uniform);
 // EN: also *es += u |x|^2 in FP64, taken before the multiply
 template <typename C, typename T, int L, bool EN = false>
@@ -240,7 +248,7 @@ __global__ __launch_bounds__((RegShape<T, L>::NTP), (sizeof(TI) == sizeof(T) ? R
       C* dst = tbuf + static_cast<size_t>(pi) * n1 * LL;
       const unsigned so = opaque((static_cast<unsigned>(j1) * LL + col) * sizeof(C));
 #pragma unroll
-      for (int c3 = 0; c3 < L; ++c3) stream_store(lane_at(dst + c3 * L, so), x[c3]);
+      for (int c3 = 0; c3 < L; ++c3) *lane_flat(dst + c3 * L, so) = x[c3];
     } else {
       C* dst = tbuf + (static_cast<size_t>(pi) * n1 + j1) * LL + col;
 #pragma unroll
@@ -399,7 +407,7 @@ __global__ __launch_bounds__((RegShape<T, L>::NTP), (RegShape<T, L>::WPE_ACC)) v
     if (valid) {
       const C* src = tbuf + pair * LL * n1 + static_cast<size_t>(j1) * LL + col;
 #pragma unroll
-      for (int c3 = 0; c3 < L; ++c3) x[c3] = stream_load(src + c3 * L);  // row (j1, c2 = col)
+      for (int c3 = 0; c3 < L; ++c3) x[c3] = sizeof(TI) == sizeof(T) ? stream_load(src + c3 * L) : src[c3 * L];  // row (j1, c2 = col)
     } else {
 #pragma unroll
       for (int c3 = 0; c3 < L; ++c3) x[c3] = C{T(0), T(0)};
@@ -765,7 +773,7 @@ __global__ __launch_bounds__((SplitShape<T, L>::NTP), (SplitShape<T, L>::WPE_ACC
     if (valid) {
       const C* src = tbuf + pair * LL * n1 + static_cast<size_t>(j1) * LL + static_cast<size_t>(h) * LH * L + col;
 #pragma unroll
-      for (int k = 0; k < LH; ++k) y[k] = stream_load(src + k * L);  // row (j1, c2 = col), c3 = h L/2 + k
+      for (int k = 0; k < LH; ++k) y[k] = sizeof(TI) == sizeof(T) ? stream_load(src + k * L) : src[k * L];  // row (j1, c2 = col), c3 = h L/2 + k
     } else {
 #pragma unroll
       for (int k = 0; k < LH; ++k) y[k] = C{T(0), T(0)};
@@ -1012,7 +1020,7 @@ __device__ __forceinline__ void pencil_apply_mixed_line(int l, int h, int LL, in
   {
     float2 f[LH];
 #pragma unroll
-    for (int m = 0; m < LH; ++m) f[m] = stream_load(lane_at(t32 + base + static_cast<size_t>(2 * m) * LL, le * 8u));  // j1 = 2m + h
+    for (int m = 0; m < LH; ++m) f[m] = *lane_flat(t32 + base + static_cast<size_t>(2 * m) * LL, le * 8u);  // j1 = 2m + h
     split_fft_fwd<float2, L>(f, h);  // f[k] at c1 = h L/2 + k
 #pragma unroll
     for (int k = 0; k < LH; ++k) y[k] = cvt<double2>(f[k]);
@@ -1022,7 +1030,7 @@ __device__ __forceinline__ void pencil_apply_mixed_line(int l, int h, int LL, in
   split_fft_inv<double2, L>(y, h);
   const unsigned so = opaque(le * 16u);
 #pragma unroll
-  for (int m = 0; m < LH; ++m) stream_store(lane_at(t64 + base + static_cast<size_t>(2 * m) * LL, so), y[m]);
+  for (int m = 0; m < LH; ++m) *lane_flat(t64 + base + static_cast<size_t>(2 * m) * LL, so) = y[m];
 }
 
 // EN: the energy variant (see k_pencil_apply_reg), from the FP32 forward
@@ -1074,7 +1082,7 @@ __device__ __forceinline__ void pencil_apply_mixinv_line(int l, int h, int LL, i
   {
     double2 y[LH];
 #pragma unroll
-    for (int m = 0; m < LH; ++m) y[m] = stream_load(lane_at(t64 + base + static_cast<size_t>(2 * m) * LL, le * 16u));  // j1 = 2m + h
+    for (int m = 0; m < LH; ++m) y[m] = *lane_flat(t64 + base + static_cast<size_t>(2 * m) * LL, le * 16u);  // j1 = 2m + h
     split_fft_fwd<double2, L>(y, h);  // y[k] at c1 = h L/2 + k
     mul_table_line_u<double2, double, LH, EN>(y, vtab + static_cast<size_t>(q) * LL * L,
                                               opaque((static_cast<unsigned>(h) * LH * LL + l) * 8u), LL, es);
@@ -1084,7 +1092,7 @@ __device__ __forceinline__ void pencil_apply_mixinv_line(int l, int h, int LL, i
   split_fft_inv<float2, L>(f, h);
   const unsigned so = opaque(le * 8u);
 #pragma unroll
-  for (int m = 0; m < LH; ++m) stream_store(lane_at(t32 + base + static_cast<size_t>(2 * m) * LL, so), f[m]);
+  for (int m = 0; m < LH; ++m) *lane_flat(t32 + base + static_cast<size_t>(2 * m) * LL, so) = f[m];
 }
 
 // EN: the energy variant (see k_pencil_apply_reg), from the FP64 spectrum
