@@ -71,12 +71,11 @@ typedef enum {
  * arithmetic (FP64 tables, twiddles and energy sums).  The two mixed
  * policies (the paper's "some of the FFTs in single precision") take
  * complex128 orbitals and outputs:
- *   FOCK_MIXED      co-densities and the forward transform along axis 1, and
- *                   the pair buffer they fill, in FP32; the rest in FP64
- *   FOCK_MIXED_INV  co-densities to the inverse transforms along axes 3 and 2
- *                   (pair energies among them) in FP64; the pair buffer they
- *                   fill, the inverse along axis 1 and the sums in FP32
- *                   (added into the FP64 outputs in FP64)
+ *   FOCK_MIXED      co-densities and forward transforms in FP32; kernel
+ *                   multiply, inverse transforms and accumulate in FP64
+ *   FOCK_MIXED_INV  co-densities, forward transforms, kernel multiply and
+ *                   pair energies in FP64; inverse transforms and the
+ *                   accumulate in FP32 (added into the FP64 outputs in FP64)
  * Both need grids N1 x L x L with N1 and L each 24, 32, 36, 40, 48, 50, 54,
  * 60, 64 or 72 (FOCK_ERR_UNSUPPORTED otherwise). */
 typedef enum {
@@ -276,6 +275,8 @@ fock_status fock_plan_stats(fock_plan_t plan, int64_t* ordered_pairs, int64_t* a
 
 /* Kernel kinds for per-kernel timing. */
 typedef enum {
+  /* (register-line passes, FP32 and mixed on N1 x L x L: axes 2, 3 in the
+   * first and third pass, axis 1 in the second) */
   FOCK_K_PLANE = 0,          /* apply: co-density + forward FFT of axis 1            */
   FOCK_K_PENCIL = 1,         /* apply: axes 2, 3 forward, x v_q, axes 3, 2 inverse   */
   FOCK_K_ACCUMULATE = 2,     /* apply: inverse FFT of axis 1 + accumulate            */

@@ -7,7 +7,8 @@
 // more than the 1e-9 that a caller who compares energies from call to call
 // should see from a faster kernel.  So E_x keeps this form, over ordered pairs
 // after an apply and over unordered ones in fock_energy, and only V_x takes the
-// faster passes.  24x24x60, 3x3x1 k, 12 bands, FP32 apply with energy: E_TIME.
+// faster passes.  24x24x60, 3x3x1 k, 12 bands, FP32 step: 3.4 ms with E_x from
+// the plane pass, 9.6 with these passes, 28.0 when V_x took this form too.
 #include <algorithm>
 
 #include "fft_lds.hpp"

@@ -24,17 +24,16 @@
 // (3.9 GB a batch) the passes take 730, 1440 and 1525 us: 5.3, 5.4 and 5.1 TB/s,
 // a large copy's 4.9 to 5.4.
 //
-// Against the passes it replaced, per call.  All transforms in LDS with a
-// barrier around every radix pass, ordered pairs (general grids): 24x24x60,
-// 3x3x1 k, 12 bands, FP32 step 27.8 -> 3.5 ms; 36x40x45, 2x1x1 k, 16 bands, FP64
-// apply 4.55 -> 0.60 ms; twelve uneven Gamma cells of 16 to 40 points a side,
-// FP32 4.23 -> 0.77 ms; 160 DFTs of 48^3 FP64 498 -> 300 us.  Plane transforms
-// over whole register lines (N1 x L x L): 48^3 Gamma mixed 2.84 -> 2.07 ms; 60^3
-// Gamma FP64 2.00 -> 1.37; 32^3 2x2x2 k FP64 step 11.3 -> 10.0; 64^3 Gamma FP32
-// gradient 16.9 -> 15.9; 72^3 2x2x2 k FP32 apply 77.0 -> 73.1; 32^3 4x4x4 k FP32
-// step 335.8 -> 336.0; apply with energy at Gamma: 24x72x72 FP32 1.24 -> 0.68,
-// FP64 1.64 -> 0.76; 36^3 FP64 1.14 -> 0.72; 60x40x40 FP32 0.73 -> 0.77, FP64
-// 1.00 -> 0.72; 72x24x24 FP32 0.71 -> 0.75, FP64 0.89 -> 0.88 ms.
+// It serves FP64 plans on every grid and V_x of FP32 plans on general grids
+// (FP32 N1 x L x L and mixed plans: pass_reg.hip; why, and FP32 energies:
+// energy_lds.hip).  Against the passes it replaced, per call.  All transforms
+// in LDS with a barrier around every radix pass, ordered pairs (general grids):
+// 24x24x60, 3x3x1 k, 12 bands, FP32 step 27.8 -> 9.6 ms; 36x40x45, 2x1x1 k, 16
+// bands, FP64 apply 4.55 -> 0.60 ms; 160 DFTs of 48^3 FP64 498 -> 300 us.  Plane
+// transforms over whole register lines (N1 x L x L): 60^3 Gamma FP64 2.00 ->
+// 1.35 ms; 32^3 2x2x2 k FP64 step 11.3 -> 10.0; apply with energy at Gamma FP64:
+// 24x72x72 1.64 -> 0.76, 36^3 1.14 -> 0.72, 60x40x40 1.00 -> 0.72, 72x24x24 0.89
+// -> 0.88 ms.
 #include <algorithm>
 
 #include "fft_lds.hpp"

@@ -1,5 +1,5 @@
-// Three-pass kernels with register-line FFTs for grids N1 x L x L that do not
-// take the whole-pair kernels, N1 and L in {24, 32, 36, 40, 48, 50, 54, 60,
+// Three-pass kernels with register-line FFTs of the FP32 and mixed plans, for
+// grids N1 x L x L that do not take the whole-pair kernels, N1 and L in {24, 32, 36, 40, 48, 50, 54, 60,
 // 64, 72}: a line per lane (FP32 up to 60 in most passes, FP64 up to 32) or a
 // line per lane pair (longer lines).  The band-pair loop on the GPU (paper,
 // "Our Implementation"; NSIM-like blocks of outputs x partners) as three
@@ -1163,7 +1163,7 @@ namespace {
 // lengths compiled with the slab pencil and the line accumulate
 template <typename T, int L>
 constexpr bool slab_len() {
-  return sizeof(T) == 4 ? true : L <= 32;  // FP64: the one-lane plane lengths
+  return sizeof(T) == 4;
 }
 
 // the line accumulate over lane pairs: FP64 where line and accumulator take
@@ -1642,8 +1642,7 @@ bool reg_len(int n) {
 bool reg_slab_supported(fock_precision prec, const int grid[3]) {
   const int n = grid[0];
   if (grid[1] != n || grid[2] != n || !reg_supported(prec, grid)) return false;
-  if (prec == FOCK_C64) return true;
-  return prec == FOCK_C128 && n <= 32;
+  return prec == FOCK_C64;
 }
 
 // measured per step: alpha boron 32^3 FP32 370 against 385 ms, FP64 758
@@ -1658,7 +1657,6 @@ bool reg_slab_supported(fock_precision prec, const int grid[3]) {
 bool reg_slab_default(fock_precision prec, const int grid[3]) {
   const int n = grid[0];
   if (!reg_slab_supported(prec, grid)) return false;
-  if (prec == FOCK_C128) return true;  // 24^3 and 32^3
   return n != 24 && n != 60;
 }
 
@@ -1685,8 +1683,7 @@ void prepare_reg_kernels(fock_precision prec, int lim) {
 #define CASE(N)                                     \
   if (prec == FOCK_C64) reg_lds_attr<float, N>(lim); \
   else if (prec == FOCK_MIXED) mixed_lds_attr<N>(lim); \
-  else if (prec == FOCK_MIXED_INV) { mixinv_lds_attr<N>(lim); reg_lds_attr<double, N>(lim); } \
-  else reg_lds_attr<double, N>(lim);
+  else if (prec == FOCK_MIXED_INV) mixinv_lds_attr<N>(lim);
   FOCK_REG_L(CASE)
 #undef CASE
 }
@@ -1695,8 +1692,7 @@ hipError_t launch_reg_apply_batch(const Plan& p, const Batch& b, const void* psi
                                   const double* gscale, double hscale, bool backward, bool energy) {
   if (p.prec == FOCK_MIXED) return mixed_apply_t(p, b, psi, occ, out, gscale, hscale, backward, energy);
   if (p.prec == FOCK_MIXED_INV) return mixinv_apply_t(p, b, psi, occ, out, gscale, hscale, backward, energy);
-  return p.prec == FOCK_C128 ? reg_apply_t<double>(p, b, psi, occ, out, gscale, hscale, backward, energy)
-                             : reg_apply_t<float>(p, b, psi, occ, out, gscale, hscale, backward, energy);
+  return reg_apply_t<float>(p, b, psi, occ, out, gscale, hscale, backward, energy);  // FP64: pass_line.hip
 }
 
 
@@ -1704,7 +1700,7 @@ hipError_t launch_reg_energy_batch(const Plan& p, const Batch& b, const void* ps
   if (p.prec == FOCK_MIXED) return mixed_energy_t(p, b, psi, occ);
   // FOCK_MIXED_INV: the energy takes the FP64 forward transforms (its FP64 pair buffer)
   if (p.prec == FOCK_MIXED_INV) return reg_energy_t<double>(p, b, psi, occ, p.tbuf64_off);
-  return p.prec == FOCK_C128 ? reg_energy_t<double>(p, b, psi, occ) : reg_energy_t<float>(p, b, psi, occ);
+  return reg_energy_t<float>(p, b, psi, occ);
 }
 
 }  // namespace fock

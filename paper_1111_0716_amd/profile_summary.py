@@ -36,7 +36,7 @@ import sys
 CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
 # source files of each kernel kind's device code (the .hip file and the
 # headers its kernels use)
-THREE_PASS_SOURCES = ["pass_line.hip", "plane_fft.hpp", "pass_common.hpp", "reg_fft.hpp", "split_fft.hpp", "fft_lds.hpp",
+THREE_PASS_SOURCES = ["pass_reg.hip", "pass_line.hip", "energy_lds.hip", "plane_fft.hpp", "pass_common.hpp", "reg_fft.hpp", "split_fft.hpp", "fft_lds.hpp",
                       "twiddle_ce.hpp", "fock_internal.hpp"]
 KIND_SOURCES = {
     "fused": ["pair_fused.hip", "reg_fft.hpp", "fft_lds.hpp", "twiddle_ce.hpp"],
