@@ -255,8 +255,6 @@ size_t plane_lds_bytes(const PlaneGeo& g, size_t csize);
 // planes_of: pairs in flight, each with n1 planes, in at most max_tiles tiles
 void plane_geometry(const int grid[3], long long planes_of, size_t csize, int max_tiles, PlaneGeo* g, int* threads);
 hipError_t launch_line_dft3(const Plan& p, int inst, int sign, int count, void* data, long long stride);
-// grids of the mixed precisions
-bool mixed_supported(const int grid[3]);
 void prepare_line_kernels(fock_precision prec, int lim);
 // eblk: if not null, the apply also writes per-block energy partials there
 hipError_t launch_fused_apply(const Plan& p, const FusedGroup& g, const void* psi, const double* occ, void* out,

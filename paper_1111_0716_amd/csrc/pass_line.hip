@@ -164,13 +164,11 @@ __global__ __launch_bounds__(64, (sizeof(TI) == sizeof(T) ? LineShape<T, L>::WPE
 // inverse transforms (an energy batch has no way back).
 // What the pass has to do is one read and one write of the tile; the rest are
 // six LDS round trips of the values.
-// TL and TS: the pair buffer read and the one written where their precision is
-// another than the transforms' (then they are two buffers).
-template <typename T, bool EN, bool BACK, typename TL = T, typename TS = T>
+template <typename T, bool EN, bool BACK>
 __global__ __launch_bounds__(512, 4) void k_plane_pair(PlaneGeo g, int nbands, int nk, int o0, int nP, int tri,
                                                         const int2* __restrict__ parts, const int* __restrict__ qmap,
                                                         const PairRef* __restrict__ pairs,
-                                                        const typename cx<TL>::t* tin, typename cx<TS>::t* tout,
+                                                        typename cx<T>::t* tbuf,
                                                         const T* __restrict__ vtab,
                                                         const typename cx<T>::t* __restrict__ tw2,
                                                         const typename cx<T>::t* __restrict__ tw3,
@@ -205,7 +203,7 @@ __global__ __launch_bounds__(512, 4) void k_plane_pair(PlaneGeo g, int nbands, i
   switch (g.n2) {
 #define CASE(N)                                              \
   case N:                                                    \
-    ax2_load<N, -1>(s, tin + at, g.n3, g.pitch, gc, tw2);    \
+    ax2_load<N, -1>(s, tbuf + at, g.n3, g.pitch, gc, tw2);    \
     __syncthreads();                                         \
     if constexpr (radix_a(N) > 1) {                          \
       ax2_b<N, -1, C>(s, g.n3, g.pitch, gc);                 \
@@ -240,7 +238,7 @@ __global__ __launch_bounds__(512, 4) void k_plane_pair(PlaneGeo g, int nbands, i
       ax2_b<N, +1, C>(s, g.n3, g.pitch, gc);                 \
       __syncthreads();                                       \
     }                                                        \
-    ax2_store<N, +1>(s, tout + at, g.n3, g.pitch, gc, t2);   \
+    ax2_store<N, +1>(s, tbuf + at, g.n3, g.pitch, gc, t2);   \
     break;
       FOCK_SMOOTH_L(CASE)
 #undef CASE
@@ -472,32 +470,22 @@ size_t plane_lds(const PlaneGeo& g, size_t csize) {
   return (static_cast<size_t>(g.g) * g.n2 * g.pitch + g.tw2 + g.tw3) * csize;
 }
 
-// axis-1 lengths compiled: every one, or the mixed precisions' where the line
-// and the orbitals differ in type
-constexpr bool mixed_len(int n) {
-  return n == 24 || n == 32 || n == 36 || n == 40 || n == 48 || n == 50 || n == 54 || n == 60 || n == 64 || n == 72;
-}
-template <typename T, typename TI>
-constexpr bool line_len(int n) {
-  return sizeof(T) == sizeof(TI) || mixed_len(n);
-}
-
-template <typename T, int L, typename TI>
+template <typename T, int L>
 void line_fwd_L(const Plan& p, const Batch& b, const Instance& in, const void* psi, const int2* parts,
                 const PairRef* pairs, typename cx<T>::t* tbuf) {
   const int plane = in.grid[1] * in.grid[2];
   const int lanes = plane * (LineShape<T, L>::SPLIT_FWD ? 2 : 1);
   const unsigned total = static_cast<unsigned>((lanes + 63) / 64) * b.npairs;
-  hipLaunchKernelGGL((k_line_fwd<T, L, TI>), dim3(xcd_grid(total)), dim3(64), 0, p.stream, plane, b.npairs, total,
-                     in.nbands, static_cast<long long>(in.band_stride), static_cast<const typename cx<TI>::t*>(psi),
+  hipLaunchKernelGGL((k_line_fwd<T, L>), dim3(xcd_grid(total)), dim3(64), 0, p.stream, plane, b.npairs, total,
+                     in.nbands, static_cast<long long>(in.band_stride), static_cast<const typename cx<T>::t*>(psi),
                      b.o0, b.nP, b.tri, parts, pairs, tbuf);
 }
 
-template <typename T, int L, typename TI, bool SPLIT>
+template <typename T, int L, bool SPLIT>
 void line_acc_launch(const Plan& p, const Batch& b, const Instance& in, const int2* parts,
                      const typename cx<T>::t* tbuf, const void* psi, const double* occ, const double* kw, void* out,
                      const double* gscale, double hscale, bool backward) {
-  using CI = typename cx<TI>::t;
+  using C = typename cx<T>::t;
   using Sh = AccShape<T, L, SPLIT>;
   const int plane = in.grid[1] * in.grid[2];
   const int lanes = plane * (SPLIT ? 2 : 1);
@@ -512,44 +500,37 @@ void line_acc_launch(const Plan& p, const Batch& b, const Instance& in, const in
   int nw = 1;
   while (nw < Sh::WAVES && total * static_cast<unsigned>(nw + 1) <= 4096u && 2 * (nw + 1) <= nsrc) ++nw;
   const size_t lds = static_cast<size_t>(nw - 1) * Sh::BYTES;
-  hipLaunchKernelGGL((k_line_acc<T, L, SPLIT, TI>), dim3(xcd_grid(total)), dim3(64 * nw), lds, p.stream, plane, rows,
+  hipLaunchKernelGGL((k_line_acc<T, L, SPLIT>), dim3(xcd_grid(total)), dim3(64 * nw), lds, p.stream, plane, rows,
                      total, in.nbands, static_cast<long long>(in.band_stride), b.o0, b.nO, b.nP, b.tri, parts, tbuf,
-                     static_cast<const CI*>(psi), occ, kw, static_cast<CI*>(out), b.first, b.first_mirror, gscale,
+                     static_cast<const C*>(psi), occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale,
                      hscale, backward ? 1 : 0);
 }
 
-template <typename T, int L, typename TI>
+template <typename T, int L>
 void line_acc_L(const Plan& p, const Batch& b, const Instance& in, const int2* parts, const typename cx<T>::t* tbuf,
                 const void* psi, const double* occ, const double* kw, void* out, const double* gscale, double hscale,
                 bool backward) {
   using Sh = LineShape<T, L>;
-  if constexpr (sizeof(TI) != sizeof(T)) {  // FP64 operands beside FP32 sums: lane pairs from 36 points up
-    line_acc_launch<T, L, TI, (L >= 36)>(p, b, in, parts, tbuf, psi, occ, kw, out, gscale, hscale, backward);
-  } else {
-    if constexpr (Sh::SPLIT_ACC_FEW) {
-      // 72^3 FP32 apply, 20 bands (1620 waves of whole lines): 0.79 against
-      // 0.81 ms, 72x24x24, 60 bands (540) 0.75 against 0.82; 64 bands (5184)
-      // 7.84 against 7.73 ms
-      const long long waves =
-          static_cast<long long>((in.grid[1] * in.grid[2] + 63) / 64) * (b.nO + (b.mirror ? b.nP : 0));
-      if (waves <= 2048) {
-        line_acc_launch<T, L, TI, true>(p, b, in, parts, tbuf, psi, occ, kw, out, gscale, hscale, backward);
-        return;
-      }
+  if constexpr (Sh::SPLIT_ACC_FEW) {
+    // 72^3 FP32, 20 bands (1620 waves of whole lines): 0.79 against 0.81 ms,
+    // 72x24x24, 60 bands (540) 0.75 against 0.82; 64 bands (5184) 7.84 against
+    // 7.73 ms
+    const long long waves =
+        static_cast<long long>((in.grid[1] * in.grid[2] + 63) / 64) * (b.nO + (b.mirror ? b.nP : 0));
+    if (waves <= 2048) {
+      line_acc_launch<T, L, true>(p, b, in, parts, tbuf, psi, occ, kw, out, gscale, hscale, backward);
+      return;
     }
-    line_acc_launch<T, L, TI, Sh::SPLIT_ACC>(p, b, in, parts, tbuf, psi, occ, kw, out, gscale, hscale, backward);
   }
+  line_acc_launch<T, L, Sh::SPLIT_ACC>(p, b, in, parts, tbuf, psi, occ, kw, out, gscale, hscale, backward);
 }
 
-// T: the line and the pair buffer; TI: the orbitals
-template <typename T, typename TI>
+template <typename T>
 hipError_t line_fwd(const Plan& p, const Batch& b, const Instance& in, const void* psi, const int2* parts,
                     const PairRef* pairs, typename cx<T>::t* tbuf) {
   switch (in.grid[0]) {
 #define CASE(N) \
-  case N:                                                                  \
-    if constexpr (line_len<T, TI>(N)) line_fwd_L<T, N, TI>(p, b, in, psi, parts, pairs, tbuf); \
-    break;
+  case N: line_fwd_L<T, N>(p, b, in, psi, parts, pairs, tbuf); break;
     FOCK_SMOOTH_L(CASE)
 #undef CASE
     default: return hipErrorInvalidValue;
@@ -557,12 +538,9 @@ hipError_t line_fwd(const Plan& p, const Batch& b, const Instance& in, const voi
   return hipGetLastError();
 }
 
-// TF: forward pass and the buffer it writes; T: plane pass; TA: the buffer the
-// plane pass writes and the accumulate; TI: orbitals and outputs
-template <typename TF, typename T, typename TA, typename TI>
+template <typename T>
 hipError_t line_apply_t(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
-                        const double* gscale, double hscale, bool backward, bool energy, size_t tin_off,
-                        size_t tout_off) {
+                        const double* gscale, double hscale, bool backward, bool energy) {
   using C = typename cx<T>::t;
   const Instance& in = p.inst[b.inst];
   const PlaneGeo& g = in.pg;
@@ -571,11 +549,10 @@ hipError_t line_apply_t(const Plan& p, const Batch& b, const void* psi, const do
   const T* vtab = reinterpret_cast<const T*>(p.ws + in.vtab_off);
   const double* kw = reinterpret_cast<const double*>(p.ws + in.kw_off);
   const C* tw = reinterpret_cast<const C*>(p.ws + p.tw_off);
-  auto* tin = reinterpret_cast<typename cx<TF>::t*>(p.ws + tin_off);
-  auto* tout = reinterpret_cast<typename cx<TA>::t*>(p.ws + tout_off);
+  C* tbuf = reinterpret_cast<C*>(p.ws + p.tbuf_off);
   double* epart = reinterpret_cast<double*>(p.ws + p.epart_off);
   p.prof.begin(FOCK_K_PLANE, p.stream);
-  hipError_t e = line_fwd<TF, TI>(p, b, in, psi, parts, nullptr, tin);
+  hipError_t e = line_fwd<T>(p, b, in, psi, parts, nullptr, tbuf);
   p.prof.end(FOCK_K_PLANE, p.stream);
   if (e != hipSuccess) return e;
   const int tiles = plane_tiles(g);
@@ -583,13 +560,13 @@ hipError_t line_apply_t(const Plan& p, const Batch& b, const void* psi, const do
   const C *tw2 = tw + twiddle_offset(g.n2), *tw3 = tw + twiddle_offset(g.n3);
   p.prof.begin(FOCK_K_PENCIL, p.stream);
   if (energy)
-    hipLaunchKernelGGL((k_plane_pair<T, true, true, TF, TA>), grid, dim3(in.pg_threads), plane_lds(g, sizeof(C)),
+    hipLaunchKernelGGL((k_plane_pair<T, true, true>), grid, dim3(in.pg_threads), plane_lds(g, sizeof(C)),
                        p.stream, g, in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap,
-                       static_cast<const PairRef*>(nullptr), tin, tout, vtab, tw2, tw3, occ, kw, epart);
+                       static_cast<const PairRef*>(nullptr), tbuf, vtab, tw2, tw3, occ, kw, epart);
   else
-    hipLaunchKernelGGL((k_plane_pair<T, false, true, TF, TA>), grid, dim3(in.pg_threads), plane_lds(g, sizeof(C)),
+    hipLaunchKernelGGL((k_plane_pair<T, false, true>), grid, dim3(in.pg_threads), plane_lds(g, sizeof(C)),
                        p.stream, g, in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap,
-                       static_cast<const PairRef*>(nullptr), tin, tout, vtab, tw2, tw3, occ, kw, epart);
+                       static_cast<const PairRef*>(nullptr), tbuf, vtab, tw2, tw3, occ, kw, epart);
   p.prof.end(FOCK_K_PENCIL, p.stream);
   if (energy) {
     e = launch_sum_slot(p, static_cast<long long>(b.npairs) * tiles, b.eslot, b.mirror ? 2.0 : 1.0);
@@ -598,10 +575,7 @@ hipError_t line_apply_t(const Plan& p, const Batch& b, const void* psi, const do
   p.prof.begin(FOCK_K_ACCUMULATE, p.stream);
   switch (g.n1) {
 #define CASE(N) \
-  case N:                                                                                                       \
-    if constexpr (line_len<TA, TI>(N))                                                                          \
-      line_acc_L<TA, N, TI>(p, b, in, parts, tout, psi, occ, kw, out, gscale, hscale, backward);                \
-    break;
+  case N: line_acc_L<T, N>(p, b, in, parts, tbuf, psi, occ, kw, out, gscale, hscale, backward); break;
     FOCK_SMOOTH_L(CASE)
 #undef CASE
     default: return hipErrorInvalidValue;
@@ -610,24 +584,24 @@ hipError_t line_apply_t(const Plan& p, const Batch& b, const void* psi, const do
   return hipGetLastError();
 }
 
-template <typename TF, typename T, typename TI>
-hipError_t line_energy_t(const Plan& p, const Batch& b, const void* psi, const double* occ, size_t tin_off) {
+template <typename T>
+hipError_t line_energy_t(const Plan& p, const Batch& b, const void* psi, const double* occ) {
   using C = typename cx<T>::t;
   const Instance& in = p.inst[b.inst];
   const PlaneGeo& g = in.pg;
   const PairRef* pairs = reinterpret_cast<const PairRef*>(p.ws + b.pair_off);
   const C* tw = reinterpret_cast<const C*>(p.ws + p.tw_off);
-  auto* tin = reinterpret_cast<typename cx<TF>::t*>(p.ws + tin_off);
+  C* tbuf = reinterpret_cast<C*>(p.ws + p.tbuf_off);
   p.prof.begin(FOCK_K_ENERGY_PLANE, p.stream);
-  const hipError_t e = line_fwd<TF, TI>(p, b, in, psi, nullptr, pairs, tin);
+  const hipError_t e = line_fwd<T>(p, b, in, psi, nullptr, pairs, tbuf);
   p.prof.end(FOCK_K_ENERGY_PLANE, p.stream);
   if (e != hipSuccess) return e;
   const int tiles = plane_tiles(g);
   p.prof.begin(FOCK_K_ENERGY_PENCIL, p.stream);
-  hipLaunchKernelGGL((k_plane_pair<T, true, false, TF>), dim3(b.npairs, tiles), dim3(in.pg_threads),
+  hipLaunchKernelGGL((k_plane_pair<T, true, false>), dim3(b.npairs, tiles), dim3(in.pg_threads),
                      plane_lds(g, sizeof(C)), p.stream, g, in.nbands, in.nk, 0, 1, 0,
-                     static_cast<const int2*>(nullptr), static_cast<const int*>(nullptr), pairs, tin,
-                     static_cast<C*>(nullptr), reinterpret_cast<const T*>(p.ws + in.vtab_off),
+                     static_cast<const int2*>(nullptr), static_cast<const int*>(nullptr), pairs, tbuf,
+                     reinterpret_cast<const T*>(p.ws + in.vtab_off),
                      tw + twiddle_offset(g.n2), tw + twiddle_offset(g.n3), occ,
                      reinterpret_cast<const double*>(p.ws + in.kw_off), reinterpret_cast<double*>(p.ws + p.epart_off));
   p.prof.end(FOCK_K_ENERGY_PENCIL, p.stream);
@@ -709,17 +683,16 @@ void plane_geometry(const int grid[3], long long planes_of, size_t csize, int ma
 
 hipError_t launch_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
                               bool energy, const double* gscale, double hscale, bool backward) {
-  const size_t t = p.tbuf_off;
   if (p.inst[b.inst].reg) return launch_reg_apply_batch(p, b, psi, occ, out, gscale, hscale, backward, energy);
   return p.prec == FOCK_C64  // its energies: energy_lds.hip
-             ? line_apply_t<float, float, float, float>(p, b, psi, occ, out, gscale, hscale, backward, false, t, t)
-             : line_apply_t<double, double, double, double>(p, b, psi, occ, out, gscale, hscale, backward, energy, t, t);
+             ? line_apply_t<float>(p, b, psi, occ, out, gscale, hscale, backward, false)
+             : line_apply_t<double>(p, b, psi, occ, out, gscale, hscale, backward, energy);
 }
 
 hipError_t launch_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ) {
   if (p.inst[b.inst].reg) return launch_reg_energy_batch(p, b, psi, occ);
   return p.prec == FOCK_C64 ? launch_lds_energy_batch(p, b, psi, occ)
-                            : line_energy_t<double, double, double>(p, b, psi, occ, p.tbuf_off);
+                            : line_energy_t<double>(p, b, psi, occ);
 }
 
 hipError_t launch_line_dft3(const Plan& p, int inst, int sign, int count, void* data, long long stride) {
