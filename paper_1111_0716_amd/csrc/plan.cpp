@@ -243,74 +243,38 @@ fock_status validate_desc(const fock_desc& d, int idx) {
   return FOCK_OK;
 }
 
-fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, void* stream, const fock_tuning* tune,
-                       Plan** out) {
-  const fock_tuning tn = tune ? *tune : fock_tuning{0, 0, 0, 0, 0, 0};
-  static std::atomic<uint64_t> next_serial{1};
-  auto p = std::make_unique<Plan>();
-  p->serial = next_serial.fetch_add(1);
-  p->prec = prec;
-  p->csize = prec == FOCK_C64 ? 8 : 16;
-  const size_t rsize = prec == FOCK_C64 ? 4 : 8;  // kernel tables: FP64 unless the whole path is FP32
-  p->stream = static_cast<hipStream_t>(stream);
-  p->inst.resize(n_inst);
+// What the parts of build_plan share beside the plan: the schedule's choices
+// that only save time, and the lists that go into the host image.
+struct Schedule {
+  // outputs per batch of an ordered schedule as for the plane-wise passes
+  // (smaller batches on thin grids)
+  bool plane_blocks = false;
+  bool can_plane_blocks = false;  // that would change a batch
+  // partner lists per group of consecutive k sharing one partner list
+  struct Group {
+    int inst, k0, k1;  // k in [k0, k1)
+    size_t off;
+    std::vector<int32_t> parts;  // (k', m) pairs
+  };
+  std::vector<Group> groups;
+  std::vector<std::vector<int32_t>> round_pairs;
+  std::vector<std::vector<PairRef>> elists;
+  bool tw1 = false;  // twiddle table of energy_lds.hip
+};
 
-  // ---- instances, transfers and kernel tables (FP64) ----
-  std::vector<std::vector<std::vector<double>>> tables(n_inst);
-  for (int i = 0; i < n_inst; ++i) {
-    const fock_desc& d = descs[i];
-    Instance& in = p->inst[i];
-    std::memcpy(in.lattice, d.lattice, sizeof(in.lattice));
-    for (int a = 0; a < 3; ++a) in.grid[a] = d.grid[a];
-    in.nk = d.nk;
-    in.kfrac.assign(d.kfrac, d.kfrac + 3 * d.nk);
-    in.kweight.resize(d.nk);
-    for (int k = 0; k < d.nk; ++k) in.kweight[k] = d.kweight ? d.kweight[k] : 1.0 / d.nk;
-    in.kpartners.assign(d.nk, {});
-    if (d.npairs == 0) {
-      for (int k = 0; k < d.nk; ++k)
-        for (int kp = 0; kp < d.nk; ++kp) in.kpartners[k].push_back(kp);
-    } else {
-      for (int e = 0; e < d.npairs; ++e) in.kpartners[d.kpairs[2 * e]].push_back(d.kpairs[2 * e + 1]);
-    }
-    std::vector<char> listed(static_cast<size_t>(d.nk) * d.nk, 0);
-    for (int k = 0; k < d.nk; ++k)
-      for (int kp : in.kpartners[k]) {
-        if (listed[static_cast<size_t>(k) * d.nk + kp])
-          return set_error(FOCK_ERR_ARG, "instance " + std::to_string(i) + ": duplicate k-pair");
-        listed[static_cast<size_t>(k) * d.nk + kp] = 1;
-      }
-    in.symmetric = true;
-    for (int k = 0; k < d.nk; ++k)
-      for (int kp = 0; kp < d.nk; ++kp)
-        if (listed[static_cast<size_t>(k) * d.nk + kp] != listed[static_cast<size_t>(kp) * d.nk + k])
-          in.symmetric = false;
-    in.nbands = d.nbands;
-    in.band_stride = d.band_stride;
-    in.mu = d.mu;
-    in.npts = static_cast<int64_t>(d.grid[0]) * d.grid[1] * d.grid[2];
-    in.omega = std::fabs(det3(d.lattice));
-    // distinct transfers q = k - k' (FP64 differences, compared bit for bit)
-    in.qmap.assign(static_cast<size_t>(d.nk) * d.nk, -1);
-    std::map<std::array<double, 3>, int> qidx;
-    for (int k = 0; k < d.nk; ++k)
-      for (int kp : in.kpartners[k]) {
-        std::array<double, 3> q = {in.kfrac[3 * k] - in.kfrac[3 * kp], in.kfrac[3 * k + 1] - in.kfrac[3 * kp + 1],
-                                   in.kfrac[3 * k + 2] - in.kfrac[3 * kp + 2]};
-        auto it = qidx.find(q);
-        int id;
-        if (it == qidx.end()) {
-          id = static_cast<int>(qidx.size());
-          qidx.emplace(q, id);
-          tables[i].emplace_back();
-          build_kernel_table(in, q.data(), tables[i].back());
-        } else {
-          id = it->second;
-        }
-        in.qmap[static_cast<size_t>(k) * d.nk + kp] = id;
-      }
-    in.nq = static_cast<int>(qidx.size());
-  }
+// Paths, batches and workspace layout of every instance; total_bytes is set.
+static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
+  const fock_precision prec = p->prec;
+  const int n_inst = static_cast<int>(p->inst.size());
+  const size_t rsize = prec == FOCK_C64 ? 4 : 8;  // kernel tables: FP64 unless the whole path is FP32
+  p->apply_batches.clear();
+  p->energy_batches.clear();
+  p->ordered_energy.clear();
+  p->fused_groups.clear();
+  p->fused_rounds.clear();
+  p->ordered_pairs = p->apply_fft_pairs = p->energy_fft_pairs = 0;
+  for (auto& in : p->inst) in.rounds = -1;
+  sc->can_plane_blocks = false;
   const char* nofused = std::getenv("FOCK_NO_FUSED");
   const bool no_fused = tn.no_fused != 0 || (nofused && *nofused && *nofused != '0');
   const char* nosym = std::getenv("FOCK_NO_PAIR_SYMMETRY");
@@ -381,7 +345,7 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
       off = align_up(off + static_cast<size_t>(kTwiddleTotal) * p->csize);
       break;
     }
-  const bool tw1 = off != p->tw1_off;
+  sc->tw1 = off != p->tw1_off;
   for (auto& in : p->inst) {
     in.vtab_off = off;
     off = align_up(off + static_cast<size_t>(in.nq) * in.npts * rsize);
@@ -390,13 +354,10 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
     in.kw_off = off;
     off = align_up(off + in.kweight.size() * sizeof(double));
   }
-  // partner lists per group of consecutive k sharing one partner list; apply batches
-  struct Group {
-    int inst, k0, k1;  // k in [k0, k1)
-    size_t off;
-    std::vector<int32_t> parts;  // (k', m) pairs
-  };
-  std::vector<Group> groups;
+  // partner lists; apply batches
+  using Group = Schedule::Group;
+  std::vector<Group>& groups = sc->groups;
+  groups.clear();
   for (int i = 0; i < n_inst; ++i) {
     const Instance& in = p->inst[i];
     int k = 0;
@@ -421,7 +382,8 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   // whole-pair path by unordered pairs (the grids whose output is
   // read-modify-written per pair anyway), on request: rounds of two
   // workgroups per CU
-  std::vector<std::vector<int32_t>> round_pairs;
+  std::vector<std::vector<int32_t>>& round_pairs = sc->round_pairs;
+  round_pairs.clear();
   for (int i = 0; i < n_inst; ++i) {
     Instance& in = p->inst[i];
     if (!(use_rounds && in.fused && in.symmetric && fused_rounds_supported(prec, in.grid))) continue;
@@ -521,9 +483,16 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
       continue;
     }
     // outputs per batch: enough accumulate workgroups (planes, or 64-lane line blocks)
-    const int per_out = in.reg ? in.grid[0] : static_cast<int>((static_cast<int64_t>(in.grid[1]) * in.grid[2] + 63) / 64);
-    int nO = std::max(1, std::min(nout, (acc_wgs + per_out - 1) / per_out));
-    nO = std::min(nO, pmax);
+    const auto outputs = [&](int per_out) {
+      return std::min(pmax, std::max(1, std::min(nout, (acc_wgs + per_out - 1) / per_out)));
+    };
+    const int by_planes = outputs(in.grid[0]);
+    int nO = in.reg ? by_planes
+                    : outputs(static_cast<int>((static_cast<int64_t>(in.grid[1]) * in.grid[2] + 63) / 64));
+    if (nO > by_planes) {
+      sc->can_plane_blocks = true;
+      if (sc->plane_blocks) nO = by_planes;
+    }
     const int nP = std::max(1, std::min(npart, pmax / nO));
     for (int ob = 0; ob < nout; ob += nO) {
       for (int pb = 0; pb < npart; pb += nP) {
@@ -544,7 +513,8 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   // outputs without partners (empty k-pair list for some k) are written as zero by
   // a dedicated apply batch with no partners: not needed, the wrapper zero-fills.
   // energy pair lists
-  std::vector<std::vector<PairRef>> elists(n_inst);
+  std::vector<std::vector<PairRef>>& elists = sc->elists;
+  elists.assign(n_inst, {});
   // FP32 on general grids: E_x from its own passes (energy_lds.hip)
   const auto lds_energy = [&](const Instance& in) { return prec == FOCK_C64 && !in.fused && !in.reg; };
   size_t max_fused_epairs = 0;
@@ -699,6 +669,92 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
     if (off > FOCK_STATIC_WORKSPACE_BYTES) off = layout(true, true);
   }
   p->total_bytes = off;
+  return FOCK_OK;
+}
+
+fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, void* stream, const fock_tuning* tune,
+                       Plan** out) {
+  const fock_tuning tn = tune ? *tune : fock_tuning{0, 0, 0, 0, 0, 0};
+  static std::atomic<uint64_t> next_serial{1};
+  auto p = std::make_unique<Plan>();
+  p->serial = next_serial.fetch_add(1);
+  p->prec = prec;
+  p->csize = prec == FOCK_C64 ? 8 : 16;
+  p->stream = static_cast<hipStream_t>(stream);
+  p->inst.resize(n_inst);
+
+  // ---- instances, transfers and kernel tables (FP64) ----
+  std::vector<std::vector<std::vector<double>>> tables(n_inst);
+  for (int i = 0; i < n_inst; ++i) {
+    const fock_desc& d = descs[i];
+    Instance& in = p->inst[i];
+    std::memcpy(in.lattice, d.lattice, sizeof(in.lattice));
+    for (int a = 0; a < 3; ++a) in.grid[a] = d.grid[a];
+    in.nk = d.nk;
+    in.kfrac.assign(d.kfrac, d.kfrac + 3 * d.nk);
+    in.kweight.resize(d.nk);
+    for (int k = 0; k < d.nk; ++k) in.kweight[k] = d.kweight ? d.kweight[k] : 1.0 / d.nk;
+    in.kpartners.assign(d.nk, {});
+    if (d.npairs == 0) {
+      for (int k = 0; k < d.nk; ++k)
+        for (int kp = 0; kp < d.nk; ++kp) in.kpartners[k].push_back(kp);
+    } else {
+      for (int e = 0; e < d.npairs; ++e) in.kpartners[d.kpairs[2 * e]].push_back(d.kpairs[2 * e + 1]);
+    }
+    std::vector<char> listed(static_cast<size_t>(d.nk) * d.nk, 0);
+    for (int k = 0; k < d.nk; ++k)
+      for (int kp : in.kpartners[k]) {
+        if (listed[static_cast<size_t>(k) * d.nk + kp])
+          return set_error(FOCK_ERR_ARG, "instance " + std::to_string(i) + ": duplicate k-pair");
+        listed[static_cast<size_t>(k) * d.nk + kp] = 1;
+      }
+    in.symmetric = true;
+    for (int k = 0; k < d.nk; ++k)
+      for (int kp = 0; kp < d.nk; ++kp)
+        if (listed[static_cast<size_t>(k) * d.nk + kp] != listed[static_cast<size_t>(kp) * d.nk + k])
+          in.symmetric = false;
+    in.nbands = d.nbands;
+    in.band_stride = d.band_stride;
+    in.mu = d.mu;
+    in.npts = static_cast<int64_t>(d.grid[0]) * d.grid[1] * d.grid[2];
+    in.omega = std::fabs(det3(d.lattice));
+    // distinct transfers q = k - k' (FP64 differences, compared bit for bit)
+    in.qmap.assign(static_cast<size_t>(d.nk) * d.nk, -1);
+    std::map<std::array<double, 3>, int> qidx;
+    for (int k = 0; k < d.nk; ++k)
+      for (int kp : in.kpartners[k]) {
+        std::array<double, 3> q = {in.kfrac[3 * k] - in.kfrac[3 * kp], in.kfrac[3 * k + 1] - in.kfrac[3 * kp + 1],
+                                   in.kfrac[3 * k + 2] - in.kfrac[3 * kp + 2]};
+        auto it = qidx.find(q);
+        int id;
+        if (it == qidx.end()) {
+          id = static_cast<int>(qidx.size());
+          qidx.emplace(q, id);
+          tables[i].emplace_back();
+          build_kernel_table(in, q.data(), tables[i].back());
+        } else {
+          id = it->second;
+        }
+        in.qmap[static_cast<size_t>(k) * d.nk + kp] = id;
+      }
+    in.nq = static_cast<int>(qidx.size());
+  }
+  // ---- schedule ----
+  // What only saves time must not take a plan out of the static workspace: one
+  // that leaves it is scheduled again with the smaller batches, and stays so if
+  // it then fits (FP64 72x4x4, two k-points of 36 bands, no_pair_symmetry: 95.7
+  // -> 48.7 MB).
+  Schedule sc;
+  fock_status st = schedule_plan(p.get(), tn, &sc);
+  if (st == FOCK_OK && p->total_bytes > FOCK_STATIC_WORKSPACE_BYTES && sc.can_plane_blocks) {
+    sc.plane_blocks = true;
+    st = schedule_plan(p.get(), tn, &sc);
+    if (st == FOCK_OK && p->total_bytes > FOCK_STATIC_WORKSPACE_BYTES) {
+      sc.plane_blocks = false;
+      st = schedule_plan(p.get(), tn, &sc);
+    }
+  }
+  if (st != FOCK_OK) return st;
   for (const auto& in : p->inst) {
     const size_t need =
         in.fused ? fused_lds_bytes(prec, in.grid[0]) + 256
@@ -731,7 +787,7 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
       }
     }
   }
-  for (int L = 2; tw1 && L <= kNMax; ++L) {
+  for (int L = 2; sc.tw1 && L <= kNMax; ++L) {
     if (!smooth235(L)) continue;
     for (int t = 0; t < L; ++t) {
       const double ang = -2.0 * M_PI * static_cast<double>(t) / static_cast<double>(L);
@@ -795,15 +851,15 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
     std::memcpy(img + in.kw_off, in.kweight.data(), in.kweight.size() * sizeof(double));
     tables[i].clear();
   }
-  for (const Group& g : groups)
+  for (const Schedule::Group& g : sc.groups)
     if (!g.parts.empty()) std::memcpy(img + g.off, g.parts.data(), g.parts.size() * sizeof(int32_t));
   for (size_t i = 0; i < p->fused_rounds.size(); ++i)
-    std::memcpy(img + p->fused_rounds[i].pairs_off, round_pairs[i].data(), round_pairs[i].size() * sizeof(int32_t));
+    std::memcpy(img + p->fused_rounds[i].pairs_off, sc.round_pairs[i].data(), sc.round_pairs[i].size() * sizeof(int32_t));
   for (int i = 0; i < n_inst; ++i) {
     const Instance& in = p->inst[i];
     if (in.n_ebatches == 0) continue;
     const size_t base = p->energy_batches[in.first_ebatch].pair_off;
-    std::memcpy(img + base, elists[i].data(), elists[i].size() * sizeof(PairRef));
+    std::memcpy(img + base, sc.elists[i].data(), sc.elists[i].size() * sizeof(PairRef));
   }
   *out = p.release();
   return FOCK_OK;

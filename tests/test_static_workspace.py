@@ -1,0 +1,36 @@
+"""Plans that have to fit the static workspace (FOCK_STATIC_WORKSPACE_BYTES):
+schedules that only save time give way where a smaller one fits.  Host only;
+each case is a plan that the plainest schedule (ordered pairs, outputs blocked
+by planes, the whole-pair kernel where there is one) holds in less."""
+import ctypes
+
+import pytest
+
+from paper_1111_0716_amd import fock, inputs
+
+
+def plan_size(prec, instances, **tuning):
+    """(workspace bytes, apply transforms) of (grid, kmesh, bands, k-pairs) instances."""
+    keep = []
+    descs = (fock.FockDesc * len(instances))(*[
+        fock.make_desc(inputs.cubic_lattice(10.0), grid, inputs.gamma_mesh(*kmesh), None, nb, None, 0.106, kpairs, keep)
+        for grid, kmesh, nb, kpairs in instances])
+    h, fft, size = ctypes.c_void_p(), ctypes.c_int64(), ctypes.c_size_t()
+    tn = fock.FockTuning(**tuning)
+    L = fock.lib()
+    assert L.fock_plan_tuned(descs, len(instances), prec, None, ctypes.byref(tn), ctypes.byref(h)) == fock.FOCK_OK
+    L.fock_plan_stats(h, None, ctypes.byref(fft), None, None)
+    L.fock_workspace_size(h, ctypes.byref(size))
+    L.fock_destroy(h)
+    return size.value, fft.value
+
+
+@pytest.mark.parametrize("prec,grid,kmesh,nb", [
+    (fock.FOCK_C128, (72, 4, 4), (2, 1, 1), 36), (fock.FOCK_C64, (30, 4, 4), (2, 2, 1), 34),
+    (fock.FOCK_C64, (50, 2, 9), (2, 2, 1), 31), (fock.FOCK_C128, (50, 10, 3), (2, 1, 1), 29)])
+def test_ordered_schedules_of_thin_grids(prec, grid, kmesh, nb):
+    """no_pair_symmetry on grids with many thin planes: output blocks by planes,
+    not by line blocks, where the latter take the pair buffer past the limit."""
+    size, fft = plan_size(prec, [(grid, kmesh, nb, None)], no_pair_symmetry=1)
+    assert size <= fock.STATIC_WORKSPACE_BYTES
+    assert fft == (kmesh[0] * kmesh[1] * kmesh[2] * nb) ** 2
