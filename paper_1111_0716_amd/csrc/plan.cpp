@@ -195,11 +195,6 @@ bool rounds_valid(const Instance& in, const std::vector<int32_t>& pairs, const s
 // 204/161, but its energies would be sums of other roundings.)
 bool fused_loses(fock_precision prec, int orb) { return prec == FOCK_C128 && orb > 8 && orb <= 56; }
 
-// the grids with that choice
-bool fused_optional(fock_precision prec, const int grid[3], bool no_fused) {
-  return !no_fused && prec == FOCK_C128 && fused_supported(prec, grid);
-}
-
 size_t env_mb(const char* name, size_t dflt) {
   const char* s = std::getenv(name);
   if (!s || !*s) return dflt;
@@ -250,6 +245,9 @@ struct Schedule {
   // (smaller batches on thin grids)
   bool plane_blocks = false;
   bool can_plane_blocks = false;  // that would change a batch
+  // the whole-pair kernel also where the three-pass path is faster
+  bool keep_fused = false;
+  bool can_keep_fused = false;
   // partner lists per group of consecutive k sharing one partner list
   struct Group {
     int inst, k0, k1;  // k in [k0, k1)
@@ -274,7 +272,7 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
   p->fused_rounds.clear();
   p->ordered_pairs = p->apply_fft_pairs = p->energy_fft_pairs = 0;
   for (auto& in : p->inst) in.rounds = -1;
-  sc->can_plane_blocks = false;
+  sc->can_plane_blocks = sc->can_keep_fused = false;
   const char* nofused = std::getenv("FOCK_NO_FUSED");
   const bool no_fused = tn.no_fused != 0 || (nofused && *nofused && *nofused != '0');
   const char* nosym = std::getenv("FOCK_NO_PAIR_SYMMETRY");
@@ -295,9 +293,12 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
     if (in.fused && !no_sym && !use_rounds && full_kset(in)) {
       // 32^3 FP32 read-modify-writes its output per partner: three passes with
       // pair symmetry take 337 against 606 ms per step (4x4x4 k, 18 bands)
-      if (fused_rounds_supported(prec, in.grid) ? reg_supported(prec, in.grid) && !no_reg
-                                                : fused_loses(prec, in.nk * in.nbands))
-        in.fused = false;
+      if (fused_rounds_supported(prec, in.grid)) {
+        in.fused = !(reg_supported(prec, in.grid) && !no_reg);
+      } else if (fused_loses(prec, in.nk * in.nbands)) {
+        sc->can_keep_fused = true;  // the whole-pair kernel needs no pair buffer
+        in.fused = sc->keep_fused;
+      }
     }
     // FP32 and mixed plans keep the register-line passes where they are (see
     // energy_lds.hip: their energies and FP64 outputs are sums of FP32 spectra)
@@ -305,27 +306,6 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
     in.slab = in.reg && (slab_force < 0 ? reg_slab_default(prec, in.grid)
                                         : slab_force == 1 && reg_slab_supported(prec, in.grid));
   }
-  // The whole-pair kernel needs no pair buffer: a plan that it keeps within the
-  // static workspace is not taken out of it.  Bytes of tables and lists, and of
-  // pair buffers with and without the instances that have the choice.
-  {
-    size_t base = 0, must = 0, may = 0;
-    for (const auto& in : p->inst) {
-      const size_t orb = static_cast<size_t>(in.nk) * in.nbands, pairs = orb * (orb + 1) / 2;
-      base += in.nq * in.npts * rsize + pairs * sizeof(PairRef) + 4096;
-      if (in.fused) {
-        may = std::max(may, 3 * orb * in.npts * p->csize);  // partner slices
-        continue;
-      }
-      const size_t t = pairs * (in.npts * p->csize + in.grid[0] * sizeof(double));
-      may = std::max(may, t);
-      if (!fused_optional(prec, in.grid, no_fused)) must = std::max(must, t);
-    }
-    if (base + must <= FOCK_STATIC_WORKSPACE_BYTES && base + may + (1u << 20) > FOCK_STATIC_WORKSPACE_BYTES)
-      for (auto& in : p->inst)
-        if (!in.fused && fused_optional(prec, in.grid, no_fused)) in.fused = true;
-  }
-
   // ---- batch shapes ----
   // pair-buffer budget: 4 GiB, 8 GiB in FP64, whose pairs are twice the
   // bytes (the same block shapes; alpha boron FP64 1.02 s per step against
@@ -741,18 +721,18 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   }
   // ---- schedule ----
   // What only saves time must not take a plan out of the static workspace: one
-  // that leaves it is scheduled again with the smaller batches, and stays so if
-  // it then fits (FP64 72x4x4, two k-points of 36 bands, no_pair_symmetry: 95.7
-  // -> 48.7 MB).
+  // that leaves it is scheduled again with smaller batches, with the whole-pair
+  // kernel kept, with both, and takes the first that fits.  FP64 72x4x4, two
+  // k-points of 36 bands, no_pair_symmetry: 95.7 -> 48.7 MB; FP64 16^3 Gamma, 56
+  // bands: 105 -> 11 MB.
   Schedule sc;
   fock_status st = schedule_plan(p.get(), tn, &sc);
-  if (st == FOCK_OK && p->total_bytes > FOCK_STATIC_WORKSPACE_BYTES && sc.can_plane_blocks) {
-    sc.plane_blocks = true;
+  const bool planes = sc.can_plane_blocks, keep = sc.can_keep_fused;
+  for (int i = 1; st == FOCK_OK && i <= 4 && p->total_bytes > FOCK_STATIC_WORKSPACE_BYTES && (planes || keep); ++i) {
+    sc.plane_blocks = (i & 1) && i < 4;  // the last: none fits, as first
+    sc.keep_fused = (i & 2) && i < 4;
+    if ((sc.plane_blocks && !planes) || (sc.keep_fused && !keep)) continue;
     st = schedule_plan(p.get(), tn, &sc);
-    if (st == FOCK_OK && p->total_bytes > FOCK_STATIC_WORKSPACE_BYTES) {
-      sc.plane_blocks = false;
-      st = schedule_plan(p.get(), tn, &sc);
-    }
   }
   if (st != FOCK_OK) return st;
   for (const auto& in : p->inst) {

@@ -34,3 +34,19 @@ def test_ordered_schedules_of_thin_grids(prec, grid, kmesh, nb):
     size, fft = plan_size(prec, [(grid, kmesh, nb, None)], no_pair_symmetry=1)
     assert size <= fock.STATIC_WORKSPACE_BYTES
     assert fft == (kmesh[0] * kmesh[1] * kmesh[2] * nb) ** 2
+
+
+@pytest.mark.parametrize("instances", [
+    # the pair buffer that counts is of the listed pairs only
+    [((3, 3, 3), (2, 1, 1), 272, [(0, 0), (1, 1)]), ((16, 16, 16), (1, 1, 1), 44, None)],
+    [((40, 10, 4), (2, 2, 1), 18, [(k, k) for k in range(4)]), ((16, 16, 16), (2, 1, 1), 26, None),
+     ((16, 6, 4), (1, 1, 1), 52, None)],
+    [((16, 16, 16), (1, 1, 1), 56, None)]])
+def test_whole_pair_kernel_stays_where_its_plan_fits(instances):
+    """FP64 16^3 instances that would take the three-pass path keep the
+    whole-pair kernel (one transform per ordered pair, no pair buffer) in plans
+    that fit with it only."""
+    size, fft = plan_size(fock.FOCK_C128, instances)
+    assert size <= fock.STATIC_WORKSPACE_BYTES
+    orb = [nb * k[0] * k[1] * k[2] for g, k, nb, _ in instances if g == (16, 16, 16)][0]
+    assert fft >= orb ** 2
