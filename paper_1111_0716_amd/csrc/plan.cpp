@@ -238,6 +238,10 @@ fock_status validate_desc(const fock_desc& d, int idx) {
   return FOCK_OK;
 }
 
+// pair-buffer bytes up to which E_x after an apply takes all ordered pairs of a
+// group in one batch (energy_lds.hip)
+constexpr size_t kOneEnergyBatch = size_t{16} << 20;
+
 // What the parts of build_plan share beside the plan: the schedule's choices
 // that only save time, and the lists that go into the host image.
 struct Schedule {
@@ -545,14 +549,24 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
     Instance& in = p->inst[i];
     in.first_aslot = slot;
     if (lds_energy(in)) {
-      // ordered pairs of every group, in batches that the pair buffer holds
-      const long long orb = static_cast<long long>(in.nk) * in.nbands;
-      const int cap = static_cast<int>(std::max<long long>(
-          1, std::min<long long>({65535, static_cast<long long>(tbuf_target / (in.npts * p->csize)), orb * (orb + 1) / 2})));
+      // Ordered pairs of every group, in batches that the pair buffer holds
+      // anyway (the unordered pairs of the energy list), or blocked by planes
+      // as the plane-wise passes were, one batch as a rule, where that is
+      // little: a half takes as long as the whole (24x24x60 Gamma, 4 bands,
+      // 4.4 MB: forward pass 14.7 us each, 15.8 in one).
+      const size_t pair_bytes = static_cast<size_t>(in.npts) * p->csize;
+      const int pmax = static_cast<int>(std::max<size_t>(1, std::min<size_t>(65535, tbuf_target / pair_bytes)));
+      int listed = 1;  // pairs of the largest energy batch
+      for (int e = 0; e < in.n_ebatches; ++e) listed = std::max(listed, p->energy_batches[in.first_ebatch + e].npairs);
       for (const Group& g : groups) {
         const int nout = (g.k1 - g.k0) * in.nbands, npart = static_cast<int>(g.parts.size() / 2);
         if (g.inst != i || npart == 0) continue;
-        const int nO = std::min(nout, cap), nP = std::max(1, std::min(npart, cap / nO));
+        int nO = std::min(pmax, std::max(1, std::min(nout, (acc_wgs + in.grid[0] - 1) / in.grid[0])));
+        int nP = std::max(1, std::min(npart, pmax / nO));
+        if (static_cast<size_t>(nO) * nP * pair_bytes > kOneEnergyBatch) {
+          nO = std::min(nout, listed);
+          nP = std::max(1, std::min(npart, listed / nO));
+        }
         for (int ob = 0; ob < nout; ob += nO)
           for (int pb = 0; pb < npart; pb += nP) {
             Batch b;

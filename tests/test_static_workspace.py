@@ -50,3 +50,14 @@ def test_whole_pair_kernel_stays_where_its_plan_fits(instances):
     assert size <= fock.STATIC_WORKSPACE_BYTES
     orb = [nb * k[0] * k[1] * k[2] for g, k, nb, _ in instances if g == (16, 16, 16)][0]
     assert fft >= orb ** 2
+
+
+@pytest.mark.parametrize("instances,tuning", [
+    ([((50, 6, 12), (3, 1, 1), 26, [(0, 0), (1, 1), (1, 2), (2, 1), (2, 2)]),
+      ((12, 6, 4), (2, 1, 1), 85, [(0, 0), (1, 1)])], {}),
+    ([((36, 6, 5), (2, 1, 1), 67, [(0, 1), (1, 0), (1, 1)])], {"acc_workgroups": 64}),
+    ([((27, 9, 4), (3, 1, 1), 48, [(0, 0), (0, 1), (1, 0), (1, 1), (2, 2)])], {})])
+def test_ordered_energy_of_listed_pairs(instances, tuning):
+    """FP32 general grids: the ordered pairs that E_x after an apply runs over
+    take no larger batches than the listed pairs and the apply's own."""
+    assert plan_size(fock.FOCK_C64, instances, **tuning)[0] <= fock.STATIC_WORKSPACE_BYTES
