@@ -117,7 +117,12 @@ fock_status fock_plan(const fock_desc* descs, int32_t n_inst, fock_precision pre
  *                   which sets the output block |O| = ceil(target / N1)
  *   tbuf_mb         three-pass path: pair-buffer budget (MiB), which bounds
  *                   |O| x |P| pairs per batch
- *   fused_split     whole-pair path: partner slices per output (1..4)
+ *   fused_split     whole-pair path: partner slices per output (1..4); set, it
+ *                   also keeps FOCK_C128 16^3 instances of 9 to 56 orbitals
+ *                   (N_k nbands, full k-pair set) on that path.  By default
+ *                   those take the three-pass path, whose pair buffer (up to
+ *                   105 MB) the whole-pair kernel does not need, as long as
+ *                   the plan fits FOCK_STATIC_WORKSPACE_BYTES
  *   no_fused        1: use the three-pass path for every grid
  *   no_pair_symmetry 1: the three-pass paths transform every ordered pair; 0: with the full k-pair set it transforms
  *                   each unordered pair once, W_nm(k,k') = conj W_mn(k',k)

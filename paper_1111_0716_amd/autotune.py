@@ -6,11 +6,12 @@ paths the plan uses (read from the kernels a default apply launches):
 
   whole-pair path   one workgroup per output with fused_split in {1, 2, 3, 4}
                     partner slices, and unordered-pair rounds (fused_rounds)
-  three-pass path   pair symmetry with the pair-buffer budget tbuf_mb in
-                    {128 .. 16384} MiB (which sets the block size; 128 and
-                    256 MiB keep a batch's pair buffer within the 256 MB
-                    Infinity Cache), and the ordered schedule over the joint
-                    grid tbuf_mb x acc_workgroups (output block size)
+  three-pass path   the whole-pair path of the cubes that have both
+                    (fused_split), pair symmetry with the pair-buffer budget
+                    tbuf_mb in {128 .. 16384} MiB (which sets the block size;
+                    128 and 256 MiB keep a batch's pair buffer within the
+                    256 MB Infinity Cache), and the ordered schedule over the
+                    joint grid tbuf_mb x acc_workgroups (output block size)
 
 Candidates whose plans come out identical (same counters and workspace on
 the host) are timed once.  Results are cached as JSON keyed by the device
@@ -39,6 +40,8 @@ def candidates(kinds):
     if "fused" in kinds:
         out += [{"fused_split": sp} for sp in FUSED_SPLITS] + [{"fused_rounds": 1}]
     if kinds & {"plane", "pencil", "accumulate"}:
+        if "fused" not in kinds:  # small cubes with both paths; elsewhere the knob changes nothing
+            out += [{"fused_split": sp} for sp in FUSED_SPLITS]
         out += [{"tbuf_mb": tb} for tb in SYM_TBUF_MB]
         out += [{"no_pair_symmetry": 1, "tbuf_mb": tb, "acc_workgroups": aw}
                 for tb in ORDERED_TBUF_MB for aw in ORDERED_ACC_WORKGROUPS]

@@ -299,7 +299,7 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
       // pair symmetry take 337 against 606 ms per step (4x4x4 k, 18 bands)
       if (fused_rounds_supported(prec, in.grid)) {
         in.fused = !(reg_supported(prec, in.grid) && !no_reg);
-      } else if (fused_loses(prec, in.nk * in.nbands)) {
+      } else if (tn.fused_split == 0 && fused_loses(prec, in.nk * in.nbands)) {
         sc->can_keep_fused = true;  // the whole-pair kernel needs no pair buffer
         in.fused = sc->keep_fused;
       }

@@ -1,4 +1,4 @@
-"""Plans that have to fit the static workspace (FOCK_STATIC_WORKSPACE_BYTES):
+"""Path choices of the planner.  Plans that have to fit the static workspace (FOCK_STATIC_WORKSPACE_BYTES):
 schedules that only save time give way where a smaller one fits.  Host only;
 each case is a plan that the plainest schedule (ordered pairs, outputs blocked
 by planes, the whole-pair kernel where there is one) holds in less."""
@@ -61,3 +61,11 @@ def test_ordered_energy_of_listed_pairs(instances, tuning):
     """FP32 general grids: the ordered pairs that E_x after an apply runs over
     take no larger batches than the listed pairs and the apply's own."""
     assert plan_size(fock.FOCK_C64, instances, **tuning)[0] <= fock.STATIC_WORKSPACE_BYTES
+
+
+def test_fused_split_asks_for_the_whole_pair_kernel():
+    """The knob is of the whole-pair path: a plan that sets it takes that path
+    where there is one, also at 16^3 FP64 with 9 to 56 orbitals."""
+    for split in (1, 2, 4):
+        assert plan_size(fock.FOCK_C128, [((16, 16, 16), (1, 1, 1), 24, None)], fused_split=split)[1] == 24 ** 2
+    assert plan_size(fock.FOCK_C128, [((16, 16, 16), (1, 1, 1), 24, None)])[1] == 24 * 25 // 2
