@@ -246,13 +246,15 @@ fock_status run_overlaps(Plan* p, const void* const* psi, void* const* vx_psi, v
 
 // E_x of every instance into ex[i].  after_apply: every instance takes its
 // energy from the partials the apply just wrote (per block of the whole-pair
-// kernel, or per apply batch of the three-pass paths).
+// kernel, or per apply batch of the three-pass paths), or from the ordered
+// pairs' own passes (energy_lds.hip).
 fock_status run_energy(Plan* p, const void* const* psi, const double* const* occ, double* ex, bool after_apply) {
-  for (const Batch& b : p->energy_batches) {
-    const bool fused = p->inst[b.inst].fused;
-    if (after_apply) continue;
+  // after an apply only the energies that are not its own are left to do
+  for (const Batch& b : after_apply ? p->ordered_energy : p->energy_batches) {
     hipError_t e;
-    if (fused) {
+    if (after_apply) {
+      e = launch_lds_energy_batch(*p, b, psi[b.inst], occ[b.inst]);
+    } else if (p->inst[b.inst].fused) {
       e = launch_fused_energy(*p, b, psi[b.inst]);
       if (e == hipSuccess) e = launch_energy_reduce(*p, b, occ[b.inst], 1);
     } else {
@@ -260,11 +262,6 @@ fock_status run_energy(Plan* p, const void* const* psi, const double* const* occ
     }
     if (e != hipSuccess) return hip_fail(e, "energy batch launch");
   }
-  if (after_apply)
-    for (const Batch& b : p->ordered_energy) {
-      const hipError_t e = launch_lds_energy_batch(*p, b, psi[b.inst], occ[b.inst]);
-      if (e != hipSuccess) return hip_fail(e, "energy batch launch");
-    }
   const hipError_t e = launch_energy_finish(*p, ex, after_apply);
   return e == hipSuccess ? FOCK_OK : hip_fail(e, "energy finish launch");
 }

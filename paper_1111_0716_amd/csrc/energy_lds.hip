@@ -24,23 +24,6 @@ struct Geo {
 };
 
 // ---------------------------------------------------------------------------
-// deterministic block reduction of a double (kBlock threads, wave64)
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double block_sum(double v, double* red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) red[wave] = v;
-  __syncthreads();
-  double t = 0.0;
-  if (threadIdx.x == 0) {
-    for (int w = 0; w < kBlock / 64; ++w) t += red[w];
-  }
-  __syncthreads();
-  return t;  // valid in thread 0
-}
-
-// ---------------------------------------------------------------------------
 // one Stockham pass of radix R over `nlines` lines of length L in LDS.
 // ROWS: elements of a line are contiguous (estride 1) and consecutive lanes
 // take consecutive butterflies of one line; otherwise lines are contiguous
@@ -173,8 +156,8 @@ __global__ __launch_bounds__(kBlock) void k_fwd_plane(Geo g, const typename cx<T
 // plane passes (plan.cpp).
 __device__ __forceinline__ int table_at(const PlaneGeo& g, int c1, int c2, int c3) {
   const int g0 = c1 / g.g * g.g, rows = min(g.g, g.n1 - g0) * g.n2;
-  const int q2 = c2 / g.a2, q3 = c3 / g.a3;
-  return g0 * g.n2 * g.n3 + (q3 * g.a3 + (c3 - q3 * g.a3)) * rows + (c1 - g0) * g.n2 + (c2 - q2 * g.a2) * g.b2 + q2;
+  const int q2 = c2 / g.a2;
+  return g0 * g.n2 * g.n3 + c3 * rows + (c1 - g0) * g.n2 + (c2 - q2 * g.a2) * g.b2 + q2;
 }
 
 // pencil pass: axis 1 of slab c2 and sum_c v_q(c)/N |P(c)|^2 in FP64.  EXPLICIT:

@@ -7,25 +7,9 @@
 
 #include "fft_lds.hpp"
 #include "fock_internal.hpp"
+#include "pass_common.hpp"
 
 namespace fock {
-
-// ---------------------------------------------------------------------------
-// deterministic block reduction of a double (kBlock threads, wave64)
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double block_sum(double v, double* red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) red[wave] = v;
-  __syncthreads();
-  double t = 0.0;
-  if (threadIdx.x == 0) {
-    for (int w = 0; w < kBlock / 64; ++w) t += red[w];
-  }
-  __syncthreads();
-  return t;  // valid in thread 0
-}
 
 // one step of a compensated (Neumaier) sum
 __device__ __forceinline__ void neumaier(double& sum, double& comp, double x) {

@@ -1,5 +1,6 @@
-// Device helpers of the three-pass kernels (pass_line.hip, plane_fft.hpp) and
-// the register-line DFT (dft_reg.hip).
+// Device helpers of the three-pass kernels (pass_line.hip, plane_fft.hpp,
+// pass_reg.hip, energy_lds.hip), the register-line DFT (dft_reg.hip) and the
+// reductions (kernels.hip).
 #pragma once
 
 #include <type_traits>
@@ -7,6 +8,23 @@
 #include "fft_lds.hpp"
 
 namespace fock {
+
+// ---------------------------------------------------------------------------
+// deterministic block reduction of a double (kBlock threads, wave64)
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ double block_sum(double v, double* red) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane == 0) red[wave] = v;
+  __syncthreads();
+  double t = 0.0;
+  if (threadIdx.x == 0) {
+    for (int w = 0; w < kBlock / 64; ++w) t += red[w];
+  }
+  __syncthreads();
+  return t;  // valid in thread 0
+}
 
 // Loads issued in batches with the next batch in flight while the current one
 // is consumed: only two batches of operands are live beside the line, and a

@@ -85,15 +85,15 @@ inline unsigned xcd_grid(unsigned total) { return ((total + 7u) >> 3) * 8u; }
 // x[j] = conj(b[j * stride]) a[j * stride] at the lane's byte offset o (a and
 // b wave-uniform): a straight into the line (all loads in flight at once),
 // then b in batches multiplied in place, so that only two batches of operands
-// are live beside the line.  Orbitals wider than the line are rounded on load.
-template <typename C, int L, typename CI>
-__device__ __forceinline__ void load_codensity_u(C* x, const CI* __restrict__ a, const CI* __restrict__ b, unsigned o,
+// are live beside the line.
+template <typename C, int L>
+__device__ __forceinline__ void load_codensity_u(C* x, const C* __restrict__ a, const C* __restrict__ b, unsigned o,
                                                  size_t stride) {
   constexpr int B = batch_of(L, kRegB);
   constexpr int NB = L / B;
 #pragma unroll
-  for (int j = 0; j < L; ++j) x[j] = cvt<C>(*lane_at(a + j * stride, o));
-  CI bb[2][B];
+  for (int j = 0; j < L; ++j) x[j] = *lane_at(a + j * stride, o);
+  C bb[2][B];
 #pragma unroll
   for (int j = 0; j < B; ++j) bb[0][j] = *lane_at(b + j * stride, o);
 #pragma unroll
@@ -104,7 +104,7 @@ __device__ __forceinline__ void load_codensity_u(C* x, const CI* __restrict__ a,
     }
     reg_fence();
 #pragma unroll
-    for (int j = 0; j < B; ++j) x[n * B + j] = cmulconj(cvt<C>(bb[n & 1][j]), x[n * B + j]);
+    for (int j = 0; j < B; ++j) x[n * B + j] = cmulconj(bb[n & 1][j], x[n * B + j]);
   }
 }
 
@@ -117,9 +117,9 @@ __device__ __forceinline__ void load_codensity_u(C* x, const CI* __restrict__ a,
 // batch's 128 partners (32^3: 16 KB each) then stay in an XCD's 4 MB while it
 // walks the pairs; four waves' slices (8 MB) come from further away.  32^3
 // 4x4x4 k FP32, 3.9 GB a batch: 1060 us at four waves, 730 at one (5.3 TB/s).
-template <typename T, int L, typename TI = T>
-__global__ __launch_bounds__(64, (sizeof(TI) == sizeof(T) ? LineShape<T, L>::WPE_FWD : 1)) void k_line_fwd(
-    int plane, int npairs, unsigned total, int nbands, long long bs, const typename cx<TI>::t* __restrict__ psi, int o0,
+template <typename T, int L>
+__global__ __launch_bounds__(64, (LineShape<T, L>::WPE_FWD)) void k_line_fwd(
+    int plane, int npairs, unsigned total, int nbands, long long bs, const typename cx<T>::t* __restrict__ psi, int o0,
     int nP, int tri, const int2* __restrict__ parts, const PairRef* __restrict__ pairs,
     typename cx<T>::t* __restrict__ tbuf) {
   using C = typename cx<T>::t;
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(64, (sizeof(TI) == sizeof(T) ? LineShape<T, L>::WPE
     pkm = r.x * nbands + r.y;
   }
   C x[LN];
-  const unsigned lo = (static_cast<unsigned>(h) * plane + l) * sizeof(typename cx<TI>::t);  // split: samples j1 = 2m + h
+  const unsigned lo = (static_cast<unsigned>(h) * plane + l) * sizeof(C);  // split: samples j1 = 2m + h
   load_codensity_u<C, LN>(x, psi + static_cast<size_t>(okn) * bs, psi + static_cast<size_t>(pkm) * bs, lo,
                           static_cast<size_t>(SPLIT ? 2 : 1) * plane);
   if constexpr (SPLIT)
@@ -269,16 +269,14 @@ __global__ __launch_bounds__(512, 4) void k_plane_pair(PlaneGeo g, int nbands, i
 // one wave is what the pass takes (two memory latencies each).
 // Once they do, loading a partner's orbital together with its pair gains no
 // more (the batch of twelve cells 834 -> 822 us, 12x10x9 53.0 -> 54.6).
-// TI: orbitals and outputs, wider than the sums where the sums alone are FP32.
-template <typename T, int L, bool SPLIT, typename TI = T>
+template <typename T, int L, bool SPLIT>
 __global__ __launch_bounds__((AccShape<T, L, SPLIT>::WAVES * 64), (AccShape<T, L, SPLIT>::WPE)) void k_line_acc(
     int plane, int rows, unsigned total, int nbands, long long bs, int o0, int nO, int nP, int tri,
     const int2* __restrict__ parts, const typename cx<T>::t* __restrict__ tbuf,
-    const typename cx<TI>::t* __restrict__ psi, const double* __restrict__ occ, const double* __restrict__ kw,
-    typename cx<TI>::t* __restrict__ out, int first, int first_mirror, const double* __restrict__ gscale, double hscale,
+    const typename cx<T>::t* __restrict__ psi, const double* __restrict__ occ, const double* __restrict__ kw,
+    typename cx<T>::t* __restrict__ out, int first, int first_mirror, const double* __restrict__ gscale, double hscale,
     int backward) {
   using C = typename cx<T>::t;
-  using CI = typename cx<TI>::t;
   constexpr int LN = SPLIT ? L / 2 : L;
   constexpr int B = batch_of(LN, AccShape<T, L, SPLIT>::WPE == 1 ? 16 : kRegB);
   constexpr int NB = LN / B;
@@ -295,7 +293,7 @@ __global__ __launch_bounds__((AccShape<T, L, SPLIT>::WAVES * 64), (AccShape<T, L
   const int o = mirror ? row - nO : row;
   const int nsrc = mirror ? nO : nP;
   const unsigned lt = (static_cast<unsigned>(h) * LN * plane + l) * sizeof(C);  // split: c1 = h L/2 + k
-  const unsigned lu = (static_cast<unsigned>(h) * plane + l) * sizeof(CI);      // split: j1 = 2m + h
+  const unsigned lu = (static_cast<unsigned>(h) * plane + l) * sizeof(C);       // split: j1 = 2m + h
   const size_t us = static_cast<size_t>(SPLIT ? 2 : 1) * plane;
   C acc[LN];
 #pragma unroll
@@ -322,8 +320,8 @@ __global__ __launch_bounds__((AccShape<T, L, SPLIT>::WAVES * 64), (AccShape<T, L
       for (int j = 0; j < LN; ++j) x[j].y = -x[j].y;
     }
     const T coef = static_cast<T>(-kw[sb / nbands] * occ[sb]);
-    const CI* um = psi + static_cast<size_t>(sb) * bs;
-    CI mb[2][B];
+    const C* um = psi + static_cast<size_t>(sb) * bs;
+    C mb[2][B];
 #pragma unroll
     for (int j = 0; j < B; ++j) mb[0][j] = lane_load(um + j * us, ou);
 #pragma unroll
@@ -335,7 +333,7 @@ __global__ __launch_bounds__((AccShape<T, L, SPLIT>::WAVES * 64), (AccShape<T, L
       reg_fence();
 #pragma unroll
       for (int j = 0; j < B; ++j) {
-        const C w = cmul(cvt<C>(mb[n & 1][j]), x[n * B + j]);
+        const C w = cmul(mb[n & 1][j], x[n * B + j]);
         acc[n * B + j].x += coef * w.x;
         acc[n * B + j].y += coef * w.y;
       }
@@ -359,24 +357,19 @@ __global__ __launch_bounds__((AccShape<T, L, SPLIT>::WAVES * 64), (AccShape<T, L
   double f = hscale;
   if (gscale) f *= gscale[0];
   if (backward) f *= kw[okn / nbands] * occ[okn];
-  const TI ft = static_cast<TI>(f);
-  CI* dst = out + static_cast<size_t>(okn) * bs;
+  const T ft = static_cast<T>(f);
+  C* dst = out + static_cast<size_t>(okn) * bs;
   const unsigned ou = opaque(lu);
   if (!(mirror ? first_mirror : first)) {
-    // loaded before the first store, so the loads overlap (wide outputs in
-    // batches, which the registers hold)
-    constexpr int OB = sizeof(TI) == sizeof(T) ? LN : batch_of(LN, kRegB);
+    // loaded before the first store, so the loads overlap
+    C old[LN];
 #pragma unroll
-    for (int n = 0; n < LN; n += OB) {
-      CI old[OB];
+    for (int j = 0; j < LN; ++j) old[j] = lane_load(dst + j * us, ou);
 #pragma unroll
-      for (int j = 0; j < OB; ++j) old[j] = lane_load(dst + (n + j) * us, ou);
-#pragma unroll
-      for (int j = 0; j < OB; ++j) lane_store(dst + (n + j) * us, ou, cadd(old[j], cscale(cvt<CI>(acc[n + j]), ft)));
-    }
+    for (int j = 0; j < LN; ++j) lane_store(dst + j * us, ou, cadd(old[j], cscale(acc[j], ft)));
   } else {
 #pragma unroll
-    for (int j = 0; j < LN; ++j) lane_store(dst + j * us, ou, cscale(cvt<CI>(acc[j]), ft));
+    for (int j = 0; j < LN; ++j) lane_store(dst + j * us, ou, cscale(acc[j], ft));
   }
 }
 
@@ -559,8 +552,10 @@ hipError_t line_apply_t(const Plan& p, const Batch& b, const void* psi, const do
   const dim3 grid(b.npairs, tiles);
   const C *tw2 = tw + twiddle_offset(g.n2), *tw3 = tw + twiddle_offset(g.n3);
   p.prof.begin(FOCK_K_PENCIL, p.stream);
+  if constexpr (sizeof(T) == 4) energy = false;  // energy_lds.hip
+  constexpr bool EN = sizeof(T) == 8;
   if (energy)
-    hipLaunchKernelGGL((k_plane_pair<T, true, true>), grid, dim3(in.pg_threads), plane_lds(g, sizeof(C)),
+    hipLaunchKernelGGL((k_plane_pair<T, EN, true>), grid, dim3(in.pg_threads), plane_lds(g, sizeof(C)),
                        p.stream, g, in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap,
                        static_cast<const PairRef*>(nullptr), tbuf, vtab, tw2, tw3, occ, kw, epart);
   else
@@ -584,8 +579,8 @@ hipError_t line_apply_t(const Plan& p, const Batch& b, const void* psi, const do
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t line_energy_t(const Plan& p, const Batch& b, const void* psi, const double* occ) {
+hipError_t line_energy(const Plan& p, const Batch& b, const void* psi, const double* occ) {
+  using T = double;
   using C = typename cx<T>::t;
   const Instance& in = p.inst[b.inst];
   const PlaneGeo& g = in.pg;
@@ -634,9 +629,10 @@ hipError_t line_dft3_t(const Plan& p, const PlaneGeo& g, int threads, int count,
 
 template <typename T>
 void plane_lds_attr(int lim) {
-  const void* fs[] = {reinterpret_cast<const void*>(&k_plane_pair<T, true, true>),
-                      reinterpret_cast<const void*>(&k_plane_pair<T, false, true>),
-                      reinterpret_cast<const void*>(&k_plane_pair<T, true, false>),
+  constexpr bool EN = sizeof(T) == 8;  // FP32 energies: energy_lds.hip
+  const void* fs[] = {reinterpret_cast<const void*>(&k_plane_pair<T, false, true>),
+                      reinterpret_cast<const void*>(&k_plane_pair<T, EN, true>),
+                      reinterpret_cast<const void*>(&k_plane_pair<T, EN, !EN>),
                       reinterpret_cast<const void*>(&k_dft_plane<T, -1>),
                       reinterpret_cast<const void*>(&k_dft_plane<T, +1>)};
   for (const void* f : fs)
@@ -684,15 +680,15 @@ void plane_geometry(const int grid[3], long long planes_of, size_t csize, int ma
 hipError_t launch_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
                               bool energy, const double* gscale, double hscale, bool backward) {
   if (p.inst[b.inst].reg) return launch_reg_apply_batch(p, b, psi, occ, out, gscale, hscale, backward, energy);
-  return p.prec == FOCK_C64  // its energies: energy_lds.hip
-             ? line_apply_t<float>(p, b, psi, occ, out, gscale, hscale, backward, false)
+  return p.prec == FOCK_C64
+             ? line_apply_t<float>(p, b, psi, occ, out, gscale, hscale, backward, energy)
              : line_apply_t<double>(p, b, psi, occ, out, gscale, hscale, backward, energy);
 }
 
 hipError_t launch_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ) {
   if (p.inst[b.inst].reg) return launch_reg_energy_batch(p, b, psi, occ);
   return p.prec == FOCK_C64 ? launch_lds_energy_batch(p, b, psi, occ)
-                            : line_energy_t<double>(p, b, psi, occ);
+                            : line_energy(p, b, psi, occ);
 }
 
 hipError_t launch_line_dft3(const Plan& p, int inst, int sign, int count, void* data, long long stride) {

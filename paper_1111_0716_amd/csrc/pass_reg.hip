@@ -1160,22 +1160,18 @@ namespace {
 // compiled for the line length N1 and takes the line count L^2 at run time.
 // Each pass is dispatched on its own length.
 
-// lengths compiled with the slab pencil and the line accumulate
-template <typename T, int L>
-constexpr bool slab_len() {
+// the slab pencil and the line accumulate are FP32 only
+template <typename T>
+constexpr bool slab_type() {
   return sizeof(T) == 4;
 }
 
-// the line accumulate over lane pairs: FP64 where line and accumulator take
-// over 160 registers, FP32 at 60 and 64 points.  Measured on the slab path
+// the line accumulate over lane pairs: at 60 and 64 points.  Measured
 // (cubic cells, 2x2x2 k, apply + energy + gradient per step), one lane per
 // line against lane pairs: 48^3 70.7 against 71.1 ms, 50^3 84.5 against
 // 89.9, 54^3 111.9 against 119.0, 60^3 105.0 against 93.7, 64^3 54.9 against
 // 42.8; at 72^3 one lane wins (beta boron)
-template <typename T, int L>
-constexpr bool line_split() {
-  return sizeof(T) == 4 ? (L == 60 || L == 64) : 2 * RegShape<T, L>::LINE_REGS > 160;
-}
+constexpr bool line_split(int L) { return L == 60 || L == 64; }
 
 template <typename T, int L, bool EXPLICIT, typename TI = T>
 void launch_plane(const Plan& p, const Batch& b, const Instance& in, const void* psi, const int2* parts,
@@ -1197,18 +1193,16 @@ void launch_plane(const Plan& p, const Batch& b, const Instance& in, const void*
                        Sh::LDS, p.stream, n1, in.nbands, bs, static_cast<const C*>(psi), o0, nP, tri, parts, pairs, tbuf);
   } else {
     using Sh = RegShape<T, L>;
-    if constexpr (slab_len<T, L>()) {
+    if constexpr (slab_type<T>()) {
       if (in.slab) {  // pair buffer [j1][c2][c3] for the slab pencil
-        constexpr int pf = sizeof(T) == 8 ? 1 : 0;  // as below
-        const int nxb = (n1 + Sh::PL - 1) / Sh::PL;
-        hipLaunchKernelGGL((k_plane_reg<T, L, EXPLICIT, T, true>), pf ? dim3(b.npairs, nxb) : dim3(nxb, b.npairs),
+        hipLaunchKernelGGL((k_plane_reg<T, L, EXPLICIT, T, true>), dim3((n1 + Sh::PL - 1) / Sh::PL, b.npairs),
                            dim3(Sh::NTP), Sh::LDS, p.stream, n1, in.nbands, bs, static_cast<const C*>(psi), o0, nP,
-                           tri, parts, pairs, tbuf, pf);
+                           tri, parts, pairs, tbuf, 0);
         return;
       }
     }
-    // FP64: pairs fastest in the grid (alpha boron FP64 plane pass 180 against
-    // 207 ms per step; FP32 on the slab path loses with it)
+    // FP64 (FOCK_MIXED_INV): pairs fastest in the grid (32^3 4x4x4 k, FP64 plane
+    // pass 180 against 207 ms per step; FP32 loses with it)
     constexpr int pf = sizeof(T) == 8 ? 1 : 0;
     const int nxb = (n1 + Sh::PL - 1) / Sh::PL;
     hipLaunchKernelGGL((k_plane_reg<T, L, EXPLICIT>), pf ? dim3(b.npairs, nxb) : dim3(nxb, b.npairs), dim3(Sh::NTP),
@@ -1222,7 +1216,7 @@ void launch_plane(const Plan& p, const Batch& b, const Instance& in, const void*
 template <typename T, int L>
 int launch_pencil_slab(const Plan& p, const Batch& b, const Instance& in, const int2* parts, const int* qmap,
                        typename cx<T>::t* tbuf, const T* vtab, const double* occ, const double* kw, double* epart) {
-  if constexpr (slab_len<T, L>()) {
+  if constexpr (slab_type<T>()) {
     using Sh = RegShape<T, L>;
     const int nlb = (L + Sh::PL - 1) / Sh::PL;
     if (epart)
@@ -1243,10 +1237,10 @@ template <typename T, int L>
 bool launch_acc_line(const Plan& p, const Batch& b, const Instance& in, const int2* parts,
                      const typename cx<T>::t* tbuf, const void* psi, const double* occ, const double* kw, void* out,
                      const double* gscale, double hscale, bool backward) {
-  if constexpr (slab_len<T, L>()) {
+  if constexpr (slab_type<T>()) {
     using C = typename cx<T>::t;
     const int rows = b.nO + (b.mirror ? b.nP : 0);
-    if constexpr (line_split<T, L>())
+    if constexpr (line_split(L))
       hipLaunchKernelGGL((k_acc_line_split<T, L>), dim3(rows, (L * L + 127) / 128), dim3(256), 0, p.stream,
                          in.nbands, static_cast<long long>(in.band_stride), b.o0, b.nO, b.nP, b.tri, parts, tbuf,
                          static_cast<const C*>(psi), occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale,
@@ -1365,7 +1359,7 @@ void reg_lds_attr(int lim) {
   fs[3] = fs[2];
   for (const void* f : fs)
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) != hipSuccess) (void)hipGetLastError();
-  if constexpr (slab_len<T, L>()) {
+  if constexpr (slab_type<T>()) {
     const void* gs[4] = {reinterpret_cast<const void*>(&k_plane_reg<T, L, false, T, true>),
                          reinterpret_cast<const void*>(&k_plane_reg<T, L, true, T, true>),
                          reinterpret_cast<const void*>(&k_pencil_slab<T, L, false>),
@@ -1645,15 +1639,14 @@ bool reg_slab_supported(fock_precision prec, const int grid[3]) {
   return prec == FOCK_C64;
 }
 
-// measured per step: alpha boron 32^3 FP32 370 against 385 ms, FP64 758
-// against 886 ms; beta boron 72^3 7.20 against 8.04 s; the 64^3 preset FP32
-// 42.8 against 46.5 ms (with the lane-pair line accumulate; one lane per
-// line, a whole SIMD's registers, took 54.9 ms).  Cubic cells with 2x2x2 k
-// (apply + energy + gradient): FP32 36^3 69.9 against 72.5 ms, 40^3 92.9
-// against 100.9, 48^3 70.7 against 72.9, 50^3 84.5 against 100.5, 54^3 111.9
-// against 116.5; FP64 24^3 34.7 against 43.9.  Kept plane-wise: FP32 60^3
-// (93.7 against 87.6 ms); FP32 24^3 stays on the whole-pair kernel (17.1 ms
-// against 19.8 on the slab path).
+// Slab form against plane-wise passes, FP32, per step: 32^3 4x4x4 k 370 against
+// 385 ms; 72^3 7.20 against 8.04 s; 64^3 42.8 against 46.5 ms (with the
+// lane-pair line accumulate; one lane per line, a whole SIMD's registers, took
+// 54.9 ms).  Cubic cells with 2x2x2 k (apply + energy + gradient): 36^3 69.9
+// against 72.5 ms, 40^3 92.9 against 100.9, 48^3 70.7 against 72.9, 50^3 84.5
+// against 100.5, 54^3 111.9 against 116.5.  Kept plane-wise: 60^3 (93.7 against
+// 87.6 ms); 24^3 stays on the whole-pair kernel (17.1 ms against 19.8 on the
+// slab path).
 bool reg_slab_default(fock_precision prec, const int grid[3]) {
   const int n = grid[0];
   if (!reg_slab_supported(prec, grid)) return false;

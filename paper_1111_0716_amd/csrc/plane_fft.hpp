@@ -120,11 +120,10 @@ __device__ __forceinline__ C twid(C w) { return S < 0 ? w : cconj(w); }
 // (plan.cpp), at twiddle_offset(n) of the plan's table.
 constexpr int twiddle_count(int n) { return (radix_a(n) - 1) * (n / radix_a(n)); }
 
-// axis 2, pass a (or the only pass), from the planes in memory (in their own
-// precision): consecutive lanes take consecutive elements, so every load is
+// axis 2, pass a (or the only pass), from the planes in memory: consecutive lanes take consecutive elements, so every load is
 // coalesced
-template <int N, int S, typename C, typename CI>
-__device__ __forceinline__ void ax2_load(C* s, const CI* src, int n3, int pitch, int gc,
+template <int N, int S, typename C>
+__device__ __forceinline__ void ax2_load(C* s, const C* src, int n3, int pitch, int gc,
                                          const C* __restrict__ tw) {
   constexpr int A = radix_a(N), R = A > 1 ? A : N, M = N / R;
   const int mn = M * n3, total = gc * mn;
@@ -132,10 +131,10 @@ __device__ __forceinline__ void ax2_load(C* s, const CI* src, int n3, int pitch,
   for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
     const int gg = gc > 1 ? fdiv(idx, rmn) : 0, rem = idx - __mul24(gg, mn);
     const int m = M > 1 ? fdiv(rem, r3) : 0, j3 = rem - __mul24(m, n3);
-    const unsigned o = static_cast<unsigned>(__mul24(gg, N * n3) + rem) * sizeof(CI);
+    const unsigned o = static_cast<unsigned>(__mul24(gg, N * n3) + rem) * sizeof(C);
     C v[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = cvt<C>(stream_load(lane_at(src + r * mn, o)));
+    for (int r = 0; r < R; ++r) v[r] = stream_load(lane_at(src + r * mn, o));
     Dft<R, S, C>::run(v);
     if constexpr (M > 1) {
 #pragma unroll
@@ -148,8 +147,8 @@ __device__ __forceinline__ void ax2_load(C* s, const CI* src, int n3, int pitch,
 }
 
 // axis 2, inverse pass a, to the planes in memory
-template <int N, int S, typename C, typename CO>
-__device__ __forceinline__ void ax2_store(const C* s, CO* dst, int n3, int pitch, int gc, const C* tw) {
+template <int N, int S, typename C>
+__device__ __forceinline__ void ax2_store(const C* s, C* dst, int n3, int pitch, int gc, const C* tw) {
   constexpr int A = radix_a(N), R = A > 1 ? A : N, M = N / R;
   const int mn = M * n3, total = gc * mn;
   const float rmn = rcp_of(mn), r3 = rcp_of(n3);
@@ -165,9 +164,9 @@ __device__ __forceinline__ void ax2_store(const C* s, CO* dst, int n3, int pitch
       for (int r = 1; r < R; ++r) v[r] = cmul(v[r], twid<S>(tw[(r - 1) * M + m]));
     }
     Dft<R, S, C>::run(v);
-    const unsigned o = static_cast<unsigned>(__mul24(gg, N * n3) + rem) * sizeof(CO);
+    const unsigned o = static_cast<unsigned>(__mul24(gg, N * n3) + rem) * sizeof(C);
 #pragma unroll
-    for (int r = 0; r < R; ++r) stream_store(lane_at(dst + r * mn, o), cvt<CO>(v[r]));
+    for (int r = 0; r < R; ++r) stream_store(lane_at(dst + r * mn, o), v[r]);
   }
 }
 
