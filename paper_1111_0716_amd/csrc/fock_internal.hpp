@@ -7,6 +7,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/fock.h"
@@ -204,6 +205,39 @@ struct Plan {
   }
   ~Plan();
 };
+
+// Whether a batch marks its pair-buffer accesses non-temporal (STREAM,
+// pass_common.hpp).  Plain / marked, us a call (apply unless said):
+//   A buffer above the 256 MB last-level cache: marked.  64^3 FP32, 16 bands (285
+//   MB) 364 / 350; 24x24x60 FP64, 2x2x1 k, 8 bands (292 MB) 312 / 301; 64^3 FP64,
+//   16 bands (570 MB) 797 / 672.
+//   One that the cache holds is read by the next pass from there, which marked
+//   accesses forgo: plain.  36^3 FP32, 16 bands (51 MB) 98 / 128; 30^3 FP64, 30
+//   bands (201 MB) 189 / 245; 48^3 FP32, 24 bands (265 MB) 306 / 334.
+//   Line path, within the L2s (32 MB): their dirty lines go to memory at the end
+//   of a pass, and a marked store is there already.  64^3 FP64, 2 bands (13 MB)
+//   44 / 35; 72x4x4 FP64, 2 k, 20 bands (15 MB) 212 / 161; 48^3 FP64, 4 bands (18
+//   MB) 38.6 / 35.5.
+//   The energies of the register-line passes write the buffer and read it once:
+//   marked where rows are whole 64-byte pieces.  24x72x72 FP32, 8 bands (36 MB)
+//   40.4 / 35.6; 36^3 FP32, 16 bands (51 MB) 37 / 45.
+constexpr size_t kL2Bytes = size_t{32} << 20, kLastLevelBytes = size_t{256} << 20;
+inline bool pair_streams(const Plan& p, const Batch& b) {
+  const Instance& in = p.inst[b.inst];
+  const bool both = p.prec == FOCK_MIXED || p.prec == FOCK_MIXED_INV;  // an FP32 and an FP64 buffer
+  const size_t bytes = static_cast<size_t>(b.npairs) * static_cast<size_t>(in.npts) * (both ? 24 : p.csize);
+  if (bytes > kLastLevelBytes) return true;
+  if (!in.reg) return bytes <= kL2Bytes;
+  return b.nO == 0 && in.grid[1] % 8 == 0;  // nO == 0: an energy batch
+}
+// f(stream), stream a constant: the kernel's STREAM
+template <typename F>
+void by_stream(const Plan& p, const Batch& b, F f) {
+  if (pair_streams(p, b))
+    f(std::integral_constant<bool, true>{});
+  else
+    f(std::integral_constant<bool, false>{});
+}
 
 // status helpers (thread-local last error)
 fock_status set_error(fock_status s, const std::string& msg);

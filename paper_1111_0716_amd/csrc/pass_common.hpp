@@ -82,25 +82,31 @@ __device__ __forceinline__ C* lane_at(C* u, unsigned o) {
   return reinterpret_cast<C*>(reinterpret_cast<Byte*>(u) + o);
 }
 
-// The pair buffer goes through memory once per pass and fits no cache: its
-// accesses are marked non-temporal, so that they do not push the orbitals and
-// tables out of L2 (the accumulate's reads included, although a pair is read
-// once for each of its orders: the two reads are far apart).  Without and with,
-// per call: 32^3 4x4x4 k FP32 step 367.5 -> 336.6 ms, 32^3 2x2x2 k FP64 12.40
+// STREAM: a pair buffer larger than the caches goes through memory once per pass,
+// and its accesses are marked non-temporal, so that they do not push the
+// orbitals and tables out of L2 (the accumulate's reads included, although a
+// pair is read once for each of its orders: the two reads are far apart).  A
+// buffer that the caches hold is read by the next pass from there, and marked
+// accesses lose that (by_stream has the line).  Without and with, per call: 32^3 4x4x4 k FP32 step 367.5 -> 336.6 ms, 32^3 2x2x2 k FP64 12.40
 // -> 11.48, 64^3 Gamma FP32 17.85 -> 17.05, 24x24x60 FP32 4.02 -> 3.70, 60^3
 // Gamma FP64 1.76 -> 1.50; 72^3 FP32 77.0 -> 76.5.  Stores alone: 344.9, 11.89,
 // 17.32, 3.82, 1.69; all but the accumulate's reads: 340.9, 11.71, 17.47, 3.76,
 // 1.66, and 0.62 against 0.65 ms at 36x40x45 FP64, whose 0.5 GB buffer lies
 // partly in the last-level cache.
-template <typename C>
+template <bool STREAM, typename C>
 __device__ __forceinline__ C stream_load(const C* p) {
   typedef decltype(C{}.x) V2 __attribute__((ext_vector_type(2)));
+  if constexpr (!STREAM) return *p;
   const V2 v = __builtin_nontemporal_load(reinterpret_cast<const V2*>(p));
   return C{v.x, v.y};
 }
-template <typename C>
+template <bool STREAM, typename C>
 __device__ __forceinline__ void stream_store(C* p, C a) {
   typedef decltype(C{}.x) V2 __attribute__((ext_vector_type(2)));
+  if constexpr (!STREAM) {
+    *p = a;
+    return;
+  }
   V2 v;
   v.x = a.x;
   v.y = a.y;
@@ -127,23 +133,20 @@ __device__ __forceinline__ R from_vec(V v) {
   else
     return R{v.x, v.y};
 }
-template <typename C>
+template <bool STREAM = false, typename C>
 __device__ __forceinline__ C lane_load(const C* u, unsigned o) {
-  return from_vec<C>(*lane_ptr<typename lane_vec<C>::type>(u, o));
+  const auto* p = lane_ptr<typename lane_vec<C>::type>(u, o);
+  if constexpr (STREAM) return from_vec<C>(__builtin_nontemporal_load(p));
+  return from_vec<C>(*p);
 }
-template <typename C>
-__device__ __forceinline__ C lane_load_nt(const C* u, unsigned o) {
-  return from_vec<C>(__builtin_nontemporal_load(lane_ptr<typename lane_vec<C>::type>(u, o)));
-}
-template <typename C>
+template <bool STREAM = false, typename C>
 __device__ __forceinline__ void lane_store(C* u, unsigned o, C a) {
   typename lane_vec<C>::type v = {a.x, a.y};
-  *lane_ptr<typename lane_vec<C>::type>(u, o) = v;
-}
-template <typename C>
-__device__ __forceinline__ void lane_store_nt(C* u, unsigned o, C a) {
-  typename lane_vec<C>::type v = {a.x, a.y};
-  __builtin_nontemporal_store(v, lane_ptr<typename lane_vec<C>::type>(u, o));
+  auto* p = lane_ptr<typename lane_vec<C>::type>(u, o);
+  if constexpr (STREAM)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
 }
 
 // v, through an empty asm the compiler cannot see through: addresses built

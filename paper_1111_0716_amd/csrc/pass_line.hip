@@ -117,7 +117,7 @@ __device__ __forceinline__ void load_codensity_u(C* x, const C* __restrict__ a, 
 // batch's 128 partners (32^3: 16 KB each) then stay in an XCD's 4 MB while it
 // walks the pairs; four waves' slices (8 MB) come from further away.  32^3
 // 4x4x4 k FP32, 3.9 GB a batch: 1060 us at four waves, 730 at one (5.3 TB/s).
-template <typename T, int L>
+template <typename T, int L, bool STREAM>
 __global__ __launch_bounds__(64, (LineShape<T, L>::WPE_FWD)) void k_line_fwd(
     int plane, int npairs, unsigned total, int nbands, long long bs, const typename cx<T>::t* __restrict__ psi, int o0,
     int nP, int tri, const int2* __restrict__ parts, const PairRef* __restrict__ pairs,
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(64, (LineShape<T, L>::WPE_FWD)) void k_line_fwd(
   C* base = tbuf + static_cast<size_t>(pi) * plane * L;
   const unsigned so = opaque((static_cast<unsigned>(h) * LN * plane + l) * sizeof(C));
 #pragma unroll
-  for (int k = 0; k < LN; ++k) lane_store_nt(base + static_cast<size_t>(k) * plane, so, x[k]);
+  for (int k = 0; k < LN; ++k) lane_store<STREAM>(base + static_cast<size_t>(k) * plane, so, x[k]);
 }
 
 // ---------------------------------------------------------------------------
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(64, (LineShape<T, L>::WPE_FWD)) void k_line_fwd(
 // inverse transforms (an energy batch has no way back).
 // What the pass has to do is one read and one write of the tile; the rest are
 // six LDS round trips of the values.
-template <typename T, bool EN, bool BACK>
+template <typename T, bool EN, bool BACK, bool STREAM>
 __global__ __launch_bounds__(512, 4) void k_plane_pair(PlaneGeo g, int nbands, int nk, int o0, int nP, int tri,
                                                         const int2* __restrict__ parts, const int* __restrict__ qmap,
                                                         const PairRef* __restrict__ pairs,
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(512, 4) void k_plane_pair(PlaneGeo g, int nbands, i
   switch (g.n2) {
 #define CASE(N)                                              \
   case N:                                                    \
-    ax2_load<N, -1>(s, tbuf + at, g.n3, g.pitch, gc, tw2);    \
+    ax2_load<N, -1, STREAM>(s, tbuf + at, g.n3, g.pitch, gc, tw2); \
     __syncthreads();                                         \
     if constexpr (radix_a(N) > 1) {                          \
       ax2_b<N, -1, C>(s, g.n3, g.pitch, gc);                 \
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(512, 4) void k_plane_pair(PlaneGeo g, int nbands, i
       ax2_b<N, +1, C>(s, g.n3, g.pitch, gc);                 \
       __syncthreads();                                       \
     }                                                        \
-    ax2_store<N, +1>(s, tbuf + at, g.n3, g.pitch, gc, t2);   \
+    ax2_store<N, +1, STREAM>(s, tbuf + at, g.n3, g.pitch, gc, t2); \
     break;
       FOCK_SMOOTH_L(CASE)
 #undef CASE
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(512, 4) void k_plane_pair(PlaneGeo g, int nbands, i
 // one wave is what the pass takes (two memory latencies each).
 // Once they do, loading a partner's orbital together with its pair gains no
 // more (the batch of twelve cells 834 -> 822 us, 12x10x9 53.0 -> 54.6).
-template <typename T, int L, bool SPLIT>
+template <typename T, int L, bool SPLIT, bool STREAM>
 __global__ __launch_bounds__((AccShape<T, L, SPLIT>::WAVES * 64), (AccShape<T, L, SPLIT>::WPE)) void k_line_acc(
     int plane, int rows, unsigned total, int nbands, long long bs, int o0, int nO, int nP, int tri,
     const int2* __restrict__ parts, const typename cx<T>::t* __restrict__ tbuf,
@@ -310,7 +310,7 @@ __global__ __launch_bounds__((AccShape<T, L, SPLIT>::WAVES * 64), (AccShape<T, L
     const unsigned ot = opaque(lt), ou = opaque(lu);
     C x[LN];
 #pragma unroll
-    for (int k = 0; k < LN; ++k) x[k] = lane_load_nt(src + static_cast<size_t>(k) * plane, ot);
+    for (int k = 0; k < LN; ++k) x[k] = lane_load<STREAM>(src + static_cast<size_t>(k) * plane, ot);
     if constexpr (SPLIT)
       split_fft_inv<C, L>(x, h);
     else
@@ -422,7 +422,7 @@ __global__ __launch_bounds__(512, 4) void k_dft_plane(PlaneGeo g, typename cx<T>
   switch (g.n2) {
 #define CASE(N)                                              \
   case N:                                                    \
-    ax2_load<N, S>(s, t, g.n3, g.pitch, gc, tw2);            \
+    ax2_load<N, S, true>(s, t, g.n3, g.pitch, gc, tw2);      \
     if constexpr (radix_a(N) > 1) {                          \
       __syncthreads();                                       \
       ax2_b<N, S, C>(s, g.n3, g.pitch, gc);                  \
@@ -469,9 +469,11 @@ void line_fwd_L(const Plan& p, const Batch& b, const Instance& in, const void* p
   const int plane = in.grid[1] * in.grid[2];
   const int lanes = plane * (LineShape<T, L>::SPLIT_FWD ? 2 : 1);
   const unsigned total = static_cast<unsigned>((lanes + 63) / 64) * b.npairs;
-  hipLaunchKernelGGL((k_line_fwd<T, L>), dim3(xcd_grid(total)), dim3(64), 0, p.stream, plane, b.npairs, total,
-                     in.nbands, static_cast<long long>(in.band_stride), static_cast<const typename cx<T>::t*>(psi),
-                     b.o0, b.nP, b.tri, parts, pairs, tbuf);
+  by_stream(p, b, [&](auto stream) {
+    hipLaunchKernelGGL((k_line_fwd<T, L, stream()>), dim3(xcd_grid(total)), dim3(64), 0, p.stream, plane, b.npairs,
+                       total, in.nbands, static_cast<long long>(in.band_stride),
+                       static_cast<const typename cx<T>::t*>(psi), b.o0, b.nP, b.tri, parts, pairs, tbuf);
+  });
 }
 
 template <typename T, int L, bool SPLIT>
@@ -493,10 +495,12 @@ void line_acc_launch(const Plan& p, const Batch& b, const Instance& in, const in
   int nw = 1;
   while (nw < Sh::WAVES && total * static_cast<unsigned>(nw + 1) <= 4096u && 2 * (nw + 1) <= nsrc) ++nw;
   const size_t lds = static_cast<size_t>(nw - 1) * Sh::BYTES;
-  hipLaunchKernelGGL((k_line_acc<T, L, SPLIT>), dim3(xcd_grid(total)), dim3(64 * nw), lds, p.stream, plane, rows,
-                     total, in.nbands, static_cast<long long>(in.band_stride), b.o0, b.nO, b.nP, b.tri, parts, tbuf,
-                     static_cast<const C*>(psi), occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale,
-                     hscale, backward ? 1 : 0);
+  by_stream(p, b, [&](auto stream) {
+    hipLaunchKernelGGL((k_line_acc<T, L, SPLIT, stream()>), dim3(xcd_grid(total)), dim3(64 * nw), lds, p.stream, plane,
+                       rows, total, in.nbands, static_cast<long long>(in.band_stride), b.o0, b.nO, b.nP, b.tri, parts,
+                       tbuf, static_cast<const C*>(psi), occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale,
+                       hscale, backward ? 1 : 0);
+  });
 }
 
 template <typename T, int L>
@@ -554,14 +558,16 @@ hipError_t line_apply_t(const Plan& p, const Batch& b, const void* psi, const do
   p.prof.begin(FOCK_K_PENCIL, p.stream);
   if constexpr (sizeof(T) == 4) energy = false;  // energy_lds.hip
   constexpr bool EN = sizeof(T) == 8;
-  if (energy)
-    hipLaunchKernelGGL((k_plane_pair<T, EN, true>), grid, dim3(in.pg_threads), plane_lds(g, sizeof(C)),
-                       p.stream, g, in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap,
-                       static_cast<const PairRef*>(nullptr), tbuf, vtab, tw2, tw3, occ, kw, epart);
-  else
-    hipLaunchKernelGGL((k_plane_pair<T, false, true>), grid, dim3(in.pg_threads), plane_lds(g, sizeof(C)),
-                       p.stream, g, in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap,
-                       static_cast<const PairRef*>(nullptr), tbuf, vtab, tw2, tw3, occ, kw, epart);
+  by_stream(p, b, [&](auto stream) {
+    if (energy)
+      hipLaunchKernelGGL((k_plane_pair<T, EN, true, stream()>), grid, dim3(in.pg_threads), plane_lds(g, sizeof(C)),
+                         p.stream, g, in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap,
+                         static_cast<const PairRef*>(nullptr), tbuf, vtab, tw2, tw3, occ, kw, epart);
+    else
+      hipLaunchKernelGGL((k_plane_pair<T, false, true, stream()>), grid, dim3(in.pg_threads), plane_lds(g, sizeof(C)),
+                         p.stream, g, in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap,
+                         static_cast<const PairRef*>(nullptr), tbuf, vtab, tw2, tw3, occ, kw, epart);
+  });
   p.prof.end(FOCK_K_PENCIL, p.stream);
   if (energy) {
     e = launch_sum_slot(p, static_cast<long long>(b.npairs) * tiles, b.eslot, b.mirror ? 2.0 : 1.0);
@@ -593,12 +599,15 @@ hipError_t line_energy(const Plan& p, const Batch& b, const void* psi, const dou
   if (e != hipSuccess) return e;
   const int tiles = plane_tiles(g);
   p.prof.begin(FOCK_K_ENERGY_PENCIL, p.stream);
-  hipLaunchKernelGGL((k_plane_pair<T, true, false>), dim3(b.npairs, tiles), dim3(in.pg_threads),
-                     plane_lds(g, sizeof(C)), p.stream, g, in.nbands, in.nk, 0, 1, 0,
-                     static_cast<const int2*>(nullptr), static_cast<const int*>(nullptr), pairs, tbuf,
-                     reinterpret_cast<const T*>(p.ws + in.vtab_off),
-                     tw + twiddle_offset(g.n2), tw + twiddle_offset(g.n3), occ,
-                     reinterpret_cast<const double*>(p.ws + in.kw_off), reinterpret_cast<double*>(p.ws + p.epart_off));
+  by_stream(p, b, [&](auto stream) {
+    hipLaunchKernelGGL((k_plane_pair<T, true, false, stream()>), dim3(b.npairs, tiles), dim3(in.pg_threads),
+                       plane_lds(g, sizeof(C)), p.stream, g, in.nbands, in.nk, 0, 1, 0,
+                       static_cast<const int2*>(nullptr), static_cast<const int*>(nullptr), pairs, tbuf,
+                       reinterpret_cast<const T*>(p.ws + in.vtab_off),
+                       tw + twiddle_offset(g.n2), tw + twiddle_offset(g.n3), occ,
+                       reinterpret_cast<const double*>(p.ws + in.kw_off),
+                       reinterpret_cast<double*>(p.ws + p.epart_off));
+  });
   p.prof.end(FOCK_K_ENERGY_PENCIL, p.stream);
   return launch_sum_slot(p, static_cast<long long>(b.npairs) * tiles, b.slot, 1.0);
 }
@@ -630,9 +639,12 @@ hipError_t line_dft3_t(const Plan& p, const PlaneGeo& g, int threads, int count,
 template <typename T>
 void plane_lds_attr(int lim) {
   constexpr bool EN = sizeof(T) == 8;  // FP32 energies: energy_lds.hip
-  const void* fs[] = {reinterpret_cast<const void*>(&k_plane_pair<T, false, true>),
-                      reinterpret_cast<const void*>(&k_plane_pair<T, EN, true>),
-                      reinterpret_cast<const void*>(&k_plane_pair<T, EN, !EN>),
+  const void* fs[] = {reinterpret_cast<const void*>(&k_plane_pair<T, false, true, false>),
+                      reinterpret_cast<const void*>(&k_plane_pair<T, false, true, true>),
+                      reinterpret_cast<const void*>(&k_plane_pair<T, EN, true, false>),
+                      reinterpret_cast<const void*>(&k_plane_pair<T, EN, true, true>),
+                      reinterpret_cast<const void*>(&k_plane_pair<T, EN, !EN, false>),
+                      reinterpret_cast<const void*>(&k_plane_pair<T, EN, !EN, true>),
                       reinterpret_cast<const void*>(&k_dft_plane<T, -1>),
                       reinterpret_cast<const void*>(&k_dft_plane<T, +1>)};
   for (const void* f : fs)

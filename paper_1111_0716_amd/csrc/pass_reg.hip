@@ -20,6 +20,7 @@
 // the plane count N1 at run time; the pencil pass is compiled for the line
 // length N1 and takes the line count L^2 at run time.
 #include <algorithm>
+#include <initializer_list>
 
 #include "fft_lds.hpp"
 #include "fock_internal.hpp"
@@ -200,7 +201,7 @@ __device__ __forceinline__ void lds_round_trip(C* x, T* sp, int col) {
 // wide operands fit beside the line without spilling)
 // SLAB: the pair buffer leaves as [j1][c2][c3] (one more transpose) for the
 // slab pencil; otherwise as [j1][c3][c2]
-template <typename T, int L, bool EXPLICIT, typename TI = T, bool SLAB = false>
+template <typename T, int L, bool EXPLICIT, typename TI = T, bool SLAB = false, bool STREAM = false>
 __global__ __launch_bounds__((RegShape<T, L>::NTP), (sizeof(TI) == sizeof(T) ? RegShape<T, L>::WPE_PLANE : 1)) void k_plane_reg(
     int n1, int nbands, long long bs, const typename cx<TI>::t* __restrict__ psi, int o0, int nP, int tri,
     const int2* __restrict__ parts, const PairRef* __restrict__ pairs, typename cx<T>::t* __restrict__ tbuf, int pf) {
@@ -252,7 +253,7 @@ __global__ __launch_bounds__((RegShape<T, L>::NTP), (sizeof(TI) == sizeof(T) ? R
     } else {
       C* dst = tbuf + (static_cast<size_t>(pi) * n1 + j1) * LL + col;
 #pragma unroll
-      for (int c3 = 0; c3 < L; ++c3) stream_store(dst + c3 * L, x[c3]);
+      for (int c3 = 0; c3 < L; ++c3) stream_store<STREAM>(dst + c3 * L, x[c3]);
     }
   }
 }
@@ -262,7 +263,7 @@ __global__ __launch_bounds__((RegShape<T, L>::NTP), (sizeof(TI) == sizeof(T) ? R
 // ---------------------------------------------------------------------------
 // EN: the apply also yields the pair energies (the spectrum is at hand after
 // FFT_1): w_o f_o w'_p f'_p sum v/N |P|^2 per line block into epart.
-template <typename T, int L, bool EN>
+template <typename T, int L, bool EN, bool STREAM>
 __device__ __forceinline__ void pencil_apply_line(int l, int LL, int pi, int q, typename cx<T>::t* __restrict__ tbuf,
                                                   const T* __restrict__ vtab, double* es) {
   using C = typename cx<T>::t;
@@ -270,17 +271,17 @@ __device__ __forceinline__ void pencil_apply_line(int l, int LL, int pi, int q, 
   const unsigned lo = static_cast<unsigned>(l) * sizeof(C);
   C x[L];
 #pragma unroll
-  for (int j1 = 0; j1 < L; ++j1) x[j1] = stream_load(lane_at(base + static_cast<size_t>(j1) * LL, lo));
+  for (int j1 = 0; j1 < L; ++j1) x[j1] = stream_load<STREAM>(lane_at(base + static_cast<size_t>(j1) * LL, lo));
   reg_fft<C, L, -1>(x);
   mul_table_line_u<C, T, L, EN>(x, vtab + static_cast<size_t>(q) * LL * L,
                                 opaque(static_cast<unsigned>(l) * sizeof(T)), LL, es);
   reg_fft<C, L, +1>(x);
   const unsigned so = opaque(lo);
 #pragma unroll
-  for (int j1 = 0; j1 < L; ++j1) stream_store(lane_at(base + static_cast<size_t>(j1) * LL, so), x[j1]);
+  for (int j1 = 0; j1 < L; ++j1) stream_store<STREAM>(lane_at(base + static_cast<size_t>(j1) * LL, so), x[j1]);
 }
 
-template <typename T, int L, bool EN = false>
+template <typename T, int L, bool EN = false, bool STREAM = false>
 __global__ __launch_bounds__(256, (RegShape<T, L>::WPE_PENCIL)) void k_pencil_apply_reg(int ll, int nbands, int nk, int o0, int nP,
                                                           int tri, const int2* __restrict__ parts, const int* __restrict__ qmap,
                                                           typename cx<T>::t* __restrict__ tbuf,
@@ -296,10 +297,10 @@ __global__ __launch_bounds__(256, (RegShape<T, L>::WPE_PENCIL)) void k_pencil_ap
   const int q = qmap[ok * nk + r.x];
   if constexpr (!EN) {
     if (l >= LL) return;  // no barrier in this variant
-    pencil_apply_line<T, L, false>(l, LL, pi, q, tbuf, vtab, nullptr);
+    pencil_apply_line<T, L, false, STREAM>(l, LL, pi, q, tbuf, vtab, nullptr);
   } else {
     double e = 0.0;
-    if (l < LL) pencil_apply_line<T, L, true>(l, LL, pi, q, tbuf, vtab, &e);
+    if (l < LL) pencil_apply_line<T, L, true, STREAM>(l, LL, pi, q, tbuf, vtab, &e);
     // an unordered pair of a block with itself stands for both orders
     store_line_energy(e, (tri && o != p ? 2.0 : 1.0) * kw[ok] * occ[o0 + o] * kw[r.x] * occ[r.x * nbands + r.y],
                       epart);
@@ -309,7 +310,7 @@ __global__ __launch_bounds__(256, (RegShape<T, L>::WPE_PENCIL)) void k_pencil_ap
 // ---------------------------------------------------------------------------
 // pencil pass, energy: FFT_1 and sum v_q/N |P|^2 in FP64 per line block
 // ---------------------------------------------------------------------------
-template <typename T, int L, typename TV = T>
+template <typename T, int L, typename TV = T, bool STREAM = false>
 __global__ __launch_bounds__(256, (RegShape<T, L>::WPE_PENCIL)) void k_pencil_energy_reg(int ll, const PairRef* __restrict__ pairs,
                                                            const typename cx<T>::t* __restrict__ tbuf,
                                                            const TV* __restrict__ vtab, double* __restrict__ epart) {
@@ -324,7 +325,7 @@ __global__ __launch_bounds__(256, (RegShape<T, L>::WPE_PENCIL)) void k_pencil_en
     const C* base = tbuf + static_cast<size_t>(pi) * LL * L;
     C x[L];
 #pragma unroll
-    for (int j1 = 0; j1 < L; ++j1) x[j1] = stream_load(lane_at(base + static_cast<size_t>(j1) * LL, static_cast<unsigned>(l) * sizeof(C)));
+    for (int j1 = 0; j1 < L; ++j1) x[j1] = stream_load<STREAM>(lane_at(base + static_cast<size_t>(j1) * LL, static_cast<unsigned>(l) * sizeof(C)));
     reg_fft<C, L, -1>(x);
     const TV* v = vtab + static_cast<size_t>(q) * LL * L;
     const unsigned lv = opaque(static_cast<unsigned>(l) * sizeof(TV));
@@ -369,7 +370,7 @@ __device__ __forceinline__ void prefetch_done(const unsigned (&v)[PER]) {
 // PF: while a partner is transformed, the next partner's pair-buffer rows of
 // the workgroup's planes are pulled into L2 (prefetch_l2), so that their
 // loads wait on L2 rather than on HBM
-template <typename T, int L, typename TI = T, bool PF = false>
+template <typename T, int L, typename TI = T, bool PF = false, bool STREAM = false>
 __global__ __launch_bounds__((RegShape<T, L>::NTP), (RegShape<T, L>::WPE_ACC)) void k_acc_reg(
     int n1, int nbands, long long bs, int o0, int nO, int nP, int tri, const int2* __restrict__ parts,
     const typename cx<T>::t* __restrict__ tbuf, const typename cx<TI>::t* __restrict__ psi,
@@ -407,7 +408,7 @@ __global__ __launch_bounds__((RegShape<T, L>::NTP), (RegShape<T, L>::WPE_ACC)) v
     if (valid) {
       const C* src = tbuf + pair * LL * n1 + static_cast<size_t>(j1) * LL + col;
 #pragma unroll
-      for (int c3 = 0; c3 < L; ++c3) x[c3] = sizeof(TI) == sizeof(T) ? stream_load(src + c3 * L) : src[c3 * L];  // row (j1, c2 = col)
+      for (int c3 = 0; c3 < L; ++c3) x[c3] = stream_load<STREAM>(src + c3 * L);  // row (j1, c2 = col)
     } else {
 #pragma unroll
       for (int c3 = 0; c3 < L; ++c3) x[c3] = C{T(0), T(0)};
@@ -539,7 +540,7 @@ __device__ __forceinline__ void transpose_split(C* y, T* sp, int col, int h) {
   for (int k = 0; k < LH; ++k) y[k].y = sp[col * LP + (EO_IN ? h * LH + k : 2 * k + h)];
 }
 
-template <typename T, int L, bool EXPLICIT>
+template <typename T, int L, bool EXPLICIT, bool STREAM = false>
 __global__ __launch_bounds__((SplitShape<T, L>::NTP), (SplitShape<T, L>::WPE_LINE)) void k_plane_split(
     int n1, int nbands, long long bs, const typename cx<T>::t* __restrict__ psi, int o0, int nP, int tri,
     const int2* __restrict__ parts, const PairRef* __restrict__ pairs, typename cx<T>::t* __restrict__ tbuf) {
@@ -578,11 +579,11 @@ __global__ __launch_bounds__((SplitShape<T, L>::NTP), (SplitShape<T, L>::WPE_LIN
   if (valid) {
     C* dst = tbuf + (static_cast<size_t>(pi) * n1 + j1) * LL + static_cast<size_t>(h) * LH * L + col;
 #pragma unroll
-    for (int k = 0; k < LH; ++k) stream_store(dst + k * L, y[k]);
+    for (int k = 0; k < LH; ++k) stream_store<STREAM>(dst + k * L, y[k]);
   }
 }
 
-template <typename T, int L, bool EN>
+template <typename T, int L, bool EN, bool STREAM>
 __device__ __forceinline__ void pencil_apply_split_line(int l, int h, int LL, int pi, int q,
                                                         typename cx<T>::t* __restrict__ tbuf,
                                                         const T* __restrict__ vtab, double* es) {
@@ -592,17 +593,17 @@ __device__ __forceinline__ void pencil_apply_split_line(int l, int h, int LL, in
   const unsigned lo = (static_cast<unsigned>(h) * LL + l) * sizeof(C);
   C y[LH];
 #pragma unroll
-  for (int m = 0; m < LH; ++m) y[m] = stream_load(lane_at(base + static_cast<size_t>(2 * m) * LL, lo));  // j1 = 2m + h
+  for (int m = 0; m < LH; ++m) y[m] = stream_load<STREAM>(lane_at(base + static_cast<size_t>(2 * m) * LL, lo));  // j1 = 2m + h
   split_fft_fwd<C, L>(y, h);  // y[k] at c1 = h L/2 + k
   mul_table_line_u<C, T, LH, EN>(y, vtab + static_cast<size_t>(q) * LL * L,
                                  opaque((static_cast<unsigned>(h) * LH * LL + l) * sizeof(T)), LL, es);
   split_fft_inv<C, L>(y, h);
   const unsigned so = opaque(lo);
 #pragma unroll
-  for (int m = 0; m < LH; ++m) stream_store(lane_at(base + static_cast<size_t>(2 * m) * LL, so), y[m]);
+  for (int m = 0; m < LH; ++m) stream_store<STREAM>(lane_at(base + static_cast<size_t>(2 * m) * LL, so), y[m]);
 }
 
-template <typename T, int L, bool EN = false>
+template <typename T, int L, bool EN = false, bool STREAM = false>
 __global__ __launch_bounds__(256, (SplitShape<T, L>::WPE_LINE)) void k_pencil_apply_split(
     int ll, int nbands, int nk, int o0, int nP, int tri, const int2* __restrict__ parts, const int* __restrict__ qmap,
     typename cx<T>::t* __restrict__ tbuf, const T* __restrict__ vtab, const double* __restrict__ occ,
@@ -619,10 +620,10 @@ __global__ __launch_bounds__(256, (SplitShape<T, L>::WPE_LINE)) void k_pencil_ap
   const int q = qmap[ok * nk + r.x];
   if constexpr (!EN) {
     if (l >= LL) return;  // uniform over the pair; no barrier in this variant
-    pencil_apply_split_line<T, L, false>(l, h, LL, pi, q, tbuf, vtab, nullptr);
+    pencil_apply_split_line<T, L, false, STREAM>(l, h, LL, pi, q, tbuf, vtab, nullptr);
   } else {
     double e = 0.0;  // each lane: its half of the spectrum
-    if (l < LL) pencil_apply_split_line<T, L, true>(l, h, LL, pi, q, tbuf, vtab, &e);
+    if (l < LL) pencil_apply_split_line<T, L, true, STREAM>(l, h, LL, pi, q, tbuf, vtab, &e);
     store_line_energy(e, (tri && o != p ? 2.0 : 1.0) * kw[ok] * occ[o0 + o] * kw[r.x] * occ[r.x * nbands + r.y],
                       epart);
   }
@@ -637,7 +638,7 @@ __global__ __launch_bounds__(256, (SplitShape<T, L>::WPE_LINE)) void k_pencil_ap
 // leaves as [j1][c2][j3], read by the line accumulate along axis 2.  The
 // table is in grid order [c1][c2][c3].
 // ---------------------------------------------------------------------------
-template <typename T, int L, bool EN>
+template <typename T, int L, bool EN, bool STREAM>
 __global__ __launch_bounds__((RegShape<T, L>::NTP), (RegShape<T, L>::WPE_PLANE)) void k_pencil_slab(
     int nbands, int nk, int o0, int nP, int tri, const int2* __restrict__ parts, const int* __restrict__ qmap,
     typename cx<T>::t* __restrict__ tbuf, const T* __restrict__ vtab, const double* __restrict__ occ,
@@ -662,7 +663,7 @@ __global__ __launch_bounds__((RegShape<T, L>::NTP), (RegShape<T, L>::WPE_PLANE))
   if (valid) {
     const unsigned lo = (static_cast<unsigned>(c2) * L + col) * sizeof(C);
 #pragma unroll
-    for (int j1 = 0; j1 < L; ++j1) x[j1] = stream_load(lane_at(base + static_cast<size_t>(j1) * LL, lo));
+    for (int j1 = 0; j1 < L; ++j1) x[j1] = stream_load<STREAM>(lane_at(base + static_cast<size_t>(j1) * LL, lo));
     reg_fft<C, L, -1>(x);  // axis 1: x[c1] at (c2, c3 = col)
     mul_table_line_u<C, T, L, EN>(x, vtab + static_cast<size_t>(q) * LL * L,
                                   opaque((static_cast<unsigned>(c2) * L + col) * sizeof(T)), LL, &e);
@@ -677,7 +678,7 @@ __global__ __launch_bounds__((RegShape<T, L>::NTP), (RegShape<T, L>::WPE_PLANE))
   if (valid) {
     const unsigned so = opaque((static_cast<unsigned>(c2) * L + col) * sizeof(C));
 #pragma unroll
-    for (int j1 = 0; j1 < L; ++j1) stream_store(lane_at(base + static_cast<size_t>(j1) * LL, so), x[j1]);
+    for (int j1 = 0; j1 < L; ++j1) stream_store<STREAM>(lane_at(base + static_cast<size_t>(j1) * LL, so), x[j1]);
   }
   if constexpr (EN) {
     // block sum in a fixed order (the block's last wave may be partly empty):
@@ -698,7 +699,7 @@ __global__ __launch_bounds__((RegShape<T, L>::NTP), (RegShape<T, L>::WPE_PLANE))
   }
 }
 
-template <typename T, int L, typename TV = T>
+template <typename T, int L, typename TV = T, bool STREAM = false>
 __global__ __launch_bounds__(256, (SplitShape<T, L>::WPE_LINE)) void k_pencil_energy_split(
     int ll, const PairRef* __restrict__ pairs, const typename cx<T>::t* __restrict__ tbuf, const TV* __restrict__ vtab,
     double* __restrict__ epart) {
@@ -717,7 +718,7 @@ __global__ __launch_bounds__(256, (SplitShape<T, L>::WPE_LINE)) void k_pencil_en
     const unsigned lo = (static_cast<unsigned>(h) * LL + l) * sizeof(C);
     C y[LH];
 #pragma unroll
-    for (int m = 0; m < LH; ++m) y[m] = stream_load(lane_at(base + static_cast<size_t>(2 * m) * LL, lo));
+    for (int m = 0; m < LH; ++m) y[m] = stream_load<STREAM>(lane_at(base + static_cast<size_t>(2 * m) * LL, lo));
     split_fft_fwd<C, L>(y, h);
     const TV* v = vtab + static_cast<size_t>(q) * LL * L;
     const unsigned lv = opaque((static_cast<unsigned>(h) * LH * LL + l) * sizeof(TV));
@@ -734,7 +735,7 @@ __global__ __launch_bounds__(256, (SplitShape<T, L>::WPE_LINE)) void k_pencil_en
   if (threadIdx.x == 0) epart[static_cast<size_t>(pi) * gridDim.x + blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-template <typename T, int L, typename TI = T>
+template <typename T, int L, typename TI = T, bool STREAM = false>
 __global__ __launch_bounds__((SplitShape<T, L>::NTP), (SplitShape<T, L>::WPE_ACC)) void k_acc_split(
     int n1, int nbands, long long bs, int o0, int nO, int nP, int tri, const int2* __restrict__ parts,
     const typename cx<T>::t* __restrict__ tbuf, const typename cx<TI>::t* __restrict__ psi,
@@ -773,7 +774,7 @@ __global__ __launch_bounds__((SplitShape<T, L>::NTP), (SplitShape<T, L>::WPE_ACC
     if (valid) {
       const C* src = tbuf + pair * LL * n1 + static_cast<size_t>(j1) * LL + static_cast<size_t>(h) * LH * L + col;
 #pragma unroll
-      for (int k = 0; k < LH; ++k) y[k] = sizeof(TI) == sizeof(T) ? stream_load(src + k * L) : src[k * L];  // row (j1, c2 = col), c3 = h L/2 + k
+      for (int k = 0; k < LH; ++k) y[k] = stream_load<STREAM>(src + k * L);  // row (j1, c2 = col), c3 = h L/2 + k
     } else {
 #pragma unroll
       for (int k = 0; k < LH; ++k) y[k] = C{T(0), T(0)};
@@ -849,7 +850,7 @@ __global__ __launch_bounds__((SplitShape<T, L>::NTP), (SplitShape<T, L>::WPE_ACC
 // the lines need not fill whole planes: every lane of a workgroup works.
 // Rows and partners as in k_acc_reg.
 // ---------------------------------------------------------------------------
-template <typename T, int L>
+template <typename T, int L, bool STREAM>
 __global__ __launch_bounds__(256, (RegShape<T, L>::WPE_ACC)) void k_acc_line(
     int nbands, long long bs, int o0, int nO, int nP, int tri, const int2* __restrict__ parts,
     const typename cx<T>::t* __restrict__ tbuf, const typename cx<T>::t* __restrict__ psi,
@@ -882,7 +883,7 @@ __global__ __launch_bounds__(256, (RegShape<T, L>::WPE_ACC)) void k_acc_line(
     const C* src = tbuf + pair * LL * L + eoff;
     C x[L];
 #pragma unroll
-    for (int c2 = 0; c2 < L; ++c2) x[c2] = stream_load(src + c2 * L);
+    for (int c2 = 0; c2 < L; ++c2) x[c2] = stream_load<STREAM>(src + c2 * L);
     reg_fft<C, L, +1>(x);  // inverse axis 2: x[j2] at (j1, j3)
     if (cj) {
 #pragma unroll
@@ -929,7 +930,7 @@ __global__ __launch_bounds__(256, (RegShape<T, L>::WPE_ACC)) void k_acc_line(
 // the line accumulate over lane pairs, where one lane per line would need a
 // whole SIMD's registers: lane h of a pair loads c2 = h L/2 + k of the line
 // (j1, j3) and holds j2 = 2m + h after the transform (see split_fft.hpp)
-template <typename T, int L>
+template <typename T, int L, bool STREAM>
 __global__ __launch_bounds__(256, (SplitShape<T, L>::WPE_ACC)) void k_acc_line_split(
     int nbands, long long bs, int o0, int nO, int nP, int tri, const int2* __restrict__ parts,
     const typename cx<T>::t* __restrict__ tbuf, const typename cx<T>::t* __restrict__ psi,
@@ -961,7 +962,7 @@ __global__ __launch_bounds__(256, (SplitShape<T, L>::WPE_ACC)) void k_acc_line_s
     const C* src = tbuf + pair * LL * L + eoff + static_cast<size_t>(h) * LH * L;
     C y[LH];
 #pragma unroll
-    for (int k = 0; k < LH; ++k) y[k] = stream_load(src + k * L);  // c2 = h L/2 + k
+    for (int k = 0; k < LH; ++k) y[k] = stream_load<STREAM>(src + k * L);  // c2 = h L/2 + k
     split_fft_inv<C, L>(y, h);                       // y[m] at j2 = 2m + h
     if (cj) {
 #pragma unroll
@@ -1189,15 +1190,20 @@ void launch_plane(const Plan& p, const Batch& b, const Instance& in, const void*
                        0);
   } else if constexpr (Po::SPLIT_PLANE) {
     using Sh = SplitShape<T, L>;
-    hipLaunchKernelGGL((k_plane_split<T, L, EXPLICIT>), dim3((n1 + Sh::PL - 1) / Sh::PL, b.npairs), dim3(Sh::NTP),
-                       Sh::LDS, p.stream, n1, in.nbands, bs, static_cast<const C*>(psi), o0, nP, tri, parts, pairs, tbuf);
+    by_stream(p, b, [&](auto stream) {
+      hipLaunchKernelGGL((k_plane_split<T, L, EXPLICIT, stream()>), dim3((n1 + Sh::PL - 1) / Sh::PL, b.npairs),
+                         dim3(Sh::NTP), Sh::LDS, p.stream, n1, in.nbands, bs, static_cast<const C*>(psi), o0, nP, tri,
+                         parts, pairs, tbuf);
+    });
   } else {
     using Sh = RegShape<T, L>;
     if constexpr (slab_type<T>()) {
       if (in.slab) {  // pair buffer [j1][c2][c3] for the slab pencil
-        hipLaunchKernelGGL((k_plane_reg<T, L, EXPLICIT, T, true>), dim3((n1 + Sh::PL - 1) / Sh::PL, b.npairs),
-                           dim3(Sh::NTP), Sh::LDS, p.stream, n1, in.nbands, bs, static_cast<const C*>(psi), o0, nP,
-                           tri, parts, pairs, tbuf, 0);
+        by_stream(p, b, [&](auto stream) {
+          hipLaunchKernelGGL((k_plane_reg<T, L, EXPLICIT, T, true, stream()>), dim3((n1 + Sh::PL - 1) / Sh::PL, b.npairs),
+                             dim3(Sh::NTP), Sh::LDS, p.stream, n1, in.nbands, bs, static_cast<const C*>(psi), o0, nP,
+                             tri, parts, pairs, tbuf, 0);
+        });
         return;
       }
     }
@@ -1205,9 +1211,11 @@ void launch_plane(const Plan& p, const Batch& b, const Instance& in, const void*
     // pass 180 against 207 ms per step; FP32 loses with it)
     constexpr int pf = sizeof(T) == 8 ? 1 : 0;
     const int nxb = (n1 + Sh::PL - 1) / Sh::PL;
-    hipLaunchKernelGGL((k_plane_reg<T, L, EXPLICIT>), pf ? dim3(b.npairs, nxb) : dim3(nxb, b.npairs), dim3(Sh::NTP),
-                       Sh::LDS, p.stream, n1, in.nbands, bs, static_cast<const C*>(psi), o0, nP, tri, parts, pairs, tbuf,
-                       pf);
+    by_stream(p, b, [&](auto stream) {
+      hipLaunchKernelGGL((k_plane_reg<T, L, EXPLICIT, T, false, stream()>), pf ? dim3(b.npairs, nxb) : dim3(nxb, b.npairs),
+                         dim3(Sh::NTP), Sh::LDS, p.stream, n1, in.nbands, bs, static_cast<const C*>(psi), o0, nP, tri,
+                         parts, pairs, tbuf, pf);
+    });
   }
 }
 
@@ -1219,12 +1227,14 @@ int launch_pencil_slab(const Plan& p, const Batch& b, const Instance& in, const 
   if constexpr (slab_type<T>()) {
     using Sh = RegShape<T, L>;
     const int nlb = (L + Sh::PL - 1) / Sh::PL;
-    if (epart)
-      hipLaunchKernelGGL((k_pencil_slab<T, L, true>), dim3(nlb, b.npairs), dim3(Sh::NTP), Sh::LDS, p.stream,
-                         in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, tbuf, vtab, occ, kw, epart);
-    else
-      hipLaunchKernelGGL((k_pencil_slab<T, L, false>), dim3(nlb, b.npairs), dim3(Sh::NTP), Sh::LDS, p.stream,
-                         in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, tbuf, vtab, occ, kw, epart);
+    by_stream(p, b, [&](auto stream) {
+      if (epart)
+        hipLaunchKernelGGL((k_pencil_slab<T, L, true, stream()>), dim3(nlb, b.npairs), dim3(Sh::NTP), Sh::LDS, p.stream,
+                           in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, tbuf, vtab, occ, kw, epart);
+      else
+        hipLaunchKernelGGL((k_pencil_slab<T, L, false, stream()>), dim3(nlb, b.npairs), dim3(Sh::NTP), Sh::LDS, p.stream,
+                           in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, tbuf, vtab, occ, kw, epart);
+    });
     return nlb;
   } else {
     return 0;
@@ -1240,16 +1250,18 @@ bool launch_acc_line(const Plan& p, const Batch& b, const Instance& in, const in
   if constexpr (slab_type<T>()) {
     using C = typename cx<T>::t;
     const int rows = b.nO + (b.mirror ? b.nP : 0);
-    if constexpr (line_split(L))
-      hipLaunchKernelGGL((k_acc_line_split<T, L>), dim3(rows, (L * L + 127) / 128), dim3(256), 0, p.stream,
-                         in.nbands, static_cast<long long>(in.band_stride), b.o0, b.nO, b.nP, b.tri, parts, tbuf,
-                         static_cast<const C*>(psi), occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale,
-                         hscale, backward ? 1 : 0);
-    else
-      hipLaunchKernelGGL((k_acc_line<T, L>), dim3(rows, (L * L + 255) / 256), dim3(256), 0, p.stream, in.nbands,
-                         static_cast<long long>(in.band_stride), b.o0, b.nO, b.nP, b.tri, parts, tbuf,
-                         static_cast<const C*>(psi), occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale,
-                         hscale, backward ? 1 : 0);
+    by_stream(p, b, [&](auto stream) {
+      if constexpr (line_split(L))
+        hipLaunchKernelGGL((k_acc_line_split<T, L, stream()>), dim3(rows, (L * L + 127) / 128), dim3(256), 0, p.stream,
+                           in.nbands, static_cast<long long>(in.band_stride), b.o0, b.nO, b.nP, b.tri, parts, tbuf,
+                           static_cast<const C*>(psi), occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale,
+                           hscale, backward ? 1 : 0);
+      else
+        hipLaunchKernelGGL((k_acc_line<T, L, stream()>), dim3(rows, (L * L + 255) / 256), dim3(256), 0, p.stream,
+                           in.nbands, static_cast<long long>(in.band_stride), b.o0, b.nO, b.nP, b.tri, parts, tbuf,
+                           static_cast<const C*>(psi), occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale,
+                           hscale, backward ? 1 : 0);
+    });
     return true;
   } else {
     return false;
@@ -1264,21 +1276,25 @@ int launch_pencil_apply(const Plan& p, const Batch& b, const Instance& in, const
   const int ll = in.grid[1] * in.grid[2];
   if constexpr (RegPolicy<T, L>::SPLIT_PENCIL) {
     const int nlb = (ll + SplitShape<T, L>::LPB - 1) / SplitShape<T, L>::LPB;
-    if (epart)
-      hipLaunchKernelGGL((k_pencil_apply_split<T, L, true>), dim3(nlb, b.npairs), dim3(256), 0, p.stream, ll,
-                         in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, tbuf, vtab, occ, kw, epart);
-    else
-      hipLaunchKernelGGL((k_pencil_apply_split<T, L, false>), dim3(nlb, b.npairs), dim3(256), 0, p.stream, ll,
-                         in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, tbuf, vtab, occ, kw, epart);
+    by_stream(p, b, [&](auto stream) {
+      if (epart)
+        hipLaunchKernelGGL((k_pencil_apply_split<T, L, true, stream()>), dim3(nlb, b.npairs), dim3(256), 0, p.stream, ll,
+                           in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, tbuf, vtab, occ, kw, epart);
+      else
+        hipLaunchKernelGGL((k_pencil_apply_split<T, L, false, stream()>), dim3(nlb, b.npairs), dim3(256), 0, p.stream, ll,
+                           in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, tbuf, vtab, occ, kw, epart);
+    });
     return nlb;
   } else {
     const int nlb = (ll + 255) / 256;
-    if (epart)
-      hipLaunchKernelGGL((k_pencil_apply_reg<T, L, true>), dim3(nlb, b.npairs), dim3(256), 0, p.stream, ll,
-                         in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, tbuf, vtab, occ, kw, epart);
-    else
-      hipLaunchKernelGGL((k_pencil_apply_reg<T, L, false>), dim3(nlb, b.npairs), dim3(256), 0, p.stream, ll,
-                         in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, tbuf, vtab, occ, kw, epart);
+    by_stream(p, b, [&](auto stream) {
+      if (epart)
+        hipLaunchKernelGGL((k_pencil_apply_reg<T, L, true, stream()>), dim3(nlb, b.npairs), dim3(256), 0, p.stream, ll,
+                           in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, tbuf, vtab, occ, kw, epart);
+      else
+        hipLaunchKernelGGL((k_pencil_apply_reg<T, L, false, stream()>), dim3(nlb, b.npairs), dim3(256), 0, p.stream, ll,
+                           in.nbands, in.nk, b.o0, b.nP, b.tri, parts, qmap, tbuf, vtab, occ, kw, epart);
+    });
     return nlb;
   }
 }
@@ -1290,13 +1306,17 @@ int launch_pencil_energy(const Plan& p, const Batch& b, const Instance& in, cons
   const int ll = in.grid[1] * in.grid[2];
   if constexpr (RegPolicy<T, L>::SPLIT_PENCIL) {
     const int nlb = (ll + SplitShape<T, L>::LPB - 1) / SplitShape<T, L>::LPB;
-    hipLaunchKernelGGL((k_pencil_energy_split<T, L, TV>), dim3(nlb, b.npairs), dim3(256), 0, p.stream, ll, pairs,
-                       tbuf, vtab, epart);
+    by_stream(p, b, [&](auto stream) {
+      hipLaunchKernelGGL((k_pencil_energy_split<T, L, TV, stream()>), dim3(nlb, b.npairs), dim3(256), 0, p.stream, ll,
+                         pairs, tbuf, vtab, epart);
+    });
     return nlb;
   } else {
     const int nlb = (ll + 255) / 256;
-    hipLaunchKernelGGL((k_pencil_energy_reg<T, L, TV>), dim3(nlb, b.npairs), dim3(256), 0, p.stream, ll, pairs, tbuf,
-                       vtab, epart);
+    by_stream(p, b, [&](auto stream) {
+      hipLaunchKernelGGL((k_pencil_energy_reg<T, L, TV, stream()>), dim3(nlb, b.npairs), dim3(256), 0, p.stream, ll,
+                         pairs, tbuf, vtab, epart);
+    });
     return nlb;
   }
 }
@@ -1317,18 +1337,22 @@ void launch_acc_kernel(const Plan& p, const Batch& b, const Instance& in, const 
   const int n1 = in.grid[0];
   const long long bs = static_cast<long long>(in.band_stride);
   const int rows = b.nO + (b.mirror ? b.nP : 0);
-  if constexpr (SPLIT) {
-    using Sh = SplitShape<T, L>;
-    hipLaunchKernelGGL((k_acc_split<T, L, TI>), dim3(rows, (n1 + Sh::PL - 1) / Sh::PL), dim3(Sh::NTP), Sh::LDS,
-                       p.stream, n1, in.nbands, bs, b.o0, b.nO, b.nP, b.tri, parts, tbuf, static_cast<const C*>(psi),
-                       occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale, hscale, backward ? 1 : 0);
-  } else {
-    using Sh = RegShape<T, L>;
-    constexpr bool PF = sizeof(TI) == sizeof(T) && RegPolicy<T, L>::ACC_PREFETCH;
-    hipLaunchKernelGGL((k_acc_reg<T, L, TI, PF>), dim3(rows, (n1 + Sh::PL - 1) / Sh::PL), dim3(Sh::NTP), Sh::LDS,
-                       p.stream, n1, in.nbands, bs, b.o0, b.nO, b.nP, b.tri, parts, tbuf, static_cast<const C*>(psi),
-                       occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale, hscale, backward ? 1 : 0);
-  }
+  by_stream(p, b, [&](auto stream) {
+    // FOCK_MIXED_INV's FP32 sums: plain loads (lane_flat)
+    constexpr bool STREAM = stream() && sizeof(TI) == sizeof(T);
+    if constexpr (SPLIT) {
+      using Sh = SplitShape<T, L>;
+      hipLaunchKernelGGL((k_acc_split<T, L, TI, STREAM>), dim3(rows, (n1 + Sh::PL - 1) / Sh::PL), dim3(Sh::NTP), Sh::LDS,
+                         p.stream, n1, in.nbands, bs, b.o0, b.nO, b.nP, b.tri, parts, tbuf, static_cast<const C*>(psi),
+                         occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale, hscale, backward ? 1 : 0);
+    } else {
+      using Sh = RegShape<T, L>;
+      constexpr bool PF = sizeof(TI) == sizeof(T) && RegPolicy<T, L>::ACC_PREFETCH;
+      hipLaunchKernelGGL((k_acc_reg<T, L, TI, PF, STREAM>), dim3(rows, (n1 + Sh::PL - 1) / Sh::PL), dim3(Sh::NTP), Sh::LDS,
+                         p.stream, n1, in.nbands, bs, b.o0, b.nO, b.nP, b.tri, parts, tbuf, static_cast<const C*>(psi),
+                         occ, kw, static_cast<C*>(out), b.first, b.first_mirror, gscale, hscale, backward ? 1 : 0);
+    }
+  });
 }
 
 // the accumulate pass of a batch: its outputs, and for a batch of unordered
@@ -1341,32 +1365,40 @@ void launch_acc_all(const Plan& p, const Batch& b, const Instance& in, const int
                                                      backward);
 }
 
-template <typename T, int L>
-void reg_lds_attr(int lim) {
-  using Po = RegPolicy<T, L>;
-  const void* fs[4];
-  if constexpr (Po::SPLIT_PLANE) {
-    fs[0] = reinterpret_cast<const void*>(&k_plane_split<T, L, false>);
-    fs[1] = reinterpret_cast<const void*>(&k_plane_split<T, L, true>);
-  } else {
-    fs[0] = reinterpret_cast<const void*>(&k_plane_reg<T, L, false>);
-    fs[1] = reinterpret_cast<const void*>(&k_plane_reg<T, L, true>);
-  }
-  if constexpr (Po::SPLIT_ACC)
-    fs[2] = reinterpret_cast<const void*>(&k_acc_split<T, L>);
-  else
-    fs[2] = reinterpret_cast<const void*>(&k_acc_reg<T, L, T, Po::ACC_PREFETCH>);
-  fs[3] = fs[2];
+void lds_attr(std::initializer_list<const void*> fs, int lim) {
   for (const void* f : fs)
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) != hipSuccess) (void)hipGetLastError();
-  if constexpr (slab_type<T>()) {
-    const void* gs[4] = {reinterpret_cast<const void*>(&k_plane_reg<T, L, false, T, true>),
-                         reinterpret_cast<const void*>(&k_plane_reg<T, L, true, T, true>),
-                         reinterpret_cast<const void*>(&k_pencil_slab<T, L, false>),
-                         reinterpret_cast<const void*>(&k_pencil_slab<T, L, true>)};
-    for (const void* f : gs)
-      if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) != hipSuccess) (void)hipGetLastError();
-  }
+}
+template <typename F>
+const void* fn(F* f) {
+  return reinterpret_cast<const void*>(f);
+}
+
+// the plane and accumulate kernels of a length that take dynamic LDS
+template <typename T, int L, bool STREAM>
+void plane_lds_attr(int lim) {
+  if constexpr (RegPolicy<T, L>::SPLIT_PLANE)
+    lds_attr({fn(&k_plane_split<T, L, false, STREAM>), fn(&k_plane_split<T, L, true, STREAM>)}, lim);
+  else
+    lds_attr({fn(&k_plane_reg<T, L, false, T, false, STREAM>), fn(&k_plane_reg<T, L, true, T, false, STREAM>)}, lim);
+}
+template <typename T, int L, bool STREAM>
+void acc_lds_attr(int lim) {
+  using Po = RegPolicy<T, L>;
+  if constexpr (Po::SPLIT_ACC)
+    lds_attr({fn(&k_acc_split<T, L, T, STREAM>)}, lim);
+  else
+    lds_attr({fn(&k_acc_reg<T, L, T, Po::ACC_PREFETCH, STREAM>)}, lim);
+}
+
+template <typename T, int L, bool STREAM>
+void reg_lds_attr(int lim) {
+  plane_lds_attr<T, L, STREAM>(lim);
+  acc_lds_attr<T, L, STREAM>(lim);
+  if constexpr (slab_type<T>())
+    lds_attr({fn(&k_plane_reg<T, L, false, T, true, STREAM>), fn(&k_plane_reg<T, L, true, T, true, STREAM>),
+              fn(&k_pencil_slab<T, L, false, STREAM>), fn(&k_pencil_slab<T, L, true, STREAM>)},
+             lim);
 }
 
 // FOCK_MIXED: FP32 plane pass (FP64 orbitals rounded on load), mixed pencil
@@ -1395,16 +1427,9 @@ int launch_pencil_mixed(const Plan& p, const Batch& b, const Instance& in, const
 
 template <int L>
 void mixed_lds_attr(int lim) {
-  using Acc = RegPolicy<double, L>;
-  const void* fs[4] = {reinterpret_cast<const void*>(&k_plane_reg<float, L, false, double>),
-                       reinterpret_cast<const void*>(&k_plane_reg<float, L, true, double>), nullptr, nullptr};
-  if constexpr (Acc::SPLIT_ACC)
-    fs[2] = reinterpret_cast<const void*>(&k_acc_split<double, L>);
-  else
-    fs[2] = reinterpret_cast<const void*>(&k_acc_reg<double, L, double, Acc::ACC_PREFETCH>);
-  fs[3] = fs[2];
-  for (const void* f : fs)
-    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) != hipSuccess) (void)hipGetLastError();
+  lds_attr({fn(&k_plane_reg<float, L, false, double>), fn(&k_plane_reg<float, L, true, double>)}, lim);
+  acc_lds_attr<double, L, false>(lim);
+  acc_lds_attr<double, L, true>(lim);
 }
 
 // FOCK_MIXED_INV: FP64 plane pass, mixed pencil pass, FP32 accumulate pass
@@ -1432,21 +1457,12 @@ int launch_pencil_mixinv(const Plan& p, const Batch& b, const Instance& in, cons
 
 template <int L>
 void mixinv_lds_attr(int lim) {
-  const void* fs[4] = {nullptr, nullptr, nullptr, nullptr};
-  if constexpr (RegPolicy<double, L>::SPLIT_PLANE) {
-    fs[0] = reinterpret_cast<const void*>(&k_plane_split<double, L, false>);
-    fs[1] = reinterpret_cast<const void*>(&k_plane_split<double, L, true>);
-  } else {
-    fs[0] = reinterpret_cast<const void*>(&k_plane_reg<double, L, false>);
-    fs[1] = reinterpret_cast<const void*>(&k_plane_reg<double, L, true>);
-  }
+  plane_lds_attr<double, L, false>(lim);
+  plane_lds_attr<double, L, true>(lim);
   if constexpr (split_acc<float, L, double>())
-    fs[2] = reinterpret_cast<const void*>(&k_acc_split<float, L, double>);
+    lds_attr({fn(&k_acc_split<float, L, double>)}, lim);
   else
-    fs[2] = reinterpret_cast<const void*>(&k_acc_reg<float, L, double>);
-  fs[3] = fs[2];
-  for (const void* f : fs)
-    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) != hipSuccess) (void)hipGetLastError();
+    lds_attr({fn(&k_acc_reg<float, L, double>)}, lim);
 }
 
 // the axis lengths with register-line kernels
@@ -1674,8 +1690,10 @@ size_t reg_lds_bytes(fock_precision prec, int L) {
 
 void prepare_reg_kernels(fock_precision prec, int lim) {
 #define CASE(N)                                     \
-  if (prec == FOCK_C64) reg_lds_attr<float, N>(lim); \
-  else if (prec == FOCK_MIXED) mixed_lds_attr<N>(lim); \
+  if (prec == FOCK_C64) {                            \
+    reg_lds_attr<float, N, false>(lim);              \
+    reg_lds_attr<float, N, true>(lim);               \
+  } else if (prec == FOCK_MIXED) mixed_lds_attr<N>(lim); \
   else if (prec == FOCK_MIXED_INV) mixinv_lds_attr<N>(lim);
   FOCK_REG_L(CASE)
 #undef CASE

@@ -122,7 +122,7 @@ constexpr int twiddle_count(int n) { return (radix_a(n) - 1) * (n / radix_a(n));
 
 // axis 2, pass a (or the only pass), from the planes in memory: consecutive lanes take consecutive elements, so every load is
 // coalesced
-template <int N, int S, typename C>
+template <int N, int S, bool STREAM, typename C>
 __device__ __forceinline__ void ax2_load(C* s, const C* src, int n3, int pitch, int gc,
                                          const C* __restrict__ tw) {
   constexpr int A = radix_a(N), R = A > 1 ? A : N, M = N / R;
@@ -134,7 +134,7 @@ __device__ __forceinline__ void ax2_load(C* s, const C* src, int n3, int pitch, 
     const unsigned o = static_cast<unsigned>(__mul24(gg, N * n3) + rem) * sizeof(C);
     C v[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = stream_load(lane_at(src + r * mn, o));
+    for (int r = 0; r < R; ++r) v[r] = stream_load<STREAM>(lane_at(src + r * mn, o));
     Dft<R, S, C>::run(v);
     if constexpr (M > 1) {
 #pragma unroll
@@ -147,7 +147,7 @@ __device__ __forceinline__ void ax2_load(C* s, const C* src, int n3, int pitch, 
 }
 
 // axis 2, inverse pass a, to the planes in memory
-template <int N, int S, typename C>
+template <int N, int S, bool STREAM, typename C>
 __device__ __forceinline__ void ax2_store(const C* s, C* dst, int n3, int pitch, int gc, const C* tw) {
   constexpr int A = radix_a(N), R = A > 1 ? A : N, M = N / R;
   const int mn = M * n3, total = gc * mn;
@@ -166,7 +166,7 @@ __device__ __forceinline__ void ax2_store(const C* s, C* dst, int n3, int pitch,
     Dft<R, S, C>::run(v);
     const unsigned o = static_cast<unsigned>(__mul24(gg, N * n3) + rem) * sizeof(C);
 #pragma unroll
-    for (int r = 0; r < R; ++r) stream_store(lane_at(dst + r * mn, o), v[r]);
+    for (int r = 0; r < R; ++r) stream_store<STREAM>(lane_at(dst + r * mn, o), v[r]);
   }
 }
 
