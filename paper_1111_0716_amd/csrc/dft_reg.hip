@@ -1,10 +1,10 @@
-// Register-line kernels of the batched 3-D DFT (fock_dft3) on small grids
-// N1 x L x L: every 1-D transform runs in one lane's registers on a whole line
+// Register-line kernels of the batched 3-D DFT (fock_dft3) on grids N1 x L x L:
+// every 1-D transform runs in one lane's registers on a whole line
 // (reg_fft.hpp), a plane switches axes through a padded LDS transpose.  One
-// barrier chain shorter than the tiles of pass_line.hip, which counts where a
-// call is short: 256 DFTs of 16^3 FP32 10 against 15.5 us, 75 of 24^3 13.8
-// against 16.7; large batches are bound by memory on both (2048 of 32^3 413
-// against 426 us, 4854 of 24^3 412 against 404).
+// barrier chain shorter than the tiles of pass_line.hip, which counts on small
+// grids where a call is short (256 DFTs of 16^3 FP32 10 against 15.5 us, 75 of
+// 24^3 13.8 against 16.7) and up to 48 points in FP32 where the caches hold the
+// data (reg_dft_use); large batches are bound by memory on both.
 #include <algorithm>
 
 #include "fft_lds.hpp"
@@ -109,10 +109,14 @@ void dft_pencil_L(const Plan& p, int ll, int count, typename cx<T>::t* d, long l
 }
 
 // the lengths that run here (32 in FP64 and longer lines: pass_line.hip is as fast or faster)
-#define FOCK_DFT_F32(X) X(16) X(24) X(32)
+#define FOCK_DFT_F32(X) X(16) X(24) X(32) X(36) X(40) X(48)
 #define FOCK_DFT_F64(X) X(16) X(24)
 
+// the lengths that run here at any size, and those that do at some
 bool dft_len(fock_precision prec, int n) { return n == 16 || n == 24 || (n == 32 && prec == FOCK_C64); }
+bool dft_len_cached(fock_precision prec, int n) {
+  return dft_len(prec, n) || (prec == FOCK_C64 && (n == 36 || n == 40 || n == 48));
+}
 
 template <typename T, int S>
 hipError_t reg_dft3_t(const Plan& p, int inst, int count, void* data, long long stride) {
@@ -144,8 +148,16 @@ hipError_t reg_dft3_t(const Plan& p, int inst, int count, void* data, long long 
 
 }  // namespace
 
-bool reg_dft_supported(fock_precision prec, const int grid[3]) {
-  return grid[1] == grid[2] && dft_len(prec, grid[0]) && dft_len(prec, grid[1]);
+// FP32 lines of 36 to 48 points: where the batch fits the last-level cache but
+// not the L2s.  Here / pass_line.hip, us: 36^3 FP32, 16 DFTs 16.6/15.8, 64 (24
+// MB) 23.0/24.3, 128 31.4/35.5, 512 (191 MB) 99.9/103, 1024 (382 MB) 293/279;
+// 40^3, 32 25.9/24.9, 64 (33 MB) 24.4/26.0; 48^3, 64 (57 MB) 36.4/38.3; 36x24x24,
+// 256 (42 MB) 27.7/30.7.
+bool reg_dft_use(fock_precision prec, const int grid[3], size_t bytes) {
+  if (grid[1] != grid[2]) return false;
+  if (dft_len(prec, grid[0]) && dft_len(prec, grid[1])) return true;
+  return dft_len_cached(prec, grid[0]) && dft_len_cached(prec, grid[1]) && bytes > (size_t{20} << 20) &&
+         bytes <= kLastLevelBytes;
 }
 
 hipError_t launch_reg_dft3(const Plan& p, int inst, int sign, int count, void* data, long long stride) {

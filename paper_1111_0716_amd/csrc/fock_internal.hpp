@@ -253,7 +253,8 @@ hipError_t launch_energy_batch(const Plan& p, const Batch& b, const void* psi, c
 hipError_t launch_energy_finish(const Plan& p, double* ex, bool after_apply);
 hipError_t launch_zero_outputs(const Plan& p, int inst, void* out);
 hipError_t launch_zero_all_bands(const Plan& p, int inst, void* out);
-bool reg_dft_supported(fock_precision prec, const int grid[3]);
+// whether a DFT batch of that many bytes runs on the register-line kernels
+bool reg_dft_use(fock_precision prec, const int grid[3], size_t bytes);
 hipError_t launch_reg_dft3(const Plan& p, int inst, int sign, int count, void* data, long long stride);
 hipError_t launch_dft3(const Plan& p, int inst, int sign, long long count, void* data, long long stride);
 hipError_t launch_pw_to_grid(const Plan& p, int inst, const void* coef, const int* gidx, const int* npw, int npw_max,

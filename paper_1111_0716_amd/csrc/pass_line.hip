@@ -422,7 +422,7 @@ __global__ __launch_bounds__(512, 4) void k_dft_plane(PlaneGeo g, typename cx<T>
   switch (g.n2) {
 #define CASE(N)                                              \
   case N:                                                    \
-    ax2_load<N, S, true>(s, t, g.n3, g.pitch, gc, tw2);      \
+    ax2_load<N, S, false>(s, t, g.n3, g.pitch, gc, tw2);     \
     if constexpr (radix_a(N) > 1) {                          \
       __syncthreads();                                       \
       ax2_b<N, S, C>(s, g.n3, g.pitch, gc);                  \

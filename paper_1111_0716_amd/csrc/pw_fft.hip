@@ -67,7 +67,8 @@ hipError_t dft3_t(const Plan& p, int inst, int sign, long long count, void* data
     const int nb = static_cast<int>(std::min<long long>(65535, count - b0));
     C* db = d + static_cast<size_t>(b0) * stride;
     p.prof.begin(FOCK_K_DFT, p.stream);
-    const hipError_t e = reg_dft_supported(p.prec, in.grid) ? launch_reg_dft3(p, inst, sign, nb, db, stride)
+    const size_t bytes = static_cast<size_t>(nb) * in.npts * sizeof(C);
+    const hipError_t e = reg_dft_use(p.prec, in.grid, bytes) ? launch_reg_dft3(p, inst, sign, nb, db, stride)
                                                             : launch_line_dft3(p, inst, sign, nb, db, stride);
     p.prof.end(FOCK_K_DFT, p.stream);
     if (e != hipSuccess) return e;
