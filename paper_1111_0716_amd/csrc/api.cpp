@@ -254,7 +254,7 @@ fock_status run_energy(Plan* p, const void* const* psi, const double* const* occ
     hipError_t e;
     if (after_apply) {
       e = launch_lds_energy_batch(*p, b, psi[b.inst], occ[b.inst]);
-    } else if (p->inst[b.inst].fused) {
+    } else if (p->inst[b.inst].fused_energy) {
       e = launch_fused_energy(*p, b, psi[b.inst]);
       if (e == hipSuccess) e = launch_energy_reduce(*p, b, occ[b.inst], 1);
     } else {

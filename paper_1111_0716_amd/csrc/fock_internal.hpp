@@ -93,6 +93,7 @@ struct Instance {
   std::vector<std::vector<int>> kpartners;  // k -> list of k'
   bool symmetric = true;                     // (k, k') listed iff (k', k) listed
   bool fused = false;                        // whole-pair path (cubic grid that fits one CU)
+  bool fused_energy = false;                 // fock_energy on the whole-pair kernel
   int rounds = -1;                           // whole-pair path by unordered pairs: its FusedRounds
   bool reg = false;                          // register-line passes (pass_reg.hip; not FP64)
   bool slab = false;                         // their slab form (pair buffer [j1][c2][c3])
@@ -107,6 +108,7 @@ struct Instance {
   std::vector<int> qmap;  // [nk*nk] -> table index or -1
   // workspace offsets (bytes)
   size_t vtab_off = 0, kw_off = 0, qmap_off = 0;
+  size_t etab_off = 0;  // the kernel tables in the order of fock_energy's passes (may be vtab_off)
   int ovl_span = 0;  // grid points per split-K chunk of the overlap
   int first_ebatch = 0, n_ebatches = 0;
   int first_eblk = 0, n_eblk = 0;  // whole-pair apply-with-energy partials of this instance

@@ -749,7 +749,7 @@ hipError_t fused_energy_L(const Plan& p, const Batch& b, const void* psi) {
   hipLaunchKernelGGL((k_pair_energy_fused<T, L>), dim3(nwg), dim3(Sh::NT), lds, p.stream, in.nbands,
                      static_cast<long long>(in.band_stride), static_cast<const C*>(psi),
                      reinterpret_cast<const PairRef*>(p.ws + b.pair_off), b.npairs, per_wg,
-                     reinterpret_cast<const T*>(p.ws + in.vtab_off), reinterpret_cast<double*>(p.ws + p.epart_off));
+                     reinterpret_cast<const T*>(p.ws + in.etab_off), reinterpret_cast<double*>(p.ws + p.epart_off));
   p.prof.end(FOCK_K_ENERGY_FUSED, p.stream);
   return hipGetLastError();
 }

@@ -249,6 +249,9 @@ struct Schedule {
   // (smaller batches on thin grids)
   bool plane_blocks = false;
   bool can_plane_blocks = false;  // that would change a batch
+  // no second kernel table for energies whose passes read another order
+  bool one_table = false;
+  bool can_one_table = false;
   // the whole-pair kernel also where the three-pass path is faster
   bool keep_fused = false;
   bool can_keep_fused = false;
@@ -276,7 +279,7 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
   p->fused_rounds.clear();
   p->ordered_pairs = p->apply_fft_pairs = p->energy_fft_pairs = 0;
   for (auto& in : p->inst) in.rounds = -1;
-  sc->can_plane_blocks = sc->can_keep_fused = false;
+  sc->can_plane_blocks = sc->can_one_table = sc->can_keep_fused = false;
   const char* nofused = std::getenv("FOCK_NO_FUSED");
   const bool no_fused = tn.no_fused != 0 || (nofused && *nofused && *nofused != '0');
   const char* nosym = std::getenv("FOCK_NO_PAIR_SYMMETRY");
@@ -303,6 +306,14 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
         sc->can_keep_fused = true;  // the whole-pair kernel needs no pair buffer
         in.fused = sc->keep_fused;
       }
+    }
+    // Energies alone: the whole-pair kernel wins at any number of orbitals (16^3
+    // FP64 Gamma, whole-pair / three-pass, us: 9 bands 16.6/18.5, 24 16.5/21.0, 40
+    // 18.0/32.9); its table is in another order than the three passes'.
+    in.fused_energy = in.fused;
+    if (!in.fused && prec == FOCK_C128 && fused_supported(prec, in.grid) && !no_fused) {
+      sc->can_one_table = true;
+      in.fused_energy = !sc->one_table;
     }
     // FP32 and mixed plans keep the register-line passes where they are (see
     // energy_lds.hip: their energies and FP64 outputs are sums of FP32 spectra)
@@ -333,6 +344,11 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
   for (auto& in : p->inst) {
     in.vtab_off = off;
     off = align_up(off + static_cast<size_t>(in.nq) * in.npts * rsize);
+    in.etab_off = in.vtab_off;
+    if (in.fused_energy != in.fused) {
+      in.etab_off = off;
+      off = align_up(off + static_cast<size_t>(in.nq) * in.npts * rsize);
+    }
     in.qmap_off = off;
     off = align_up(off + in.qmap.size() * sizeof(int32_t));
     in.kw_off = off;
@@ -521,7 +537,7 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
     for (int k = 0; k < in.nk; ++k) p->ordered_pairs += static_cast<int64_t>(in.kpartners[k].size()) * in.nbands * in.nbands;
     const size_t pair_bytes = static_cast<size_t>(in.npts) * p->csize;
     size_t pmax = std::max<size_t>(1, std::min<size_t>(65535, tbuf_target / pair_bytes));
-    if (in.fused) pmax = std::max<size_t>(1, L.size());  // one launch; no pair buffer
+    if (in.fused_energy) pmax = std::max<size_t>(1, L.size());  // one launch; no pair buffer
     in.first_ebatch = slot;
     in.n_ebatches = 0;
     const size_t base = off;
@@ -533,7 +549,7 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
       b.npairs = static_cast<int32_t>(std::min(pmax, L.size() - s0));
       b.slot = slot++;
       in.n_ebatches++;
-      if (in.fused) {
+      if (in.fused_energy) {
         b.per_wg = std::max(1, b.npairs / 1024);
         max_fused_epairs = std::max(max_fused_epairs, static_cast<size_t>(b.npairs));
       } else {
@@ -640,7 +656,7 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
     for (const auto* bs : {&p->energy_batches, &p->apply_batches, &p->ordered_energy})
       for (const Batch& b : *bs) {
         const Instance& in = p->inst[b.inst];
-        if (in.fused) continue;
+        if (bs == &p->energy_batches && in.fused_energy) continue;
         const int per_pair = prec == FOCK_C128 ? plane_tiles(in.pg) : in.grid[1];
         p->epart_bytes = std::max(p->epart_bytes, static_cast<size_t>(b.npairs) * per_pair * sizeof(double));
       }
@@ -735,25 +751,28 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   }
   // ---- schedule ----
   // What only saves time must not take a plan out of the static workspace: one
-  // that leaves it is scheduled again with smaller batches, with the whole-pair
-  // kernel kept, with both, and takes the first that fits.  FP64 72x4x4, two
-  // k-points of 36 bands, no_pair_symmetry: 95.7 -> 48.7 MB; FP64 16^3 Gamma, 56
-  // bands: 105 -> 11 MB.
+  // that leaves it is scheduled again without second tables, with smaller
+  // batches, with the whole-pair kernel kept, and with any two or all of these,
+  // and takes the first that fits.  FP64 72x4x4, two k-points of 36 bands,
+  // no_pair_symmetry: 95.7 -> 48.7 MB; FP64 16^3 Gamma, 56 bands: 105 -> 11 MB.
   Schedule sc;
   fock_status st = schedule_plan(p.get(), tn, &sc);
-  const bool planes = sc.can_plane_blocks, keep = sc.can_keep_fused;
-  for (int i = 1; st == FOCK_OK && i <= 4 && p->total_bytes > FOCK_STATIC_WORKSPACE_BYTES && (planes || keep); ++i) {
-    sc.plane_blocks = (i & 1) && i < 4;  // the last: none fits, as first
-    sc.keep_fused = (i & 2) && i < 4;
-    if ((sc.plane_blocks && !planes) || (sc.keep_fused && !keep)) continue;
+  const int can = (sc.can_one_table ? 1 : 0) | (sc.can_plane_blocks ? 2 : 0) | (sc.can_keep_fused ? 4 : 0);
+  for (int i = 1; can && i <= 8 && st == FOCK_OK && p->total_bytes > FOCK_STATIC_WORKSPACE_BYTES; ++i) {
+    const int c = i & 7;  // the last: none fits, as at first
+    if (c & ~can) continue;
+    sc.one_table = c & 1;
+    sc.plane_blocks = c & 2;
+    sc.keep_fused = c & 4;
     st = schedule_plan(p.get(), tn, &sc);
   }
   if (st != FOCK_OK) return st;
   for (const auto& in : p->inst) {
-    const size_t need =
-        in.fused ? fused_lds_bytes(prec, in.grid[0]) + 256
-                 : std::max(plane_lds_bytes(in.pg, p->csize), in.reg ? reg_lds_bytes(prec, in.grid[1]) : size_t{0}) + 64;
-    p->lds_needed = std::max(p->lds_needed, need);
+    if (in.fused_energy) p->lds_needed = std::max(p->lds_needed, fused_lds_bytes(prec, in.grid[0]) + 256);
+    if (in.fused) continue;
+    p->lds_needed = std::max(
+        p->lds_needed,
+        std::max(plane_lds_bytes(in.pg, p->csize), in.reg ? reg_lds_bytes(prec, in.grid[1]) : size_t{0}) + 64);
   }
   p->apply_launches = 0;
   for (const Batch& b : p->apply_batches) p->apply_launches += 3;
@@ -794,16 +813,26 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
     Instance& in = p->inst[i];
     for (int q = 0; q < in.nq; ++q) {
       std::vector<double>& t = tables[i][q];
-      if (in.fused) {
-        // whole-pair path reads the table in C order: (c3*L + c2)*L + c1
+      const auto put = [&](size_t at, const std::vector<double>& v) {
+        if (prec != FOCK_C64) {
+          std::memcpy(img + at + static_cast<size_t>(q) * in.npts * 8, v.data(), v.size() * 8);
+        } else {
+          float* dst = reinterpret_cast<float*>(img + at) + static_cast<size_t>(q) * in.npts;
+          for (size_t e = 0; e < v.size(); ++e) dst[e] = static_cast<float>(v[e]);
+        }
+      };
+      if (in.fused_energy) {
+        // whole-pair kernels read the table in C order: (c3*L + c2)*L + c1
         const int L = in.grid[0];
         std::vector<double> r(t.size());
         for (int c1 = 0; c1 < L; ++c1)
           for (int c2 = 0; c2 < L; ++c2)
             for (int c3 = 0; c3 < L; ++c3)
               r[(static_cast<size_t>(c3) * L + c2) * L + c1] = t[(static_cast<size_t>(c1) * L + c2) * L + c3];
-        t.swap(r);
-      } else if (in.reg) {
+        put(in.etab_off, r);
+        if (in.fused) continue;
+      }
+      if (in.reg) {
         // register-line passes read the table as [c1][c3][c2] (grids N1 x L x
         // L), their slab form in grid order
         if (!in.slab) {
@@ -833,12 +862,7 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
                 }
         t.swap(r);
       }
-      if (prec != FOCK_C64) {
-        std::memcpy(img + in.vtab_off + static_cast<size_t>(q) * in.npts * 8, t.data(), t.size() * 8);
-      } else {
-        float* dst = reinterpret_cast<float*>(img + in.vtab_off) + static_cast<size_t>(q) * in.npts;
-        for (size_t e = 0; e < t.size(); ++e) dst[e] = static_cast<float>(t[e]);
-      }
+      put(in.vtab_off, t);
     }
     std::vector<int32_t> qm(in.qmap.begin(), in.qmap.end());
     std::memcpy(img + in.qmap_off, qm.data(), qm.size() * sizeof(int32_t));
