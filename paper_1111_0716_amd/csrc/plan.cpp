@@ -335,8 +335,10 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
   p->tw_off = off;
   off = align_up(off + static_cast<size_t>(kTwiddleTotal) * p->csize);
   p->tw1_off = off;
+  // FP32 on general grids: E_x from its own passes (energy_lds.hip)
+  const auto lds_energy = [&](const Instance& in) { return prec == FOCK_C64 && !in.fused && !in.reg; };
   for (const auto& in : p->inst)
-    if (prec == FOCK_C64 && !in.fused && !in.reg) {
+    if (lds_energy(in)) {
       off = align_up(off + static_cast<size_t>(kTwiddleTotal) * p->csize);
       break;
     }
@@ -345,7 +347,9 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
     in.vtab_off = off;
     off = align_up(off + static_cast<size_t>(in.nq) * in.npts * rsize);
     in.etab_off = in.vtab_off;
-    if (in.fused_energy != in.fused) {
+    const bool lds = lds_energy(in);
+    if (lds) sc->can_one_table = true;
+    if (in.fused_energy != in.fused || (lds && !sc->one_table)) {
       in.etab_off = off;
       off = align_up(off + static_cast<size_t>(in.nq) * in.npts * rsize);
     }
@@ -515,8 +519,6 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
   // energy pair lists
   std::vector<std::vector<PairRef>>& elists = sc->elists;
   elists.assign(n_inst, {});
-  // FP32 on general grids: E_x from its own passes (energy_lds.hip)
-  const auto lds_energy = [&](const Instance& in) { return prec == FOCK_C64 && !in.fused && !in.reg; };
   size_t max_fused_epairs = 0;
   int slot = 0;
   for (int i = 0; i < n_inst; ++i) {
@@ -831,6 +833,8 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
               r[(static_cast<size_t>(c3) * L + c2) * L + c1] = t[(static_cast<size_t>(c1) * L + c2) * L + c3];
         put(in.etab_off, r);
         if (in.fused) continue;
+      } else if (in.etab_off != in.vtab_off) {
+        put(in.etab_off, t);  // grid order
       }
       if (in.reg) {
         // register-line passes read the table as [c1][c3][c2] (grids N1 x L x
