@@ -250,10 +250,11 @@ fock_status run_overlaps(Plan* p, const void* const* psi, void* const* vx_psi, v
 // pairs' own passes (energy_lds.hip).
 fock_status run_energy(Plan* p, const void* const* psi, const double* const* occ, double* ex, bool after_apply) {
   // after an apply only the energies that are not its own are left to do
+  const bool whole = after_apply && lds_energy_whole(*p);
   for (const Batch& b : after_apply ? p->ordered_energy : p->energy_batches) {
     hipError_t e;
     if (after_apply) {
-      e = launch_lds_energy_batch(*p, b, psi[b.inst], occ[b.inst]);
+      e = launch_lds_energy_batch(*p, b, psi[b.inst], occ[b.inst], whole ? ex : nullptr);
     } else if (p->inst[b.inst].fused_energy) {
       e = launch_fused_energy(*p, b, psi[b.inst]);
       if (e == hipSuccess) e = launch_energy_reduce(*p, b, occ[b.inst], 1);
@@ -262,6 +263,7 @@ fock_status run_energy(Plan* p, const void* const* psi, const double* const* occ
     }
     if (e != hipSuccess) return hip_fail(e, "energy batch launch");
   }
+  if (whole) return FOCK_OK;
   const hipError_t e = launch_energy_finish(*p, ex, after_apply);
   return e == hipSuccess ? FOCK_OK : hip_fail(e, "energy finish launch");
 }

@@ -173,7 +173,8 @@ __global__ __launch_bounds__(kBlock) void k_pencil_energy(Geo g, PlaneGeo pg, in
                                                           const T* __restrict__ vtab,
                                                           const typename cx<T>::t* __restrict__ tw,
                                                           const double* __restrict__ occ,
-                                                          const double* __restrict__ kw, double* __restrict__ epart) {
+                                                          const double* __restrict__ kw, double* __restrict__ epart,
+                                                          unsigned* done, double* __restrict__ ex, double factor) {
   using C = typename cx<T>::t;
   extern __shared__ unsigned char smem_raw[];
   __shared__ double red[kBlock / 64];
@@ -209,11 +210,39 @@ __global__ __launch_bounds__(kBlock) void k_pencil_energy(Geo g, PlaneGeo pg, in
   }
   const double tot = block_sum(acc, red);
   if (threadIdx.x == 0) epart[static_cast<size_t>(pi) * g.n2 + c2] = w * tot;
+  if constexpr (!EXPLICIT) {
+    if (!ex) return;
+    // The workgroup that ends last sums the partials, compensated and in a fixed
+    // order, and clears the counter for the next launch.
+    __shared__ bool last;
+    const unsigned n = gridDim.x * gridDim.y;
+    if (threadIdx.x == 0)
+      last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+    __syncthreads();
+    if (!last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    double sum = 0.0, comp = 0.0;
+    for (unsigned i = threadIdx.x; i < n; i += kBlock) neumaier(sum, comp, epart[i]);
+    const double all = block_sum(sum + comp, red);
+    if (threadIdx.x == 0) {
+      ex[0] = factor * all;
+      *done = 0u;
+    }
+  }
+}
+
+// One ordered batch is the whole energy, of few enough partials for one
+// workgroup: the pencil pass finishes it, without the launches of the sum and of
+// k_energy_finish, which count where a call is nothing but launches (4x4x4, 2
+// bands, apply and E_x: 32.8 us with one launch more, 28.6).
+bool lds_energy_whole(const Plan& p) {
+  return p.inst.size() == 1 && p.ordered_energy.size() == 1 &&
+         static_cast<long long>(p.ordered_energy[0].npairs) * p.inst[0].grid[1] <= 4096;
 }
 
 // b.nO > 0: the ordered pairs of a batch (weighted, into slot b.eslot), else an
 // explicit pair list (into slot b.slot)
-hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ) {
+hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, double* ex) {
   using C = float2;
   const Instance& in = p.inst[b.inst];
   const Geo g{in.grid[0], in.grid[1], in.grid[2], in.nk, in.nbands, static_cast<long long>(in.band_stride)};
@@ -223,6 +252,7 @@ hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* ps
   const int* qmap = reinterpret_cast<const int*>(p.ws + in.qmap_off);
   const float* vtab = reinterpret_cast<const float*>(p.ws + in.etab_off);
   const int tiled = in.etab_off == in.vtab_off;
+  unsigned* done = reinterpret_cast<unsigned*>(p.ws + p.tw1_off + static_cast<size_t>(kTwiddleTotal) * sizeof(C));
   const double* kw = reinterpret_cast<const double*>(p.ws + in.kw_off);
   C* tbuf = reinterpret_cast<C*>(p.ws + p.tbuf_off);
   double* epart = reinterpret_cast<double*>(p.ws + p.epart_off);
@@ -241,12 +271,13 @@ hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* ps
   if (ordered)
     hipLaunchKernelGGL((k_pencil_energy<float, false>), dim3(g.n2, b.npairs), dim3(kBlock), lds_tile, p.stream, g,
                        in.pg, tiled, b.o0, b.nP, parts, qmap, static_cast<const PairRef*>(nullptr),
-                       static_cast<const C*>(tbuf), vtab, tw, occ, kw, epart);
+                       static_cast<const C*>(tbuf), vtab, tw, occ, kw, epart, done, ex, energy_factor(in));
   else
     hipLaunchKernelGGL((k_pencil_energy<float, true>), dim3(g.n2, b.npairs), dim3(kBlock), lds_tile, p.stream, g,
                        in.pg, tiled, 0, 1, static_cast<const int2*>(nullptr), static_cast<const int*>(nullptr), pairs,
-                       static_cast<const C*>(tbuf), vtab, tw, occ, kw, epart);
+                       static_cast<const C*>(tbuf), vtab, tw, occ, kw, epart, done, static_cast<double*>(nullptr), 0.0);
   p.prof.end(FOCK_K_ENERGY_PENCIL, p.stream);
+  if (ex) return hipGetLastError();
   if (ordered) return launch_sum_slot(p, static_cast<long long>(b.npairs) * g.n2, b.eslot, 1.0);
   return launch_energy_reduce(p, b, occ, g.n2);
 }

@@ -177,7 +177,7 @@ struct Plan {
   std::vector<FusedRounds> fused_rounds;
   // workspace layout (bytes)
   size_t tw_off = 0;                  // twiddle tables of the plane passes
-  size_t tw1_off = 0;                 // and W_L^t, t < L (energy_lds.hip)
+  size_t tw1_off = 0;                 // and W_L^t, t < L, then a counter (energy_lds.hip)
   size_t const_bytes = 0;             // uploaded prefix
   size_t tbuf_off = 0, tbuf_bytes = 0;
   size_t tbuf64_off = 0;  // FOCK_MIXED: FP64 pair buffer beside the FP32 one at tbuf_off
@@ -241,6 +241,10 @@ void by_stream(const Plan& p, const Batch& b, F f) {
     f(std::integral_constant<bool, false>{});
 }
 
+// E_x of a sum over pairs: the tables hold v/N, so e = N * sum, and
+// E_x = -1/2 (Omega/N^2) * N * sum
+inline double energy_factor(const Instance& in) { return -0.5 * in.omega / static_cast<double>(in.npts); }
+
 // status helpers (thread-local last error)
 fock_status set_error(fock_status s, const std::string& msg);
 void clear_error();
@@ -284,8 +288,10 @@ void prepare_reg_kernels(fock_precision prec, int lim);
 hipError_t launch_reg_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
                                   const double* gscale, double hscale, bool backward, bool energy);
 hipError_t launch_reg_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ);
-// E_x of FP32 plans on general grids (energy_lds.hip)
-hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ);
+// E_x of FP32 plans on general grids (energy_lds.hip); ex not null: an ordered
+// batch that is all of the plan's energy and finishes it (lds_energy_whole)
+hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, double* ex);
+bool lds_energy_whole(const Plan& p);
 // three-pass path (pass_line.hip)
 int plane_tiles(const PlaneGeo& g);
 size_t plane_lds_bytes(const PlaneGeo& g, size_t csize);

@@ -11,13 +11,6 @@
 
 namespace fock {
 
-// one step of a compensated (Neumaier) sum
-__device__ __forceinline__ void neumaier(double& sum, double& comp, double x) {
-  const double t = sum + x;
-  comp += (fabs(sum) >= fabs(x)) ? (sum - t) + x : (x - t) + sum;
-  sum = t;
-}
-
 // ---------------------------------------------------------------------------
 // energy reductions
 // ---------------------------------------------------------------------------
@@ -203,8 +196,7 @@ hipError_t launch_energy_finish(const Plan& p, double* ex, bool after_apply) {
     for (int j = 0; j < m; ++j) {
       const Instance& in = p.inst[i0 + j];
       FinishItem& t = a.it[j];
-      // the tables hold v/N, so e = N * sum; E_x = -1/2 (Omega/N^2) * N * sum
-      t.factor = -0.5 * in.omega / static_cast<double>(in.npts);
+      t.factor = energy_factor(in);
       if (!after_apply) {
         t.src = slots + in.first_ebatch;
         t.count = in.n_ebatches;

@@ -26,6 +26,13 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   return t;  // valid in thread 0
 }
 
+// one step of a compensated (Neumaier) sum
+__device__ __forceinline__ void neumaier(double& sum, double& comp, double x) {
+  const double t = sum + x;
+  comp += (fabs(sum) >= fabs(x)) ? (sum - t) + x : (x - t) + sum;
+  sum = t;
+}
+
 // Loads issued in batches with the next batch in flight while the current one
 // is consumed: only two batches of operands are live beside the line, and a
 // phase costs (elements / batch) - 1 memory latencies at most.

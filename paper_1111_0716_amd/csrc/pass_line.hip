@@ -699,7 +699,7 @@ hipError_t launch_apply_batch(const Plan& p, const Batch& b, const void* psi, co
 
 hipError_t launch_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ) {
   if (p.inst[b.inst].reg) return launch_reg_energy_batch(p, b, psi, occ);
-  return p.prec == FOCK_C64 ? launch_lds_energy_batch(p, b, psi, occ)
+  return p.prec == FOCK_C64 ? launch_lds_energy_batch(p, b, psi, occ, nullptr)
                             : line_energy(p, b, psi, occ);
 }
 

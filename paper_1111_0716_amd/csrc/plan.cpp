@@ -339,7 +339,7 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
   const auto lds_energy = [&](const Instance& in) { return prec == FOCK_C64 && !in.fused && !in.reg; };
   for (const auto& in : p->inst)
     if (lds_energy(in)) {
-      off = align_up(off + static_cast<size_t>(kTwiddleTotal) * p->csize);
+      off = align_up(off + static_cast<size_t>(kTwiddleTotal + 1) * p->csize);
       break;
     }
   sc->tw1 = off != p->tw1_off;
