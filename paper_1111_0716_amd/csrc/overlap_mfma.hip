@@ -79,15 +79,20 @@ struct OvItem {
   int nbands, nk, nt, span, nchunks;
   unsigned blk1, red1;  // end of its workgroups in the product and in the reduction
 };
+// N: instances a launch has room for; one by itself, since a launch takes longer
+// by its arguments' size (apply with E_x and M of 8^3 FP64, two k-points of 3
+// bands: 36.7 us with 16, 35.2 with one).
 constexpr int kOvItems = 16;
+template <int N>
 struct OvArgs {
-  OvItem it[kOvItems];
+  OvItem it[N];
   int n;
 };
 
 // The instance of workgroup b, and b's number within it.
-template <unsigned OvItem::*END>
-__device__ __forceinline__ const OvItem& ov_item(const OvArgs& a, unsigned& b) {
+template <unsigned OvItem::*END, int N>
+__device__ __forceinline__ const OvItem& ov_item(const OvArgs<N>& a, unsigned& b) {
+  if constexpr (N == 1) return a.it[0];
   int i = 0;
   while (i + 1 < a.n && b >= a.it[i].*END) ++i;
   if (i > 0) b -= a.it[i - 1].*END;
@@ -95,11 +100,11 @@ __device__ __forceinline__ const OvItem& ov_item(const OvArgs& a, unsigned& b) {
 }
 
 // workgroups of an instance: (k, chunk, block_i * nbj + block_j), the last fastest; 256 threads
-template <typename T>
-__global__ __launch_bounds__(64 * kOvWaves) void k_overlap_mfma(const OvArgs args) {
+template <typename T, int N>
+__global__ __launch_bounds__(64 * kOvWaves) void k_overlap_mfma(const OvArgs<N> args) {
   using C = typename cx<T>::t;
   unsigned wg = blockIdx.x;
-  const OvItem& in = ov_item<&OvItem::blk1>(args, wg);
+  const OvItem& in = ov_item<&OvItem::blk1, N>(args, wg);
   const C* __restrict__ psi = static_cast<const C*>(in.psi);
   const C* __restrict__ vx = static_cast<const C*>(in.vx);
   double* __restrict__ part = in.part;
@@ -218,12 +223,12 @@ __global__ __launch_bounds__(64 * kOvWaves) void k_overlap_mfma(const OvArgs arg
 // in order, then the shares in order (one thread per element over all chunks
 // waits on one load after another: at a Gamma cell of 48 bands that chain is
 // longer than the product itself).
-template <typename T>
-__global__ __launch_bounds__(256) void k_overlap_reduce(const OvArgs args) {
+template <typename T, int N>
+__global__ __launch_bounds__(256) void k_overlap_reduce(const OvArgs<N> args) {
   using C = typename cx<T>::t;
   __shared__ double2 red[16][16];
   unsigned wg = blockIdx.x;
-  const OvItem& in = ov_item<&OvItem::red1>(args, wg);
+  const OvItem& in = ov_item<&OvItem::red1, N>(args, wg);
   const double2* __restrict__ part = reinterpret_cast<const double2*>(in.part);
   C* __restrict__ vmat = static_cast<C*>(in.vmat);
   const int nbands = in.nbands, nchunks = in.nchunks, nk = in.nk, ntj = in.nt, tiles = in.nt * in.nt;
@@ -256,11 +261,17 @@ __global__ __launch_bounds__(256) void k_overlap_reduce(const OvArgs args) {
 }
 
 template <typename T>
-hipError_t launch_items(const Plan& p, const OvArgs& a) {
+hipError_t launch_items(const Plan& p, const OvArgs<kOvItems>& a) {
   const OvItem& last = a.it[a.n - 1];
   p.prof.begin(FOCK_K_OVERLAP, p.stream);
-  hipLaunchKernelGGL((k_overlap_mfma<T>), dim3(last.blk1), dim3(64 * kOvWaves), 0, p.stream, a);
-  hipLaunchKernelGGL((k_overlap_reduce<T>), dim3(last.red1), dim3(256), 0, p.stream, a);
+  if (a.n == 1) {
+    const OvArgs<1> one{{a.it[0]}, 1};
+    hipLaunchKernelGGL((k_overlap_mfma<T, 1>), dim3(last.blk1), dim3(64 * kOvWaves), 0, p.stream, one);
+    hipLaunchKernelGGL((k_overlap_reduce<T, 1>), dim3(last.red1), dim3(256), 0, p.stream, one);
+  } else {
+    hipLaunchKernelGGL((k_overlap_mfma<T, kOvItems>), dim3(last.blk1), dim3(64 * kOvWaves), 0, p.stream, a);
+    hipLaunchKernelGGL((k_overlap_reduce<T, kOvItems>), dim3(last.red1), dim3(256), 0, p.stream, a);
+  }
   p.prof.end(FOCK_K_OVERLAP, p.stream);
   return hipGetLastError();
 }
@@ -268,7 +279,7 @@ hipError_t launch_items(const Plan& p, const OvArgs& a) {
 template <typename T>
 hipError_t overlaps_t(const Plan& p, const void* const* psi, void* const* vx, void* const* vmat) {
   const size_t room = std::max(p.tbuf_bytes, p.ovl_bytes);  // the pair buffer's memory, free by now
-  OvArgs a{};
+  OvArgs<kOvItems> a{};
   size_t used = 0;
   for (size_t i = 0; i < p.inst.size(); ++i) {
     if (!vmat[i]) continue;
