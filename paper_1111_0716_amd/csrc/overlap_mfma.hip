@@ -89,6 +89,17 @@ struct OvArgs {
   int n;
 };
 
+// Workgroups of a launch, in rows of at most 2^22: a dimension of a grid holds
+// less than 2^32 threads, which 256 of them to a workgroup reach at 2^24 (one
+// k-point of 14000 bands on 72^3).
+constexpr unsigned kOvRow = 1u << 22;
+constexpr unsigned ov_rows(unsigned total) { return (total + kOvRow - 1) / kOvRow; }
+static_assert(ov_rows(1) == 1 && ov_rows(kOvRow) == 1 && ov_rows(kOvRow + 1) == 2 && ov_rows(1u << 31) < 65536 &&
+                  static_cast<unsigned long long>(kOvRow) * 256 < (1ull << 32),
+              "grids of the overlap");
+inline dim3 ov_grid(unsigned total) { return dim3(total < kOvRow ? total : kOvRow, ov_rows(total)); }
+__device__ __forceinline__ unsigned ov_wg() { return blockIdx.y * kOvRow + blockIdx.x; }
+
 // The instance of workgroup b, and b's number within it.
 template <unsigned OvItem::*END, int N>
 __device__ __forceinline__ const OvItem& ov_item(const OvArgs<N>& a, unsigned& b) {
@@ -103,7 +114,8 @@ __device__ __forceinline__ const OvItem& ov_item(const OvArgs<N>& a, unsigned& b
 template <typename T, int N>
 __global__ __launch_bounds__(64 * kOvWaves) void k_overlap_mfma(const OvArgs<N> args) {
   using C = typename cx<T>::t;
-  unsigned wg = blockIdx.x;
+  unsigned wg = ov_wg();
+  if (wg >= args.it[args.n - 1].blk1) return;  // past the last row's end
   const OvItem& in = ov_item<&OvItem::blk1, N>(args, wg);
   const C* __restrict__ psi = static_cast<const C*>(in.psi);
   const C* __restrict__ vx = static_cast<const C*>(in.vx);
@@ -227,7 +239,8 @@ template <typename T, int N>
 __global__ __launch_bounds__(256) void k_overlap_reduce(const OvArgs<N> args) {
   using C = typename cx<T>::t;
   __shared__ double2 red[16][16];
-  unsigned wg = blockIdx.x;
+  unsigned wg = ov_wg();
+  if (wg >= args.it[args.n - 1].red1) return;
   const OvItem& in = ov_item<&OvItem::red1, N>(args, wg);
   const double2* __restrict__ part = reinterpret_cast<const double2*>(in.part);
   C* __restrict__ vmat = static_cast<C*>(in.vmat);
@@ -266,11 +279,11 @@ hipError_t launch_items(const Plan& p, const OvArgs<kOvItems>& a) {
   p.prof.begin(FOCK_K_OVERLAP, p.stream);
   if (a.n == 1) {
     const OvArgs<1> one{{a.it[0]}, 1};
-    hipLaunchKernelGGL((k_overlap_mfma<T, 1>), dim3(last.blk1), dim3(64 * kOvWaves), 0, p.stream, one);
-    hipLaunchKernelGGL((k_overlap_reduce<T, 1>), dim3(last.red1), dim3(256), 0, p.stream, one);
+    hipLaunchKernelGGL((k_overlap_mfma<T, 1>), ov_grid(last.blk1), dim3(64 * kOvWaves), 0, p.stream, one);
+    hipLaunchKernelGGL((k_overlap_reduce<T, 1>), ov_grid(last.red1), dim3(256), 0, p.stream, one);
   } else {
-    hipLaunchKernelGGL((k_overlap_mfma<T, kOvItems>), dim3(last.blk1), dim3(64 * kOvWaves), 0, p.stream, a);
-    hipLaunchKernelGGL((k_overlap_reduce<T, kOvItems>), dim3(last.red1), dim3(256), 0, p.stream, a);
+    hipLaunchKernelGGL((k_overlap_mfma<T, kOvItems>), ov_grid(last.blk1), dim3(64 * kOvWaves), 0, p.stream, a);
+    hipLaunchKernelGGL((k_overlap_reduce<T, kOvItems>), ov_grid(last.red1), dim3(256), 0, p.stream, a);
   }
   p.prof.end(FOCK_K_OVERLAP, p.stream);
   return hipGetLastError();
