@@ -231,13 +231,18 @@ __global__ __launch_bounds__(kBlock) void k_pencil_energy(Geo g, PlaneGeo pg, in
   }
 }
 
-// One ordered batch is the whole energy, of few enough partials for one
-// workgroup: the pencil pass finishes it, without the launches of the sum and of
-// k_energy_finish, which count where a call is nothing but launches (4x4x4, 2
-// bands, apply and E_x: 32.8 us with one launch more, 28.6).
+// One ordered batch is the whole energy, and small: the pencil pass finishes it,
+// without the launches of the sum and of k_energy_finish, which count where a call
+// is nothing but launches.  Every workgroup then waits for its partial to leave
+// the L2, with what else it holds: past some 500 workgroups, or a pair buffer of
+// 0.5 MB, that is longer.  Apply and E_x, with those launches / without, us: 4x4x4,
+// 2 bands 35.2/28.6; 8^3, 2 k, 3 bands (288 partials) 36.0/30.9; 12^3, 6 bands
+// (432, 0.5 MB) 35.9/30.0; 12x30x20, 4 bands (480, 0.9 MB) 36.1/37.2; 27^3, 4 bands
+// (432, 2.5 MB) 46.8/50.9; 12^3, 16 bands (3072, 3.5 MB) 36.9/90.9.
 bool lds_energy_whole(const Plan& p) {
-  return p.inst.size() == 1 && p.ordered_energy.size() == 1 &&
-         static_cast<long long>(p.ordered_energy[0].npairs) * p.inst[0].grid[1] <= 4096;
+  if (p.inst.size() != 1 || p.ordered_energy.size() != 1) return false;
+  const long long pairs = p.ordered_energy[0].npairs;
+  return pairs * p.inst[0].grid[1] <= 512 && pairs * p.inst[0].npts <= 65536;
 }
 
 // b.nO > 0: the ordered pairs of a batch (weighted, into slot b.eslot), else an
