@@ -62,6 +62,19 @@ THREE_PASS = ("plane", "pencil", "accumulate")
 THREE_PASS_UNIT = "three-pass apply (plane + pencil + accumulate of one batch)"
 
 
+REGISTER_LENGTHS = (24, 32, 36, 40, 48, 50, 54, 60, 64, 72)
+
+
+def three_pass_form(grid, s):
+    """Which three-pass kernels an instance runs on (README, grid table): FP64
+    and general grids the line passes, FP32 on N1 x L x L the register-line
+    passes, on most cubes in their slab form."""
+    n1, n2, n3 = grid
+    if s == 16 or n2 != n3 or n1 not in REGISTER_LENGTHS or n2 not in REGISTER_LENGTHS:
+        return "line"
+    return "slab" if n1 == n2 and n1 not in (24, 60) else "register"
+
+
 def kernel_model(grid, s):
     """Algorithmic flops and bytes per band pair.
 
@@ -70,25 +83,32 @@ def kernel_model(grid, s):
         the output once per ordered pair: the compulsory operand traffic)
     energy (whole-pair energy kernel):
         F = 5 N log2 N + 9 N,    B = 2 s N  (read u_m and u_n)
-    The passes of the three-pass path split the apply's flops
-        plane       F = 5 N log2 N1 + 6 N          (axis 1)
-        pencil      F = 10 N log2(N2 N3) + 2 N     (axes 2 and 3, there and back)
-        accumulate  F = 5 N log2 N1 + 8 N          (axis 1)
-    but carry no byte model of their own: what one pass moves depends on how
-    much of its operands the caches serve, so per-pass bytes are only quoted
-    from the hardware counters.  s is the complex size."""
+    The passes of the three-pass path split the apply's flops by the axes they
+    transform (F = 5 N log2 of the axes' points there and of those back, and
+    6 N, 2 N and 8 N for the products):
+        form       plane    pencil                 accumulate   energy: plane  pencil
+        line       1        2, 3 and back 2, 3     back 1       1              2, 3
+        register   2, 3     1 and back 1           back 2, 3    2, 3           1
+        slab       2, 3     1 and back 1, 3        back 2       2, 3           1
+    (FP32 general grids: the energies' passes are 2, 3 and 1) but carry no byte
+    model of their own: what one pass moves depends on how much of its operands
+    the caches serve, so per-pass bytes are only quoted from the hardware
+    counters.  s is the complex size."""
     n1, n2, n3 = grid
     n = n1 * n2 * n3
-    l23 = math.log2(n2 * n3)
-    l1 = math.log2(n1)
+    l1, l2, l3 = math.log2(n1), math.log2(n2), math.log2(n3)
+    form = three_pass_form(grid, s)
+    plane, pencil, acc = {"line": (l1, 2 * (l2 + l3), l1), "register": (l2 + l3, 2 * l1, l2 + l3),
+                          "slab": (l2 + l3, 2 * l1 + l3, l2)}[form]
+    e_plane, e_pencil = (l1, l2 + l3) if form == "line" and s == 16 else (l2 + l3, l1)
     return {
         "fused": dict(flops=10 * n * math.log2(n) + 16 * n, bytes=4 * s * n),
         "energy_fused": dict(flops=5 * n * math.log2(n) + 9 * n, bytes=2 * s * n),
-        "plane": dict(flops=5 * n * l1 + 6 * n),
-        "pencil": dict(flops=10 * n * l23 + 2 * n),
-        "accumulate": dict(flops=5 * n * l1 + 8 * n),
-        "energy_plane": dict(flops=5 * n * l1 + 6 * n),
-        "energy_pencil": dict(flops=5 * n * l23 + 3 * n),
+        "plane": dict(flops=5 * n * plane + 6 * n),
+        "pencil": dict(flops=5 * n * pencil + 2 * n),
+        "accumulate": dict(flops=5 * n * acc + 8 * n),
+        "energy_plane": dict(flops=5 * n * e_plane + 6 * n),
+        "energy_pencil": dict(flops=5 * n * e_pencil + 3 * n),
     }
 
 

@@ -124,8 +124,9 @@ fock_status fock_plan(const fock_desc* descs, int32_t n_inst, fock_precision pre
  *                   105 MB) the whole-pair kernel does not need, as long as
  *                   the plan fits FOCK_STATIC_WORKSPACE_BYTES
  *   no_fused        1: use the three-pass path for every grid
- *   no_pair_symmetry 1: the three-pass paths transform every ordered pair; 0: with the full k-pair set it transforms
- *                   each unordered pair once, W_nm(k,k') = conj W_mn(k',k)
+ *   no_pair_symmetry 1: the three-pass paths transform every ordered pair; 0:
+ *                   with the full k-pair set each unordered pair once,
+ *                   W_nm(k,k') = conj W_mn(k',k)
  *                   serving both (blocks of outputs x partners of about
  *                   sqrt(tbuf_mb / pair size) orbitals each; acc_workgroups
  *                   is then unused)
@@ -280,8 +281,10 @@ fock_status fock_plan_stats(fock_plan_t plan, int64_t* ordered_pairs, int64_t* a
 
 /* Kernel kinds for per-kernel timing. */
 typedef enum {
-  /* (register-line passes, FP32 and mixed on N1 x L x L: axes 2, 3 in the
-   * first and third pass, axis 1 in the second) */
+  /* Axes as on the line path.  Register-line passes (FP32 and mixed on N1 x L x
+   * L): axes 2, 3 in the first and third pass, axis 1 in the second; their slab
+   * form: 2, 3, then 1 and back 1, 3, then back 2; energies 2, 3, then 1.
+   * FP32 general grids: energies axes 3, 2, then 1. */
   FOCK_K_PLANE = 0,          /* apply: co-density + forward FFT of axis 1            */
   FOCK_K_PENCIL = 1,         /* apply: axes 2, 3 forward, x v_q, axes 3, 2 inverse   */
   FOCK_K_ACCUMULATE = 2,     /* apply: inverse FFT of axis 1 + accumulate            */
