@@ -2,13 +2,13 @@
 // after another over a plane (axes 3 and 2) and a slab (axis 1), FP64 sums.
 //
 // An energy is an FP64 number made of FP32 spectra, and other transform forms
-// round those differently: taken from the plane pass of pass_line.hip, E_x of
-// small cells moved by up to 6e-8 of itself (no further from its FP64 value),
-// more than the 1e-9 that a caller who compares energies from call to call
-// should see from a faster kernel.  So E_x keeps this form, over ordered pairs
-// after an apply and over unordered ones in fock_energy, and only V_x takes the
-// faster passes.  24x24x60, 3x3x1 k, 12 bands, FP32 step: 3.4 ms with E_x from
-// the plane pass, 9.6 with these passes, 28.0 when V_x took this form too.
+// round those differently: taken from the plane pass of pass_line.hip, E_x moves
+// by up to 6e-8 of itself (either form repeats bit for bit and is as far from the
+// FP64 value, within 1e-6).  It keeps this form, over ordered pairs after an
+// apply and over unordered ones in fock_energy, so that the energies of one input
+// agree to 1e-12 with those that the library gave before V_x took the faster
+// passes.  24x24x60, 3x3x1 k, 12 bands, FP32 step: 28.0 ms when V_x took this
+// form too, 9.6 with E_x alone in it, 3.4 with E_x from the plane pass.
 #include <algorithm>
 
 #include "fft_lds.hpp"

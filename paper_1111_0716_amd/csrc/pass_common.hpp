@@ -92,14 +92,11 @@ __device__ __forceinline__ C* lane_at(C* u, unsigned o) {
 // STREAM: a pair buffer larger than the caches goes through memory once per pass,
 // and its accesses are marked non-temporal, so that they do not push the
 // orbitals and tables out of L2 (the accumulate's reads included, although a
-// pair is read once for each of its orders: the two reads are far apart).  A
-// buffer that the caches hold is read by the next pass from there, and marked
-// accesses lose that (by_stream has the line).  Without and with, per call: 32^3 4x4x4 k FP32 step 367.5 -> 336.6 ms, 32^3 2x2x2 k FP64 12.40
-// -> 11.48, 64^3 Gamma FP32 17.85 -> 17.05, 24x24x60 FP32 4.02 -> 3.70, 60^3
-// Gamma FP64 1.76 -> 1.50; 72^3 FP32 77.0 -> 76.5.  Stores alone: 344.9, 11.89,
-// 17.32, 3.82, 1.69; all but the accumulate's reads: 340.9, 11.71, 17.47, 3.76,
-// 1.66, and 0.62 against 0.65 ms at 36x40x45 FP64, whose 0.5 GB buffer lies
-// partly in the last-level cache.
+// pair is read once for each of its orders: the two reads are far apart).  32^3
+// 4x4x4 k FP32 step 367.5 -> 336.6 ms (stores alone 344.9, all but the
+// accumulate's reads 340.9), 64^3 Gamma FP32 17.85 -> 17.05; 72^3 FP32 77.0 ->
+// 76.5.  A buffer that the caches hold is read by the next pass from there, and
+// marked accesses lose that: pair_streams (fock_internal.hpp) has the line.
 template <bool STREAM, typename C>
 __device__ __forceinline__ C stream_load(const C* p) {
   typedef decltype(C{}.x) V2 __attribute__((ext_vector_type(2)));

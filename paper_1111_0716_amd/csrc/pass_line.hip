@@ -20,9 +20,9 @@
 // registers live in a lane pair (split_fft.hpp).
 //
 // Every pass is meant to be bound by the pair buffer's traffic: one write, one
-// read and write, two reads (one per order of a pair).  At 32^3 4x4x4 k FP32
-// (3.9 GB a batch) the passes take 730, 1440 and 1525 us: 5.3, 5.4 and 5.1 TB/s,
-// a large copy's 4.9 to 5.4.
+// read and write, two reads (one per order of a pair).  At 32^3 4x4x4 k, 18
+// bands, FP64 (7.7 GB a batch) the passes take 1.73, 2.87 and 2.67 ms: 4.5, 5.4
+// and 5.8 TB/s, a large copy's 4.9 to 5.4.
 //
 // It serves FP64 plans on every grid and V_x of FP32 plans on general grids
 // (FP32 N1 x L x L and mixed plans: pass_reg.hip; why, and FP32 energies:
@@ -65,7 +65,8 @@ template <typename T, int L, bool SPLIT>
 struct AccShape {
   static constexpr int REGS = LineShape<T, L>::REGS / (SPLIT ? 2 : 1);
   // three waves per SIMD for FP64 where 168 registers hold them: 32^3 2x2x2 k
-  // step 10.41 -> 10.05 ms (FP32 loses: 32^3 4x4x4 k 336.0 -> 341.6 ms)
+  // step 10.41 -> 10.05 ms (FP32 loses: 32^3 4x4x4 k on this path, as with
+  // FOCK_NO_REG=1, 336.0 -> 341.6 ms)
   static constexpr int WPE = sizeof(T) == 8 && 2 * REGS <= 128 ? 3 : 2 * REGS <= 160 ? 2 : 1;
   // most waves of a workgroup: two per SIMD, or what 64 KiB of LDS take of their sums
   static constexpr int BYTES = REGS * 64 * 4;
@@ -116,7 +117,8 @@ __device__ __forceinline__ void load_codensity_u(C* x, const C* __restrict__ a, 
 // read orbitals from L2 only, so a line block is one wave: the slices of a
 // batch's 128 partners (32^3: 16 KB each) then stay in an XCD's 4 MB while it
 // walks the pairs; four waves' slices (8 MB) come from further away.  32^3
-// 4x4x4 k FP32, 3.9 GB a batch: 1060 us at four waves, 730 at one (5.3 TB/s).
+// 4x4x4 k FP32 on this path (FOCK_NO_REG=1), 3.9 GB a batch: 1060 us at four
+// waves, 730 at one (5.3 TB/s).
 template <typename T, int L, bool STREAM>
 __global__ __launch_bounds__(64, (LineShape<T, L>::WPE_FWD)) void k_line_fwd(
     int plane, int npairs, unsigned total, int nbands, long long bs, const typename cx<T>::t* __restrict__ psi, int o0,
@@ -509,9 +511,9 @@ void line_acc_L(const Plan& p, const Batch& b, const Instance& in, const int2* p
                 bool backward) {
   using Sh = LineShape<T, L>;
   if constexpr (Sh::SPLIT_ACC_FEW) {
-    // 72^3 FP32, 20 bands (1620 waves of whole lines): 0.79 against 0.81 ms,
-    // 72x24x24, 60 bands (540) 0.75 against 0.82; 64 bands (5184) 7.84 against
-    // 7.73 ms
+    // Apply, lane pairs against whole lines, on this path (FOCK_NO_REG=1): 72^3
+    // FP32, 20 bands (1620 waves of whole lines) 0.79 against 0.81 ms, 72x24x24,
+    // 60 bands (540) 0.75 against 0.82; 72^3, 64 bands (5184) 7.84 against 7.73
     const long long waves =
         static_cast<long long>((in.grid[1] * in.grid[2] + 63) / 64) * (b.nO + (b.mirror ? b.nP : 0));
     if (waves <= 2048) {

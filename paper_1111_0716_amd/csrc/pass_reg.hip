@@ -1,7 +1,8 @@
 // Three-pass kernels with register-line FFTs of the FP32 and mixed plans, for
-// grids N1 x L x L that do not take the whole-pair kernels, N1 and L in {24, 32, 36, 40, 48, 50, 54, 60,
-// 64, 72}: a line per lane (FP32 up to 60 in most passes, FP64 up to 32) or a
-// line per lane pair (longer lines).  The band-pair loop on the GPU (paper,
+// grids N1 x L x L that do not take the whole-pair kernels, N1 and L in {24, 32,
+// 36, 40, 48, 50, 54, 60, 64, 72}: a line per lane (FP32 up to 60 in most
+// passes, FP64 up to 32) or a line per lane pair (longer lines).  The band-pair
+// loop on the GPU (paper,
 // "Our Implementation"; NSIM-like blocks of outputs x partners) as three
 // passes over the FFT grid; every 1-D transform runs in one thread's registers
 // on a whole line (reg_fft.hpp), a plane switches axes through one padded LDS
@@ -19,6 +20,12 @@
 // The plane and accumulate passes are compiled for the plane side L and take
 // the plane count N1 at run time; the pencil pass is compiled for the line
 // length N1 and takes the line count L^2 at run time.
+//
+// On most FP32 cubes (reg_slab_default) the slab form runs instead: the plane
+// pass leaves T[j1][c2][c3], the pencil pass takes a slab of fixed c2 and also
+// inverts axis 3 (one LDS transpose), and the accumulate has independent lines of
+// axis 2.  All are bound by the pair buffer: at 32^3 4x4x4 k, 18 bands, FP32 (3.9
+// GB a batch) 0.89, 1.35 and 1.47 ms, 4.3, 5.7 and 5.3 TB/s.
 #include <algorithm>
 #include <initializer_list>
 
@@ -1140,7 +1147,7 @@ struct RegPolicy {
   static constexpr bool FP32 = sizeof(T) == 4;
   static constexpr bool SPLIT_PLANE = !FP32 && L >= 36;
   static constexpr bool SPLIT_PENCIL = FP32 ? L >= 64 : L >= 36;
-  // FP64 32 points over lane pairs too: alpha boron FP64 accumulate 462
+  // FP64 32 points over lane pairs too (FOCK_MIXED): 32^3 4x4x4 k accumulate 462
   // against 518 ms per step for one lane (one-wave workgroups with the L2
   // prefetch, 586 ms as four-wave ones without)
   static constexpr bool SPLIT_ACC = FP32 ? (L >= 54 && L <= 64) : L >= 32;

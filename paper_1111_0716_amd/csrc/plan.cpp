@@ -323,8 +323,8 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
   }
   // ---- batch shapes ----
   // pair-buffer budget: 4 GiB, 8 GiB in FP64, whose pairs are twice the
-  // bytes (the same block shapes; alpha boron FP64 1.02 s per step against
-  // 1.06 s at 4 GiB)
+  // bytes (the same block shapes; 32^3 4x4x4 k FP64, on the passes before the
+  // line path, 1.02 s per step against 1.06 s at 4 GiB)
   const size_t tbuf_default = prec == FOCK_C128 ? 8192 : 4096;
   const size_t tbuf_target =
       (tn.tbuf_mb > 0 ? static_cast<size_t>(tn.tbuf_mb) : env_mb("FOCK_TBUF_MB", tbuf_default)) << 20;
@@ -442,9 +442,10 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
     const size_t pair_bytes = static_cast<size_t>(in.npts) * p->csize;
     const int pmax = static_cast<int>(std::max<size_t>(1, std::min<size_t>(65535, tbuf_target / pair_bytes)));
     // Unordered pairs halve the transforms.  A call of at most 32768 points in
-    // all its ordered pairs is the time of its launches either way (12x10x9,
-    // two k-points of three bands, 38880 points: 27.3 us with unordered and
-    // 27.5 with ordered pairs; 8^3, 18432 points, 27.6) and keeps the plain order.
+    // all its ordered pairs is the time of its launches either way (12x10x9, two
+    // k-points of three bands, 38880 points: 27.3 us with unordered and 27.5 with
+    // ordered pairs) and keeps the ordered schedule, which fock_plan_stats
+    // reports for it: nothing is won by either.
     const bool tiny = !in.reg && static_cast<int64_t>(nout) * npart * in.npts <= 32768;
     if (!no_sym && !tiny && g.k0 == 0 && g.k1 == in.nk && full_kset(in)) {
       // Pair symmetry: W_ba = conj(W_ab) (the Nyquist-averaged kernel is even
