@@ -1372,7 +1372,11 @@ void launch_acc_all(const Plan& p, const Batch& b, const Instance& in, const int
                                                      backward);
 }
 
-void lds_attr(std::initializer_list<const void*> fs, int lim) {
+// Kernels of more dynamic LDS than any may have unasked (64 KiB, and their
+// few static bytes).  This runs whenever a workspace is attached and in every
+// fock_apply_energy_static, some 0.3 us a kernel.
+void lds_attr(std::initializer_list<const void*> fs, int bytes, int lim) {
+  if (bytes <= 60 * 1024) return;
   for (const void* f : fs)
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) != hipSuccess) (void)hipGetLastError();
 }
@@ -1385,17 +1389,19 @@ const void* fn(F* f) {
 template <typename T, int L, bool STREAM>
 void plane_lds_attr(int lim) {
   if constexpr (RegPolicy<T, L>::SPLIT_PLANE)
-    lds_attr({fn(&k_plane_split<T, L, false, STREAM>), fn(&k_plane_split<T, L, true, STREAM>)}, lim);
+    lds_attr({fn(&k_plane_split<T, L, false, STREAM>), fn(&k_plane_split<T, L, true, STREAM>)}, SplitShape<T, L>::LDS,
+             lim);
   else
-    lds_attr({fn(&k_plane_reg<T, L, false, T, false, STREAM>), fn(&k_plane_reg<T, L, true, T, false, STREAM>)}, lim);
+    lds_attr({fn(&k_plane_reg<T, L, false, T, false, STREAM>), fn(&k_plane_reg<T, L, true, T, false, STREAM>)},
+             RegShape<T, L>::LDS, lim);
 }
 template <typename T, int L, bool STREAM>
 void acc_lds_attr(int lim) {
   using Po = RegPolicy<T, L>;
   if constexpr (Po::SPLIT_ACC)
-    lds_attr({fn(&k_acc_split<T, L, T, STREAM>)}, lim);
+    lds_attr({fn(&k_acc_split<T, L, T, STREAM>)}, SplitShape<T, L>::LDS, lim);
   else
-    lds_attr({fn(&k_acc_reg<T, L, T, Po::ACC_PREFETCH, STREAM>)}, lim);
+    lds_attr({fn(&k_acc_reg<T, L, T, Po::ACC_PREFETCH, STREAM>)}, RegShape<T, L>::LDS, lim);
 }
 
 template <typename T, int L, bool STREAM>
@@ -1405,7 +1411,7 @@ void reg_lds_attr(int lim) {
   if constexpr (slab_type<T>())
     lds_attr({fn(&k_plane_reg<T, L, false, T, true, STREAM>), fn(&k_plane_reg<T, L, true, T, true, STREAM>),
               fn(&k_pencil_slab<T, L, false, STREAM>), fn(&k_pencil_slab<T, L, true, STREAM>)},
-             lim);
+             RegShape<T, L>::LDS, lim);
 }
 
 // FOCK_MIXED: FP32 plane pass (FP64 orbitals rounded on load), mixed pencil
@@ -1434,7 +1440,8 @@ int launch_pencil_mixed(const Plan& p, const Batch& b, const Instance& in, const
 
 template <int L>
 void mixed_lds_attr(int lim) {
-  lds_attr({fn(&k_plane_reg<float, L, false, double>), fn(&k_plane_reg<float, L, true, double>)}, lim);
+  lds_attr({fn(&k_plane_reg<float, L, false, double>), fn(&k_plane_reg<float, L, true, double>)},
+           RegShape<float, L>::LDS, lim);
   acc_lds_attr<double, L, false>(lim);
   acc_lds_attr<double, L, true>(lim);
 }
@@ -1467,9 +1474,9 @@ void mixinv_lds_attr(int lim) {
   plane_lds_attr<double, L, false>(lim);
   plane_lds_attr<double, L, true>(lim);
   if constexpr (split_acc<float, L, double>())
-    lds_attr({fn(&k_acc_split<float, L, double>)}, lim);
+    lds_attr({fn(&k_acc_split<float, L, double>)}, SplitShape<float, L>::LDS, lim);
   else
-    lds_attr({fn(&k_acc_reg<float, L, double>)}, lim);
+    lds_attr({fn(&k_acc_reg<float, L, double>)}, RegShape<float, L>::LDS, lim);
 }
 
 // the axis lengths with register-line kernels

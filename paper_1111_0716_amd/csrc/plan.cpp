@@ -785,8 +785,13 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
   // ---- host image of the constant prefix ----
   p->host_image.assign(p->const_bytes, 0);
   unsigned char* img = p->host_image.data();
+  // twiddles of the lengths that occur (a sine and a cosine for every entry of
+  // all of them are 30 us)
+  bool occurs[kNMax + 1] = {};
+  for (const auto& in : p->inst)
+    for (int n : in.grid) occurs[n] = true;
   for (int L = 2; L <= kNMax; ++L) {
-    if (!smooth235(L)) continue;
+    if (!occurs[L]) continue;
     const int o = twiddle_offset(L), a = radix_a(L), b = L / a;
     for (int t = 0; t < twiddle_count(L); ++t) {
       // W_L^{r j} = exp(-2 pi i r j / L) at (r - 1) b + j, in FP64, rounded once
@@ -804,7 +809,7 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
     }
   }
   for (int L = 2; sc.tw1 && L <= kNMax; ++L) {
-    if (!smooth235(L)) continue;
+    if (!occurs[L]) continue;
     for (int t = 0; t < L; ++t) {
       const double ang = -2.0 * M_PI * static_cast<double>(t) / static_cast<double>(L);
       float* w = reinterpret_cast<float*>(img + p->tw1_off) + 2 * (twiddle_offset(L) + t);
@@ -860,11 +865,11 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
         for (int g0 = 0; g0 < g.n1; g0 += g.g)
           for (int k2 = 0; k2 < g.b3; ++k2)
             for (int k1 = 0; k1 < g.a3; ++k1)
-              for (int c1 = g0; c1 < std::min(g0 + g.g, g.n1); ++c1)
-                for (int p2 = 0; p2 < g.n2; ++p2) {
-                  const int c2 = p2 / g.b2 + g.a2 * (p2 % g.b2), c3 = k1 + g.a3 * k2;
-                  *d++ = t[c1 * plane + static_cast<size_t>(c2) * g.n3 + c3];
-                }
+              for (int c1 = g0; c1 < std::min(g0 + g.g, g.n1); ++c1) {
+                const double* column = t.data() + c1 * plane + k1 + g.a3 * k2;
+                for (int r2 = 0; r2 < g.a2; ++r2)
+                  for (int i2 = 0; i2 < g.b2; ++i2) *d++ = column[(r2 + g.a2 * i2) * g.n3];
+              }
         t.swap(r);
       }
       put(in.vtab_off, t);
