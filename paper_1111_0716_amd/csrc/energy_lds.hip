@@ -8,7 +8,7 @@
 // apply and over unordered ones in fock_energy, so that the energies of one input
 // agree to 1e-12 with those that the library gave before V_x took the faster
 // passes.  24x24x60, 3x3x1 k, 12 bands, FP32 step: 28.0 ms when V_x took this
-// form too, 9.6 with E_x alone in it, 3.4 with E_x from the plane pass.
+// form too, 9.0 with E_x alone in it, 3.4 with E_x from the plane pass.
 #include <algorithm>
 
 #include "fft_lds.hpp"

@@ -28,7 +28,7 @@
 // (FP32 N1 x L x L and mixed plans: pass_reg.hip; why, and FP32 energies:
 // energy_lds.hip).  Against the passes it replaced, per call.  All transforms
 // in LDS with a barrier around every radix pass, ordered pairs (general grids):
-// 24x24x60, 3x3x1 k, 12 bands, FP32 step 27.8 -> 9.6 ms; 36x40x45, 2x1x1 k, 16
+// 24x24x60, 3x3x1 k, 12 bands, FP32 step 27.8 -> 9.0 ms; 36x40x45, 2x1x1 k, 16
 // bands, FP64 apply 4.55 -> 0.60 ms; 160 DFTs of 48^3 FP64 498 -> 300 us.  Plane
 // transforms over whole register lines (N1 x L x L): 60^3 Gamma FP64 2.00 ->
 // 1.35 ms; 32^3 2x2x2 k FP64 step 11.3 -> 10.0; apply with energy at Gamma FP64:
