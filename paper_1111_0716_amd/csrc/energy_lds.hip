@@ -160,8 +160,8 @@ __device__ __forceinline__ int table_at(const PlaneGeo& g, int c1, int c2, int c
   return g0 * g.n2 * g.n3 + c3 * rows + (c1 - g0) * g.n2 + (c2 - q2 * g.a2) * g.b2 + q2;
 }
 
-// pencil pass: axis 1 of slab c2 and sum_c v_q(c)/N |P(c)|^2 in FP64.  EXPLICIT:
-// a pair list; otherwise the ordered pairs of a batch, the sum weighted.  vtab
+// pencil pass: axis 1 of slab c2 and sum_c v_q(c)/N |P(c)|^2 in FP64, weighted if
+// occ is given.  EXPLICIT: a pair list; otherwise the ordered pairs of a batch.  vtab
 // is in grid order (one load of n3 values after another), or, where the plan has
 // no room for that, the plane passes' table (tiled; 24x24x60, 528 pairs: 66.4
 // -> 88.9 us).
@@ -183,7 +183,9 @@ __global__ __launch_bounds__(kBlock) void k_pencil_energy(Geo g, PlaneGeo pg, in
   int q;
   double w = 1.0;
   if constexpr (EXPLICIT) {
-    q = pairs[pi].q;
+    const PairRef pr = pairs[pi];
+    q = pr.q;
+    if (occ) w = kw[pr.k] * occ[pr.k * g.nbands + pr.n] * kw[pr.kp] * occ[pr.kp * g.nbands + pr.m];
   } else {
     const int o = pi / nP, p = pi - o * nP, ok = (o0 + o) / g.nbands;
     const int2 r = parts[p];
@@ -210,24 +212,22 @@ __global__ __launch_bounds__(kBlock) void k_pencil_energy(Geo g, PlaneGeo pg, in
   }
   const double tot = block_sum(acc, red);
   if (threadIdx.x == 0) epart[static_cast<size_t>(pi) * g.n2 + c2] = w * tot;
-  if constexpr (!EXPLICIT) {
-    if (!ex) return;
-    // The workgroup that ends last sums the partials, compensated and in a fixed
-    // order, and clears the counter for the next launch.
-    __shared__ bool last;
-    const unsigned n = gridDim.x * gridDim.y;
-    if (threadIdx.x == 0)
-      last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
-    __syncthreads();
-    if (!last) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    double sum = 0.0, comp = 0.0;
-    for (unsigned i = threadIdx.x; i < n; i += kBlock) neumaier(sum, comp, epart[i]);
-    const double all = block_sum(sum + comp, red);
-    if (threadIdx.x == 0) {
-      ex[0] = factor * all;
-      *done = 0u;
-    }
+  if (!ex) return;
+  // The workgroup that ends last sums the partials, compensated and in a fixed
+  // order, and clears the counter for the next launch.
+  __shared__ bool last;
+  const unsigned n = gridDim.x * gridDim.y;
+  if (threadIdx.x == 0)
+    last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+  __syncthreads();
+  if (!last) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  double sum = 0.0, comp = 0.0;
+  for (unsigned i = threadIdx.x; i < n; i += kBlock) neumaier(sum, comp, epart[i]);
+  const double all = block_sum(sum + comp, red);
+  if (threadIdx.x == 0) {
+    ex[0] = factor * all;
+    *done = 0u;
   }
 }
 
@@ -245,8 +245,9 @@ bool lds_energy_whole(const Plan& p) {
   return pairs * p.inst[0].grid[1] <= 512 && pairs * p.inst[0].npts <= 65536;
 }
 
-// b.nO > 0: the ordered pairs of a batch (weighted, into slot b.eslot), else an
-// explicit pair list (into slot b.slot)
+// After an apply (b.eslot >= 0): the ordered pairs of a batch, or of a list that
+// holds those of several groups, weighted, into slot b.eslot.  Else a list of
+// fock_energy, into slot b.slot.
 hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, double* ex) {
   using C = float2;
   const Instance& in = p.inst[b.inst];
@@ -263,7 +264,7 @@ hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* ps
   double* epart = reinterpret_cast<double*>(p.ws + p.epart_off);
   const size_t lds_plane = static_cast<size_t>(g.n2) * g.n3 * sizeof(C);
   const size_t lds_tile = static_cast<size_t>(g.n1) * g.n3 * sizeof(C);
-  const bool ordered = b.nO > 0;
+  const bool ordered = b.nO > 0, after = b.eslot >= 0;
   p.prof.begin(FOCK_K_ENERGY_PLANE, p.stream);
   if (ordered)
     hipLaunchKernelGGL((k_fwd_plane<float, false>), dim3(g.n1, b.npairs), dim3(kBlock), lds_plane, p.stream, g,
@@ -280,10 +281,11 @@ hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* ps
   else
     hipLaunchKernelGGL((k_pencil_energy<float, true>), dim3(g.n2, b.npairs), dim3(kBlock), lds_tile, p.stream, g,
                        in.pg, tiled, 0, 1, static_cast<const int2*>(nullptr), static_cast<const int*>(nullptr), pairs,
-                       static_cast<const C*>(tbuf), vtab, tw, occ, kw, epart, done, static_cast<double*>(nullptr), 0.0);
+                       static_cast<const C*>(tbuf), vtab, tw, after ? occ : nullptr, kw, epart, done, ex,
+                       energy_factor(in));
   p.prof.end(FOCK_K_ENERGY_PENCIL, p.stream);
   if (ex) return hipGetLastError();
-  if (ordered) return launch_sum_slot(p, static_cast<long long>(b.npairs) * g.n2, b.eslot, 1.0);
+  if (after) return launch_sum_slot(p, static_cast<long long>(b.npairs) * g.n2, b.eslot, 1.0);
   return launch_energy_reduce(p, b, occ, g.n2);
 }
 

@@ -249,7 +249,8 @@ struct Schedule {
   // (smaller batches on thin grids)
   bool plane_blocks = false;
   bool can_plane_blocks = false;  // that would change a batch
-  // no second kernel table for energies whose passes read another order
+  // no second kernel table for energies whose passes read another order, and no
+  // list of all groups' ordered pairs
   bool one_table = false;
   bool can_one_table = false;
   // the whole-pair kernel also where the three-pass path is faster
@@ -264,6 +265,7 @@ struct Schedule {
   std::vector<Group> groups;
   std::vector<std::vector<int32_t>> round_pairs;
   std::vector<std::vector<PairRef>> elists;
+  std::vector<std::pair<size_t, std::vector<PairRef>>> olists;  // (offset, list) of E_x after an apply
   bool tw1 = false;  // twiddle table of energy_lds.hip
 };
 
@@ -520,6 +522,7 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
   // energy pair lists
   std::vector<std::vector<PairRef>>& elists = sc->elists;
   elists.assign(n_inst, {});
+  sc->olists.clear();
   size_t max_fused_epairs = 0;
   int slot = 0;
   for (int i = 0; i < n_inst; ++i) {
@@ -577,9 +580,42 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
       const int pmax = static_cast<int>(std::max<size_t>(1, std::min<size_t>(65535, tbuf_target / pair_bytes)));
       int listed = 1;  // pairs of the largest energy batch
       for (int e = 0; e < in.n_ebatches; ++e) listed = std::max(listed, p->energy_batches[in.first_ebatch + e].npairs);
+      size_t total = 0;
+      int lists = 0;
+      for (const Group& g : groups) {
+        if (g.inst != i || g.parts.empty()) continue;
+        total += static_cast<size_t>(g.k1 - g.k0) * in.nbands * (g.parts.size() / 2);
+        ++lists;
+      }
+      // Several groups: one list of all their ordered pairs, in a pair buffer that
+      // is held anyway or little, up to the last-level cache.  Groups apart / one
+      // list, us (apply and E_x): 4x4x4, 8 k with themselves, 2 bands 171/82;
+      // 12x10x9, 4 k, 4 bands 93/62; 20^3, 8 k, k <= k', 4 bands (35 MB) 451/344;
+      // 36x40x45, 2 k, 8 bands (95 MB) 329/304.
+      const size_t held = std::max(kOneEnergyBatch, max_pairs_elems * p->csize);
+      const bool one = lists > 1 && !sc->one_table && total <= static_cast<size_t>(pmax) &&
+                       total * pair_bytes <= std::min(held, kLastLevelBytes);
+      if (one) {
+        std::vector<PairRef> all;
+        all.reserve(total);
+        for (int k = 0; k < in.nk; ++k)
+          for (int n = 0; n < in.nbands; ++n)
+            for (int kp : in.kpartners[k])
+              for (int m = 0; m < in.nbands; ++m)
+                all.push_back(PairRef{k, n, kp, m, in.qmap[static_cast<size_t>(k) * in.nk + kp], 1});
+        Batch b;
+        b.inst = i;
+        b.pair_off = off;
+        b.npairs = static_cast<int32_t>(total);
+        b.eslot = slot++;
+        off = align_up(off + total * sizeof(PairRef));
+        max_pairs_elems = std::max(max_pairs_elems, total * static_cast<size_t>(in.npts));
+        p->ordered_energy.push_back(b);
+        sc->olists.emplace_back(b.pair_off, std::move(all));
+      }
       for (const Group& g : groups) {
         const int nout = (g.k1 - g.k0) * in.nbands, npart = static_cast<int>(g.parts.size() / 2);
-        if (g.inst != i || npart == 0) continue;
+        if (one || g.inst != i || npart == 0) continue;
         int nO = std::min(pmax, std::max(1, std::min(nout, (acc_wgs + in.grid[0] - 1) / in.grid[0])));
         int nP = std::max(1, std::min(npart, pmax / nO));
         if (static_cast<size_t>(nO) * nP * pair_bytes > kOneEnergyBatch) {
@@ -889,6 +925,7 @@ fock_status build_plan(const fock_desc* descs, int n_inst, fock_precision prec, 
     const size_t base = p->energy_batches[in.first_ebatch].pair_off;
     std::memcpy(img + base, sc.elists[i].data(), sc.elists[i].size() * sizeof(PairRef));
   }
+  for (const auto& l : sc.olists) std::memcpy(img + l.first, l.second.data(), l.second.size() * sizeof(PairRef));
   *out = p.release();
   return FOCK_OK;
 }

@@ -76,3 +76,50 @@ def test_energy_finished_by_its_last_workgroup(nb, device):
             stream.synchronize()
             assert float(ex.item()) == eager[0]
         graph.close()
+
+
+def _klist(nk, kind):
+    if kind == "diagonal":
+        return [[k, k] for k in range(nk)]
+    if kind == "upper":
+        return [[k, kp] for k in range(nk) for kp in range(k, nk)]
+    return [[0, kp] for kp in range(nk)] + [[k, k] for k in range(1, nk - 1)]  # the last k has no partner
+
+
+@pytest.mark.parametrize("kind", ["diagonal", "upper", "uneven"])
+@pytest.mark.parametrize("grid,nb", [((5, 8, 6), 1), ((5, 8, 6), 3), ((12, 10, 9), 4)])
+def test_energy_of_several_groups_in_one_launch(grid, nb, kind, device):
+    """FP32 general grid, k-points with partner lists of their own: the ordered
+    pairs of all of them go through one pass each, with and without the finishing
+    workgroup; E_x against the oracle, eagerly and from a replayed graph."""
+    import torch
+
+    from paper_1111_0716_amd import fock
+
+    print(f"energy groups {grid} {nb} {kind}", file=sys.stderr, flush=True)
+    inst = inputs.small_instance(grid=grid, kmesh=(4, 1, 1), nbands=nb, seed=(992, nb), full_grid=True)
+    kpairs = np.array(_klist(inst.nk, kind), dtype=np.int32)
+    u = inst.psi.astype(np.complex64)
+    psi, occ = torch.from_numpy(np.ascontiguousarray(u)).to(device), torch.from_numpy(inst.occ).to(device)
+    vref, eref = Oracle.from_instance(inst, kpairs=kpairs).apply(u.astype(np.complex128), inst.occ)
+    stream = torch.cuda.Stream(device=device)
+    with torch.cuda.stream(stream):
+        plan = fock.Plan([inst], precision="c64", device=device, stream=stream, kpairs=[kpairs])
+        plan.profile(True)
+        (v,), _, ex = plan.fock_apply_energy([psi], [occ])
+        first = float(ex.item())
+        launches = plan.profile_read()
+        plan.profile(False)
+        assert launches["energy_plane"][1] == launches["energy_pencil"][1] == 1
+        assert abs(first - eref) <= 1e-6 * abs(eref)
+        vh = v.cpu().numpy()
+        assert np.linalg.norm(vh - vref) <= 1e-6 * np.linalg.norm(vref)
+        plan.set_graph(True)
+        for _ in range(3):
+            ex.zero_()
+            plan.fock_apply_energy([psi], [occ], out=[v], ex=ex)
+            e2 = plan.fock_energy([psi], [occ])
+            stream.synchronize()
+            assert float(ex.item()) == first
+            assert abs(float(e2.item()) - eref) <= 1e-6 * abs(eref)
+        plan.close()
