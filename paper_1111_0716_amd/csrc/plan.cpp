@@ -587,12 +587,14 @@ static fock_status schedule_plan(Plan* p, const fock_tuning& tn, Schedule* sc) {
         total += static_cast<size_t>(g.k1 - g.k0) * in.nbands * (g.parts.size() / 2);
         ++lists;
       }
-      // Several groups: one list of all their ordered pairs, in a pair buffer that
-      // is held anyway or little, up to the last-level cache.  Groups apart / one
-      // list, us (apply and E_x): 4x4x4, 8 k with themselves, 2 bands 171/82;
-      // 12x10x9, 4 k, 4 bands 93/62; 20^3, 8 k, k <= k', 4 bands (35 MB) 451/344;
-      // 36x40x45, 2 k, 8 bands (95 MB) 329/304.
-      const size_t held = std::max(kOneEnergyBatch, max_pairs_elems * p->csize);
+      // Several groups: one list of all their ordered pairs, up to the last-level
+      // cache and in a pair buffer that is little or at most twice what is held
+      // anyway (the energy list of a symmetric k-pair list has half the pairs).
+      // Groups apart / one list, us (apply and E_x): 4x4x4, 8 k with themselves, 2
+      // bands 171/82; 12x10x9, 4 k, 4 bands 93/62; 20^3, 8 k, k <= k', 4 bands (35 MB)
+      // 451/344; 24x24x60, 8 k with themselves, 4 bands (34 MB) 412/256; 36x40x45, 2 k,
+      // 8 bands (95 MB) 329/304.
+      const size_t held = std::max(kOneEnergyBatch, 2 * max_pairs_elems * p->csize);
       const bool one = lists > 1 && !sc->one_table && total <= static_cast<size_t>(pmax) &&
                        total * pair_bytes <= std::min(held, kLastLevelBytes);
       if (one) {
