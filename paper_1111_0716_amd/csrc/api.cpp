@@ -254,7 +254,7 @@ fock_status run_energy(Plan* p, const void* const* psi, const double* const* occ
   for (const Batch& b : after_apply ? p->ordered_energy : p->energy_batches) {
     hipError_t e;
     if (after_apply) {
-      e = launch_lds_energy_batch(*p, b, psi[b.inst], occ[b.inst], whole ? ex : nullptr);
+      e = launch_lds_energy_batch(*p, b, psi[b.inst], occ[b.inst], whole ? ex + b.inst : nullptr);
     } else if (p->inst[b.inst].fused_energy) {
       e = launch_fused_energy(*p, b, psi[b.inst]);
       if (e == hipSuccess) e = launch_energy_reduce(*p, b, occ[b.inst], 1);

@@ -231,23 +231,32 @@ __global__ __launch_bounds__(kBlock) void k_pencil_energy(Geo g, PlaneGeo pg, in
   }
 }
 
-// One ordered batch is the whole energy, and small: the pencil pass finishes it,
-// without the launches of the sum and of k_energy_finish, which count where a call
-// is nothing but launches.  Every workgroup then waits for its partial to leave
-// the L2, with what else it holds: past some 500 workgroups, or a pair buffer of
-// 0.5 MB, that is longer.  Apply and E_x, with those launches / without, us: 4x4x4,
-// 2 bands 35.2/28.6; 8^3, 2 k, 3 bands (288 partials) 36.0/30.9; 12^3, 6 bands
-// (432, 0.5 MB) 35.9/30.0; 12x30x20, 4 bands (480, 0.9 MB) 36.1/37.2; 27^3, 4 bands
-// (432, 2.5 MB) 46.8/50.9; 12^3, 16 bands (3072, 3.5 MB) 36.9/90.9.
+// Small batches after an apply: the pencil pass sums its partials, without the
+// launch of the sum, and where every instance has one such batch finishes E_x,
+// without k_energy_finish's too.  Every workgroup then waits for its partial to
+// leave the L2, with what else it holds, which past some 300 workgroups or 20000
+// points takes as long as the launches.  Apply and E_x at Gamma, with those launches /
+// without, us: 4x4x4, 2 bands 28.3/25.4; four instances, by partials of each, 8^3, 3
+// bands (72) 98.7/83.5, 4x4x4, 8 bands (256) 100/88, 5x8x6, 6 bands (288) 99/100, 8^3, 8
+// bands (512) 101/116; by points, 12x10x9, 4 bands (17280) 99/95, 5 bands (27000)
+// 101/112, 10x4x20, 9 bands (64800) 110/131.
+static bool finishes(const Instance& in, const Batch& b) {
+  const long long pairs = b.npairs;
+  return pairs * in.grid[1] <= 288 && pairs * in.npts <= 20480;
+}
+
 bool lds_energy_whole(const Plan& p) {
-  if (p.inst.size() != 1 || p.ordered_energy.size() != 1) return false;
-  const long long pairs = p.ordered_energy[0].npairs;
-  return pairs * p.inst[0].grid[1] <= 512 && pairs * p.inst[0].npts <= 65536;
+  if (p.ordered_energy.size() != p.inst.size()) return false;
+  for (const Batch& b : p.ordered_energy) {
+    const Instance& in = p.inst[b.inst];
+    if (in.n_aslot != 1 || !finishes(in, b)) return false;
+  }
+  return true;
 }
 
 // After an apply (b.eslot >= 0): the ordered pairs of a batch, or of a list that
-// holds those of several groups, weighted, into slot b.eslot.  Else a list of
-// fock_energy, into slot b.slot.
+// holds those of several groups, weighted, into slot b.eslot, or E_x if ex is
+// given.  Else a list of fock_energy, into slot b.slot.
 hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, double* ex) {
   using C = float2;
   const Instance& in = p.inst[b.inst];
@@ -265,6 +274,8 @@ hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* ps
   const size_t lds_plane = static_cast<size_t>(g.n2) * g.n3 * sizeof(C);
   const size_t lds_tile = static_cast<size_t>(g.n1) * g.n3 * sizeof(C);
   const bool ordered = b.nO > 0, after = b.eslot >= 0;
+  const double factor = ex ? energy_factor(in) : 1.0;
+  if (!ex && after && finishes(in, b)) ex = reinterpret_cast<double*>(p.ws + p.ebsum_off) + b.eslot;
   p.prof.begin(FOCK_K_ENERGY_PLANE, p.stream);
   if (ordered)
     hipLaunchKernelGGL((k_fwd_plane<float, false>), dim3(g.n1, b.npairs), dim3(kBlock), lds_plane, p.stream, g,
@@ -277,12 +288,12 @@ hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* ps
   if (ordered)
     hipLaunchKernelGGL((k_pencil_energy<float, false>), dim3(g.n2, b.npairs), dim3(kBlock), lds_tile, p.stream, g,
                        in.pg, tiled, b.o0, b.nP, parts, qmap, static_cast<const PairRef*>(nullptr),
-                       static_cast<const C*>(tbuf), vtab, tw, occ, kw, epart, done, ex, energy_factor(in));
+                       static_cast<const C*>(tbuf), vtab, tw, occ, kw, epart, done, ex, factor);
   else
     hipLaunchKernelGGL((k_pencil_energy<float, true>), dim3(g.n2, b.npairs), dim3(kBlock), lds_tile, p.stream, g,
                        in.pg, tiled, 0, 1, static_cast<const int2*>(nullptr), static_cast<const int*>(nullptr), pairs,
                        static_cast<const C*>(tbuf), vtab, tw, after ? occ : nullptr, kw, epart, done, ex,
-                       energy_factor(in));
+                       factor);
   p.prof.end(FOCK_K_ENERGY_PENCIL, p.stream);
   if (ex) return hipGetLastError();
   if (after) return launch_sum_slot(p, static_cast<long long>(b.npairs) * g.n2, b.eslot, 1.0);

@@ -288,8 +288,8 @@ void prepare_reg_kernels(fock_precision prec, int lim);
 hipError_t launch_reg_apply_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, void* out,
                                   const double* gscale, double hscale, bool backward, bool energy);
 hipError_t launch_reg_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ);
-// E_x of FP32 plans on general grids (energy_lds.hip); ex not null: an ordered
-// batch that is all of the plan's energy and finishes it (lds_energy_whole)
+// E_x of FP32 plans on general grids (energy_lds.hip); ex not null: the batch is
+// all of its instance's energy and finishes it (lds_energy_whole: each is)
 hipError_t launch_lds_energy_batch(const Plan& p, const Batch& b, const void* psi, const double* occ, double* ex);
 bool lds_energy_whole(const Plan& p);
 // three-pass path (pass_line.hip)
